@@ -535,7 +535,7 @@ def bench_admission(g, synth, big):
 
 # traversal kernel launched for each mapping code reported in the stats
 KERNEL_OF_MAPPING = {3: "k_traverse8", 0: "k_traverse<8>", 4: "k_traverse<7>", 2: "k_traverse_wg<8>",
-                     1: "k_traverse_wg<16>", 5: "k_traverse<6, true>", 6: "k_fill2_thread"}
+                     1: "k_traverse_wg<16>", 5: "k_traverse<6, true>", 6: "k_fill2_thread", 7: "k_bm_factor"}
 
 
 def main():

@@ -84,8 +84,9 @@ typedef enum {
 #define GSOFA_LEVEL_ORDER       0x20u /* ablation: the paper's breadth-first frontier
                                          order instead of windowed order; results are
                                          unchanged, work grows                        */
-/* traversal mapping (tuning knob, results unchanged); none set -> the
- * autotuner's choice, by default one wavefront per source row with 32-bit labels */
+/* traversal mapping (tuning knob, results unchanged); none set -> the block path
+ * (64 rows at a time as bit masks), or where that does not apply the autotuner's
+ * choice, by default one wavefront per source row with 32-bit labels */
 #define GSOFA_MAP_WAVE32        0x40u  /* one wavefront per source row, 32-bit labels  */
 #define GSOFA_MAP_WG8           0x80u  /* eight wavefronts per source row              */
 #define GSOFA_MAP_WG16          0x100u /* sixteen wavefronts per source row            */
@@ -103,13 +104,16 @@ typedef enum {
  * a call on one matrix of at most 65,536 rows, whose phases are too short for
  * capture to pay; results are identical. */
 #define GSOFA_EAGER             0x200u
-/* With window = 0, concurrent_sources = 0 and no mapping or ablation flag, the
- * window span, the mapping and the sources in flight are autotuned: for each
- * size class (device, log2 of the largest n, mean row length, batch size) the
- * first call with at least 65,536 source rows times every candidate on one
- * stratified sample of its rows and keeps the fastest for later calls; smaller
- * calls of an untuned class use window 16 with 32-bit labels. GSOFA_TUNE_NOW
- * times the candidates in this call whatever its size, and re-tunes its class.
+/* With window = 0, concurrent_sources = 0 and no mapping or ablation flag, a call
+ * takes the block path: no per-source traversal, nothing to tune. Matrices of more
+ * than 2^22 rows and calls whose mem_budget_bytes does not hold its working memory
+ * take the traversal, whose window span, mapping and sources in flight are then
+ * autotuned: for each size class (device, log2 of the largest n, mean row length,
+ * batch size) the first call with at least 65,536 source rows times every
+ * candidate on one stratified sample of its rows and keeps the fastest for later
+ * calls; smaller calls of an untuned class use window 16 with 32-bit labels.
+ * GSOFA_TUNE_NOW times the candidates in this call whatever its size, re-tunes its
+ * class, and makes later calls of the class use the tuned traversal.
  * Results are identical for every choice. */
 #define GSOFA_TUNE_NOW          0x400u
 /* Never time tuner trials in this call (latency-sensitive callers): use the size
@@ -161,12 +165,15 @@ typedef struct {
 typedef struct {
     int32_t status;             /* per-matrix status (batch, serve)                       */
     int32_t concurrent_sources; /* sources in flight at once (#C)                         */
-    uint64_t iterations;        /* frontier-expansion steps, summed over sources          */
-    uint64_t windows;           /* threshold windows, summed over sources                 */
+    uint64_t iterations;        /* frontier-expansion steps, summed over sources (block
+                                   path: merges of one block into another)                */
+    uint64_t windows;           /* threshold windows, summed over sources (block path:
+                                   blocks of 64 rows)                                     */
     uint64_t edges_alg;         /* algorithmic edges: for each source row, deg(src) plus
                                    deg(v) of every v < src reachable from src through
                                    vertices < src (each counted once per source)          */
-    uint64_t edges_gpu;         /* edges actually scanned, revisits included              */
+    uint64_t edges_gpu;         /* edges actually scanned, revisits included (block path:
+                                   column masks merged)                                   */
     uint64_t peak_device_bytes; /* device working memory of this call                     */
     double t_traverse_ms;       /* fill-detection kernel time: the per-source seed (the
                                    source row's own entries) runs inside the traversal
@@ -174,13 +181,14 @@ typedef struct {
     double t_emit_ms;           /* pointer scans and per-row sort into CSR                */
     double t_supernode_ms;
     double t_total_ms;          /* whole call, host copies included                       */
-    int32_t window;             /* threshold-window span used                             */
+    int32_t window;             /* threshold-window span used (0: block path)             */
     int32_t mapping;            /* traversal mapping used: 0 one wavefront per source with
                                    32-bit labels, 4 the same compiled for seven wavefronts
                                    per SIMD, 3 one wavefront with byte states, 2 / 1 eight
                                    / sixteen wavefronts per source, 5 the memory-budget
                                    kernel (GSOFA_BUDGET_MODE), 6 one thread per source
-                                   (GSOFA_MAP_THREAD, comparison baseline)                */
+                                   (GSOFA_MAP_THREAD, comparison baseline), 7 the block
+                                   path                                                   */
     double t_tune_ms;           /* autotuner trial time spent in this call (0 if none)    */
     uint64_t spilled_entries;   /* worklist and row-buffer entries written to host memory
                                    (GSOFA_BUDGET_MODE; 0 otherwise)                       */

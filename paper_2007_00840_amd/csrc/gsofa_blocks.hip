@@ -1,0 +1,1111 @@
+// Block path: symbolic factorisation by 64-row blocks of bit masks.
+//
+// A block holds 64 consecutive rows; bit r of a 64-bit mask stands for its row
+// r. For every column v the block keeps one mask: the rows whose structure
+// (row of L+U) contains v. By the fill-path theorem (Background) the structure
+// of a row s is the smallest set that contains the row's own entries and, with
+// every k < s in it, the entries of U(k,:) (split a fill path at its largest
+// intermediate vertex k: s -> k puts k into L(s,:), and the rest of the path
+// puts its end into U(k,:)). So a block takes its rows' entries, then merges
+// the finished U rows of the earlier blocks that its masks name, 64 rows at
+// once, and finally its own rows among each other. The per-source traversal
+// (k_traverse) walks every vertex reachable from every source instead: on the
+// 64^3 27-point stencil 51 G edge visits, where the block path makes 2.8e5 block
+// merges of 3.6e6 64-column tiles: 7.5 ms instead of 221 (1000^2 9-point stencil:
+// 4.7 instead of 218 ms; 512 batch members: 3.3 instead of 90 ms).
+//
+// What bounds it is the chain of blocks that wait for one another, not
+// throughput, and three things keep that chain short:
+//   * two publications per block. The rows that depend on no earlier block
+//     (whole small subtrees and the first rows of a larger one) are finished
+//     and published at once, before the block waits for anything. With one
+//     publication a nested-dissection order would run almost serially: a block
+//     that holds the end of one subtree and the start of the next would make
+//     the second wait for the first (modelled on the 1000^2 9-point stencil:
+//     a chain of 102 ms with one publication, 1.8 ms with two).
+//   * pruning (Eisenstat and Liu's symmetric pruning). Where U(a,k) and L(k,a)
+//     are both nonzero, every later row with a in its structure has k too, and
+//     U(k,:) holds the rest of U(a,:): of row a only the entries up to k are
+//     needed. kmatch[a] is the smallest such k found so far.
+//   * several wavefronts per block that merge pending blocks, and the tiles of a
+//     long list, side by side. Merging is monotone, so a block merged too early is merged again when bits of it
+//     arrive later.
+//
+// Blocks are taken from a counter in an order in which every block comes after
+// the ones it can depend on (ascending inside a matrix), so a block waits only
+// for blocks that resident workgroups have already taken, and the first
+// unfinished one waits for nothing: the launch always drains. Every wait also
+// ends on the abort word and after kSpinLimit polls.
+//
+// Data that crosses workgroups (masks, columns, headers, kmatch, flags) is
+// written and read with device-scope atomics, which reach memory past the
+// XCD's L2; the writer waits for its stores (s_waitcnt) before the flag.
+#include <algorithm>
+#include "gsofa_internal.h"
+#include "gsofa.h"
+
+namespace gsofa {
+
+typedef unsigned long long u64;
+
+namespace {
+
+constexpr int kThreads = 256;         // threads of the kernels after the factorisation
+constexpr int kRangeTiles = 1024;     // column tiles (64 columns) listed at a time
+constexpr uint32_t kSpinLimit = 1u << 22;
+constexpr int32_t kNoMatch = 0x7FFFFFFF;
+
+__device__ __forceinline__ int lane() { return (int)(threadIdx.x & 63); }
+__device__ __forceinline__ int rfl(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+__device__ __forceinline__ uint32_t below_count(u64 m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+__device__ __forceinline__ u64 readlane64(u64 v, int l) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
+    return ((u64)hi << 32) | lo;
+}
+
+__device__ __forceinline__ int incl_scan(int v) {
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int t = __shfl_up(v, (unsigned)d, 64);
+        if (lane() >= d) v += t;
+    }
+    return v;
+}
+
+__device__ __forceinline__ int max64(int v) {
+#pragma unroll
+    for (int d = 32; d; d >>= 1) v = max(v, __shfl_xor(v, d, 64));
+    return v;
+}
+
+__device__ __forceinline__ int min64(int v) {
+#pragma unroll
+    for (int d = 32; d; d >>= 1) v = min(v, __shfl_xor(v, d, 64));
+    return v;
+}
+
+__device__ __forceinline__ u64 or64(u64 v) {
+#pragma unroll
+    for (int d = 32; d; d >>= 1) v |= __shfl_xor(v, d, 64);
+    return v;
+}
+
+__device__ __forceinline__ u64 sum64(u64 v) {
+#pragma unroll
+    for (int d = 32; d; d >>= 1) v += __shfl_xor(v, d, 64);
+    return v;
+}
+
+// device scope: data published to other workgroups
+template <typename T>
+__device__ __forceinline__ T ld_dev(const T* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void st_dev(T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// workgroup scope: a block's own column masks
+__device__ __forceinline__ u64 ld_wg(const u64* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ u64 or_wg(u64* p, u64 v) {
+    return __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// order this wavefront's earlier LDS and global accesses before its later ones
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// this wavefront's device-scope stores have reached memory
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+__device__ __forceinline__ u64 above(int k) { return k < 63 ? ~0ull << (k + 1) : 0ull; }
+__device__ __forceinline__ u64 below(int k) { return (1ull << k) - 1ull; }
+
+// y[b] = x[b] | OR of x[a] over the bits a of set[b] (lane b), through sixteen
+// 16-entry tables in LDS (the OR of every subset of four lanes' words): the
+// lookups of a table touch 16 consecutive words, so they never conflict.
+// Following the up to 63 bits of a set one by one costs several times as much.
+__device__ __forceinline__ u64 lane_product(u64 x, u64 set, u64* xs, u64* tab) {
+    const int ln = lane();
+    wave_sync();
+    xs[ln] = x;
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int e = ln + 64 * i;
+        const u64* q = &xs[(e >> 4) * 4];
+        u64 t = 0;
+        if (e & 1) t |= q[0];
+        if (e & 2) t |= q[1];
+        if (e & 4) t |= q[2];
+        if (e & 8) t |= q[3];
+        tab[e] = t;
+    }
+    wave_sync();
+    u64 y = x;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) y |= tab[i * 16 + (int)((set >> (4 * i)) & 15ull)];
+    return y;
+}
+
+// One block's rows among each other. x: lane b's word is the mask of the
+// block's own column b. Row k's pattern right of k goes to every row r > k that
+// holds k, for the rows k of S in ascending order; with `narrow` a row that
+// depends on a row outside S leaves S (S then ends as the rows finished
+// without any earlier block). match (lane k): the first b with U(k,b) and
+// L(b,k) both nonzero, or -1.
+template <bool narrow>
+__device__ __forceinline__ void eliminate(u64& x, u64& S, int& match) {
+    const int ln = lane();
+    match = -1;
+    for (int k = 0; k < 64; ++k) {
+        const u64 L = readlane64(x, k) & above(k);
+        if (!((S >> k) & 1ull)) {
+            if (narrow) S &= ~L;
+            continue;
+        }
+        if (L == 0ull) continue;
+        const bool has = ln > k && ((x >> k) & 1ull);
+        const u64 U = __ballot(has);
+        if (has) x |= L;
+        const u64 both = U & L;
+        if (both != 0ull && ln == k) match = __builtin_ctzll(both);
+    }
+}
+
+// Transitive closures over the rows of S: C (lane k): the rows of the block
+// that take in row k directly or through others; T (lane b): the rows whose
+// pattern brings in column b of the block.
+__device__ __forceinline__ void closures(u64 x, u64 S, u64& C, u64& T) {
+    const int ln = lane();
+    C = ((S >> ln) & 1ull) ? x & above(ln) : 0ull;
+    T = x & below(ln) & S;
+    for (u64 todo = S; todo;) {
+        const int j = __builtin_ctzll(todo);
+        todo &= todo - 1ull;
+        const u64 cj = readlane64(C, j), tj = readlane64(T, j);
+        if ((C >> j) & 1ull) C |= cj;
+        if ((T >> j) & 1ull) T |= tj;
+    }
+}
+
+}  // namespace
+
+// ------------------------------------------------------------- factorisation
+
+// One workgroup of W wavefronts per block at a time.
+//
+// A block's result is a list of tiles, 64 columns each: tile ids and 64 masks
+// per tile, U beyond the block (read by later blocks) and L before it. Whole
+// tiles need no counting and no prefix sums before they are written, are read
+// as 512 consecutive bytes, and hold about half set columns on the stencils.
+template <int W>
+__global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
+    constexpr int kTasks = 4;
+    extern __shared__ u64 s_bits[];  // touched column tiles, pending blocks
+    __shared__ u64 s_xs[W][64];
+    __shared__ u64 s_tab[W][256];
+    __shared__ u64 s_C[64];
+    __shared__ uint16_t s_tile[kRangeTiles];
+    __shared__ int32_t s_rp[65];
+    // merges of long lists, shared by the wavefronts: the rows' masks, the list,
+    // (tiles << 16 | next tile), tiles done, owned
+    __shared__ u64 s_ty[kTasks][64];
+    __shared__ u64 s_toff[kTasks], s_tuse[kTasks], s_topen[kTasks];
+    __shared__ int32_t s_tblk[kTasks];
+    __shared__ uint32_t s_tnext[kTasks];
+    __shared__ int s_tdone[kTasks], s_town[kTasks];
+    __shared__ u64 s_ext, s_S, s_off, s_arena, s_arena_end;
+    __shared__ int s_item, s_active, s_stop, s_ntile, s_total;
+
+    const int tid = threadIdx.x, ln = lane(), wv = rfl(tid >> 6);
+    u64* X = a.x + (int64_t)blockIdx.x * a.x_stride;
+    const int nw = a.bit_words;
+    u64* touch = s_bits;
+    u64* pend = s_bits + nw;
+    u64* xs = s_xs[wv];
+    u64* tab = s_tab[wv];
+    if (tid == 0) s_arena = s_arena_end = 0;
+    if (tid < kTasks) {
+        s_tnext[tid] = 0;
+        s_town[tid] = 0;
+    }
+
+    for (;;) {
+        if (tid == 0) {
+            s_item = (int)atomicAdd(&a.ctl[kBmNext], 1u);
+            s_stop = ld_dev(&a.ctl[kBmAbort]) != 0u;
+            s_ext = 0;
+            s_active = 0;
+        }
+        for (int i = tid; i < 2 * nw; i += 64 * W) s_bits[i] = 0ull;
+        __syncthreads();
+        const int item = s_item;
+        if (item >= a.nblocks || s_stop) break;
+        const int32_t gb = a.items ? a.items[item] : item;
+        const int32_t jb = a.blk_job ? a.blk_job[gb] : 0;
+        const Job* J = &a.jobs[jb];
+        const int32_t n = J->n;
+        const int32_t b0 = (int32_t)J->item_base;  // first block of the matrix
+        const int32_t g = gb - b0;
+        const int32_t nr = min(64, n - 64 * g);
+        const u64 rows = nr == 64 ? ~0ull : (1ull << nr) - 1ull;
+        const int32_t* rp = J->row_ptr + 64 * (int64_t)g;
+        const int32_t* ci = J->col_idx;
+        const int32_t ntiles = (n + 63) >> 6;
+        if (tid <= nr) s_rp[tid] = rp[tid];
+        __syncthreads();
+
+        // ---- the rows' own entries
+        u64 ext = 0;
+        bool dup = false;
+        int ndiag = 0;
+        for (int32_t e = s_rp[0] + tid; e < s_rp[nr]; e += 64 * W) {
+            const int32_t w = ci[e];
+            int lo = 0, hi = nr - 1;
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (s_rp[mid] <= e) lo = mid;
+                else hi = mid - 1;
+            }
+            const u64 bit = 1ull << lo;
+            const int32_t t = w >> 6;
+            if (or_wg(&X[w], bit) & bit) dup = true;
+            if (w == 64 * g + lo) ++ndiag;
+            if (!((touch[t >> 6] >> (t & 63)) & 1ull)) atomicOr(&touch[t >> 6], 1ull << (t & 63));
+            if (t < g) {
+                ext |= bit;
+                if (!((pend[t >> 6] >> (t & 63)) & 1ull)) atomicOr(&pend[t >> 6], 1ull << (t & 63));
+            }
+        }
+        ext = or64(ext);
+        const u64 dups = __ballot(dup);
+        const u64 nd = sum64((u64)ndiag);
+        if (ln == 0) {
+            if (ext) atomicOr(&s_ext, ext);
+            if (dups) atomicOr(&a.jstats[jb].err, kErrDuplicate);
+            if (nd) atomicAdd(&a.jstats[jb].diag, nd);
+        }
+        __syncthreads();
+        if (tid < nr) or_wg(&X[64 * (int64_t)g + tid], 1ull << tid);
+        if (tid == 0) atomicOr(&touch[g >> 6], 1ull << (g & 63));
+        __syncthreads();
+
+        // words of the touched tiles in [lo, hi)
+        auto touched = [&](int wi, int lo, int hi) -> u64 {
+            if (wi >= nw) return 0ull;
+            u64 w = touch[wi];
+            const int t0 = wi * 64;
+            if (t0 < lo) w &= lo - t0 >= 64 ? 0ull : ~0ull << (lo - t0);
+            if (t0 + 64 > hi) w &= hi - t0 <= 0 ? 0ull : hi - t0 >= 64 ? ~0ull : (1ull << (hi - t0)) - 1ull;
+            return w;
+        };
+        // Lists the touched tiles of [lo, hi) (kRangeTiles ids at a time), takes
+        // room in the pool and writes their ids and the bits `keep` of their
+        // masks, ascending; the block's closures s_C are applied first where S is
+        // not empty (rows of S pass their pattern on), and the masks cleared
+        // behind a `last` list. s_off, s_total: where the list is. Unless
+        // state is 0 the list is published as (part, state): the header, then the
+        // flag behind all stores.
+        auto write_list = [&](int lo, int hi, u64 keep, u64 S, bool last, int part, uint32_t state, u64 con) -> bool {
+            const int R0 = lo / kRangeTiles, R1 = hi > lo ? (hi - 1) / kRangeTiles : R0 - 1;
+            if (wv == 0) {
+                int c = 0;
+                for (int wi = lo / 64 + ln; wi * 64 < hi; wi += 64) c += __popcll(touched(wi, lo, hi));
+                const int total = rfl((int)sum64((u64)c));
+                if (ln == 0) {
+                    s_total = total;
+                    // room from the workgroup's own stretch of the pool, 64 tiles at a time
+                    if (s_arena + (u64)total > s_arena_end) {
+                        const u64 take = (u64)max(total, 64);
+                        s_arena = atomicAdd(a.pool_tail, take);
+                        s_arena_end = s_arena + take;
+                        if (s_arena_end > (u64)a.pool_cap) {
+                            s_stop = 1;
+                            st_dev(&a.ctl[kBmAbort], (uint32_t)kBmOverflow);
+                        }
+                    }
+                    s_off = s_arena;
+                    s_arena += (u64)total;
+                    if (state) {
+                        u64* h = a.head + (int64_t)gb * kBmHeadWords + part * (kBmHeadWords / 2);
+                        st_dev(&h[0], keep);
+                        st_dev(&h[1], s_off);
+                        st_dev(&h[2], (u64)total);
+                        st_dev(&h[3], con);  // rows whose entries beyond the block others need
+                    }
+                }
+            }
+            int64_t base = 0;
+            for (int R = R0; R <= R1; ++R) {
+                if (wv == 0) {
+                    const u64 w0 = ln < kRangeTiles / 64 ? touched(R * (kRangeTiles / 64) + ln, lo, hi) : 0ull;
+                    const int c = __popcll(w0);
+                    const int inc = incl_scan(c);
+                    int o = inc - c;
+                    for (u64 w = w0; w; w &= w - 1ull) s_tile[o++] = (uint16_t)(ln * 64 + __builtin_ctzll(w));
+                    if (ln == 63) s_ntile = inc;
+                }
+                __syncthreads();
+                if (s_stop) return false;
+                const int nt = s_ntile;
+                for (int i = wv; i < nt; i += W) {
+                    const int32_t t = R * kRangeTiles + s_tile[i];
+                    u64* xp = &X[64 * (int64_t)t + ln];
+                    u64 m = ld_wg(xp);
+                    const u64 m0 = m;
+                    for (u64 q = m & S; q;) {
+                        const int k = __builtin_ctzll(q);
+                        const u64 ck = s_C[k];
+                        m |= ck;
+                        q &= ~(ck | (1ull << k));
+                    }
+                    if (last) {
+                        if (m0) *xp = 0ull;
+                    } else if (m != m0) {
+                        *xp = m;
+                    }
+                    const int64_t q = (int64_t)s_off + base + i;
+                    if (state) {
+                        if (ln == 0) st_dev(&a.tids[q], t);
+                        st_dev(&a.masks[64 * q + ln], m & keep);
+                    } else {
+                        a.masks[64 * q + ln] = m & keep;
+                        if (ln == 0) {
+                            a.tids[q] = t;
+                            a.slot[q] = atomicAdd(&a.tcount[b0 + t], 1);
+                        }
+                    }
+                }
+                base += nt;
+                if (R < R1) __syncthreads();
+            }
+            if (R0 > R1) {
+                __syncthreads();
+                if (s_stop) return false;
+            }
+            if (state) {
+                stores_done();
+                __syncthreads();
+                if (tid == 0) st_dev(&a.flag[gb], state);
+            }
+            return true;
+        };
+
+        int32_t* km = a.kmatch + 64 * (int64_t)gb;
+        const u64 s_ext0 = s_ext;
+        bool first_done = false;
+        bool stop = false;
+
+        // ---- rows that depend on no earlier block: finish and publish them now
+        if (s_ext0 != 0ull && (rows & ~s_ext0) != 0ull) {
+            u64 nc = 0;
+            if (wv == 0) {
+                u64 x = ld_wg(&X[64 * (int64_t)g + ln]);
+                u64 S = rows & ~s_ext0, C, T;
+                int match;
+                eliminate<true>(x, S, match);
+                closures(x, S, C, T);
+                s_C[ln] = C;
+                X[64 * (int64_t)g + ln] = x;
+                st_dev(&a.tcl[(int64_t)gb * 128 + ln], T);
+                st_dev(&km[ln], match >= 0 ? 64 * g + match : kNoMatch);
+                nc = __ballot(match >= 0);
+                if (ln == 0) s_S = S;
+            }
+            __syncthreads();
+            const u64 S = s_S;
+            if (S != 0ull) {
+                stop = !write_list(g + 1, ntiles, S, S, false, 0, 1u, S & ~nc);
+                first_done = true;
+            }
+        }
+
+        // ---- merge the earlier blocks that the masks name
+        uint32_t n_merge = 0, n_read = 0;
+        if (!stop && s_ext0 != 0ull) {
+            const int npw = (g + 63) >> 6;
+            uint32_t spins = 0;
+            // ORs tile q of a published list into this block's masks: for every
+            // column the masks y of the rows in `use` that hold it
+            auto merge_tile = [&](int32_t t, u64 m, const u64* y, u64 use, u64 open, int64_t hb) {
+                u64 z = 0;
+                for (u64 w = m & use; w; w &= w - 1ull) z |= y[__builtin_ctzll(w)];
+                if (t == g) {
+                    // U(k, v) with v a row of this block: a match where L(v, k) is
+                    // there too (of interest for rows k that have none yet)
+                    for (u64 w = open; w; w &= w - 1ull) {
+                        const int k = __builtin_ctzll(w);
+                        const u64 both = __ballot(((m >> k) & 1ull) && ((y[k] >> ln) & 1ull));
+                        if (both != 0ull && ln == 0) atomicMin(&a.kmatch[64 * hb + k], 64 * g + __builtin_ctzll(both));
+                    }
+                }
+                bool fresh = false;
+                if (z) fresh = (z & ~or_wg(&X[64 * (int64_t)t + ln], z)) != 0ull;
+                if (__ballot(fresh) != 0ull && ln == 0) {
+                    atomicOr(&touch[t >> 6], 1ull << (t & 63));
+                    if (t < g) atomicOr(&pend[t >> 6], 1ull << (t & 63));
+                }
+            };
+            for (;;) {
+                // tiles of a shared merge first
+                bool did = false;
+#pragma unroll
+                for (int k = 0; k < kTasks; ++k) {
+                    const uint32_t peek = (uint32_t)rfl((int)*(volatile uint32_t*)&s_tnext[k]);
+                    if ((peek & 0xFFFFu) >= (peek >> 16)) continue;
+                    uint32_t w = 0;
+                    if (ln == 0) w = atomicAdd(&s_tnext[k], 1u);
+                    w = (uint32_t)rfl((int)w);
+                    const uint32_t i = w & 0xFFFFu, nt = w >> 16;
+                    if (i >= nt) continue;
+                    wave_sync();
+                    const int64_t q = (int64_t)s_toff[k] + i;
+                    const int32_t t = rfl(ld_dev(&a.tids[q]));
+                    merge_tile(t, ld_dev(&a.masks[64 * q + ln]), s_ty[k], s_tuse[k], s_topen[k], b0 + s_tblk[k]);
+                    wave_sync();
+                    if (ln == 0 && atomicAdd(&s_tdone[k], 1) + 1 == (int)nt) {
+                        atomicExch(&s_town[k], 0);
+                        atomicSub(&s_active, 1);
+                    }
+                    ++n_read;
+                    did = true;
+                }
+                if (did) continue;
+                // Take the lowest pending block. A wavefront counts itself active
+                // before it clears a block's bit and no longer once it has merged
+                // it, and looks again after every merge: with nothing pending and
+                // nobody active the merging is done, and whoever marks a block
+                // takes it if nobody else does. (A wavefront that only looks must
+                // not count: several in step would keep each other here.)
+                int h = -1;
+                for (int w0 = 0; w0 < npw && h < 0; w0 += 64) {
+                    for (;;) {
+                        const u64 w = w0 + ln < npw ? *(volatile u64*)&pend[w0 + ln] : 0ull;
+                        const u64 nz = __ballot(w != 0ull);
+                        if (nz == 0ull) break;
+                        const int l = __builtin_ctzll(nz);
+                        const int b = __builtin_ctzll(readlane64(w, l));
+                        int got = 0;
+                        if (ln == 0) {
+                            atomicAdd(&s_active, 1);
+                            got = (int)((atomicAnd(&pend[w0 + l], ~(1ull << b)) >> b) & 1ull);
+                            if (!got) atomicSub(&s_active, 1);
+                        }
+                        if (rfl(got)) {
+                            h = (w0 + l) * 64 + b;
+                            break;
+                        }
+                    }
+                }
+                if (h < 0) {
+                    const int act = rfl(*(volatile int*)&s_active);
+                    if (act == 0 || rfl(*(volatile int*)&s_stop)) break;
+                    __builtin_amdgcn_s_sleep(2);
+                    continue;
+                }
+                wave_sync();
+                const int64_t hb = b0 + h;
+                // wait until the rows this block needs of block h are published
+                u64 y = 0;
+                uint32_t need = 1;
+                bool dead = false;
+                u64 h_off = 0, h_con = 0;
+                int h_cnt = 0, match = 0;
+                for (;;) {
+                    // one lane's view for the wavefront: a load's lanes may be
+                    // served at different times and see different publications
+                    uint32_t f = (uint32_t)rfl((int)ld_dev(&a.flag[hb]));
+                    while (f < need) {
+                        ++spins;
+                        if ((spins & 15u) == 0u) {
+                            if (spins > kSpinLimit) st_dev(&a.ctl[kBmAbort], (uint32_t)kBmStall);
+                            if (rfl((int)ld_dev(&a.ctl[kBmAbort])) != 0) {
+                                dead = true;
+                                break;
+                            }
+                        }
+                        __builtin_amdgcn_s_sleep(1);
+                        f = (uint32_t)rfl((int)ld_dev(&a.flag[hb]));
+                    }
+                    if (dead) break;
+                    asm volatile("" ::: "memory");
+                    const int part = f >= 2u ? 1 : 0;
+                    const u64* hd = a.head + hb * kBmHeadWords + part * (kBmHeadWords / 2);
+                    const u64 w = ln < 4 ? ld_dev(&hd[ln]) : 0ull;
+                    const u64 T = ld_dev(&a.tcl[hb * 128 + part * 64 + ln]);
+                    const u64 x = ld_wg(&X[64 * (int64_t)h + ln]);
+                    match = ld_dev(&a.kmatch[64 * hb + ln]);
+                    y = lane_product(x, T, xs, tab);
+                    const u64 S = readlane64(w, 0);
+                    h_off = readlane64(w, 1);
+                    h_cnt = (int)readlane64(w, 2);
+                    h_con = readlane64(w, 3);
+                    if (part == 0 && (__ballot(y != 0ull) & ~S) != 0ull) {
+                        need = 2;  // rows of the second publication are needed
+                        continue;
+                    }
+                    if (y != x) or_wg(&X[64 * (int64_t)h + ln], y);
+                    break;
+                }
+                if (dead) {
+                    if (ln == 0) {
+                        s_stop = 1;
+                        atomicSub(&s_active, 1);
+                    }
+                    break;
+                }
+                spins = 0;
+                ++n_merge;
+                const u64 have = __ballot(y != 0ull);
+                const u64 use = have & h_con;
+                // Tiles beyond the last first match of the rows in use are not
+                // needed. Only a match below this block counts: a row takes the
+                // rest from its match's row if that comes before it.
+                const u64 open = use & __ballot(match >= 64 * g);
+                int tmax = -1;
+                if ((use >> ln) & 1ull) tmax = match >= 64 * g ? kNoMatch : match >> 6;
+                tmax = rfl(max64(tmax));
+                int cnt = 0;
+                int32_t t = 0;
+                if (tmax >= 0) {
+                    for (int i0 = 0; i0 < h_cnt; i0 += 64) {
+                        const int32_t ti = i0 + ln < h_cnt ? ld_dev(&a.tids[(int64_t)h_off + i0 + ln]) : kNoMatch;
+                        if (i0 == 0) t = ti;
+                        const int c = __popcll(__ballot(ti <= tmax && ti != kNoMatch));
+                        cnt += c;
+                        if (c < 64) break;
+                    }
+                }
+                int task = -1;
+                if (cnt > 3) {
+                    if (ln == 0)
+                        for (int k = 0; k < kTasks && task < 0; ++k)
+                            if (atomicCAS(&s_town[k], 0, 1) == 0) task = k;
+                    task = rfl(task);
+                }
+                if (task >= 0) {
+                    // a long list: any wavefront takes tiles of it
+                    s_ty[task][ln] = y;
+                    if (ln == 0) {
+                        s_toff[task] = h_off;
+                        s_tuse[task] = use;
+                        s_topen[task] = open;
+                        s_tblk[task] = h;
+                        s_tdone[task] = 0;
+                    }
+                    wave_sync();
+                    if (ln == 0) atomicExch(&s_tnext[task], (uint32_t)cnt << 16);
+                    continue;
+                }
+                wave_sync();
+                xs[ln] = y;
+                wave_sync();
+                for (int i = 0; i < cnt; ++i) {
+                    const int64_t q = (int64_t)h_off + i;
+                    const int32_t ti = i < 64 ? __builtin_amdgcn_readlane(t, i) : rfl(ld_dev(&a.tids[q]));
+                    merge_tile(ti, ld_dev(&a.masks[64 * q + ln]), xs, use, open, hb);
+                }
+                n_read += (uint32_t)cnt;
+                wave_sync();
+                if (ln == 0) atomicSub(&s_active, 1);
+            }
+            __syncthreads();
+            stop = s_stop != 0;
+        }
+        if (stop) break;
+
+        // ---- the block's own rows among each other, then everything published
+        u64 own = 0, C = 0, nc = 0;
+        if (wv == 0) {
+            u64 x = ld_wg(&X[64 * (int64_t)g + ln]);
+            u64 S = rows, T;
+            int match;
+            eliminate<false>(x, S, match);
+            closures(x, S, C, T);
+            s_C[ln] = C;
+            own = x;
+            st_dev(&a.tcl[(int64_t)gb * 128 + 64 + ln], T);
+            if (!first_done) st_dev(&km[ln], match >= 0 ? 64 * g + match : kNoMatch);
+            else if (match >= 0) atomicMin(&km[ln], 64 * g + match);
+            nc = __ballot(match >= 0);
+            X[64 * (int64_t)g + ln] = 0ull;
+        }
+        __syncthreads();
+        if (!write_list(g + 1, ntiles, rows, rows, true, 1, 2u, rows & ~nc)) break;
+        const u64 u_off = s_off;
+        const int u_cnt = s_total;
+        __syncthreads();
+
+        // ---- what only later kernels read
+        if (!write_list(0, g, rows, 0ull, true, 0, 0u, 0ull)) break;
+        if (wv == 0) {
+            a.diag[64 * (int64_t)gb + ln] = own;
+            // rows of the closure: lane r, the rows of the block that r takes in
+            u64 M = 0;
+            for (int r = 0; r < 64; ++r) {
+                const u64 w = __ballot((C >> r) & 1ull);
+                if (ln == r) M = w;
+            }
+            a.lcl[64 * (int64_t)gb + ln] = M;
+            if (ln == 0) {
+                BlockRec* r = &a.rec[gb];
+                r->u_off = (int64_t)u_off;
+                r->u_cnt = u_cnt;
+                r->l_off = (int64_t)s_off;
+                r->l_cnt = s_total;
+            }
+        }
+        if (ln == 0) {
+            if (n_merge) atomicAdd(&a.jstats[jb].iterations, (u64)n_merge);
+            if (n_read) atomicAdd(&a.jstats[jb].edges_gpu, (u64)n_read * 64ull);
+        }
+        __syncthreads();
+    }
+}
+
+// -------------------------------------------------------------- row counts
+
+// Entries of L and U per row: a row's count is the popcount of a ballot over 64
+// columns' masks; each of the four wavefronts counts 16 of the block's rows.
+__global__ __launch_bounds__(kThreads) void k_bm_count(BlockArgs a) {
+    const int ln = lane(), wv = rfl(threadIdx.x >> 6);
+    if (ld_dev(&a.ctl[kBmAbort]) != 0u) return;
+    const int32_t gb = blockIdx.x;
+    const int32_t jb = a.blk_job ? a.blk_job[gb] : 0;
+    const Job* J = &a.jobs[jb];
+    const int32_t g = gb - (int32_t)J->item_base;
+    const int32_t nr = min(64, J->n - 64 * g);
+    const BlockRec rec = a.rec[gb];
+    int32_t lc = 0, uc = 0;  // lane i < 16: row 16 wv + i
+    auto add = [&](u64 m, int32_t& c) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int p = __popcll(__ballot((m >> (16 * wv + i)) & 1ull));
+            if (ln == i) c += p;
+        }
+    };
+    const u64 d = a.diag[64 * (int64_t)gb + ln];
+    add(d & above(ln), lc);
+    add(d & ~above(ln), uc);
+    for (int i = 0; i < rec.l_cnt; ++i) add(a.masks[64 * (rec.l_off + i) + ln], lc);
+    for (int i = 0; i < rec.u_cnt; ++i) add(a.masks[64 * (rec.u_off + i) + ln], uc);
+    const int r = 16 * wv + ln;
+    if (ln < 16 && r < nr) {
+        const int64_t row = J->row_base + 64 * (int64_t)g + r;
+        a.row_lcnt[row] = lc;
+        a.row_ucnt[row] = uc;
+    }
+}
+
+// ---------------------------------------------------------- L by columns
+//
+// L's tiles seen from the columns: for every block of columns the blocks of
+// rows with a tile there. k_bm_scatter puts each tile into its column block's
+// list (in the place it took during the factorisation), k_bm_lists sorts the
+// lists by row block and counts the entries of every column.
+
+__global__ __launch_bounds__(kThreads) void k_bm_scatter(BlockArgs a, BlockCols c) {
+    if (ld_dev(&a.ctl[kBmAbort]) != 0u) return;
+    const int32_t gb = blockIdx.x;
+    const int32_t jb = a.blk_job ? a.blk_job[gb] : 0;
+    const int32_t b0 = (int32_t)a.jobs[jb].item_base;
+    const BlockRec rec = a.rec[gb];
+    for (int i = threadIdx.x; i < rec.l_cnt; i += kThreads) {
+        const int64_t q = rec.l_off + i;
+        const int64_t d = c.ptr[b0 + a.tids[q]] + a.slot[q];
+        c.blk[d] = gb - b0;
+        c.tile[d] = (int32_t)q;
+    }
+}
+
+// One wavefront per block of columns. Lists of more than 64 tiles are ranked in a
+// bitmap over the row blocks (dynamic LDS: one bit and one prefix per 64 blocks).
+__global__ __launch_bounds__(64) void k_bm_lists(BlockArgs a, BlockCols c, int32_t* col_cnt) {
+    extern __shared__ u64 s_dyn[];
+    if (ld_dev(&a.ctl[kBmAbort]) != 0u) return;
+    const int ln = lane();
+    const int32_t cb = blockIdx.x;
+    const int32_t jb = a.blk_job ? a.blk_job[cb] : 0;
+    const Job* J = &a.jobs[jb];
+    const int32_t c0 = cb - (int32_t)J->item_base;
+    const int64_t e0 = c.ptr[cb], e1 = c.ptr[cb + 1];
+    const int cnt = (int)(e1 - e0);
+    int32_t sum = __popcll(a.diag[64 * (int64_t)cb + ln] & above(ln));
+    if (cnt <= 64) {
+        const int32_t b = ln < cnt ? c.blk[e0 + ln] : kNoMatch;
+        const int32_t q = ln < cnt ? c.tile[e0 + ln] : 0;
+        int rank = 0;
+        for (int i = 0; i < cnt; ++i) {
+            rank += __builtin_amdgcn_readlane(b, i) < b ? 1 : 0;
+            sum += __popcll(a.masks[64 * (int64_t)__builtin_amdgcn_readlane(q, i) + ln]);
+        }
+        if (ln < cnt) {
+            c.blk2[e0 + rank] = b;
+            c.tile2[e0 + rank] = q;
+        }
+    } else {
+        const int nw = a.bit_words;
+        u64* bits = s_dyn;
+        int32_t* pre = (int32_t*)(s_dyn + nw);
+        for (int i = ln; i < nw; i += 64) bits[i] = 0ull;
+        wave_sync();
+        for (int64_t e = e0 + ln; e < e1; e += 64) atomicOr(&bits[c.blk[e] >> 6], 1ull << (c.blk[e] & 63));
+        wave_sync();
+        int run = 0;
+        for (int i0 = 0; i0 < nw; i0 += 64) {
+            const int p = i0 + ln < nw ? __popcll(bits[i0 + ln]) : 0;
+            const int inc = incl_scan(p);
+            if (i0 + ln < nw) pre[i0 + ln] = run + inc - p;
+            run += rfl(__shfl(inc, 63, 64));
+        }
+        wave_sync();
+        for (int64_t f0 = e0; f0 < e1; f0 += 64) {
+            const int k = (int)min((int64_t)64, e1 - f0);
+            const int32_t q = ln < k ? c.tile[f0 + ln] : 0;
+            if (ln < k) {
+                const int32_t b = c.blk[f0 + ln];
+                const int64_t d = e0 + pre[b >> 6] + __popcll(bits[b >> 6] & below(b & 63));
+                c.blk2[d] = b;
+                c.tile2[d] = q;
+            }
+            for (int i = 0; i < k; ++i)
+                sum += __popcll(a.masks[64 * (int64_t)__builtin_amdgcn_readlane(q, i) + ln]);
+        }
+    }
+    const int64_t v = 64 * (int64_t)c0 + ln;
+    if (v < J->n) col_cnt[J->row_base + v] = sum;
+}
+
+// ---------------------------------------------------------------- emission
+
+// Sixteen rows (or columns) of a tile at a time: the ids of row r0 + i are the
+// set bits of a ballot over the lanes' masks, stored consecutively at the
+// position that lane i carries.
+__device__ __forceinline__ void emit16(u64 m, int r0, int32_t id, int64_t& at, int32_t* idx) {
+#pragma unroll 4
+    for (int i = 0; i < 16; ++i) {
+        const bool has = (m >> (r0 + i)) & 1ull;
+        const u64 b = __ballot(has);
+        const int64_t base = (int64_t)readlane64((u64)at, i);
+        if (has) idx[base + (int)below_count(b)] = id;
+        if (lane() == i) at += __popcll(b);
+    }
+}
+
+// Rows of U, or of L row-wise; each of the four wavefronts writes 16 of the
+// block's rows.
+template <bool upper>
+__global__ __launch_bounds__(kThreads) void k_bm_rows(BlockArgs a, const int64_t* ptr, int32_t* idx) {
+    const int ln = lane(), wv = rfl(threadIdx.x >> 6);
+    const int32_t gb = blockIdx.x;
+    const int32_t jb = a.blk_job ? a.blk_job[gb] : 0;
+    const Job* J = &a.jobs[jb];
+    const int32_t g = gb - (int32_t)J->item_base;
+    const int32_t nr = min(64, J->n - 64 * g);
+    const BlockRec rec = a.rec[gb];
+    const int r0 = 16 * wv;
+    if (r0 >= nr) return;
+    int64_t at = 0;
+    if (ln < 16 && r0 + ln < nr) at = ptr[J->row_base + 64 * (int64_t)g + r0 + ln];
+    const u64 d = a.diag[64 * (int64_t)gb + ln];
+    if (upper) emit16(d & ~above(ln), r0, 64 * g + ln, at, idx);
+    const int64_t off = upper ? rec.u_off : rec.l_off;
+    const int32_t cnt = upper ? rec.u_cnt : rec.l_cnt;
+    for (int i = 0; i < cnt; ++i) emit16(a.masks[64 * (off + i) + ln], r0, 64 * a.tids[off + i] + ln, at, idx);
+    if (!upper) emit16(d & above(ln), r0, 64 * g + ln, at, idx);
+}
+
+// Columns of L: the tiles of a block of columns by ascending row block, the rows
+// of a column being the set bits of its mask; each of the four wavefronts
+// writes 16 of the block's columns.
+__global__ __launch_bounds__(kThreads) void k_bm_cols(BlockArgs a, BlockCols c, const int64_t* l_ptr, int32_t* l_idx) {
+    const int ln = lane(), wv = rfl(threadIdx.x >> 6);
+    const int32_t cb = blockIdx.x;
+    const int32_t jb = a.blk_job ? a.blk_job[cb] : 0;
+    const Job* J = &a.jobs[jb];
+    const int32_t c0 = cb - (int32_t)J->item_base;
+    const int nc = min(16, J->n - 64 * c0 - 16 * wv);
+    if (nc <= 0) return;
+    int64_t at = 0;
+    if (ln < nc) at = l_ptr[J->row_base + 64 * (int64_t)c0 + 16 * wv + ln];
+    auto put = [&](int32_t g, u64 m) {
+#pragma unroll 4
+        for (int i = 0; i < 16; ++i) {
+            const u64 w = readlane64(m, i);
+            if (w == 0ull) continue;
+            const int64_t base = (int64_t)readlane64((u64)at, i);
+            if ((w >> ln) & 1ull) l_idx[base + (int)below_count(w)] = 64 * g + ln;
+            if (ln == i) at += __popcll(w);
+        }
+    };
+    const int col = 16 * wv + (ln & 15);  // lane i < 16: the mask of column 16 wv + i
+    put(c0, a.diag[64 * (int64_t)cb + col] & above(col));
+    for (int64_t e = c.ptr[cb]; e < c.ptr[cb + 1]; ++e)
+        put(c.blk2[e], a.masks[64 * (int64_t)c.tile2[e] + col]);
+}
+
+// ------------------------------------------------------------------- reach
+//
+// edges_alg counts, for every source s, the degrees of the vertices reachable
+// from s through vertices below s. Such a vertex v is in L(s,:) or reachable
+// from some k of L(s,:) (the largest vertex of the path), so the sources that
+// reach v are the ancestors of v in the graph of L's columns. One wavefront
+// takes 64 vertices (a block c) and carries, for one block of rows after the
+// other, the mask of c's vertices that each row reaches: rows of a block among
+// each other through the closure lcl, later blocks through L's tiles up to
+// each column's match (a row beyond the match reaches everything through it).
+// Few blocks wait at a time, so they sit in kReachTiles LDS tiles; a wavefront
+// that needs more hands its block to k_bm_reach_big.
+
+namespace {
+constexpr int kReachTiles = 8;
+constexpr int kReachWaves = 4;
+
+// the rows of block g up to (and with) a column's match
+__device__ __forceinline__ u64 upto(u64 m, int32_t g, int32_t match) {
+    if (g < (match >> 6)) return m;
+    if (g > (match >> 6)) return 0ull;
+    return m & ~above(match & 63);
+}
+
+// sum of the degrees in a mask: bit planes of the degrees, one popcount each
+__device__ __forceinline__ u64 weigh(u64 z, const u64* planes, int np) {
+    u64 s = 0;
+    for (int j = 0; j < np; ++j) s += (u64)__popcll(z & planes[j]) << j;
+    return s;
+}
+
+__device__ __forceinline__ int degree_planes(const Job* J, int32_t c, u64* planes) {
+    const int ln = lane();
+    const int64_t v = 64 * (int64_t)c + ln;
+    const uint32_t deg = v < J->n ? (uint32_t)(J->row_ptr[v + 1] - J->row_ptr[v]) : 0u;
+    const uint32_t top = (uint32_t)rfl(max64((int)deg));
+    const int np = top ? 32 - __builtin_clz(top) : 0;
+    for (int j = 0; j < np; ++j) {
+        const u64 p = __ballot((deg >> j) & 1u);
+        if (ln == 0) planes[j] = p;
+    }
+    return np;
+}
+}  // namespace
+
+__global__ __launch_bounds__(64 * kReachWaves) void k_bm_reach(BlockArgs a, BlockCols cl) {
+    __shared__ u64 s_tile[kReachWaves][kReachTiles][64];
+    __shared__ u64 s_xs[kReachWaves][64];
+    __shared__ u64 s_tab[kReachWaves][256];
+    __shared__ u64 s_planes[kReachWaves][32];
+    const int ln = lane(), wv = rfl(threadIdx.x >> 6);
+    const int32_t cb = blockIdx.x * kReachWaves + wv;
+    if (cb >= a.nblocks || ld_dev(&a.ctl[kBmAbort]) != 0u) return;
+    const int32_t jb = a.blk_job ? a.blk_job[cb] : 0;
+    const Job* J = &a.jobs[jb];
+    const int32_t b0 = (int32_t)J->item_base;
+    const int32_t c = cb - b0;
+    u64(*tile)[64] = s_tile[wv];
+    u64* planes = s_planes[wv];
+    const int np = degree_planes(J, c, planes);
+    int32_t key = kNoMatch;  // lane i < kReachTiles: block waiting in tile i
+    if (ln == 0) key = c;
+    tile[0][ln] = 64 * (int64_t)c + ln < J->n ? 1ull << ln : 0ull;
+    wave_sync();
+    u64 sum = 0;
+    bool over = false;
+    for (;;) {
+        const int32_t h = rfl(min64(key));
+        if (h == kNoMatch) break;
+        const int sl = __builtin_ctzll(__ballot(key == h));
+        const int64_t hb = b0 + h;
+        const u64 M = a.lcl[64 * hb + ln];
+        const int32_t match = a.kmatch[64 * hb + ln];
+        const int64_t e0 = cl.ptr[hb], e1 = cl.ptr[hb + 1];
+        const u64 z = lane_product(tile[sl][ln], M, s_xs[wv], s_tab[wv]);
+        if (ln == sl) key = kNoMatch;
+        sum += weigh(h == c ? z & ~(1ull << ln) : z, planes, np);
+        // later blocks, up to the last match of the columns in use
+        const int32_t gmax = rfl(max64(z != 0ull ? match >> 6 : -1));
+        for (int64_t e = e0; e < e1; ++e) {
+            const int32_t g = cl.blk2[e];
+            if (g > gmax) break;
+            const u64 m = z != 0ull ? upto(a.masks[64 * (int64_t)cl.tile2[e] + ln], g, match) : 0ull;
+            if (__ballot(m != 0ull) == 0ull) continue;
+            const u64 hit = __ballot(key == g);
+            int s2;
+            if (hit) {
+                s2 = __builtin_ctzll(hit);
+            } else {
+                const u64 fr = __ballot(ln < kReachTiles && key == kNoMatch);
+                if (fr == 0ull) {
+                    over = true;
+                    break;
+                }
+                s2 = __builtin_ctzll(fr);
+                if (ln == s2) key = g;
+                tile[s2][ln] = 0ull;
+                wave_sync();
+            }
+            for (u64 t = m; t; t &= t - 1ull) atomicOr(&tile[s2][__builtin_ctzll(t)], z);
+            wave_sync();
+        }
+        if (over) break;
+    }
+    if (over) {
+        if (ln == 0) cl.big[atomicAdd(cl.nbig, 1)] = cb;
+        return;
+    }
+    sum = sum64(sum);
+    if (ln == 0 && sum) atomicAdd(&a.jstats[jb].edges_alg, sum);
+}
+
+// The same with the waiting blocks' masks in a slot of X (all zero between
+// uses) and a bitmap of the waiting blocks in LDS.
+__global__ __launch_bounds__(64) void k_bm_reach_big(BlockArgs a, BlockCols cl) {
+    extern __shared__ u64 s_bits[];
+    __shared__ u64 s_xs[64];
+    __shared__ u64 s_tab[256];
+    __shared__ u64 s_planes[32];
+    if (ld_dev(&a.ctl[kBmAbort]) != 0u) return;
+    const int ln = lane();
+    u64* Z = a.x + (int64_t)blockIdx.x * a.x_stride;
+    const int nw = a.bit_words;
+    const int32_t total = *cl.nbig;
+    for (int32_t q = blockIdx.x; q < total; q += gridDim.x) {
+        const int32_t cb = cl.big[q];
+        const int32_t jb = a.blk_job ? a.blk_job[cb] : 0;
+        const Job* J = &a.jobs[jb];
+        const int32_t b0 = (int32_t)J->item_base;
+        const int32_t c = cb - b0;
+        for (int i = ln; i < nw; i += 64) s_bits[i] = 0ull;
+        wave_sync();
+        const int np = degree_planes(J, c, s_planes);
+        if (ln == 0) s_bits[c >> 6] = 1ull << (c & 63);
+        if (64 * (int64_t)c + ln < J->n) Z[64 * (int64_t)c + ln] = 1ull << ln;
+        wave_sync();
+        u64 sum = 0;
+        for (int w0 = c >> 6; w0 < nw;) {
+            const u64 word = s_bits[w0];
+            if (word == 0ull) {
+                ++w0;
+                continue;
+            }
+            const int32_t h = w0 * 64 + __builtin_ctzll(word);
+            wave_sync();
+            if (ln == 0) s_bits[w0] = word & (word - 1ull);
+            const int64_t hb = b0 + h;
+            u64 z = ld_wg(&Z[64 * (int64_t)h + ln]);
+            Z[64 * (int64_t)h + ln] = 0ull;
+            z = lane_product(z, a.lcl[64 * hb + ln], s_xs, s_tab);
+            sum += weigh(h == c ? z & ~(1ull << ln) : z, s_planes, np);
+            const int32_t match = a.kmatch[64 * hb + ln];
+            const int32_t gmax = rfl(max64(z != 0ull ? match >> 6 : -1));
+            for (int64_t e = cl.ptr[hb]; e < cl.ptr[hb + 1]; ++e) {
+                const int32_t g = cl.blk2[e];
+                if (g > gmax) break;
+                const u64 m = z != 0ull ? upto(a.masks[64 * (int64_t)cl.tile2[e] + ln], g, match) : 0ull;
+                if (__ballot(m != 0ull) == 0ull) continue;
+                for (u64 t = m; t; t &= t - 1ull) or_wg(&Z[64 * (int64_t)g + __builtin_ctzll(t)], z);
+                if (ln == 0) s_bits[g >> 6] |= 1ull << (g & 63);
+            }
+            wave_sync();
+        }
+        sum = sum64(sum);
+        if (ln == 0 && sum) atomicAdd(&a.jstats[jb].edges_alg, sum);
+        wave_sync();
+    }
+}
+
+// ------------------------------------------------------------------ launches
+
+// Several matrices: blocks with the same local index are taken together, so
+// that the chains of all matrices advance side by side.
+__global__ void k_bm_tables(const Job* jobs, const int32_t* ord, const int64_t* cum, int32_t max_blocks,
+                            int32_t nblocks, int32_t* items, int32_t* blk_job) {
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nblocks; i += gridDim.x * blockDim.x) {
+        int32_t lo = 0, hi = max_blocks - 1;
+        while (lo < hi) {
+            const int32_t mid = (lo + hi + 1) >> 1;
+            if (cum[mid] <= i) lo = mid;
+            else hi = mid - 1;
+        }
+        const int32_t j = ord[i - cum[lo]];
+        const int32_t b = (int32_t)jobs[j].item_base + lo;
+        items[i] = b;
+        blk_job[b] = j;
+    }
+}
+
+hipError_t launch_block_tables(const Job* jobs, const int32_t* ord, const int64_t* cum, int32_t max_blocks,
+                               int32_t nblocks, int32_t* items, int32_t* blk_job, hipStream_t st) {
+    if (nblocks <= 0) return hipSuccess;
+    const unsigned g = (unsigned)std::min<int64_t>((nblocks + 255) / 256, 1024);
+    hipLaunchKernelGGL(k_bm_tables, dim3(g), dim3(256), 0, st, jobs, ord, cum, max_blocks, nblocks, items, blk_job);
+    return hipGetLastError();
+}
+
+namespace {
+using FactorKernel = void (*)(BlockArgs);
+FactorKernel factor_kernel(int waves) {
+    return waves >= 16 ? k_bm_factor<16> : waves >= 8 ? k_bm_factor<8> : k_bm_factor<4>;
+}
+}  // namespace
+
+int32_t block_resident_groups(int cus, int waves, int bit_words) {
+    int blocks = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, factor_kernel(waves), 64 * waves,
+                                                     (size_t)bit_words * 16) != hipSuccess ||
+        blocks <= 0) {
+        (void)hipGetLastError();
+        blocks = 1;
+    }
+    return blocks * cus;
+}
+
+hipError_t launch_block_factor(const BlockArgs& a, hipStream_t st) {
+    if (a.nblocks <= 0) return hipSuccess;
+    hipLaunchKernelGGL(factor_kernel(a.waves), dim3((unsigned)a.nslots), dim3((unsigned)(64 * a.waves)),
+                       (size_t)a.bit_words * 16, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_block_counts(const BlockArgs& a, const BlockCols& c, int32_t* col_cnt, hipStream_t st) {
+    if (a.nblocks <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_bm_count, dim3((unsigned)a.nblocks), dim3(kThreads), 0, st, a);
+    hipLaunchKernelGGL(k_bm_scatter, dim3((unsigned)a.nblocks), dim3(kThreads), 0, st, a, c);
+    hipLaunchKernelGGL(k_bm_lists, dim3((unsigned)a.nblocks), dim3(64), (size_t)a.bit_words * 12 + 8, st, a, c,
+                       col_cnt);
+    return hipGetLastError();
+}
+
+hipError_t launch_block_rows(const BlockArgs& a, bool upper, const int64_t* ptr, int32_t* idx, hipStream_t st) {
+    if (a.nblocks <= 0) return hipSuccess;
+    if (upper) hipLaunchKernelGGL(k_bm_rows<true>, dim3((unsigned)a.nblocks), dim3(kThreads), 0, st, a, ptr, idx);
+    else hipLaunchKernelGGL(k_bm_rows<false>, dim3((unsigned)a.nblocks), dim3(kThreads), 0, st, a, ptr, idx);
+    return hipGetLastError();
+}
+
+hipError_t launch_block_cols(const BlockArgs& a, const BlockCols& c, const int64_t* l_ptr, int32_t* l_idx,
+                             hipStream_t st) {
+    if (a.nblocks <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_bm_cols, dim3((unsigned)a.nblocks), dim3(kThreads), 0, st, a, c, l_ptr, l_idx);
+    return hipGetLastError();
+}
+
+hipError_t launch_block_reach(const BlockArgs& a, const BlockCols& c, hipStream_t st) {
+    if (a.nblocks <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_bm_reach, dim3((unsigned)((a.nblocks + kReachWaves - 1) / kReachWaves)),
+                       dim3(64 * kReachWaves), 0, st, a, c);
+    hipLaunchKernelGGL(k_bm_reach_big, dim3((unsigned)std::min(a.nslots, 256)), dim3(64), (size_t)a.bit_words * 8, st,
+                       a, c);
+    return hipGetLastError();
+}
+
+}  // namespace gsofa

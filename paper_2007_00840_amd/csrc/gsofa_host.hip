@@ -695,16 +695,70 @@ void give_slots(std::unique_ptr<SlotSet> s) {
     }
 }
 
+// Column masks of the block path's workgroups: all zero between calls.
+struct MaskSet {
+    DBuf buf;
+    int64_t stride = 0;  // 64-bit words per workgroup
+    int32_t nslots = 0;
+};
+
+std::vector<std::unique_ptr<MaskSet>>& idle_masks() {
+    static auto* v = new std::vector<std::unique_ptr<MaskSet>>();
+    return *v;
+}
+
+std::unique_ptr<MaskSet> take_masks(int64_t stride, int32_t nslots, hipStream_t st) {
+    const int64_t words = stride * nslots;
+    if (!t_calloc) {
+        std::lock_guard<std::mutex> g(g_slot_mu);
+        auto& v = idle_masks();
+        for (size_t i = 0; i < v.size(); ++i) {
+            const int64_t have = (int64_t)(v[i]->buf.bytes / 8);
+            if (have < words || have > 4 * words + (64 << 20)) continue;
+            auto s = std::move(v[i]);
+            v.erase(v.begin() + (long)i);
+            s->buf.st = st;
+            s->buf.synced = false;
+            s->stride = stride;
+            s->nslots = nslots;
+            return s;
+        }
+    }
+    auto s = std::make_unique<MaskSet>();
+    s->buf = DBuf((size_t)words * 8);
+    s->stride = stride;
+    s->nslots = nslots;
+    chk(launch_zero_i32(s->buf.as<int32_t>(), words * 2, st));
+    return s;
+}
+
+// Called once the launches that used the masks have completed and left them zero.
+void give_masks(std::unique_ptr<MaskSet> s) {
+    s->buf.synced = true;
+    if (s->buf.ca) return;
+    std::unique_ptr<MaskSet> drop;
+    std::lock_guard<std::mutex> g(g_slot_mu);
+    auto& v = idle_masks();
+    v.push_back(std::move(s));
+    if (v.size() > 4) {
+        drop = std::move(v.front());
+        v.erase(v.begin());
+    }
+}
+
 void drop_idle_slots() {
     std::vector<std::unique_ptr<SlotSet>> drop;
+    std::vector<std::unique_ptr<MaskSet>> drop_masks;
     std::lock_guard<std::mutex> g(g_slot_mu);
     drop.swap(idle_slots());
+    drop_masks.swap(idle_masks());
 }
 
 size_t idle_slot_bytes() {
     std::lock_guard<std::mutex> g(g_slot_mu);
     size_t t = 0;
     for (auto& s : idle_slots()) t += s->buf.bytes;
+    for (auto& s : idle_masks()) t += s->buf.bytes;
     return t;
 }
 
@@ -714,23 +768,24 @@ struct DeviceInfo {
     size_t reclaimable = 0;  // idle memory this library caches and gives back on demand
 };
 
-DeviceInfo device_info() {
-    DeviceInfo d;
+// compute units of the current device, queried once per device
+int device_cus() {
     int dev = 0;
     chk(hipGetDevice(&dev));
-    // compute-unit counts per device, queried once
     static std::mutex mu;
     static std::map<int, int> cus;
-    {
-        std::lock_guard<std::mutex> g(mu);
-        auto it = cus.find(dev);
-        if (it != cus.end()) d.cus = it->second;
-        else {
-            int c = 0;
-            chk(hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev));
-            cus[dev] = d.cus = c;
-        }
-    }
+    std::lock_guard<std::mutex> g(mu);
+    auto it = cus.find(dev);
+    if (it != cus.end()) return it->second;
+    int c = 0;
+    chk(hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev));
+    cus[dev] = c;
+    return c;
+}
+
+DeviceInfo device_info() {
+    DeviceInfo d;
+    d.cus = device_cus();
     chk(hipMemGetInfo(&d.free_b, &d.total_b));
     d.reclaimable = cache().idle_bytes() + idle_slot_bytes();
     return d;
@@ -784,6 +839,9 @@ struct MatIn {
 
 // Largest order of a one-matrix call that launches its phases eagerly.
 constexpr int64_t kEagerMaxRows = 65536;
+
+// Mapping code of the block path (gsofa_stats.mapping).
+constexpr int32_t kMapBlocks = 7;
 
 // Calls with fewer sources are latency-bound and use the defaults untuned.
 constexpr int64_t kTuneMinSources = 65536;
@@ -905,6 +963,16 @@ struct EngineOut {
     std::vector<int> job_status;
 };
 
+// Tiles per 64-row block of the block path, per size class: sizes the pool of
+// later calls. A class not seen yet starts at kBlockTiles (the 64^3 27-point
+// stencil needs 61 a block, batch members 14, the 1000^2 9-point stencil 16); a pool
+// that overflows all the same is grown and the call's launch repeated.
+constexpr double kBlockTiles = 80.0;
+std::map<TuneKey, double>& block_ratios() {
+    static auto* m = new std::map<TuneKey, double>();
+    return *m;
+}
+
 // Per-launch fill-ratio memory used to size the output pool of later calls.
 std::atomic<double> g_fill_ratio{48.0};
 // The same per size class (the tuner's key): a batch of small 3D stencils fills
@@ -984,6 +1052,7 @@ __global__ void k_rebase_ptr(int32_t njobs, const int64_t* job_row_base, const i
 struct YieldHooks {
     uint32_t* flag = nullptr;
     std::function<void()> enqueued, finished, before_resume, before_traverse;
+    bool sources_set = false;  // the server's options name the sources in flight
 };
 
 struct Engine {
@@ -1125,6 +1194,14 @@ struct Engine {
             if (any_bad) return finish_failed(jstat, t0);
         }
 
+        // ---- the block path, where nothing asks for the per-source traversal
+        const TuneKey key{device_cus(), ceil_log2(N), ceil_log2(std::max<int64_t>(total_nnz * 4 / std::max<int64_t>(nrows, 1), 1)),
+                          nj > 1 ? ceil_log2(nj) : 0};
+        if (blocks_apply(N, key)) {
+            int rc = GSOFA_OK;
+            if (run_blocks(jobs, row_base, nnz, jstat, nrows, total_nnz, N, key, h2d, t0, rc)) return rc;
+        }
+
         // ---- plan the concurrent sources
         const SlotLayout lay = slot_layout(N);
         const DeviceInfo di = device_info();
@@ -1157,8 +1234,6 @@ struct Engine {
         };
         int mapping = choose_mapping(plan.flags, plan.window);
         double t_tune = 0;
-        const TuneKey key{di.cus, ceil_log2(N), ceil_log2(std::max<int64_t>(total_nnz * 4 / std::max<int64_t>(nrows, 1), 1)),
-                          nj > 1 ? ceil_log2(nj) : 0};
         const double fill_ratio = fill_ratio_for(key);
         if (plan.window_auto) {
             bool found = false;
@@ -1629,7 +1704,7 @@ struct Engine {
         if (have_sn) {
             const hipStream_t s = ph_sn.stream();
             chk(launch_supernodes(rs, nbk, d_bf, d_bl, u_ptr.as<int64_t>(), l_rptr.as<int64_t>(),
-                                  l_ridx.as<int32_t>(), is_start.as<int32_t>(), s));
+                                  l_ridx.as<int32_t>(), false, is_start.as<int32_t>(), s));
             chk(launch_scan_counts(is_start.as<int32_t>(), nullptr, nrows, start_scan.as<int64_t>(),
                                    scan_scr.as<int64_t>(), s));
             chk(launch_supernode_assemble(rs, nj, is_start.as<int32_t>(), start_scan.as<int64_t>(),
@@ -1679,11 +1754,61 @@ struct Engine {
         chk(hipEventElapsedTime(&t_emit, ev[1], ev[2]));
         chk(hipEventElapsedTime(&t_sn, ev[2], ev[3]));
 
+        std::vector<JobStats> js(nj);
+        for (int32_t j = 0; j < nj; ++j) js[j] = hst[jt_of[j]];
+        gsofa_stats cs{};
+        cs.concurrent_sources = budget_mode ? budget_max_c : ta.nslots;
+        cs.peak_device_bytes =
+            (uint64_t)((budget_mode ? budget_peak_slots : nslots * lay.bytes_per_slot) + pool_cap * 4 + nrows * 48 +
+                       (nnz_u + 3 * nnz_l) * 4);
+        cs.t_traverse_ms = t_trav;
+        cs.t_emit_ms = t_emit;
+        cs.t_supernode_ms = t_sn;
+        cs.window = plan.window;
+        cs.mapping = mapping;
+        cs.t_tune_ms = t_tune;
+        cs.launches = n_launches;
+        Factors f;
+        f.u_ptr = std::move(u_ptr);
+        f.u_idx = std::move(u_idx);
+        f.l_ptr = l_csr ? std::move(l_rptr) : std::move(l_cptr);
+        f.l_idx = l_csr ? std::move(l_ridx) : std::move(l_cidx);
+        f.u_ptr_loc = std::move(u_ptr_loc);
+        f.l_ptr_loc = std::move(l_ptr_loc);
+        f.xsup = std::move(xsup_all);
+        f.supno = std::move(supno_all);
+        f.nnz_u = nnz_u;
+        f.nnz_l = nnz_l;
+        return finish(f, h_b.as<int64_t>(), jstat, js, nnz, row_base, nrows, cs, t0);
+    }
+
+    // The factors of every matrix of a call, in the call's row space: U row-wise,
+    // L as asked for. With several matrices the *_loc arrays hold each one's own
+    // pointers (starting at 0) side by side.
+    struct Factors {
+        DBuf u_ptr, u_idx, l_ptr, l_idx, u_ptr_loc, l_ptr_loc, xsup, supno;
+        int64_t nnz_u = 0, nnz_l = 0;
+    };
+
+    // Results from the factors: host copies or the device arrays themselves.
+    // bounds: values of u_ptr, l_ptr and the supernode scan at the matrix
+    // boundaries (nj + 1 each). js: the statistics per matrix; cs: the call's.
+    int finish(Factors& f, const int64_t* bounds, std::vector<int>& jstat, const std::vector<JobStats>& js,
+               const std::vector<int64_t>& nnz, const std::vector<int64_t>& row_base, int64_t nrows,
+               const gsofa_stats& cs, double t0) {
+        const int32_t nj = (int32_t)mats.size();
+        const bool want_sn = (plan.flags & GSOFA_NO_SUPERNODES) == 0;
+        const bool have_sn = want_sn && nrows > 0;
+        const int64_t nnz_u = f.nnz_u, nnz_l = f.nnz_l;
+        DBuf &u_idx = f.u_idx, &xsup_all = f.xsup, &supno_all = f.supno;
+        const int64_t* Up_loc = (nj > 1 ? f.u_ptr_loc : f.u_ptr).as<int64_t>();
+        const int64_t* Lp_loc = (nj > 1 ? f.l_ptr_loc : f.l_ptr).as<int64_t>();
+        const int32_t* Li = f.l_idx.as<int32_t>();
         // ---- results
         const bool dev_out = (plan.flags & GSOFA_RESULT_ON_DEVICE) != 0;
         std::vector<int64_t> ujb(nj + 1), ljb(nj + 1), sjb(nj + 1, 0);
         {
-            const int64_t* hb = h_b.as<int64_t>();
+            const int64_t* hb = bounds;
             for (int32_t j = 0; j <= nj; ++j) {
                 ujb[j] = hb[j];
                 ljb[j] = hb[nj + 1 + j];
@@ -1780,32 +1905,21 @@ struct Engine {
         for (int32_t j = 0; j < nj; ++j) {
             gsofa_result* r = new_result();
             results[j] = r;
-            const int32_t q = jt_of[j];
             r->n = mats[j].n;
             r->flags = plan.flags;
+            r->stats = cs;
             r->stats.status = jstat[j];
-            r->stats.edges_alg = hst[q].edges_alg;
-            r->stats.edges_gpu = hst[q].edges_gpu;
-            r->stats.iterations = hst[q].iterations;
-            r->stats.windows = hst[q].windows;
-            r->stats.concurrent_sources = budget_mode ? budget_max_c : ta.nslots;
-            r->stats.peak_device_bytes =
-                (uint64_t)((budget_mode ? budget_peak_slots : nslots * lay.bytes_per_slot) + pool_cap * 4 + nrows * 48 +
-                           (nnz_u + 3 * nnz_l) * 4);
-            r->stats.t_traverse_ms = t_trav;
-            r->stats.t_emit_ms = t_emit;
-            r->stats.t_supernode_ms = t_sn;
-            r->stats.window = plan.window;
-            r->stats.mapping = mapping;
-            r->stats.t_tune_ms = t_tune;
-            r->stats.launches = n_launches;
-            r->stats.spilled_entries = hst[q].spilled;
+            r->stats.edges_alg = js[j].edges_alg;
+            r->stats.edges_gpu = js[j].edges_gpu;
+            r->stats.iterations = js[j].iterations;
+            r->stats.windows = js[j].windows;
+            r->stats.spilled_entries = js[j].spilled;
             if (jstat[j] != GSOFA_OK) continue;
             const int64_t n = mats[j].n, b = row_base[j];
             r->nnz_a = nnz[j];
             r->nnz_u = ujb[j + 1] - ujb[j];
             r->nnz_l = ljb[j + 1] - ljb[j];
-            r->fills = r->nnz_u + r->nnz_l - (nnz[j] + n - (int64_t)hst[q].diag);
+            r->fills = r->nnz_u + r->nnz_l - (nnz[j] + n - (int64_t)js[j].diag);
             r->nsuper = want_sn ? (int32_t)(sjb[j + 1] - sjb[j]) : 0;
             auto* own = static_cast<ResultOwner*>(r->internal_);
             if (!dev_out) {
@@ -1832,22 +1946,10 @@ struct Engine {
             }
         }
         if (dev_out) {
-            for (DBuf* db : {&u_idx, &u_ptr, &l_rptr, &l_ridx, &l_cptr, &l_cidx, &xsup_all, &supno_all,
-                             &u_ptr_loc, &l_ptr_loc})
+            for (DBuf* db : {&f.u_idx, &f.u_ptr, &f.l_ptr, &f.l_idx, &f.xsup, &f.supno, &f.u_ptr_loc, &f.l_ptr_loc}) {
                 db->synced = true;
-            keep->push_back(std::move(u_idx));
-            keep->push_back(std::move(u_ptr));
-            if (l_csr) {
-                keep->push_back(std::move(l_rptr));
-                keep->push_back(std::move(l_ridx));
-            } else {
-                keep->push_back(std::move(l_cptr));
-                keep->push_back(std::move(l_cidx));
+                keep->push_back(std::move(*db));
             }
-            keep->push_back(std::move(xsup_all));
-            keep->push_back(std::move(supno_all));
-            keep->push_back(std::move(u_ptr_loc));
-            keep->push_back(std::move(l_ptr_loc));
         }
         const double t1 = now_ms();
         int first_bad = GSOFA_OK;
@@ -1856,6 +1958,358 @@ struct Engine {
             if (jstat[j] != GSOFA_OK && first_bad == GSOFA_OK) first_bad = jstat[j];
         }
         return first_bad;
+    }
+
+    // Whether the block path may take the call: no option names a traversal
+    // (window, sources in flight, mapping, ablation), none is tuned for its size
+    // class, and the order is within the bitmaps of the kernels.
+    bool blocks_apply(int64_t N, const TuneKey& key) const {
+        if (!plan.window_auto || (plan.flags & GSOFA_TUNE_NOW) || N > kBlockMaxRows) return false;
+        if (yh && yh->sources_set) return false;
+        std::lock_guard<std::mutex> lk(g_tune_mu);
+        return tune_table().count(key) == 0;
+    }
+
+    // Wavefronts per block. Sixteen shorten a block's own work (up to 95 tiles on
+    // the 64^3 27-point stencil: 7.5 ms with sixteen, 9.5 with four), four put more
+    // blocks in flight, which counts where the blocks are many and their chains
+    // short (1000^2 9-point, 15,625 blocks: 4.7 ms with four, 7.5 with sixteen; 512
+    // batch members, 20,000 blocks: 3.3 and 4.1). 100,000 rows of a 2D stencil
+    // (1,561 blocks) take 1.09 and 1.02 ms.
+    static int32_t block_waves(int64_t nblocks) { return nblocks <= 8192 ? 16 : 4; }
+
+    // The block path (gsofa_blocks.hip). False: the call's memory budget does not
+    // hold it, the general path takes the call.
+    template <typename Upload>
+    bool run_blocks(const std::vector<Job>& jobs, const std::vector<int64_t>& row_base, const std::vector<int64_t>& nnz,
+                    std::vector<int>& jstat, int64_t nrows, int64_t total_nnz, int64_t N, const TuneKey& key,
+                    Upload& h2d, double t0, int& rc) {
+        const int32_t nj = (int32_t)mats.size();
+        // blocks of all matrices side by side
+        std::vector<Job> jt(nj);
+        int64_t nblocks = 0;
+        for (int32_t j = 0; j < nj; ++j) {
+            jt[j] = jobs[j];
+            jt[j].n = mats[j].n;
+            jt[j].row_base = row_base[j];
+            jt[j].item_base = nblocks;
+            nblocks += (mats[j].n + 63) / 64;
+        }
+        if (nblocks > 0x7FFFFF00ll) return false;
+        const int64_t max_blocks = (N + 63) / 64;
+        const int32_t words = (int32_t)((max_blocks + 63) / 64);
+        const int64_t stride = max_blocks * 64;
+        // workgroups in flight: all resident ones, at most 8 GiB of column masks
+        // (the 1000^2 stencil's 1,024 workgroups fill that); a served request
+        // takes the part of them that its traversal slots are of all
+        const int32_t waves = block_waves(nblocks);
+        int64_t ns = block_resident_groups(device_cus(), waves, words);
+        if (plan.nslots > 0) ns = std::min<int64_t>(ns, ns * plan.nslots / traverse_resident_slots(device_cus(), 0));
+        ns = std::min<int64_t>(ns, std::max<int64_t>(nblocks, 1));
+        ns = std::max<int64_t>(1, std::min<int64_t>(ns, (int64_t(1) << 30) / stride));
+        double ratio = kBlockTiles;
+        {
+            std::lock_guard<std::mutex> g(g_fill_mu);
+            auto it = block_ratios().find(key);
+            if (it != block_ratios().end()) ratio = it->second;
+        }
+        int64_t cap = (int64_t)(ratio * 1.15 * (double)nblocks) + 64 * ns + 64;
+        constexpr int64_t kPerBlock = 8 * kBmHeadWords + 1024 + 256 + 512 + 512 + sizeof(BlockRec) + 16;
+        auto need = [&](int64_t tiles) {
+            return fixed_bytes(nrows, total_nnz) + nrows * 64 + nblocks * kPerBlock + ns * stride * 8 + tiles * 540 + 24 * total_nnz;
+        };
+        auto fits = [&](int64_t tiles) {
+            if (plan.budget > 0) return need(tiles) <= plan.budget;
+            if (need(tiles) < (int64_t(4) << 30)) return true;
+            const DeviceInfo di = device_info();
+            return need(tiles) <= (int64_t)((double)(di.free_b + di.reclaimable) * 0.9);
+        };
+        while (!fits(cap) && ns > 64) ns /= 2;
+        if (!fits(cap)) return false;
+
+        const bool want_sn = (plan.flags & GSOFA_NO_SUPERNODES) == 0;
+        const bool have_sn = want_sn && nrows > 0;
+        const bool l_csr = (plan.flags & GSOFA_L_CSR) != 0;
+        const bool graphs = (plan.flags & GSOFA_EAGER) == 0 && !(nj == 1 && N <= kEagerMaxRows);
+        const int64_t nr1 = std::max<int64_t>(nrows, 1), nb1 = std::max<int64_t>(nblocks, 1);
+        auto up16 = [](int64_t b) { return (b + 15) & ~int64_t(15); };
+
+        // small host tables in one upload: jobs, matrix bounds, block order,
+        // supernode blocks
+        std::vector<int64_t> bf;
+        std::vector<int32_t> bl;
+        if (have_sn)
+            for (int32_t j = 0; j < nj; ++j) {
+                const int64_t M = plan.max_super > 0 ? plan.max_super : std::max<int64_t>(mats[j].n, 1);
+                for (int64_t b = 0; b < mats[j].n; b += M) {
+                    bf.push_back(row_base[j] + b);
+                    bl.push_back((int32_t)std::min<int64_t>(M, mats[j].n - b));
+                }
+            }
+        const int64_t nbk = (int64_t)bf.size();
+        const int64_t o_jn = up16((int64_t)sizeof(Job) * nj), o_jrb = o_jn + up16(4 * (int64_t)nj),
+                      o_ord = o_jrb + up16(8 * (int64_t)nj), o_cum = o_ord + up16(4 * (int64_t)nj),
+                      o_bf = o_cum + up16(8 * (max_blocks + 1)), o_bl = o_bf + up16(8 * nbk),
+                      up_bytes = o_bl + up16(4 * nbk) + 16;
+        PinnedBuf h_up((size_t)up_bytes);
+        DBuf d_up((size_t)up_bytes);
+        {
+            char* c = h_up.as<char>();
+            std::memcpy(c, jt.data(), sizeof(Job) * (size_t)nj);
+            int32_t* jn = reinterpret_cast<int32_t*>(c + o_jn);
+            int64_t* jrb = reinterpret_cast<int64_t*>(c + o_jrb);
+            int32_t* ord = reinterpret_cast<int32_t*>(c + o_ord);
+            int64_t* cum = reinterpret_cast<int64_t*>(c + o_cum);
+            for (int32_t j = 0; j < nj; ++j) {
+                jn[j] = mats[j].n;
+                jrb[j] = row_base[j];
+                ord[j] = j;
+            }
+            if (nj > 1) {
+                std::stable_sort(ord, ord + nj, [&](int32_t x, int32_t y) { return mats[x].n > mats[y].n; });
+                int64_t at = 0, m = nj;  // m matrices have more than b blocks
+                for (int64_t b = 0; b <= max_blocks; ++b) {
+                    cum[b] = at;
+                    while (m > 0 && (mats[ord[m - 1]].n + 63) / 64 <= b) --m;
+                    at += m;
+                }
+            }
+            if (nbk) {
+                std::memcpy(c + o_bf, bf.data(), 8 * (size_t)nbk);
+                std::memcpy(c + o_bl, bl.data(), 4 * (size_t)nbk);
+            }
+        }
+        char* const du = d_up.as<char>();
+        const Job* d_jobs = reinterpret_cast<const Job*>(du);
+        const int32_t* d_jn = reinterpret_cast<const int32_t*>(du + o_jn);
+        const int64_t* d_jrb = reinterpret_cast<const int64_t*>(du + o_jrb);
+        const int64_t* d_bf = reinterpret_cast<const int64_t*>(du + o_bf);
+        const int32_t* d_bl = reinterpret_cast<const int32_t*>(du + o_bl);
+
+        // arrays cleared before the factorisation: control words, tile counts,
+        // flags, per-matrix statistics
+        const int64_t z_cnt = 64, z_flag = z_cnt + up16(4 * nb1), z_js = z_flag + up16(4 * nb1),
+                      z_bytes = z_js + up16((int64_t)sizeof(JobStats) * std::max(nj, 1));
+        DBuf zero((size_t)z_bytes);
+        uint32_t* d_ctl = zero.as<uint32_t>();  // [0] next block, [1] abort, [4] reach list, [8..9] pool tail
+        JobStats* d_js = reinterpret_cast<JobStats*>(zero.as<char>() + z_js);
+        DBuf head(8 * kBmHeadWords * (size_t)nb1), tcl(1024 * (size_t)nb1), kmatch(256 * (size_t)nb1),
+            diag(512 * (size_t)nb1), lcl(512 * (size_t)nb1), rec(sizeof(BlockRec) * (size_t)nb1);
+        DBuf row_ucnt(4 * (size_t)nr1), row_lcnt(4 * (size_t)nr1), col_cnt(4 * (size_t)nr1);
+        DBuf u_ptr(8 * (size_t)(nrows + 1)), l_ptr(8 * (size_t)(nrows + 1)), list_ptr(8 * (size_t)(nb1 + 1));
+        DBuf scan_scr(8 * (size_t)scan_scratch_elems(nrows + 1) + 64);
+        DBuf items, blk_job, row_job, big(4 * (size_t)nb1);
+        if (nj > 1) {
+            items = DBuf(4 * (size_t)nb1);
+            blk_job = DBuf(4 * (size_t)nb1);
+            row_job = DBuf(4 * (size_t)nr1);
+        }
+        PinnedBuf h_st((size_t)(64 + 32 + sizeof(JobStats) * (size_t)std::max(nj, 1)));
+        uint32_t* h_ctl = h_st.as<uint32_t>();
+        int64_t* h_tot = reinterpret_cast<int64_t*>(h_st.as<char>() + 64);
+        JobStats* h_js = reinterpret_cast<JobStats*>(h_st.as<char>() + 96);
+        EventSet ev;
+
+        auto masks = take_masks(stride, (int32_t)ns, st);
+        BlockArgs ba{};
+        ba.jobs = d_jobs;
+        ba.blk_job = blk_job.as<int32_t>();
+        ba.items = items.as<int32_t>();
+        ba.nblocks = (int32_t)nblocks;
+        ba.nslots = masks->nslots;
+        ba.waves = waves;
+        ba.x = masks->buf.as<unsigned long long>();
+        ba.x_stride = stride;
+        ba.bit_words = words;
+        ba.ctl = d_ctl;
+        ba.flag = reinterpret_cast<uint32_t*>(zero.as<char>() + z_flag);
+        ba.head = head.as<unsigned long long>();
+        ba.tcl = tcl.as<unsigned long long>();
+        ba.kmatch = kmatch.as<int32_t>();
+        ba.diag = diag.as<unsigned long long>();
+        ba.lcl = lcl.as<unsigned long long>();
+        ba.rec = rec.as<BlockRec>();
+        ba.pool_tail = reinterpret_cast<unsigned long long*>(d_ctl + 8);
+        ba.tcount = reinterpret_cast<int32_t*>(zero.as<char>() + z_cnt);
+        ba.row_ucnt = row_ucnt.as<int32_t>();
+        ba.row_lcnt = row_lcnt.as<int32_t>();
+        ba.jstats = d_js;
+
+        if (yh && yh->before_traverse) yh->before_traverse();
+        chk(hipEventRecord(ev[0], st));
+        int32_t launches = 0;
+        DBuf tiles, tabs;  // tabs: tile ids, list places, lists unsorted and sorted
+        BlockCols bc{};
+        bc.ptr = list_ptr.as<int64_t>();
+        bc.big = big.as<int32_t>();
+        bc.nbig = reinterpret_cast<int32_t*>(d_ctl + 4);
+        for (;;) {
+            if (cap > 0x7FFFFFFFll) {
+                chk(hipStreamSynchronize(st));
+                give_masks(std::move(masks));
+                if (yh && yh->finished) yh->finished();
+                return false;
+            }
+            tiles = DBuf(512 * (size_t)cap);
+            tabs = DBuf(24 * (size_t)cap);
+            ba.masks = tiles.as<unsigned long long>();
+            ba.tids = tabs.as<int32_t>();
+            ba.slot = ba.tids + cap;
+            bc.blk = ba.tids + 2 * cap;
+            bc.tile = ba.tids + 3 * cap;
+            bc.blk2 = ba.tids + 4 * cap;
+            bc.tile2 = ba.tids + 5 * cap;
+            ba.pool_cap = cap;
+            {
+                Phase ph(kPhaseTraverse, graphs, st);
+                const hipStream_t s = ph.stream();
+                h2d(d_up.p, h_up.p, (size_t)up_bytes, s, true);
+                chk(launch_zero_i32(zero.as<int32_t>(), z_bytes / 4, s));
+                if (nj > 1) {
+                    chk(launch_block_tables(d_jobs, reinterpret_cast<const int32_t*>(du + o_ord),
+                                            reinterpret_cast<const int64_t*>(du + o_cum), (int32_t)max_blocks,
+                                            (int32_t)nblocks, items.as<int32_t>(), blk_job.as<int32_t>(), s));
+                    chk(launch_row_job(d_jobs, nj, N, row_job.as<int32_t>(), s));
+                }
+                chk(launch_block_factor(ba, s));
+                chk(launch_scan_counts(ba.tcount, nullptr, nblocks, list_ptr.as<int64_t>(), scan_scr.as<int64_t>(), s));
+                chk(launch_block_counts(ba, bc, col_cnt.as<int32_t>(), s));
+                chk(launch_scan_counts(row_ucnt.as<int32_t>(), nullptr, nrows, u_ptr.as<int64_t>(),
+                                       scan_scr.as<int64_t>(), s));
+                chk(launch_scan_counts(l_csr ? row_lcnt.as<int32_t>() : col_cnt.as<int32_t>(), nullptr, nrows,
+                                       l_ptr.as<int64_t>(), scan_scr.as<int64_t>(), s));
+                chk(launch_copy_to_host(h_ctl, d_ctl, 64, s));
+                chk(launch_copy_to_host(h_tot, u_ptr.as<int64_t>() + nrows, 8, s));
+                chk(launch_copy_to_host(h_tot + 1, l_ptr.as<int64_t>() + nrows, 8, s));
+                chk(launch_copy_to_host(h_js, d_js, sizeof(JobStats) * (size_t)nj, s));
+                ph.launch();
+                ++launches;
+                if (yh && yh->enqueued) yh->enqueued();
+                chk(hipEventRecord(ev[4], st));
+                chk(hipStreamSynchronize(st));
+                ph.done();
+            }
+            if (h_ctl[kBmAbort] == 0) break;
+            // an aborted launch leaves masks behind: clear them for the next one
+            chk(launch_zero_i32(masks->buf.as<int32_t>(), masks->stride * masks->nslots * 2, st));
+            if (h_ctl[kBmAbort] != kBmOverflow) throw HipError{hipErrorLaunchTimeOut};
+            tiles.reset();
+            tabs.reset();
+            cap = 4 * std::max<int64_t>(cap, (int64_t)*reinterpret_cast<unsigned long long*>(h_ctl + 8));
+            if (!fits(cap)) {
+                chk(hipStreamSynchronize(st));
+                give_masks(std::move(masks));
+                if (yh && yh->finished) yh->finished();
+                return false;
+            }
+        }
+        if (yh && yh->finished) yh->finished();
+        if (nblocks > 0) {
+            const double used = (double)*reinterpret_cast<unsigned long long*>(h_ctl + 8);
+            std::lock_guard<std::mutex> g(g_fill_mu);
+            block_ratios()[key] = std::max(4.0, used / (double)nblocks);
+        }
+        for (int32_t j = 0; j < nj; ++j)
+            if (h_js[j].err & kErrDuplicate) jstat[j] = GSOFA_EINVAL;
+        const int64_t nnz_u = h_tot[0], nnz_l = h_tot[1];
+        if (total_nnz > 0) note_fill_ratio(key, std::max(4.0, (double)(nnz_u + nnz_l) / (double)total_nnz));
+        chk(hipEventRecord(ev[1], st));
+
+        // ---- rows of U, columns (or rows) of L, the reach counts, supernodes
+        Factors f;
+        f.u_idx = DBuf(4 * (size_t)std::max<int64_t>(nnz_u, 1));
+        f.l_idx = DBuf(4 * (size_t)std::max<int64_t>(nnz_l, 1));
+        RowSpace rs{nrows, nullptr, nullptr};
+        if (nj > 1) {
+            rs.row_job = row_job.as<int32_t>();
+            rs.job_row_base = d_jrb;
+        }
+        DBuf is_start, start_scan;
+        if (have_sn) {
+            is_start = DBuf(4 * (size_t)nrows);
+            start_scan = DBuf(8 * (size_t)(nrows + 1));
+            f.xsup = DBuf(4 * (size_t)(nrows + nj));
+            f.supno = DBuf(4 * (size_t)nrows);
+        }
+        if (nj > 1) {
+            f.u_ptr_loc = DBuf(8 * (size_t)(nrows + nj));
+            f.l_ptr_loc = DBuf(8 * (size_t)(nrows + nj));
+        }
+        DBuf d_b(8 * 3 * (size_t)(nj + 1));
+        PinnedBuf h_b(8 * 3 * (size_t)(nj + 1));
+
+        Phase ph_emit(kPhaseSort, graphs, st);
+        {
+            const hipStream_t s = ph_emit.stream();
+            chk(launch_block_rows(ba, true, u_ptr.as<int64_t>(), f.u_idx.as<int32_t>(), s));
+            if (l_csr) chk(launch_block_rows(ba, false, l_ptr.as<int64_t>(), f.l_idx.as<int32_t>(), s));
+            else chk(launch_block_cols(ba, bc, l_ptr.as<int64_t>(), f.l_idx.as<int32_t>(), s));
+            chk(launch_block_reach(ba, bc, s));
+            chk(launch_copy_to_host(h_js, d_js, sizeof(JobStats) * (size_t)nj, s));
+            ph_emit.launch();
+        }
+        chk(hipEventRecord(ev[2], st));
+        Phase ph_sn(kPhaseSupernodes, graphs, st);
+        {
+            const hipStream_t s = ph_sn.stream();
+            if (have_sn) {
+                chk(launch_supernodes(rs, nbk, d_bf, d_bl, u_ptr.as<int64_t>(), l_ptr.as<int64_t>(),
+                                      f.l_idx.as<int32_t>(), !l_csr, is_start.as<int32_t>(), s));
+                chk(launch_scan_counts(is_start.as<int32_t>(), nullptr, nrows, start_scan.as<int64_t>(),
+                                       scan_scr.as<int64_t>(), s));
+                chk(launch_supernode_assemble(rs, nj, is_start.as<int32_t>(), start_scan.as<int64_t>(),
+                                              f.xsup.as<int32_t>(), f.supno.as<int32_t>(), s));
+                chk(launch_supernode_terminals(nj, d_jrb, d_jn, start_scan.as<int64_t>(), f.xsup.as<int32_t>(), s));
+            }
+            if (nj > 1) {
+                const unsigned gx = (unsigned)std::min<int64_t>((N + 256) / 256, 64);
+                hipLaunchKernelGGL(k_rebase_ptr, dim3(gx, nj), dim3(256), 0, s, nj, d_jrb, d_jn, u_ptr.as<int64_t>(),
+                                   f.u_ptr_loc.as<int64_t>());
+                hipLaunchKernelGGL(k_rebase_ptr, dim3(gx, nj), dim3(256), 0, s, nj, d_jrb, d_jn, l_ptr.as<int64_t>(),
+                                   f.l_ptr_loc.as<int64_t>());
+            }
+            const dim3 gb((nj + 1 + 255) / 256);
+            hipLaunchKernelGGL(k_gather_bounds, gb, dim3(256), 0, s, nj, d_jrb, nrows, u_ptr.as<int64_t>(),
+                               d_b.as<int64_t>());
+            hipLaunchKernelGGL(k_gather_bounds, gb, dim3(256), 0, s, nj, d_jrb, nrows, l_ptr.as<int64_t>(),
+                               d_b.as<int64_t>() + (nj + 1));
+            if (have_sn)
+                hipLaunchKernelGGL(k_gather_bounds, gb, dim3(256), 0, s, nj, d_jrb, nrows, start_scan.as<int64_t>(),
+                                   d_b.as<int64_t>() + 2 * (nj + 1));
+            chk(hipGetLastError());
+            chk(launch_copy_to_host(h_b.p, d_b.p, 8 * 3 * (size_t)(nj + 1), s));
+            ph_sn.launch();
+        }
+        chk(hipEventRecord(ev[3], st));
+        chk(hipStreamSynchronize(st));
+        ph_emit.done();
+        ph_sn.done();
+        give_masks(std::move(masks));
+
+        std::vector<JobStats> js(h_js, h_js + nj);
+        for (int32_t j = 0; j < nj; ++j) {
+            js[j].edges_alg += (unsigned long long)nnz[j];  // every source's own degree
+            js[j].windows = (unsigned long long)((mats[j].n + 63) / 64);
+        }
+        gsofa_stats cs{};
+        float t = 0;
+        chk(hipEventElapsedTime(&t, ev[0], ev[4]));
+        cs.t_traverse_ms = t;
+        chk(hipEventElapsedTime(&t, ev[1], ev[2]));
+        cs.t_emit_ms = t;
+        chk(hipEventElapsedTime(&t, ev[2], ev[3]));
+        cs.t_supernode_ms = t;
+        cs.concurrent_sources = (int32_t)std::min<int64_t>(64 * ns, std::max<int64_t>(nrows, 1));
+        cs.mapping = kMapBlocks;
+        cs.launches = launches;
+        cs.peak_device_bytes = (uint64_t)(ns * stride * 8 + cap * 536 + nblocks * kPerBlock + nrows * 64 +
+                                          4 * (nnz_u + nnz_l));
+        f.u_ptr = std::move(u_ptr);
+        f.l_ptr = std::move(l_ptr);
+        f.nnz_u = nnz_u;
+        f.nnz_l = nnz_l;
+        rc = finish(f, h_b.as<int64_t>(), jstat, js, nnz, row_base, nrows, cs, t0);
+        return true;
     }
 
     // Times every tuner candidate on one stratified sample of the call's
@@ -2290,6 +2744,7 @@ struct gsofa_server {
     uint64_t admit_seq = 0;
     std::map<uint64_t, bool> admits_pending;  // admissions whose traversal is not enqueued yet
     uint64_t yields = 0;                       // yield requests made (statistics)
+    double last_large_ms = -1e300;             // last admission of a large request
 };
 
 namespace {
@@ -2339,6 +2794,10 @@ int32_t serve_slots_alone(const gsofa_server* s, int32_t n, int64_t nnz) {
 // call: one persistent traversal launch over all their sources, as in
 // gsofa_batch. Larger requests run alone (their own launch fills the device).
 constexpr int32_t kServeSmallRows = 65536;
+// A large request that follows another within this time is not treated as a lone
+// one: a stream of large requests keeps to its shares, so that the next one finds
+// room at once (a 48^3 27-point stencil holds the device for a few milliseconds).
+constexpr double kServeLoneGapMs = 100.0;
 constexpr size_t kServeMaxGroup = 64;
 constexpr int64_t kServeGroupRows = 1 << 20;
 
@@ -2405,7 +2864,11 @@ void serve_worker(gsofa_server* s, int sid) {
                     }
                 }
             }
-            if (grp.size() == 1 && s->inflight == 0 && s->queue.empty() && s->opts.concurrent_sources <= 0) {
+            const bool large = grp.size() == 1 && grp[0].n > kServeSmallRows;
+            const double admitted = now_ms();
+            const bool lone = admitted - s->last_large_ms > kServeLoneGapMs || !large;
+            if (large) s->last_large_ms = admitted;
+            if (grp.size() == 1 && s->inflight == 0 && s->queue.empty() && s->opts.concurrent_sources <= 0 && lone) {
                 const int32_t slots = serve_slots_alone(s, grp[0].n, (int64_t)grp[0].ci.size());
                 if (slots > grp[0].nslots) {
                     me.alone = me.alone_trav = true;
@@ -2458,6 +2921,7 @@ void serve_worker(gsofa_server* s, int sid) {
         // no tuner trials inside a request (they would add to its latency), but
         // the size class's cached choice of mapping and window applies
         YieldHooks hooks;
+        hooks.sources_set = s->opts.concurrent_sources > 0;
         hooks.flag = me.yieldable ? me.flag : nullptr;
         // a request set it after this worker's previous traversal had ended
         __atomic_store_n(me.flag, 0u, __ATOMIC_RELEASE);

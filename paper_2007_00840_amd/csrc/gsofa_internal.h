@@ -98,6 +98,78 @@ struct TraverseArgs {
                                       // are finished); item_counter then tells where to resume
 };
 
+// ---- block path (gsofa_blocks.hip): 64 rows at a time as bit masks
+
+constexpr int64_t kBlockMaxRows = int64_t(1) << 22;  // LDS bitmaps: one bit per 64 columns
+constexpr int kBmHeadWords = 32;                     // 64-bit words per block: two headers of 128 bytes
+enum BmCtl { kBmNext = 0, kBmAbort = 1 };
+enum BmAbortCode { kBmOverflow = 1, kBmStall = 2 };
+
+// Where a finished block's tiles lie in the pool: U beyond the block, L before it.
+struct BlockRec {
+    int64_t u_off, l_off;
+    int32_t u_cnt, l_cnt;
+};
+
+// Blocks of all matrices of a launch share one index space: matrix j owns
+// blocks [item_base, item_base + ceil(n / 64)) (Job::item_base) and rows
+// [row_base, row_base + n).
+struct BlockArgs {
+    const Job* jobs;
+    const int32_t* blk_job;       // block -> matrix (nullptr: one matrix)
+    const int32_t* items;         // order in which blocks are taken (nullptr: ascending)
+    int32_t nblocks;
+    int32_t nslots;               // workgroups, each with a slot of x
+    int32_t waves;                // wavefronts per workgroup: 4, 8 or 16
+    unsigned long long* x;        // nslots * x_stride column masks, all zero between uses
+    int64_t x_stride;
+    int32_t bit_words;            // 64-bit words of a bitmap over the blocks of the largest matrix
+    uint32_t* ctl;                // BmCtl
+    uint32_t* flag;               // per block: publications so far
+    unsigned long long* head;     // per block: kBmHeadWords
+    unsigned long long* tcl;      // per block: 2 x 64 (closure of U inside the block, per publication)
+    int32_t* kmatch;              // per block: 64 first matches
+    unsigned long long* diag;     // per block: 64 masks of its own columns
+    unsigned long long* lcl;      // per block: 64 (closure of L inside the block, per row)
+    BlockRec* rec;
+    int32_t* tids;                // pool of tiles: column block,
+    unsigned long long* masks;    // 64 masks,
+    int32_t* slot;                // L tiles: place in their column block's list
+    unsigned long long* pool_tail;
+    int64_t pool_cap;
+    int32_t* tcount;              // per block: L tiles in its columns
+    int32_t* row_ucnt;
+    int32_t* row_lcnt;
+    JobStats* jstats;             // per matrix
+};
+
+// L's tiles by columns: block c's list is entries [ptr[c], ptr[c + 1]) of (row
+// block, tile), unsorted and sorted by row block.
+struct BlockCols {
+    const int64_t* ptr;
+    int32_t *blk, *tile, *blk2, *tile2;
+    int32_t* big;                 // per block
+    int32_t* nbig;                // zero beforehand
+};
+
+// workgroups of the factorisation kernel resident at once
+int32_t block_resident_groups(int cus, int waves, int bit_words);
+// items and blk_job of a launch over several matrices: ord lists the matrices by
+// falling block count, cum[b] counts the blocks with a local index below b
+hipError_t launch_block_tables(const Job* jobs, const int32_t* ord, const int64_t* cum, int32_t max_blocks,
+                               int32_t nblocks, int32_t* items, int32_t* blk_job, hipStream_t st);
+// structure of every block
+hipError_t launch_block_factor(const BlockArgs& a, hipStream_t st);
+// entries of L and U per row, L's tiles by columns, entries of L per column
+hipError_t launch_block_counts(const BlockArgs& a, const BlockCols& c, int32_t* col_cnt, hipStream_t st);
+// rows of U (upper) or L from the masks, at ptr (per row of the row space)
+hipError_t launch_block_rows(const BlockArgs& a, bool upper, const int64_t* ptr, int32_t* idx, hipStream_t st);
+// columns of L at l_ptr (per row of the row space)
+hipError_t launch_block_cols(const BlockArgs& a, const BlockCols& c, const int64_t* l_ptr, int32_t* l_idx,
+                             hipStream_t st);
+// edges_alg less the sources' own degrees, added to jstats
+hipError_t launch_block_reach(const BlockArgs& a, const BlockCols& c, hipStream_t st);
+
 // Row-space description shared by the assembly kernels. With one job,
 // row_job == nullptr and every base is 0.
 struct RowSpace {
@@ -144,10 +216,11 @@ hipError_t launch_transpose_l(RowSpace rs, const int64_t* l_rptr, const int32_t*
                               int64_t* scan_scratch, int32_t* cursor, int32_t* tmp,
                               int32_t* big_list, int32_t* big_count, hipStream_t st);
 hipError_t launch_zero_i32(int32_t* p, int64_t n, hipStream_t st);
-// Supernode starts (Definition T3) per block of rows.
+// Supernode starts (Definition T3) per block of rows. l_ptr / l_idx hold L
+// row-wise or, with by_col, column-wise.
 hipError_t launch_supernodes(RowSpace rs, int64_t nblocks, const int64_t* block_first_row,
                              const int32_t* block_len, const int64_t* u_ptr,
-                             const int64_t* l_rptr, const int32_t* l_ridx,
+                             const int64_t* l_ptr, const int32_t* l_idx, bool by_col,
                              int32_t* is_start, hipStream_t st);
 // xsup/supno from the start flags and their exclusive scan.
 hipError_t launch_supernode_assemble(RowSpace rs, int32_t njobs, const int32_t* is_start,

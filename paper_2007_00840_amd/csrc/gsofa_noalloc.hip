@@ -292,7 +292,7 @@ int run_noalloc(int32_t n, const int32_t* row_ptr, const int32_t* col_idx, const
                             big_cnt, st));
     const double ts0 = now_ms();
     if (want_sn) {
-        NA_CHK(launch_supernodes(rs, nblocks, bfirst, blen, u_ptr, l_rptr, l_ridx, is_start, st));
+        NA_CHK(launch_supernodes(rs, nblocks, bfirst, blen, u_ptr, l_rptr, l_ridx, false, is_start, st));
         NA_CHK(launch_scan_counts(is_start, nullptr, n, start_scan, scan_scr, st));
         NA_CHK(launch_supernode_assemble(rs, 1, is_start, start_scan, xsup, supno, st));
         NA_CHK(launch_supernode_terminals(1, d_jrb, d_jn, start_scan, xsup, st));
