@@ -11,11 +11,11 @@
 // once, and finally its own rows among each other. The per-source traversal
 // (k_traverse) walks every vertex reachable from every source instead: on the
 // 64^3 27-point stencil 51 G edge visits, where the block path makes 2.8e5 block
-// merges of 3.6e6 64-column tiles: 7.5 ms instead of 221 (1000^2 9-point stencil:
-// 4.7 instead of 218 ms; 512 batch members: 3.3 instead of 90 ms).
+// merges of 3.2e6 64-column tiles: 5.4 ms instead of 221 (1000^2 9-point stencil:
+// 3.7 instead of 218 ms; 512 batch members: 2.7 instead of 90 ms).
 //
 // What bounds it is the chain of blocks that wait for one another, not
-// throughput, and three things keep that chain short:
+// throughput, and four things keep that chain short:
 //   * two publications per block. The rows that depend on no earlier block
 //     (whole small subtrees and the first rows of a larger one) are finished
 //     and published at once, before the block waits for anything. With one
@@ -28,8 +28,14 @@
 //     U(k,:) holds the rest of U(a,:): of row a only the entries up to k are
 //     needed. kmatch[a] is the smallest such k found so far.
 //   * several wavefronts per block that merge pending blocks, and the tiles of a
-//     long list, side by side. Merging is monotone, so a block merged too early is merged again when bits of it
-//     arrive later.
+//     long list, side by side. Merging is monotone, so a block merged too early
+//     is merged again when bits of it arrive later.
+//   * few round trips from one block's publication to the next one's: the reader
+//     polls a 128-byte header that carries its own state, the rows and the first
+//     tile ids; reductions go by data-parallel moves, the elimination inside a
+//     block by table lookups, and barriers between wavefronts wait for LDS only.
+//     (Per block of a separator, from the last dependency's publication to its
+//     own: 17.5 us with flags, shuffles and a branching elimination loop, 5.5 us.)
 //
 // Blocks are taken from a counter in an order in which every block comes after
 // the ones it can depend on (ascending inside a matrix), so a block waits only
@@ -54,6 +60,11 @@ constexpr int kThreads = 256;         // threads of the kernels after the factor
 constexpr int kRangeTiles = 1024;     // column tiles (64 columns) listed at a time
 constexpr uint32_t kSpinLimit = 1u << 22;
 constexpr int32_t kNoMatch = 0x7FFFFFFF;
+constexpr int kHeadTiles = 20;        // tile ids in a list's header
+
+// word of the header that holds tiles i and i + 1 (i even), and the other way
+__device__ __forceinline__ int head_word(int i) { return i < 6 ? 4 + (i >> 1) : 8 + ((i - 6) >> 1); }
+__device__ __forceinline__ int head_tile(int w) { return w < 8 ? 2 * (w - 4) : 6 + 2 * (w - 8); }
 
 __device__ __forceinline__ int lane() { return (int)(threadIdx.x & 63); }
 __device__ __forceinline__ int rfl(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -68,31 +79,50 @@ __device__ __forceinline__ u64 readlane64(u64 v, int l) {
     return ((u64)hi << 32) | lo;
 }
 
-__device__ __forceinline__ int incl_scan(int v) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int t = __shfl_up(v, (unsigned)d, 64);
-        if (lane() >= d) v += t;
+// Scans and reductions over the wavefront by data-parallel-primitive moves
+// (six vector instructions) rather than shuffles through LDS, whose latency six
+// times over a chain of blocks pays for.
+#define GSOFA_DPP_STEP(ctrl, rmask, id, op)                                                          \
+    {                                                                                                \
+        const int t = __builtin_amdgcn_update_dpp(id, v, ctrl, rmask, 0xf, false);                   \
+        v = op(v, t);                                                                                \
     }
+#define GSOFA_DPP_SCAN(id, op)              \
+    GSOFA_DPP_STEP(0x111, 0xf, id, op) /* row_shr:1 */ \
+    GSOFA_DPP_STEP(0x112, 0xf, id, op) /* row_shr:2 */ \
+    GSOFA_DPP_STEP(0x114, 0xf, id, op) /* row_shr:4 */ \
+    GSOFA_DPP_STEP(0x118, 0xf, id, op) /* row_shr:8 */ \
+    GSOFA_DPP_STEP(0x142, 0xa, id, op) /* row_bcast:15 */ \
+    GSOFA_DPP_STEP(0x143, 0xc, id, op) /* row_bcast:31 */
+
+__device__ __forceinline__ int op_add(int a, int b) { return a + b; }
+__device__ __forceinline__ int op_or(int a, int b) { return a | b; }
+__device__ __forceinline__ int op_max(int a, int b) { return a > b ? a : b; }
+__device__ __forceinline__ int op_min(int a, int b) { return a < b ? a : b; }
+
+__device__ __forceinline__ int incl_scan(int v) {
+    GSOFA_DPP_SCAN(0, op_add)
     return v;
 }
-
+// every lane gets the result
+__device__ __forceinline__ int sum32(int v) {
+    GSOFA_DPP_SCAN(0, op_add)
+    return __builtin_amdgcn_readlane(v, 63);
+}
 __device__ __forceinline__ int max64(int v) {
-#pragma unroll
-    for (int d = 32; d; d >>= 1) v = max(v, __shfl_xor(v, d, 64));
-    return v;
+    GSOFA_DPP_SCAN((int)0x80000000, op_max)
+    return __builtin_amdgcn_readlane(v, 63);
 }
-
 __device__ __forceinline__ int min64(int v) {
-#pragma unroll
-    for (int d = 32; d; d >>= 1) v = min(v, __shfl_xor(v, d, 64));
-    return v;
+    GSOFA_DPP_SCAN(0x7FFFFFFF, op_min)
+    return __builtin_amdgcn_readlane(v, 63);
 }
-
+__device__ __forceinline__ int or32(int v) {
+    GSOFA_DPP_SCAN(0, op_or)
+    return __builtin_amdgcn_readlane(v, 63);
+}
 __device__ __forceinline__ u64 or64(u64 v) {
-#pragma unroll
-    for (int d = 32; d; d >>= 1) v |= __shfl_xor(v, d, 64);
-    return v;
+    return (u64)(uint32_t)or32((int)(uint32_t)v) | ((u64)(uint32_t)or32((int)(uint32_t)(v >> 32)) << 32);
 }
 
 __device__ __forceinline__ u64 sum64(u64 v) {
@@ -118,10 +148,22 @@ __device__ __forceinline__ u64 or_wg(u64* p, u64 v) {
     return __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// order this wavefront's earlier LDS and global accesses before its later ones
+// Order this wavefront's earlier LDS accesses before its later ones: the LDS
+// serves a wavefront's accesses in order, so only the compiler is told. (A fence
+// of workgroup scope also waits for every global store to be acknowledged.)
 __device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+// The same with its global accesses.
+__device__ __forceinline__ void wave_sync_all() {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     __builtin_amdgcn_wave_barrier();
+}
+// Barrier of the workgroup for what its wavefronts pass on in LDS; global stores
+// may still be on their way.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // this wavefront's device-scope stores have reached memory
@@ -130,72 +172,127 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 __device__ __forceinline__ u64 above(int k) { return k < 63 ? ~0ull << (k + 1) : 0ull; }
 __device__ __forceinline__ u64 below(int k) { return (1ull << k) - 1ull; }
 
-// y[b] = x[b] | OR of x[a] over the bits a of set[b] (lane b), through sixteen
-// 16-entry tables in LDS (the OR of every subset of four lanes' words): the
+// Lane b: the OR of the lanes' words w[a] over the bits a of set[b], through
+// sixteen 16-entry tables in LDS (the OR of every subset of four words): the
 // lookups of a table touch 16 consecutive words, so they never conflict.
 // Following the up to 63 bits of a set one by one costs several times as much.
-__device__ __forceinline__ u64 lane_product(u64 x, u64 set, u64* xs, u64* tab) {
+// xs: 64 words, tab: 256 words of the wavefront's own.
+__device__ __forceinline__ u64 lane_or(u64 w, u64 set, u64* xs, u64* tab) {
     const int ln = lane();
+    const u64 m0 = 0ull - (u64)(ln & 1), m1 = 0ull - (u64)((ln >> 1) & 1), m2 = 0ull - (u64)((ln >> 2) & 1),
+              m3 = 0ull - (u64)((ln >> 3) & 1);
     wave_sync();
-    xs[ln] = x;
+    xs[ln] = w;
     wave_sync();
+    u64 t[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int e = ln + 64 * i;
-        const u64* q = &xs[(e >> 4) * 4];
-        u64 t = 0;
-        if (e & 1) t |= q[0];
-        if (e & 2) t |= q[1];
-        if (e & 4) t |= q[2];
-        if (e & 8) t |= q[3];
-        tab[e] = t;
+        const u64* q = &xs[((ln >> 4) + 4 * i) * 4];  // entry ln & 15 of nibble (ln >> 4) + 4 i
+        t[i] = (q[0] & m0) | (q[1] & m1) | (q[2] & m2) | (q[3] & m3);
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) tab[ln + 64 * i] = t[i];
     wave_sync();
-    u64 y = x;
+    u64 y = 0;
 #pragma unroll
     for (int i = 0; i < 16; ++i) y |= tab[i * 16 + (int)((set >> (4 * i)) & 15ull)];
     return y;
 }
 
+__device__ __forceinline__ uint32_t lo32(u64 v) { return (uint32_t)v; }
+__device__ __forceinline__ uint32_t hi32(u64 v) { return (uint32_t)(v >> 32); }
+__device__ __forceinline__ uint32_t rl32(uint32_t v, int l) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+}
+// all ones where bit k of v is set
+__device__ __forceinline__ uint32_t bit_mask(uint32_t v, int k) { return (uint32_t)__builtin_amdgcn_sbfe((int)v, k, 1); }
+
 // One block's rows among each other. x: lane b's word is the mask of the
 // block's own column b. Row k's pattern right of k goes to every row r > k that
 // holds k, for the rows k of S in ascending order; with `narrow` a row that
 // depends on a row outside S leaves S (S then ends as the rows finished
-// without any earlier block). match (lane k): the first b with U(k,b) and
-// L(b,k) both nonzero, or -1.
+// without any earlier block). The 64 steps depend on one another; a step is six
+// instructions without a branch (broadcast column k, spread bit k of the own
+// word, and-or) and takes 40 ns all the same, the way of a word through the
+// scalar registers.
 template <bool narrow>
-__device__ __forceinline__ void eliminate(u64& x, u64& S, int& match) {
-    const int ln = lane();
-    match = -1;
-    for (int k = 0; k < 64; ++k) {
-        const u64 L = readlane64(x, k) & above(k);
-        if (!((S >> k) & 1ull)) {
-            if (narrow) S &= ~L;
-            continue;
+__device__ __forceinline__ void eliminate(u64& x, u64& S) {
+    const u64 up = below(lane());
+    const uint32_t ulo = lo32(up), uhi = hi32(up);
+    uint32_t lo = lo32(x), hi = hi32(x);
+#pragma unroll 8
+    for (int k = 0; k < 32; ++k) {
+        uint32_t Ll = rl32(lo, k) & (uint32_t)(0xFFFFFFFEull << k), Lh = rl32(hi, k);
+        if (narrow) {
+            const uint32_t in = (uint32_t)0 - (uint32_t)((S >> k) & 1ull);
+            S &= ~(((u64)(Lh & ~in) << 32) | (Ll & ~in));
+            Ll &= in;
+            Lh &= in;
         }
-        if (L == 0ull) continue;
-        const bool has = ln > k && ((x >> k) & 1ull);
-        const u64 U = __ballot(has);
-        if (has) x |= L;
-        const u64 both = U & L;
-        if (both != 0ull && ln == k) match = __builtin_ctzll(both);
+        const uint32_t t = bit_mask(lo & ulo, k);
+        lo |= t & Ll;
+        hi |= t & Lh;
+    }
+#pragma unroll 8
+    for (int k = 32; k < 64; ++k) {
+        uint32_t Lh = rl32(hi, k) & (uint32_t)(0xFFFFFFFEull << (k - 32));
+        if (narrow) {
+            const uint32_t in = (uint32_t)0 - (uint32_t)((S >> k) & 1ull);
+            S &= ~((u64)(Lh & ~in) << 32);
+            Lh &= in;
+        }
+        hi |= bit_mask(hi & uhi, k - 32) & Lh;
+    }
+    x = ((u64)hi << 32) | lo;
+}
+
+// The same for all rows at once: every pass adds to each column b the rows that
+// reach it through any k < b (the rule of a step above, for the entries known
+// so far), until a pass adds nothing. Blocks deep in a separator are nearly
+// full when their turn comes and need two or three passes of 0.2 us, on the
+// path from block to block; one that needs more than kPasses goes step by step.
+__device__ __forceinline__ void eliminate_all(u64& x, u64* xs, u64* tab) {
+    constexpr int kPasses = 6;
+    const int ln = lane();
+    const u64 up = below(ln), dn = above(ln);
+    for (int i = 0; i < kPasses; ++i) {
+        const u64 y = x | lane_or(x & dn, x & up, xs, tab);
+        const bool more = y != x;
+        x = y;
+        if (__ballot(more) == 0ull) return;
+    }
+    u64 S = ~0ull;
+    eliminate<false>(x, S);
+}
+
+// Transitive closure of a relation on the block's rows: lane k holds the rows
+// that k leads to. A pass doubles the lengths of the chains covered, so there are
+// at most seven; a full block is closed already and needs one.
+__device__ __forceinline__ u64 closure(u64 c, u64* xs, u64* tab) {
+    for (;;) {
+        const u64 d = c | lane_or(c, c, xs, tab);
+        const bool more = d != c;
+        c = d;
+        if (__ballot(more) == 0ull) return c;
     }
 }
 
-// Transitive closures over the rows of S: C (lane k): the rows of the block
-// that take in row k directly or through others; T (lane b): the rows whose
-// pattern brings in column b of the block.
-__device__ __forceinline__ void closures(u64 x, u64 S, u64& C, u64& T) {
+// Lane k: the first b with U(k,b) and L(b,k) both nonzero, or -1, for the rows
+// of S of an eliminated block (x, and all its words in xw). In a full block that
+// is the first row below, so the candidates are tried one by one.
+__device__ __forceinline__ int first_match(u64 x, u64 S, const u64* xw) {
     const int ln = lane();
-    C = ((S >> ln) & 1ull) ? x & above(ln) : 0ull;
-    T = x & below(ln) & S;
-    for (u64 todo = S; todo;) {
-        const int j = __builtin_ctzll(todo);
-        todo &= todo - 1ull;
-        const u64 cj = readlane64(C, j), tj = readlane64(T, j);
-        if ((C >> j) & 1ull) C |= cj;
-        if ((T >> j) & 1ull) T |= tj;
+    int match = -1;
+    u64 cand = ((S >> ln) & 1ull) ? x & above(ln) : 0ull;
+    while (cand != 0ull) {
+        const int b = __builtin_ctzll(cand);
+        cand &= cand - 1ull;
+        if ((xw[b] >> ln) & 1ull) {
+            match = b;
+            cand = 0;
+        }
     }
+    return match;
 }
 
 }  // namespace
@@ -212,9 +309,9 @@ template <int W>
 __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
     constexpr int kTasks = 4;
     extern __shared__ u64 s_bits[];  // touched column tiles, pending blocks
-    __shared__ u64 s_xs[W][64];
+    __shared__ __attribute__((aligned(16))) u64 s_xs[W][64];
     __shared__ u64 s_tab[W][256];
-    __shared__ u64 s_C[64];
+    __shared__ u64 s_C[64], s_x[64];
     __shared__ uint16_t s_tile[kRangeTiles];
     __shared__ int32_t s_rp[65];
     // merges of long lists, shared by the wavefronts: the rows' masks, the list,
@@ -224,7 +321,7 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
     __shared__ int32_t s_tblk[kTasks];
     __shared__ uint32_t s_tnext[kTasks];
     __shared__ int s_tdone[kTasks], s_town[kTasks];
-    __shared__ u64 s_ext, s_S, s_off, s_arena, s_arena_end;
+    __shared__ u64 s_ext, s_S, s_con, s_off, s_arena, s_arena_end;
     __shared__ int s_item, s_active, s_stop, s_ntile, s_total;
 
     const int tid = threadIdx.x, ln = lane(), wv = rfl(tid >> 6);
@@ -289,7 +386,7 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
         }
         ext = or64(ext);
         const u64 dups = __ballot(dup);
-        const u64 nd = sum64((u64)ndiag);
+        const u64 nd = (u64)sum32(ndiag);
         if (ln == 0) {
             if (ext) atomicOr(&s_ext, ext);
             if (dups) atomicOr(&a.jstats[jb].err, kErrDuplicate);
@@ -316,12 +413,35 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
         // behind a `last` list. s_off, s_total: where the list is. Unless
         // state is 0 the list is published as (part, state): the header, then the
         // flag behind all stores.
-        auto write_list = [&](int lo, int hi, u64 keep, u64 S, bool last, int part, uint32_t state, u64 con) -> bool {
+        auto write_list = [&](int lo, int hi, u64 keep, u64 S, bool last, int part, uint32_t state) -> bool {
             const int R0 = lo / kRangeTiles, R1 = hi > lo ? (hi - 1) / kRangeTiles : R0 - 1;
+            u64* head = a.head + (int64_t)gb * kBmHeadWords + part * (kBmHeadWords / 2);
+            // Header of a published list, one word per lane: the rows it covers, the
+            // rows whose entries beyond the block others need, where the tiles
+            // are, how many, and the ids of the first kHeadTiles (n of the list's
+            // first range). Words 7 and 15 stay 0 until everything is stored: each
+            // 64-byte half of the line carries its own state.
+            auto header = [&](int n, int t0) {
+                wave_sync();
+                n = min(n, kHeadTiles);
+                if (ln < 16 && (ln & 7) != 7) {
+                    u64 v;
+                    if (ln == 0) v = keep;
+                    else if (ln == 1) v = s_con;
+                    else if (ln == 2) v = s_off;
+                    else if (ln == 3) v = (u64)s_total | ((u64)n << 32);
+                    else {
+                        const int i = head_tile(ln);
+                        v = (u64)(uint32_t)(i < n ? t0 + s_tile[i] : kNoMatch) |
+                            ((u64)(uint32_t)(i + 1 < n ? t0 + s_tile[i + 1] : kNoMatch) << 32);
+                    }
+                    st_dev(&head[ln], v);
+                }
+            };
             if (wv == 0) {
                 int c = 0;
                 for (int wi = lo / 64 + ln; wi * 64 < hi; wi += 64) c += __popcll(touched(wi, lo, hi));
-                const int total = rfl((int)sum64((u64)c));
+                const int total = sum32(c);
                 if (ln == 0) {
                     s_total = total;
                     // room from the workgroup's own stretch of the pool, 64 tiles at a time
@@ -336,13 +456,6 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
                     }
                     s_off = s_arena;
                     s_arena += (u64)total;
-                    if (state) {
-                        u64* h = a.head + (int64_t)gb * kBmHeadWords + part * (kBmHeadWords / 2);
-                        st_dev(&h[0], keep);
-                        st_dev(&h[1], s_off);
-                        st_dev(&h[2], (u64)total);
-                        st_dev(&h[3], con);  // rows whose entries beyond the block others need
-                    }
                 }
             }
             int64_t base = 0;
@@ -354,8 +467,9 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
                     int o = inc - c;
                     for (u64 w = w0; w; w &= w - 1ull) s_tile[o++] = (uint16_t)(ln * 64 + __builtin_ctzll(w));
                     if (ln == 63) s_ntile = inc;
+                    if (state && R == R0) header(__builtin_amdgcn_readlane(inc, 63), R * kRangeTiles);
                 }
-                __syncthreads();
+                lds_barrier();
                 if (s_stop) return false;
                 const int nt = s_ntile;
                 for (int i = wv; i < nt; i += W) {
@@ -387,45 +501,65 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
                     }
                 }
                 base += nt;
-                if (R < R1) __syncthreads();
+                if (R < R1) lds_barrier();
             }
             if (R0 > R1) {
-                __syncthreads();
+                if (state && wv == 0) header(0, 0);
+                lds_barrier();
                 if (s_stop) return false;
             }
             if (state) {
                 stores_done();
-                __syncthreads();
-                if (tid == 0) st_dev(&a.flag[gb], state);
+                lds_barrier();
+                if (tid < 2) st_dev(&head[8 * tid + 7], (u64)state);
             }
             return true;
         };
 
-        int32_t* km = a.kmatch + 64 * (int64_t)gb;
+        // After the elimination of rows S (own tile in s_x): what a publication
+        // needs of the block's inside, a wavefront each. C in s_C (lane k: the rows
+        // of the block that take in row k directly or through others; returned to
+        // wavefront 0), the closure of U for the blocks that will merge this one
+        // (lane b: the rows whose pattern brings in column b), the first matches.
+        auto close_rows = [&](u64 S, int part, bool known) -> u64 {
+            const u64 x = s_x[ln];
+            u64 r = 0;
+            if (wv == 0) {
+                r = closure(((S >> ln) & 1ull) ? x & above(ln) : 0ull, xs, tab);
+                s_C[ln] = r;
+            } else if (wv == 1) {
+                st_dev(&a.tcl[(int64_t)gb * 128 + 64 * part + ln], closure(x & below(ln) & S, xs, tab));
+            } else if (wv == 2) {
+                int32_t* km = a.kmatch + 64 * (int64_t)gb;
+                const int match = first_match(x, S, s_x);
+                if (!known) st_dev(&km[ln], match >= 0 ? 64 * g + match : kNoMatch);
+                else if (match >= 0) atomicMin(&km[ln], 64 * g + match);
+                const u64 nc = __ballot(match >= 0);
+                if (ln == 0) s_con = S & ~nc;
+            }
+            lds_barrier();
+            return r;
+        };
+
         const u64 s_ext0 = s_ext;
         bool first_done = false;
         bool stop = false;
 
         // ---- rows that depend on no earlier block: finish and publish them now
         if (s_ext0 != 0ull && (rows & ~s_ext0) != 0ull) {
-            u64 nc = 0;
             if (wv == 0) {
                 u64 x = ld_wg(&X[64 * (int64_t)g + ln]);
-                u64 S = rows & ~s_ext0, C, T;
-                int match;
-                eliminate<true>(x, S, match);
-                closures(x, S, C, T);
-                s_C[ln] = C;
+                u64 S = rows & ~s_ext0;
+                eliminate<true>(x, S);
                 X[64 * (int64_t)g + ln] = x;
-                st_dev(&a.tcl[(int64_t)gb * 128 + ln], T);
-                st_dev(&km[ln], match >= 0 ? 64 * g + match : kNoMatch);
-                nc = __ballot(match >= 0);
+                s_x[ln] = x;
                 if (ln == 0) s_S = S;
             }
-            __syncthreads();
+            __syncthreads();  // (the store to X too: other wavefronts OR into it next)
             const u64 S = s_S;
             if (S != 0ull) {
-                stop = !write_list(g + 1, ntiles, S, S, false, 0, 1u, S & ~nc);
+                (void)close_rows(S, 0, false);
+                stop = !write_list(g + 1, ntiles, S, S, false, 0, 1u);
                 first_done = true;
             }
         }
@@ -516,16 +650,17 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
                 wave_sync();
                 const int64_t hb = b0 + h;
                 // wait until the rows this block needs of block h are published
-                u64 y = 0;
-                uint32_t need = 1;
-                bool dead = false;
-                u64 h_off = 0, h_con = 0;
-                int h_cnt = 0, match = 0;
+                u64 y = 0, w = 0, m[3] = {0, 0, 0};
+                int part = 0, match = 0;
+                bool both = false, dead = false;
                 for (;;) {
-                    // one lane's view for the wavefront: a load's lanes may be
-                    // served at different times and see different publications
-                    uint32_t f = (uint32_t)rfl((int)ld_dev(&a.flag[hb]));
-                    while (f < need) {
+                    for (;;) {
+                        w = ln < kBmHeadWords ? ld_dev(&a.head[hb * kBmHeadWords + ln]) : 0ull;
+                        // every lane's words of one load: a uniform view
+                        if (readlane64(w, 23) != 0ull && readlane64(w, 31) != 0ull) part = 1;
+                        else if (!both && readlane64(w, 7) != 0ull && readlane64(w, 15) != 0ull) part = 0;
+                        else part = -1;
+                        if (part >= 0) break;
                         ++spins;
                         if ((spins & 15u) == 0u) {
                             if (spins > kSpinLimit) st_dev(&a.ctl[kBmAbort], (uint32_t)kBmStall);
@@ -535,23 +670,21 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
                             }
                         }
                         __builtin_amdgcn_s_sleep(1);
-                        f = (uint32_t)rfl((int)ld_dev(&a.flag[hb]));
                     }
                     if (dead) break;
                     asm volatile("" ::: "memory");
-                    const int part = f >= 2u ? 1 : 0;
-                    const u64* hd = a.head + hb * kBmHeadWords + part * (kBmHeadWords / 2);
-                    const u64 w = ln < 4 ? ld_dev(&hd[ln]) : 0ull;
                     const u64 T = ld_dev(&a.tcl[hb * 128 + part * 64 + ln]);
                     const u64 x = ld_wg(&X[64 * (int64_t)h + ln]);
                     match = ld_dev(&a.kmatch[64 * hb + ln]);
-                    y = lane_product(x, T, xs, tab);
-                    const u64 S = readlane64(w, 0);
-                    h_off = readlane64(w, 1);
-                    h_cnt = (int)readlane64(w, 2);
-                    h_con = readlane64(w, 3);
-                    if (part == 0 && (__ballot(y != 0ull) & ~S) != 0ull) {
-                        need = 2;  // rows of the second publication are needed
+                    // the first tiles' masks with the same round trip
+                    const int64_t q = (int64_t)readlane64(w, 16 * part + 2);
+                    const int cnt = (int)lo32(readlane64(w, 16 * part + 3));
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+                        if (i < cnt) m[i] = ld_dev(&a.masks[64 * (q + i) + ln]);
+                    y = x | lane_or(x, T, xs, tab);
+                    if (part == 0 && (__ballot(y != 0ull) & ~readlane64(w, 0)) != 0ull) {
+                        both = true;  // rows of the second publication are needed
                         continue;
                     }
                     if (y != x) or_wg(&X[64 * (int64_t)h + ln], y);
@@ -566,24 +699,29 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
                 }
                 spins = 0;
                 ++n_merge;
-                const u64 have = __ballot(y != 0ull);
-                const u64 use = have & h_con;
+                const u64 use = __ballot(y != 0ull) & readlane64(w, 16 * part + 1);
+                const u64 h_off = readlane64(w, 16 * part + 2);
+                const u64 h_num = readlane64(w, 16 * part + 3);
+                const int h_cnt = (int)lo32(h_num), h_inl = (int)hi32(h_num);
                 // Tiles beyond the last first match of the rows in use are not
                 // needed. Only a match below this block counts: a row takes the
                 // rest from its match's row if that comes before it.
                 const u64 open = use & __ballot(match >= 64 * g);
                 int tmax = -1;
                 if ((use >> ln) & 1ull) tmax = match >= 64 * g ? kNoMatch : match >> 6;
-                tmax = rfl(max64(tmax));
+                tmax = (max64(tmax));
+                // lane i: tile i of the list, from the header as far as it goes
                 int cnt = 0;
-                int32_t t = 0;
+                int32_t t = kNoMatch;
                 if (tmax >= 0) {
-                    for (int i0 = 0; i0 < h_cnt; i0 += 64) {
+                    const int src = 16 * part + head_word(ln & ~1);
+                    const int tl = __shfl((int)lo32(w), src, 64), th = __shfl((int)hi32(w), src, 64);
+                    if (ln < h_inl) t = (ln & 1) ? th : tl;
+                    else if (ln < h_cnt) t = ld_dev(&a.tids[(int64_t)h_off + ln]);
+                    cnt = __popcll(__ballot(t <= tmax && t != kNoMatch));
+                    for (int i0 = 64; i0 < h_cnt && cnt == i0; i0 += 64) {
                         const int32_t ti = i0 + ln < h_cnt ? ld_dev(&a.tids[(int64_t)h_off + i0 + ln]) : kNoMatch;
-                        if (i0 == 0) t = ti;
-                        const int c = __popcll(__ballot(ti <= tmax && ti != kNoMatch));
-                        cnt += c;
-                        if (c < 64) break;
+                        cnt += __popcll(__ballot(ti <= tmax && ti != kNoMatch));
                     }
                 }
                 int task = -1;
@@ -610,7 +748,11 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
                 wave_sync();
                 xs[ln] = y;
                 wave_sync();
-                for (int i = 0; i < cnt; ++i) {
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    if (i < cnt) merge_tile(__builtin_amdgcn_readlane(t, i), m[i], xs, use, open, hb);
+                // (no task free for a longer list)
+                for (int i = 3; i < cnt; ++i) {
                     const int64_t q = (int64_t)h_off + i;
                     const int32_t ti = i < 64 ? __builtin_amdgcn_readlane(t, i) : rfl(ld_dev(&a.tids[q]));
                     merge_tile(ti, ld_dev(&a.masks[64 * q + ln]), xs, use, open, hb);
@@ -619,35 +761,28 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
                 wave_sync();
                 if (ln == 0) atomicSub(&s_active, 1);
             }
-            __syncthreads();
+            lds_barrier();
             stop = s_stop != 0;
         }
         if (stop) break;
 
         // ---- the block's own rows among each other, then everything published
-        u64 own = 0, C = 0, nc = 0;
+        u64 own = 0;
         if (wv == 0) {
-            u64 x = ld_wg(&X[64 * (int64_t)g + ln]);
-            u64 S = rows, T;
-            int match;
-            eliminate<false>(x, S, match);
-            closures(x, S, C, T);
-            s_C[ln] = C;
-            own = x;
-            st_dev(&a.tcl[(int64_t)gb * 128 + 64 + ln], T);
-            if (!first_done) st_dev(&km[ln], match >= 0 ? 64 * g + match : kNoMatch);
-            else if (match >= 0) atomicMin(&km[ln], 64 * g + match);
-            nc = __ballot(match >= 0);
-            X[64 * (int64_t)g + ln] = 0ull;
+            own = ld_wg(&X[64 * (int64_t)g + ln]);
+            eliminate_all(own, xs, tab);
+            s_x[ln] = own;
         }
-        __syncthreads();
-        if (!write_list(g + 1, ntiles, rows, rows, true, 1, 2u, rows & ~nc)) break;
+        lds_barrier();
+        const u64 C = close_rows(rows, 1, first_done);
+        if (wv == 0) X[64 * (int64_t)g + ln] = 0ull;
+        if (!write_list(g + 1, ntiles, rows, rows, true, 1, 2u)) break;
         const u64 u_off = s_off;
         const int u_cnt = s_total;
-        __syncthreads();
+        lds_barrier();
 
         // ---- what only later kernels read
-        if (!write_list(0, g, rows, 0ull, true, 0, 0u, 0ull)) break;
+        if (!write_list(0, g, rows, 0ull, true, 0, 0u)) break;
         if (wv == 0) {
             a.diag[64 * (int64_t)gb + ln] = own;
             // rows of the closure: lane r, the rows of the block that r takes in
@@ -766,7 +901,7 @@ __global__ __launch_bounds__(64) void k_bm_lists(BlockArgs a, BlockCols c, int32
             const int p = i0 + ln < nw ? __popcll(bits[i0 + ln]) : 0;
             const int inc = incl_scan(p);
             if (i0 + ln < nw) pre[i0 + ln] = run + inc - p;
-            run += rfl(__shfl(inc, 63, 64));
+            run += __builtin_amdgcn_readlane(inc, 63);
         }
         wave_sync();
         for (int64_t f0 = e0; f0 < e1; f0 += 64) {
@@ -889,7 +1024,7 @@ __device__ __forceinline__ int degree_planes(const Job* J, int32_t c, u64* plane
     const int ln = lane();
     const int64_t v = 64 * (int64_t)c + ln;
     const uint32_t deg = v < J->n ? (uint32_t)(J->row_ptr[v + 1] - J->row_ptr[v]) : 0u;
-    const uint32_t top = (uint32_t)rfl(max64((int)deg));
+    const uint32_t top = (uint32_t)(max64((int)deg));
     const int np = top ? 32 - __builtin_clz(top) : 0;
     for (int j = 0; j < np; ++j) {
         const u64 p = __ballot((deg >> j) & 1u);
@@ -901,7 +1036,7 @@ __device__ __forceinline__ int degree_planes(const Job* J, int32_t c, u64* plane
 
 __global__ __launch_bounds__(64 * kReachWaves) void k_bm_reach(BlockArgs a, BlockCols cl) {
     __shared__ u64 s_tile[kReachWaves][kReachTiles][64];
-    __shared__ u64 s_xs[kReachWaves][64];
+    __shared__ __attribute__((aligned(16))) u64 s_xs[kReachWaves][64];
     __shared__ u64 s_tab[kReachWaves][256];
     __shared__ u64 s_planes[kReachWaves][32];
     const int ln = lane(), wv = rfl(threadIdx.x >> 6);
@@ -921,18 +1056,19 @@ __global__ __launch_bounds__(64 * kReachWaves) void k_bm_reach(BlockArgs a, Bloc
     u64 sum = 0;
     bool over = false;
     for (;;) {
-        const int32_t h = rfl(min64(key));
+        const int32_t h = (min64(key));
         if (h == kNoMatch) break;
         const int sl = __builtin_ctzll(__ballot(key == h));
         const int64_t hb = b0 + h;
         const u64 M = a.lcl[64 * hb + ln];
         const int32_t match = a.kmatch[64 * hb + ln];
         const int64_t e0 = cl.ptr[hb], e1 = cl.ptr[hb + 1];
-        const u64 z = lane_product(tile[sl][ln], M, s_xs[wv], s_tab[wv]);
+        const u64 z0 = tile[sl][ln];
+        const u64 z = z0 | lane_or(z0, M, s_xs[wv], s_tab[wv]);
         if (ln == sl) key = kNoMatch;
         sum += weigh(h == c ? z & ~(1ull << ln) : z, planes, np);
         // later blocks, up to the last match of the columns in use
-        const int32_t gmax = rfl(max64(z != 0ull ? match >> 6 : -1));
+        const int32_t gmax = (max64(z != 0ull ? match >> 6 : -1));
         for (int64_t e = e0; e < e1; ++e) {
             const int32_t g = cl.blk2[e];
             if (g > gmax) break;
@@ -970,7 +1106,7 @@ __global__ __launch_bounds__(64 * kReachWaves) void k_bm_reach(BlockArgs a, Bloc
 // uses) and a bitmap of the waiting blocks in LDS.
 __global__ __launch_bounds__(64) void k_bm_reach_big(BlockArgs a, BlockCols cl) {
     extern __shared__ u64 s_bits[];
-    __shared__ u64 s_xs[64];
+    __shared__ __attribute__((aligned(16))) u64 s_xs[64];
     __shared__ u64 s_tab[256];
     __shared__ u64 s_planes[32];
     if (ld_dev(&a.ctl[kBmAbort]) != 0u) return;
@@ -985,11 +1121,11 @@ __global__ __launch_bounds__(64) void k_bm_reach_big(BlockArgs a, BlockCols cl) 
         const int32_t b0 = (int32_t)J->item_base;
         const int32_t c = cb - b0;
         for (int i = ln; i < nw; i += 64) s_bits[i] = 0ull;
-        wave_sync();
+        wave_sync_all();
         const int np = degree_planes(J, c, s_planes);
         if (ln == 0) s_bits[c >> 6] = 1ull << (c & 63);
         if (64 * (int64_t)c + ln < J->n) Z[64 * (int64_t)c + ln] = 1ull << ln;
-        wave_sync();
+        wave_sync_all();
         u64 sum = 0;
         for (int w0 = c >> 6; w0 < nw;) {
             const u64 word = s_bits[w0];
@@ -998,15 +1134,15 @@ __global__ __launch_bounds__(64) void k_bm_reach_big(BlockArgs a, BlockCols cl) 
                 continue;
             }
             const int32_t h = w0 * 64 + __builtin_ctzll(word);
-            wave_sync();
+            wave_sync_all();
             if (ln == 0) s_bits[w0] = word & (word - 1ull);
             const int64_t hb = b0 + h;
             u64 z = ld_wg(&Z[64 * (int64_t)h + ln]);
             Z[64 * (int64_t)h + ln] = 0ull;
-            z = lane_product(z, a.lcl[64 * hb + ln], s_xs, s_tab);
+            z |= lane_or(z, a.lcl[64 * hb + ln], s_xs, s_tab);
             sum += weigh(h == c ? z & ~(1ull << ln) : z, s_planes, np);
             const int32_t match = a.kmatch[64 * hb + ln];
-            const int32_t gmax = rfl(max64(z != 0ull ? match >> 6 : -1));
+            const int32_t gmax = (max64(z != 0ull ? match >> 6 : -1));
             for (int64_t e = cl.ptr[hb]; e < cl.ptr[hb + 1]; ++e) {
                 const int32_t g = cl.blk2[e];
                 if (g > gmax) break;
@@ -1015,11 +1151,11 @@ __global__ __launch_bounds__(64) void k_bm_reach_big(BlockArgs a, BlockCols cl) 
                 for (u64 t = m; t; t &= t - 1ull) or_wg(&Z[64 * (int64_t)g + __builtin_ctzll(t)], z);
                 if (ln == 0) s_bits[g >> 6] |= 1ull << (g & 63);
             }
-            wave_sync();
+            wave_sync_all();
         }
         sum = sum64(sum);
         if (ln == 0 && sum) atomicAdd(&a.jstats[jb].edges_alg, sum);
-        wave_sync();
+        wave_sync_all();
     }
 }
 

@@ -2086,14 +2086,14 @@ struct Engine {
         const int64_t* d_bf = reinterpret_cast<const int64_t*>(du + o_bf);
         const int32_t* d_bl = reinterpret_cast<const int32_t*>(du + o_bl);
 
-        // arrays cleared before the factorisation: control words, tile counts,
-        // flags, per-matrix statistics
-        const int64_t z_cnt = 64, z_flag = z_cnt + up16(4 * nb1), z_js = z_flag + up16(4 * nb1),
+        // arrays cleared before the factorisation: control words, headers, tile
+        // counts, per-matrix statistics
+        const int64_t z_head = 256, z_cnt = z_head + 8 * kBmHeadWords * nb1, z_js = z_cnt + up16(4 * nb1),
                       z_bytes = z_js + up16((int64_t)sizeof(JobStats) * std::max(nj, 1));
         DBuf zero((size_t)z_bytes);
         uint32_t* d_ctl = zero.as<uint32_t>();  // [0] next block, [1] abort, [4] reach list, [8..9] pool tail
         JobStats* d_js = reinterpret_cast<JobStats*>(zero.as<char>() + z_js);
-        DBuf head(8 * kBmHeadWords * (size_t)nb1), tcl(1024 * (size_t)nb1), kmatch(256 * (size_t)nb1),
+        DBuf tcl(1024 * (size_t)nb1), kmatch(256 * (size_t)nb1),
             diag(512 * (size_t)nb1), lcl(512 * (size_t)nb1), rec(sizeof(BlockRec) * (size_t)nb1);
         DBuf row_ucnt(4 * (size_t)nr1), row_lcnt(4 * (size_t)nr1), col_cnt(4 * (size_t)nr1);
         DBuf u_ptr(8 * (size_t)(nrows + 1)), l_ptr(8 * (size_t)(nrows + 1)), list_ptr(8 * (size_t)(nb1 + 1));
@@ -2122,8 +2122,7 @@ struct Engine {
         ba.x_stride = stride;
         ba.bit_words = words;
         ba.ctl = d_ctl;
-        ba.flag = reinterpret_cast<uint32_t*>(zero.as<char>() + z_flag);
-        ba.head = head.as<unsigned long long>();
+        ba.head = reinterpret_cast<unsigned long long*>(zero.as<char>() + z_head);
         ba.tcl = tcl.as<unsigned long long>();
         ba.kmatch = kmatch.as<int32_t>();
         ba.diag = diag.as<unsigned long long>();

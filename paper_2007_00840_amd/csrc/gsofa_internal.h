@@ -101,7 +101,7 @@ struct TraverseArgs {
 // ---- block path (gsofa_blocks.hip): 64 rows at a time as bit masks
 
 constexpr int64_t kBlockMaxRows = int64_t(1) << 22;  // LDS bitmaps: one bit per 64 columns
-constexpr int kBmHeadWords = 32;                     // 64-bit words per block: two headers of 128 bytes
+constexpr int kBmHeadWords = 32;                     // 64-bit words per block: headers of its two publications
 enum BmCtl { kBmNext = 0, kBmAbort = 1 };
 enum BmAbortCode { kBmOverflow = 1, kBmStall = 2 };
 
@@ -125,8 +125,7 @@ struct BlockArgs {
     int64_t x_stride;
     int32_t bit_words;            // 64-bit words of a bitmap over the blocks of the largest matrix
     uint32_t* ctl;                // BmCtl
-    uint32_t* flag;               // per block: publications so far
-    unsigned long long* head;     // per block: kBmHeadWords
+    unsigned long long* head;     // per block: kBmHeadWords, zero beforehand
     unsigned long long* tcl;      // per block: 2 x 64 (closure of U inside the block, per publication)
     int32_t* kmatch;              // per block: 64 first matches
     unsigned long long* diag;     // per block: 64 masks of its own columns
