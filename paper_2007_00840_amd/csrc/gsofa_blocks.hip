@@ -10,9 +10,9 @@
 // the finished U rows of the earlier blocks that its masks name, 64 rows at
 // once, and finally its own rows among each other. The per-source traversal
 // (k_traverse) walks every vertex reachable from every source instead: on the
-// 64^3 27-point stencil 51 G edge visits, where the block path makes 2.8e5 block
-// merges of 3.2e6 64-column tiles: 5.4 ms instead of 221 (1000^2 9-point stencil:
-// 3.7 instead of 218 ms; 512 batch members: 2.7 instead of 90 ms).
+// 64^3 27-point stencil 51 G edge visits, where the block path makes 1.8e5 block
+// merges of 2.5e6 64-column tiles: 4.6 ms instead of 221 (1000^2 9-point stencil:
+// 3.1 instead of 218 ms; 512 batch members: 2.5 instead of 90 ms).
 //
 // What bounds it is the chain of blocks that wait for one another, not
 // throughput, and four things keep that chain short:
@@ -144,6 +144,11 @@ __device__ __forceinline__ void st_dev(T* p, T v) {
 __device__ __forceinline__ u64 ld_wg(const u64* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
+// LDS words that other wavefronts change
+template <typename T>
+__device__ __forceinline__ T ld_lds(const T* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
 __device__ __forceinline__ u64 or_wg(u64* p, u64 v) {
     return __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
@@ -214,7 +219,8 @@ __device__ __forceinline__ uint32_t bit_mask(uint32_t v, int k) { return (uint32
 // without any earlier block). The 64 steps depend on one another; a step is six
 // instructions without a branch (broadcast column k, spread bit k of the own
 // word, and-or) and takes 40 ns all the same, the way of a word through the
-// scalar registers.
+// scalar registers (two rows a step, the second one's column brought up to date
+// there, took longer).
 template <bool narrow>
 __device__ __forceinline__ void eliminate(u64& x, u64& S) {
     const u64 up = below(lane());
@@ -247,22 +253,32 @@ __device__ __forceinline__ void eliminate(u64& x, u64& S) {
 }
 
 // The same for all rows at once: every pass adds to each column b the rows that
-// reach it through any k < b (the rule of a step above, for the entries known
-// so far), until a pass adds nothing. Blocks deep in a separator are nearly
-// full when their turn comes and need two or three passes of 0.2 us, on the
-// path from block to block; one that needs more than kPasses goes step by step.
-__device__ __forceinline__ void eliminate_all(u64& x, u64* xs, u64* tab) {
-    constexpr int kPasses = 6;
+// reach it through any k < b of S (the rule of a step above, for the entries
+// known so far), until a pass adds nothing. Blocks deep in a separator are
+// nearly full when their turn comes and need two or three passes of 0.25 us,
+// those of a band five or six; one that needs more than kPasses goes step by
+// step. With `narrow`, S then loses the rows that depend on one outside it.
+template <bool narrow>
+__device__ __forceinline__ void eliminate_all(u64& x, u64& S, u64* xs, u64* tab) {
+    constexpr int kPasses = 8;
     const int ln = lane();
-    const u64 up = below(ln), dn = above(ln);
-    for (int i = 0; i < kPasses; ++i) {
+    const u64 up = below(ln) & S, dn = above(ln);
+    int i = 0;
+    for (; i < kPasses; ++i) {
         const u64 y = x | lane_or(x & dn, x & up, xs, tab);
         const bool more = y != x;
         x = y;
-        if (__ballot(more) == 0ull) return;
+        if (__ballot(more) == 0ull) break;
     }
-    u64 S = ~0ull;
-    eliminate<false>(x, S);
+    if (i == kPasses) {
+        eliminate<narrow>(x, S);
+    } else if (narrow) {
+        for (;;) {
+            const u64 T = S & ~or64((S >> ln) & 1ull ? 0ull : x & dn);
+            if (T == S) break;
+            S = T;
+        }
+    }
 }
 
 // Transitive closure of a relation on the block's rows: lane k holds the rows
@@ -306,29 +322,32 @@ __device__ __forceinline__ int first_match(u64 x, u64 S, const u64* xw) {
 // tiles need no counting and no prefix sums before they are written, are read
 // as 512 consecutive bytes, and hold about half set columns on the stencils.
 template <int W>
-__global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
+__global__ __launch_bounds__(64 * W, 4) void k_bm_factor(BlockArgs a) {
     constexpr int kTasks = 4;
-    extern __shared__ u64 s_bits[];  // touched column tiles, pending blocks
+    extern __shared__ u64 s_bits[];  // five bitmaps: touched column tiles, blocks to merge
     __shared__ __attribute__((aligned(16))) u64 s_xs[W][64];
     __shared__ u64 s_tab[W][256];
     __shared__ u64 s_C[64], s_x[64];
     __shared__ uint16_t s_tile[kRangeTiles];
     __shared__ int32_t s_rp[65];
     // merges of long lists, shared by the wavefronts: the rows' masks, the list,
-    // (tiles << 16 | next tile), tiles done, owned
+    // (tiles << 32 | next tile), tiles done, owned
     __shared__ u64 s_ty[kTasks][64];
     __shared__ u64 s_toff[kTasks], s_tuse[kTasks], s_topen[kTasks];
     __shared__ int32_t s_tblk[kTasks];
-    __shared__ uint32_t s_tnext[kTasks];
-    __shared__ int s_tdone[kTasks], s_town[kTasks];
+    __shared__ u64 s_tnext[kTasks];
+    __shared__ int s_tdone[kTasks], s_town[kTasks], s_tstep[kTasks];
     __shared__ u64 s_ext, s_S, s_con, s_off, s_arena, s_arena_end;
-    __shared__ int s_item, s_active, s_stop, s_ntile, s_total;
+    __shared__ int s_item, s_active, s_wait, s_poll, s_stop, s_ntile, s_total;
 
     const int tid = threadIdx.x, ln = lane(), wv = rfl(tid >> 6);
     u64* X = a.x + (int64_t)blockIdx.x * a.x_stride;
     const int nw = a.bit_words;
     u64* touch = s_bits;
-    u64* pend = s_bits + nw;
+    u64* pend = s_bits + nw;       // blocks to merge, not looked at yet,
+    u64* ready = s_bits + 2 * nw;  // known to be published,
+    u64* wait1 = s_bits + 3 * nw;  // found unpublished,
+    u64* wait2 = s_bits + 4 * nw;  // without their second publication
     u64* xs = s_xs[wv];
     u64* tab = s_tab[wv];
     if (tid == 0) s_arena = s_arena_end = 0;
@@ -343,8 +362,10 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
             s_stop = ld_dev(&a.ctl[kBmAbort]) != 0u;
             s_ext = 0;
             s_active = 0;
+            s_poll = 0;
+            s_wait = 0;
         }
-        for (int i = tid; i < 2 * nw; i += 64 * W) s_bits[i] = 0ull;
+        for (int i = tid; i < 5 * nw; i += 64 * W) s_bits[i] = 0ull;
         __syncthreads();
         const int item = s_item;
         if (item >= a.nblocks || s_stop) break;
@@ -472,31 +493,44 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
                 lds_barrier();
                 if (s_stop) return false;
                 const int nt = s_ntile;
-                for (int i = wv; i < nt; i += W) {
-                    const int32_t t = R * kRangeTiles + s_tile[i];
-                    u64* xp = &X[64 * (int64_t)t + ln];
-                    u64 m = ld_wg(xp);
-                    const u64 m0 = m;
-                    for (u64 q = m & S; q;) {
-                        const int k = __builtin_ctzll(q);
-                        const u64 ck = s_C[k];
-                        m |= ck;
-                        q &= ~(ck | (1ull << k));
+                // four tiles of a wavefront at once: their round trips overlap
+                for (int i0 = wv; i0 < nt; i0 += 4 * W) {
+                    int32_t t[4];
+                    u64 m[4], m0[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        m[j] = 0;
+                        if (i0 + j * W < nt) {
+                            t[j] = R * kRangeTiles + s_tile[i0 + j * W];
+                            m[j] = ld_wg(&X[64 * (int64_t)t[j] + ln]);
+                        }
+                        m0[j] = m[j];
                     }
-                    if (last) {
-                        if (m0) *xp = 0ull;
-                    } else if (m != m0) {
-                        *xp = m;
-                    }
-                    const int64_t q = (int64_t)s_off + base + i;
-                    if (state) {
-                        if (ln == 0) st_dev(&a.tids[q], t);
-                        st_dev(&a.masks[64 * q + ln], m & keep);
-                    } else {
-                        a.masks[64 * q + ln] = m & keep;
-                        if (ln == 0) {
-                            a.tids[q] = t;
-                            a.slot[q] = atomicAdd(&a.tcount[b0 + t], 1);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if (i0 + j * W >= nt) break;
+                        for (u64 q = m[j] & S; q;) {
+                            const int k = __builtin_ctzll(q);
+                            const u64 ck = s_C[k];
+                            m[j] |= ck;
+                            q &= ~(ck | (1ull << k));
+                        }
+                        u64* xp = &X[64 * (int64_t)t[j] + ln];
+                        if (last) {
+                            if (m0[j]) *xp = 0ull;
+                        } else if (m[j] != m0[j]) {
+                            *xp = m[j];
+                        }
+                        const int64_t q = (int64_t)s_off + base + i0 + j * W;
+                        if (state) {
+                            if (ln == 0) st_dev(&a.tids[q], t[j]);
+                            st_dev(&a.masks[64 * q + ln], m[j] & keep);
+                        } else {
+                            a.masks[64 * q + ln] = m[j] & keep;
+                            if (ln == 0) {
+                                a.tids[q] = t[j];
+                                a.slot[q] = atomicAdd(&a.tcount[b0 + t[j]], 1);
+                            }
                         }
                     }
                 }
@@ -550,7 +584,7 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
             if (wv == 0) {
                 u64 x = ld_wg(&X[64 * (int64_t)g + ln]);
                 u64 S = rows & ~s_ext0;
-                eliminate<true>(x, S);
+                eliminate_all<true>(x, S, xs, tab);
                 X[64 * (int64_t)g + ln] = x;
                 s_x[ln] = x;
                 if (ln == 0) s_S = S;
@@ -569,62 +603,48 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
         if (!stop && s_ext0 != 0ull) {
             const int npw = (g + 63) >> 6;
             uint32_t spins = 0;
-            // ORs tile q of a published list into this block's masks: for every
-            // column the masks y of the rows in `use` that hold it
-            auto merge_tile = [&](int32_t t, u64 m, const u64* y, u64 use, u64 open, int64_t hb) {
-                u64 z = 0;
-                for (u64 w = m & use; w; w &= w - 1ull) z |= y[__builtin_ctzll(w)];
-                if (t == g) {
-                    // U(k, v) with v a row of this block: a match where L(v, k) is
-                    // there too (of interest for rows k that have none yet)
-                    for (u64 w = open; w; w &= w - 1ull) {
-                        const int k = __builtin_ctzll(w);
-                        const u64 both = __ballot(((m >> k) & 1ull) && ((y[k] >> ln) & 1ull));
-                        if (both != 0ull && ln == 0) atomicMin(&a.kmatch[64 * hb + k], 64 * g + __builtin_ctzll(both));
+            // ORs up to four tiles t (masks m) of a published list into this block's
+            // masks: for every column the masks y of the rows in `use` that hold it
+            auto merge_tiles = [&](int cnt, const int32_t (&t)[4], const u64 (&m)[4], const u64* y, u64 use, u64 open,
+                                   int64_t hb) {
+                u64 z[4], o[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    z[i] = o[i] = 0;
+                    if (i < cnt) {
+                        for (u64 w = m[i] & use; w; w &= w - 1ull) z[i] |= y[__builtin_ctzll(w)];
+                        if (z[i]) o[i] = or_wg(&X[64 * (int64_t)t[i] + ln], z[i]);
                     }
                 }
-                bool fresh = false;
-                if (z) fresh = (z & ~or_wg(&X[64 * (int64_t)t + ln], z)) != 0ull;
-                if (__ballot(fresh) != 0ull && ln == 0) {
-                    atomicOr(&touch[t >> 6], 1ull << (t & 63));
-                    if (t < g) atomicOr(&pend[t >> 6], 1ull << (t & 63));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (i >= cnt) break;
+                    if (t[i] == g) {
+                        // U(k, v) with v a row of this block: a match where L(v, k) is
+                        // there too (of interest for rows k that have none yet)
+                        for (u64 w = open; w; w &= w - 1ull) {
+                            const int k = __builtin_ctzll(w);
+                            const u64 both = __ballot(((m[i] >> k) & 1ull) && ((y[k] >> ln) & 1ull));
+                            if (both != 0ull && ln == 0)
+                                atomicMin(&a.kmatch[64 * hb + k], 64 * g + __builtin_ctzll(both));
+                        }
+                    }
+                    if (__ballot((z[i] & ~o[i]) != 0ull) != 0ull && ln == 0) {
+                        atomicOr(&touch[t[i] >> 6], 1ull << (t[i] & 63));
+                        if (t[i] < g) atomicOr(&pend[t[i] >> 6], 1ull << (t[i] & 63));
+                    }
                 }
             };
-            for (;;) {
-                // tiles of a shared merge first
-                bool did = false;
-#pragma unroll
-                for (int k = 0; k < kTasks; ++k) {
-                    const uint32_t peek = (uint32_t)rfl((int)*(volatile uint32_t*)&s_tnext[k]);
-                    if ((peek & 0xFFFFu) >= (peek >> 16)) continue;
-                    uint32_t w = 0;
-                    if (ln == 0) w = atomicAdd(&s_tnext[k], 1u);
-                    w = (uint32_t)rfl((int)w);
-                    const uint32_t i = w & 0xFFFFu, nt = w >> 16;
-                    if (i >= nt) continue;
-                    wave_sync();
-                    const int64_t q = (int64_t)s_toff[k] + i;
-                    const int32_t t = rfl(ld_dev(&a.tids[q]));
-                    merge_tile(t, ld_dev(&a.masks[64 * q + ln]), s_ty[k], s_tuse[k], s_topen[k], b0 + s_tblk[k]);
-                    wave_sync();
-                    if (ln == 0 && atomicAdd(&s_tdone[k], 1) + 1 == (int)nt) {
-                        atomicExch(&s_town[k], 0);
-                        atomicSub(&s_active, 1);
-                    }
-                    ++n_read;
-                    did = true;
-                }
-                if (did) continue;
-                // Take the lowest pending block. A wavefront counts itself active
-                // before it clears a block's bit and no longer once it has merged
-                // it, and looks again after every merge: with nothing pending and
-                // nobody active the merging is done, and whoever marks a block
-                // takes it if nobody else does. (A wavefront that only looks must
-                // not count: several in step would keep each other here.)
-                int h = -1;
-                for (int w0 = 0; w0 < npw && h < 0; w0 += 64) {
+            // Takes the lowest block of a bitmap. A wavefront counts itself active
+            // before it clears a block's bit and no longer once it has merged it,
+            // and looks again after every merge: with nothing waiting and nobody
+            // active the merging is done, and whoever marks a block takes it if
+            // nobody else does. (A wavefront that only looks must not count:
+            // several in step would keep each other here.)
+            auto take = [&](u64* bits) -> int {
+                for (int w0 = 0; w0 < npw; w0 += 64) {
                     for (;;) {
-                        const u64 w = w0 + ln < npw ? *(volatile u64*)&pend[w0 + ln] : 0ull;
+                        const u64 w = w0 + ln < npw ? ld_lds(&bits[w0 + ln]) : 0ull;
                         const u64 nz = __ballot(w != 0ull);
                         if (nz == 0ull) break;
                         const int l = __builtin_ctzll(nz);
@@ -632,27 +652,152 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
                         int got = 0;
                         if (ln == 0) {
                             atomicAdd(&s_active, 1);
-                            got = (int)((atomicAnd(&pend[w0 + l], ~(1ull << b)) >> b) & 1ull);
+                            got = (int)((atomicAnd(&bits[w0 + l], ~(1ull << b)) >> b) & 1ull);
                             if (!got) atomicSub(&s_active, 1);
                         }
-                        if (rfl(got)) {
-                            h = (w0 + l) * 64 + b;
-                            break;
+                        if (rfl(got)) return (w0 + l) * 64 + b;
+                    }
+                }
+                return -1;
+            };
+            // Moves the waiting blocks that are published by now to `ready`: the
+            // states of 64 blocks per round trip.
+            auto poll = [&]() -> bool {
+                uint32_t* list = (uint32_t*)tab;  // 512 ids
+                bool any = false;
+                for (int w0 = 0; w0 < npw; w0 += 64) {
+                    u64 w = 0, w2 = 0;
+                    if (w0 + ln < npw) {
+                        w2 = ld_lds(&wait2[w0 + ln]);
+                        w = ld_lds(&wait1[w0 + ln]) | w2;
+                    }
+                    const int c = __popcll(w);
+                    int o = incl_scan(c) - c;
+                    const int total = min(sum32(c), 512);
+                    for (; w && o < 512; w &= w - 1ull, ++o) {
+                        const int b = __builtin_ctzll(w);
+                        list[o] = (uint32_t)((w0 + ln) * 64 + b) | ((w2 >> b) & 1ull ? 0x80000000u : 0u);
+                    }
+                    wave_sync();
+                    for (int i0 = 0; i0 < total; i0 += 64) {
+                        if (i0 + ln < total) {
+                            const uint32_t id = list[i0 + ln];
+                            const bool second = id >= 0x80000000u;
+                            const int b = (int)(id & 0x7FFFFFFFu);
+                            const u64 bit = 1ull << (b & 63);
+                            const u64* hd = a.head + (b0 + (int64_t)b) * kBmHeadWords;
+                            const u64 s1 = ld_dev(&hd[7]), s2 = ld_dev(&hd[23]);
+                            if (s2 != 0ull || (s1 != 0ull && !second)) {
+                                // (another wavefront may have taken it meanwhile)
+                                if (atomicAnd(second ? &wait2[b >> 6] : &wait1[b >> 6], ~bit) & bit) {
+                                    any = true;
+                                    atomicOr(&ready[b >> 6], bit);
+                                }
+                            }
+                        }
+                    }
+                    wave_sync();
+                }
+                return __ballot(any) != 0ull;
+            };
+            for (;;) {
+                // tiles of a shared merge first
+                bool did = false;
+#pragma unroll
+                for (int k = 0; k < kTasks; ++k) {
+                    const u64 peek = ld_lds(&s_tnext[k]);
+                    if (rfl((int)lo32(peek)) >= rfl((int)hi32(peek))) continue;
+                    u64 w = 0;
+                    const int step = rfl(ld_lds(&s_tstep[k]));
+                    if (ln == 0) w = atomicAdd(&s_tnext[k], (u64)step);
+                    const int i = rfl((int)lo32(w)), nt = rfl((int)hi32(w));
+                    if (i >= nt) continue;
+                    wave_sync();
+                    const int c = min(step, nt - i);
+                    const int64_t q = (int64_t)s_toff[k] + i;
+                    const int32_t tl = ln < c ? ld_dev(&a.tids[q + ln]) : 0;
+                    u64 m[4];
+                    int32_t t[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) m[j] = j < c ? ld_dev(&a.masks[64 * (q + j) + ln]) : 0ull;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) t[j] = __builtin_amdgcn_readlane(tl, j);
+                    merge_tiles(c, t, m, s_ty[k], s_tuse[k], s_topen[k], b0 + s_tblk[k]);
+                    wave_sync();
+                    if (ln == 0 && atomicAdd(&s_tdone[k], c) + c == nt) {
+                        atomicExch(&s_town[k], 0);
+                        atomicSub(&s_active, 1);
+                    }
+                    n_read += (uint32_t)c;
+                    did = true;
+                }
+                if (did) continue;
+                // then blocks known to be published, then new ones; else half of the
+                // wavefronts wait for a block each (polling its header, the shortest
+                // way on) and one of the others polls all further ones that wait
+                bool both = false, wait = false;
+                int h = take(ready);
+                if (h < 0) h = take(pend);
+                if (h < 0) {
+                    int c = 0;
+                    for (int w0 = ln; w0 < npw; w0 += 64) c += __popcll(ld_lds(&wait1[w0])) + __popcll(ld_lds(&wait2[w0]));
+                    c = sum32(c);
+                    if (c > 0) {
+                        int r = 0;  // 1: may wait, 2: may poll
+                        if (ln == 0) {
+                            if (atomicAdd(&s_wait, 1) < W / 2) {
+                                r = 1;
+                            } else {
+                                atomicSub(&s_wait, 1);
+                                atomicAdd(&s_active, 1);
+                                if (atomicExch(&s_poll, 1) == 0) r = 2;
+                                else atomicSub(&s_active, 1);
+                            }
+                        }
+                        r = rfl(r);
+                        if (r == 1) {
+                            wait = true;
+                            h = take(wait2);
+                            both = h >= 0;
+                            if (h < 0) h = take(wait1);
+                            if (h < 0) {
+                                if (ln == 0) atomicSub(&s_wait, 1);
+                                continue;
+                            }
+                        } else {
+                            bool idle = true, dead = false;
+                            if (r == 2) {
+                                idle = !poll();
+                                if (!idle) spins = 0;
+                                else if (((++spins) & 15u) == 0u) {
+                                    if (spins > kSpinLimit) st_dev(&a.ctl[kBmAbort], (uint32_t)kBmStall);
+                                    dead = rfl((int)ld_dev(&a.ctl[kBmAbort])) != 0;
+                                }
+                                if (ln == 0) {
+                                    if (dead) s_stop = 1;
+                                    atomicExch(&s_poll, 0);
+                                    atomicSub(&s_active, 1);
+                                }
+                            }
+                            if (dead || rfl(ld_lds(&s_stop))) break;
+                            if (idle) __builtin_amdgcn_s_sleep(2);
+                            continue;
                         }
                     }
                 }
                 if (h < 0) {
-                    const int act = rfl(*(volatile int*)&s_active);
-                    if (act == 0 || rfl(*(volatile int*)&s_stop)) break;
+                    const int act = rfl(ld_lds(&s_active));
+                    if (act == 0 || rfl(ld_lds(&s_stop))) break;
                     __builtin_amdgcn_s_sleep(2);
                     continue;
                 }
                 wave_sync();
                 const int64_t hb = b0 + h;
-                // wait until the rows this block needs of block h are published
-                u64 y = 0, w = 0, m[3] = {0, 0, 0};
+                // wait until the rows this block needs of block h are published, or
+                // put it back
+                u64 y = 0, w = 0, m[4] = {0, 0, 0, 0};
                 int part = 0, match = 0;
-                bool both = false, dead = false;
+                bool dead = false, back = false;
                 for (;;) {
                     for (;;) {
                         w = ln < kBmHeadWords ? ld_dev(&a.head[hb * kBmHeadWords + ln]) : 0ull;
@@ -661,6 +806,10 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
                         else if (!both && readlane64(w, 7) != 0ull && readlane64(w, 15) != 0ull) part = 0;
                         else part = -1;
                         if (part >= 0) break;
+                        if (!wait) {
+                            back = true;
+                            break;
+                        }
                         ++spins;
                         if ((spins & 15u) == 0u) {
                             if (spins > kSpinLimit) st_dev(&a.ctl[kBmAbort], (uint32_t)kBmStall);
@@ -671,7 +820,7 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
                         }
                         __builtin_amdgcn_s_sleep(1);
                     }
-                    if (dead) break;
+                    if (dead || back) break;
                     asm volatile("" ::: "memory");
                     const u64 T = ld_dev(&a.tcl[hb * 128 + part * 64 + ln]);
                     const u64 x = ld_wg(&X[64 * (int64_t)h + ln]);
@@ -680,7 +829,7 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
                     const int64_t q = (int64_t)readlane64(w, 16 * part + 2);
                     const int cnt = (int)lo32(readlane64(w, 16 * part + 3));
 #pragma unroll
-                    for (int i = 0; i < 3; ++i)
+                    for (int i = 0; i < 4; ++i)
                         if (i < cnt) m[i] = ld_dev(&a.masks[64 * (q + i) + ln]);
                     y = x | lane_or(x, T, xs, tab);
                     if (part == 0 && (__ballot(y != 0ull) & ~readlane64(w, 0)) != 0ull) {
@@ -689,6 +838,14 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
                     }
                     if (y != x) or_wg(&X[64 * (int64_t)h + ln], y);
                     break;
+                }
+                if (wait && ln == 0) atomicSub(&s_wait, 1);
+                if (back) {
+                    if (ln == 0) {
+                        atomicOr(both ? &wait2[h >> 6] : &wait1[h >> 6], 1ull << (h & 63));
+                        atomicSub(&s_active, 1);
+                    }
+                    continue;
                 }
                 if (dead) {
                     if (ln == 0) {
@@ -725,14 +882,15 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
                     }
                 }
                 int task = -1;
-                if (cnt > 3) {
+                if (cnt > 4) {
                     if (ln == 0)
                         for (int k = 0; k < kTasks && task < 0; ++k)
                             if (atomicCAS(&s_town[k], 0, 1) == 0) task = k;
                     task = rfl(task);
                 }
                 if (task >= 0) {
-                    // a long list: any wavefront takes tiles of it
+                    // a long list: any wavefront takes tiles of it, all but the four
+                    // that are loaded here already
                     s_ty[task][ln] = y;
                     if (ln == 0) {
                         s_toff[task] = h_off;
@@ -740,26 +898,39 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
                         s_topen[task] = open;
                         s_tblk[task] = h;
                         s_tdone[task] = 0;
+                        s_tstep[task] = min(4, (cnt - 4 + W - 1) / W);
                     }
                     wave_sync();
-                    if (ln == 0) atomicExch(&s_tnext[task], (uint32_t)cnt << 16);
-                    continue;
+                    if (ln == 0) atomicExch(&s_tnext[task], ((u64)cnt << 32) | 4ull);
                 }
                 wave_sync();
                 xs[ln] = y;
                 wave_sync();
+                for (int i0 = 0; i0 < (task >= 0 ? 4 : cnt); i0 += 4) {
+                    const int c = min(4, cnt - i0);
+                    const int64_t q = (int64_t)h_off + i0;
+                    int32_t tt[4];
+                    if (i0 > 0) {  // (no task free for a longer list)
+                        const int32_t tl = ln < c ? ld_dev(&a.tids[q + ln]) : 0;
 #pragma unroll
-                for (int i = 0; i < 3; ++i)
-                    if (i < cnt) merge_tile(__builtin_amdgcn_readlane(t, i), m[i], xs, use, open, hb);
-                // (no task free for a longer list)
-                for (int i = 3; i < cnt; ++i) {
-                    const int64_t q = (int64_t)h_off + i;
-                    const int32_t ti = i < 64 ? __builtin_amdgcn_readlane(t, i) : rfl(ld_dev(&a.tids[q]));
-                    merge_tile(ti, ld_dev(&a.masks[64 * q + ln]), xs, use, open, hb);
+                        for (int j = 0; j < 4; ++j) {
+                            m[j] = j < c ? ld_dev(&a.masks[64 * (q + j) + ln]) : 0ull;
+                            tt[j] = __builtin_amdgcn_readlane(tl, j);
+                        }
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) tt[j] = __builtin_amdgcn_readlane(t, j);
+                    }
+                    merge_tiles(c, tt, m, xs, use, open, hb);
                 }
-                n_read += (uint32_t)cnt;
+                n_read += (uint32_t)(task >= 0 ? 4 : cnt);
                 wave_sync();
-                if (ln == 0) atomicSub(&s_active, 1);
+                if (task < 0) {
+                    if (ln == 0) atomicSub(&s_active, 1);
+                } else if (ln == 0 && atomicAdd(&s_tdone[task], 4) + 4 == cnt) {
+                    atomicExch(&s_town[task], 0);
+                    atomicSub(&s_active, 1);
+                }
             }
             lds_barrier();
             stop = s_stop != 0;
@@ -770,7 +941,8 @@ __global__ __launch_bounds__(64 * W) void k_bm_factor(BlockArgs a) {
         u64 own = 0;
         if (wv == 0) {
             own = ld_wg(&X[64 * (int64_t)g + ln]);
-            eliminate_all(own, xs, tab);
+            u64 S = rows;
+            eliminate_all<false>(own, S, xs, tab);
             s_x[ln] = own;
         }
         lds_barrier();
@@ -1190,14 +1362,14 @@ hipError_t launch_block_tables(const Job* jobs, const int32_t* ord, const int64_
 namespace {
 using FactorKernel = void (*)(BlockArgs);
 FactorKernel factor_kernel(int waves) {
-    return waves >= 16 ? k_bm_factor<16> : waves >= 8 ? k_bm_factor<8> : k_bm_factor<4>;
+    return waves >= 8 ? k_bm_factor<8> : k_bm_factor<4>;
 }
 }  // namespace
 
 int32_t block_resident_groups(int cus, int waves, int bit_words) {
     int blocks = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, factor_kernel(waves), 64 * waves,
-                                                     (size_t)bit_words * 16) != hipSuccess ||
+                                                     (size_t)bit_words * 40) != hipSuccess ||
         blocks <= 0) {
         (void)hipGetLastError();
         blocks = 1;
@@ -1208,7 +1380,7 @@ int32_t block_resident_groups(int cus, int waves, int bit_words) {
 hipError_t launch_block_factor(const BlockArgs& a, hipStream_t st) {
     if (a.nblocks <= 0) return hipSuccess;
     hipLaunchKernelGGL(factor_kernel(a.waves), dim3((unsigned)a.nslots), dim3((unsigned)(64 * a.waves)),
-                       (size_t)a.bit_words * 16, st, a);
+                       (size_t)a.bit_words * 40, st, a);
     return hipGetLastError();
 }
 

@@ -1970,13 +1970,16 @@ struct Engine {
         return tune_table().count(key) == 0;
     }
 
-    // Wavefronts per block. Sixteen shorten a block's own work (up to 95 tiles on
-    // the 64^3 27-point stencil: 7.5 ms with sixteen, 9.5 with four), four put more
-    // blocks in flight, which counts where the blocks are many and their chains
-    // short (1000^2 9-point, 15,625 blocks: 4.7 ms with four, 7.5 with sixteen; 512
-    // batch members, 20,000 blocks: 3.3 and 4.1). 100,000 rows of a 2D stencil
-    // (1,561 blocks) take 1.09 and 1.02 ms.
-    static int32_t block_waves(int64_t nblocks) { return nblocks <= 8192 ? 16 : 4; }
+    // Wavefronts per block. Eight shorten a block's own work, four put more blocks
+    // in flight, which counts for one matrix of many blocks, whose separators wait
+    // for chains far behind them (1000^2 9-point, 15,625 blocks: 3.1 ms with four,
+    // 3.6 with eight, 4.9 with sixteen; 64^3 27-point, 4,096 blocks: 5.4, 4.6 and
+    // 4.7; 20,000 blocks of 512 batch members: 2.7, 2.5 and 3.3). Batches with a
+    // member of more than 2^21 rows take four too: the bitmaps and eight
+    // wavefronts' tables together would pass 64 KiB of LDS.
+    static int32_t block_waves(int64_t nblocks, int32_t nj, int32_t words) {
+        return (nj == 1 && nblocks > 8192) || words > 512 ? 4 : 8;
+    }
 
     // The block path (gsofa_blocks.hip). False: the call's memory budget does not
     // hold it, the general path takes the call.
@@ -2002,7 +2005,7 @@ struct Engine {
         // workgroups in flight: all resident ones, at most 8 GiB of column masks
         // (the 1000^2 stencil's 1,024 workgroups fill that); a served request
         // takes the part of them that its traversal slots are of all
-        const int32_t waves = block_waves(nblocks);
+        const int32_t waves = block_waves(nblocks, nj, words);
         int64_t ns = block_resident_groups(device_cus(), waves, words);
         if (plan.nslots > 0) ns = std::min<int64_t>(ns, ns * plan.nslots / traverse_resident_slots(device_cus(), 0));
         ns = std::min<int64_t>(ns, std::max<int64_t>(nblocks, 1));

@@ -120,7 +120,7 @@ struct BlockArgs {
     const int32_t* items;         // order in which blocks are taken (nullptr: ascending)
     int32_t nblocks;
     int32_t nslots;               // workgroups, each with a slot of x
-    int32_t waves;                // wavefronts per workgroup: 4, 8 or 16
+    int32_t waves;                // wavefronts per workgroup: 4 or 8
     unsigned long long* x;        // nslots * x_stride column masks, all zero between uses
     int64_t x_stride;
     int32_t bit_words;            // 64-bit words of a bitmap over the blocks of the largest matrix
