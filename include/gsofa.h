@@ -342,7 +342,8 @@ GSOFA_API int gsofa_graph_counters(uint64_t* out);
  *     supernodes (may be NULL with GSOFA_NO_SUPERNODES). All device pointers,
  *     caller-owned; n >= 0 and u_ptr, l_ptr non-NULL even for n = 0.
  *   counts (host, caller-owned): nnz and fill totals, nsuper, statistics, and
- *     scratch_bytes, the scratch the call needed (or would have needed).
+ *     scratch_bytes, the scratch the call needed (or would have needed) with
+ *     one traversal per source, whichever path it took.
  *   opts: stream, window, concurrent_sources, max_supernode and the flags
  *     GSOFA_NO_SUPERNODES, GSOFA_L_CSR, GSOFA_NO_LINE95, GSOFA_LEVEL_ORDER,
  *     GSOFA_MAP_WAVE32, GSOFA_MAP_WAVE32_7, GSOFA_INPUT_ON_DEVICE,

@@ -840,9 +840,6 @@ struct MatIn {
 // Largest order of a one-matrix call that launches its phases eagerly.
 constexpr int64_t kEagerMaxRows = 65536;
 
-// Mapping code of the block path (gsofa_stats.mapping).
-constexpr int32_t kMapBlocks = 7;
-
 // Calls with fewer sources are latency-bound and use the defaults untuned.
 constexpr int64_t kTuneMinSources = 65536;
 // Memory-budget mode: pinned host memory for worklist and row-buffer overflow,

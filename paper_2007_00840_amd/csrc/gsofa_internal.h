@@ -101,6 +101,7 @@ struct TraverseArgs {
 // ---- block path (gsofa_blocks.hip): 64 rows at a time as bit masks
 
 constexpr int64_t kBlockMaxRows = int64_t(1) << 22;  // LDS bitmaps: one bit per 64 columns
+constexpr int32_t kMapBlocks = 7;                    // the path's number in stats.mapping
 constexpr int kBmHeadWords = 32;                     // 64-bit words per block: headers of its two publications
 enum BmCtl { kBmNext = 0, kBmAbort = 1 };
 enum BmAbortCode { kBmOverflow = 1, kBmStall = 2 };

@@ -1,5 +1,5 @@
-// gsofa_symbolic_noalloc: the one-matrix pipeline of gsofa_symbolic (fill
-// detection, row sort, supernodes, L transpose) on device-resident input,
+// gsofa_symbolic_noalloc: the one-matrix pipeline of gsofa_symbolic (block path,
+// or fill detection, row sort, supernodes, L transpose) on device-resident input,
 // writing into caller-provided device arrays, with every working buffer carved
 // from one fixed scratch array in device memory. Nothing here allocates device
 // memory: no hipMalloc, no hipFree, no caller allocator.
@@ -11,6 +11,10 @@
 //   span A: the source slots during fill detection; afterwards (the slots are
 //     dead then) the row-wise L and the transpose's staging array;
 //   span B: the output pool, then whatever of it the pool did not use.
+// The block path keeps its arrays, column masks and tiles where spans A and B
+// lie. Which calls fit is the traversal's layout in both cases (a call's rows and
+// statistics do not depend on the path, its limits may not either); what fits
+// there and not the block path's arrays is traversed.
 #include <chrono>
 #include <map>
 #include <mutex>
@@ -102,6 +106,160 @@ constexpr uint32_t kAllowed = GSOFA_NO_SUPERNODES | GSOFA_L_CSR | GSOFA_NO_LINE9
             return GSOFA_EDEVICE;                  \
         }                                          \
     } while (0)
+
+constexpr int kNotHere = -1000;  // blocks_noalloc: the arrays do not fit
+
+// What both paths know when fill detection starts.
+struct Call {
+    int32_t n;
+    int64_t nnz, u_cap, l_cap;
+    int64_t *u_ptr, *l_ptr;
+    int32_t *u_idx, *l_idx, *xsup, *supno;
+    bool want_sn, l_csr;
+    const Job* job;
+    JobStats* js;
+    const int64_t* jrb;
+    const int32_t* jn;
+    int64_t* scan_scr;
+    int32_t *row_ucnt, *row_lcnt, *is_start;
+    int64_t* start_scan;
+    const int64_t* bfirst;
+    const int32_t* blen;
+    int64_t nsb;                  // supernode blocks
+    size_t slot_cap, pool_at;     // the traversal's layout: bytes of its slots, its
+    int64_t pool_cap;             // pool's place and entries
+    hipStream_t st;
+    int cus;
+};
+
+// The block path (gsofa_blocks.hip) in [base, base + cap) of the scratch, the
+// tiles taking what the other arrays leave. Whole calls, traversal and blocks:
+// 44 x 45 9-point 1.6 and 0.45 ms, 100 x 100 8.1 and 0.61, 30^3 27-point 210 and
+// 1.17, 350 x 350 2,234 and 2.6 (the traversal has few slots there). Left to the
+// traversal: the options that name it, and matrices whose tiles hold few entries
+// and overflow the pool, which an aborted launch of a few milliseconds finds.
+int blocks_noalloc(const Call& k, uint8_t* base, size_t cap, double t0, gsofa_counts* c) {
+    const hipStream_t st = k.st;
+    const int64_t nb = ((int64_t)k.n + 63) / 64, stride = 64 * nb;
+    const int32_t words = (int32_t)((nb + 63) / 64);
+    Span sp{base, cap, 0};
+    // cleared before the launch: control words, headers, tile counts
+    const int64_t z_cnt = 256 + 8 * kBmHeadWords * nb, z_bytes = (z_cnt + 4 * nb + 15) & ~int64_t(15);
+    uint8_t* zero = sp.take<uint8_t>(z_bytes);
+    BlockArgs a{};
+    a.jobs = k.job;
+    a.nblocks = (int32_t)nb;
+    a.waves = 8;
+    a.x_stride = stride;
+    a.bit_words = words;
+    a.jstats = k.js;
+    a.row_ucnt = k.row_ucnt;
+    a.row_lcnt = k.row_lcnt;
+    a.tcl = sp.take<unsigned long long>(128 * nb);
+    a.kmatch = sp.take<int32_t>(64 * nb);
+    a.diag = sp.take<unsigned long long>(64 * nb);
+    a.lcl = sp.take<unsigned long long>(64 * nb);
+    a.rec = sp.take<BlockRec>(nb);
+    int32_t* col_cnt = sp.take<int32_t>(k.n);
+    int64_t* list_ptr = sp.take<int64_t>(nb + 1);
+    BlockCols bc{};
+    bc.ptr = list_ptr;
+    bc.big = sp.take<int32_t>(nb);
+    if (sp.off + 4096 >= cap) return kNotHere;
+    // column masks of all resident workgroups, at most a third of what is left
+    int64_t ns = std::min<int64_t>(block_resident_groups(k.cus, a.waves, words), nb);
+    ns = std::min<int64_t>(ns, (int64_t)((cap - sp.off) / 3) / (8 * stride));
+    if (ns < 1) return kNotHere;
+    a.nslots = (int32_t)ns;
+    a.x = sp.take<unsigned long long>(ns * stride);
+    const int64_t tiles = ((int64_t)(cap - sp.off) - 8 * 256) / (512 + 24);
+    if (tiles < 2 * nb) return kNotHere;
+    a.masks = sp.take<unsigned long long>(64 * tiles);
+    a.tids = sp.take<int32_t>(tiles);
+    a.slot = sp.take<int32_t>(tiles);
+    bc.blk = sp.take<int32_t>(tiles);
+    bc.tile = sp.take<int32_t>(tiles);
+    bc.blk2 = sp.take<int32_t>(tiles);
+    bc.tile2 = sp.take<int32_t>(tiles);
+    if (sp.off > cap) return kNotHere;
+    a.pool_cap = tiles;
+    a.ctl = reinterpret_cast<uint32_t*>(zero);
+    a.head = reinterpret_cast<unsigned long long*>(zero + 256);
+    a.tcount = reinterpret_cast<int32_t*>(zero + z_cnt);
+    a.pool_tail = reinterpret_cast<unsigned long long*>(a.ctl + 8);
+    bc.nbig = reinterpret_cast<int32_t*>(a.ctl + 4);
+
+    const double tt0 = now_ms();
+    NA_CHK(launch_zero_i32(reinterpret_cast<int32_t*>(zero), z_bytes / 4, st));
+    NA_CHK(launch_zero_i32(reinterpret_cast<int32_t*>(a.x), 2 * ns * stride, st));
+    NA_CHK(launch_block_factor(a, st));
+    uint32_t ctl[16];
+    NA_CHK(hipMemcpyAsync(ctl, a.ctl, sizeof(ctl), hipMemcpyDeviceToHost, st));
+    NA_CHK(launch_scan_counts(a.tcount, nullptr, nb, list_ptr, k.scan_scr, st));
+    NA_CHK(launch_block_counts(a, bc, col_cnt, st));
+    NA_CHK(launch_scan_counts(k.row_ucnt, nullptr, k.n, k.u_ptr, k.scan_scr, st));
+    NA_CHK(launch_scan_counts(k.l_csr ? k.row_lcnt : col_cnt, nullptr, k.n, k.l_ptr, k.scan_scr, st));
+    JobStats hs{};
+    int64_t tot[2] = {0, 0};
+    NA_CHK(hipMemcpyAsync(&tot[0], k.u_ptr + k.n, 8, hipMemcpyDeviceToHost, st));
+    NA_CHK(hipMemcpyAsync(&tot[1], k.l_ptr + k.n, 8, hipMemcpyDeviceToHost, st));
+    NA_CHK(hipMemcpyAsync(&hs, k.js, sizeof(JobStats), hipMemcpyDeviceToHost, st));
+    NA_CHK(hipStreamSynchronize(st));
+    const double tt1 = now_ms();
+    if (ctl[kBmAbort] == (uint32_t)kBmOverflow) return kNotHere;
+    if (ctl[kBmAbort] != 0u) return GSOFA_EDEVICE;
+    if (hs.err & kErrDuplicate) return GSOFA_EINVAL;
+
+    // what fits is what the traversal's pool and its row-wise L would
+    const int64_t nnz_u = tot[0], nnz_l = tot[1];
+    c->scratch_bytes = (int64_t)k.pool_at + 4 * (nnz_u + nnz_l);
+    if (nnz_u + nnz_l > k.pool_cap) return GSOFA_ECAPACITY;
+    c->nnz_u = nnz_u;
+    c->nnz_l = nnz_l;
+    c->fills = nnz_u + nnz_l - (k.nnz + k.n - (int64_t)hs.diag);
+    if (nnz_u > k.u_cap || nnz_l > k.l_cap) return GSOFA_ECAPACITY;
+    if (!k.l_csr) {
+        Span slots{base, k.slot_cap, 0}, rest{base, 4 * (size_t)k.pool_cap, 4 * (size_t)(nnz_u + nnz_l)};
+        for (int i = 0; i < 2; ++i)
+            if (!slots.take<int32_t>(nnz_l) && !rest.take<int32_t>(nnz_l)) {
+                c->scratch_bytes += 8 * nnz_l + 512;
+                return GSOFA_ECAPACITY;
+            }
+    }
+
+    NA_CHK(launch_block_rows(a, true, k.u_ptr, k.u_idx, st));
+    if (k.l_csr) NA_CHK(launch_block_rows(a, false, k.l_ptr, k.l_idx, st));
+    else NA_CHK(launch_block_cols(a, bc, k.l_ptr, k.l_idx, st));
+    NA_CHK(launch_block_reach(a, bc, st));
+    const double ts0 = now_ms();
+    if (k.want_sn) {
+        const RowSpace rs{k.n, nullptr, nullptr};
+        NA_CHK(launch_supernodes(rs, k.nsb, k.bfirst, k.blen, k.u_ptr, k.l_ptr, k.l_idx, !k.l_csr, k.is_start, st));
+        NA_CHK(launch_scan_counts(k.is_start, nullptr, k.n, k.start_scan, k.scan_scr, st));
+        NA_CHK(launch_supernode_assemble(rs, 1, k.is_start, k.start_scan, k.xsup, k.supno, st));
+        NA_CHK(launch_supernode_terminals(1, k.jrb, k.jn, k.start_scan, k.xsup, st));
+    }
+    int64_t h_ns = 0;
+    NA_CHK(hipMemcpyAsync(&hs, k.js, sizeof(JobStats), hipMemcpyDeviceToHost, st));
+    if (k.want_sn) NA_CHK(hipMemcpyAsync(&h_ns, k.start_scan + k.n, 8, hipMemcpyDeviceToHost, st));
+    NA_CHK(hipStreamSynchronize(st));
+    const double t1 = now_ms();
+
+    c->nsuper = (int32_t)h_ns;
+    c->stats.concurrent_sources = (int32_t)std::min<int64_t>(64 * ns, k.n);
+    c->stats.iterations = hs.iterations;
+    c->stats.windows = (uint64_t)nb;
+    c->stats.edges_alg = hs.edges_alg + (uint64_t)k.nnz;
+    c->stats.edges_gpu = hs.edges_gpu;
+    c->stats.peak_device_bytes = (uint64_t)c->scratch_bytes;
+    c->stats.t_traverse_ms = tt1 - tt0;
+    c->stats.t_emit_ms = ts0 - tt1;
+    c->stats.t_supernode_ms = t1 - ts0;
+    c->stats.t_total_ms = t1 - t0;
+    c->stats.mapping = kMapBlocks;
+    c->stats.launches = 1;
+    return GSOFA_OK;
+}
 
 int run_noalloc(int32_t n, const int32_t* row_ptr, const int32_t* col_idx, const gsofa_opts* o,
                 int64_t* u_ptr, int32_t* u_idx, int64_t u_cap, int64_t* l_ptr, int32_t* l_idx,
@@ -220,6 +378,44 @@ int run_noalloc(int32_t n, const int32_t* row_ptr, const int32_t* col_idx, const
     NA_CHK(hipStreamSynchronize(st));
     if (h_bad || h_last < 0) return GSOFA_EINVAL;
     c->nnz_a = h_last;
+
+    // ---- the block path, unless an option names the traversal
+    constexpr uint32_t kTraversal = GSOFA_NO_LINE95 | GSOFA_LEVEL_ORDER | GSOFA_MAP_WAVE32 | GSOFA_MAP_WAVE32_7;
+    if ((flags & kTraversal) == 0 && !(o && (o->window > 0 || o->concurrent_sources > 0)) && n <= kBlockMaxRows) {
+        Call k{};
+        k.n = n;
+        k.nnz = h_last;
+        k.u_cap = u_cap;
+        k.l_cap = l_cap;
+        k.u_ptr = u_ptr;
+        k.l_ptr = l_ptr;
+        k.u_idx = u_idx;
+        k.l_idx = l_idx;
+        k.xsup = xsup;
+        k.supno = supno;
+        k.want_sn = want_sn;
+        k.l_csr = l_csr;
+        k.job = d_job;
+        k.js = d_js;
+        k.jrb = d_jrb;
+        k.jn = d_jn;
+        k.scan_scr = scan_scr;
+        k.row_ucnt = row_cnt;
+        k.row_lcnt = row_lcnt;
+        k.is_start = is_start;
+        k.start_scan = start_scan;
+        k.bfirst = bfirst;
+        k.blen = blen;
+        k.nsb = nblocks;
+        k.slot_cap = spA.cap;
+        k.pool_at = (size_t)(spB.base - base);
+        k.pool_cap = pool_cap;
+        k.st = st;
+        k.cus = cus;
+        const int rc = blocks_noalloc(k, slots, (size_t)(base + kScratchBytes - slots), t0, c);
+        if (rc != kNotHere) return rc;
+        NA_CHK(launch_zero_i32(reinterpret_cast<int32_t*>(d_js), (int64_t)(sizeof(JobStats) / 4), st));
+    }
 
     // ---- fill detection
     const double tt0 = now_ms();

@@ -113,3 +113,60 @@ def test_block_path_repeated_column_is_refused(g):
     assert e.value.code == g.EINVAL
     n, rp, ci = _stencil(9, (20, 20), True, 8)
     assert g.symbolic(n, rp, ci).fills == oracle.fills(oracle.symbolic(n, rp, ci), rp, ci)
+
+
+def _pairs(n, seed):
+    """Rows coupled two by two at random: a tile per entry, which the block path's
+    share of the fixed scratch does not hold."""
+    p = np.random.default_rng(seed).permutation(n)
+    mate = np.empty(n, dtype=np.int64)
+    mate[p[0::2]], mate[p[1::2]] = p[1::2], p[0::2]
+    rows = np.sort(np.stack([np.arange(n), mate], axis=1), axis=1)
+    return n, np.arange(0, 2 * n + 1, 2, dtype=np.int32), rows.reshape(-1).astype(np.int32)
+
+
+NOALLOC = {
+    **{f"band_n{n}": (lambda n=n: _band(n, 9, 11, n), {}, 7) for n in (1, 63, 64, 65, 129)},
+    "nd_2d": (lambda: _stencil(9, (70, 61), True, 5), {}, 7),
+    "nd_3d": (lambda: _stencil(27, (19, 18, 17), True, 6), {}, 7),
+    "sources_named": (lambda: _stencil(9, (70, 61), True, 5), {"concurrent_sources": 64}, 0),
+    "window_named": (lambda: _stencil(9, (70, 61), True, 5), {"window": 16}, 0),
+    "tiles_do_not_fit": (lambda: _pairs(200000, 9), {}, 0),
+}
+
+
+@pytest.mark.parametrize("name", NOALLOC)
+def test_noalloc_path_and_result(g, name):
+    import torch
+    make, opts, mapping = NOALLOC[name]
+    n, rp, ci = make()
+    print(f"noalloc {name} n={n} nnz={len(ci)}", flush=True)
+    ref = oracle.symbolic(n, rp, ci)
+    # (one entry more than the matrix has: an empty tensor has no address)
+    drp, dci = torch.from_numpy(rp).cuda(), torch.from_numpy(np.append(ci, np.int32(0))).cuda()
+    nu, nl = int(ref.u_ptr[-1]), int(ref.l_ptr[-1])
+    for flags in (0, g.L_CSR):
+        out = {k: torch.full((m,), -7, dtype=t, device="cuda")
+               for k, m, t in (("u_ptr", n + 1, torch.int64), ("l_ptr", n + 1, torch.int64),
+                               ("u_idx", nu + 3, torch.int32), ("l_idx", nl + 3, torch.int32),
+                               ("xsup", n + 1, torch.int32), ("supno", n, torch.int32))}
+        c = g.symbolic_noalloc(n, drp, dci, **out, flags=flags, **opts)
+        assert c["stats"]["mapping"] == mapping
+        got = {k: v.cpu().numpy() for k, v in out.items()}
+        assert (c["nnz_u"], c["nnz_l"], c["stats"]["edges_alg"]) == (nu, nl, ref.edges_alg)
+        assert np.array_equal(got["u_ptr"], ref.u_ptr) and np.array_equal(got["u_idx"][:nu], ref.u_idx)
+        assert np.array_equal(got["l_ptr"], ref.l_rptr if flags else ref.l_ptr)
+        assert np.array_equal(got["l_idx"][:nl], ref.l_ridx if flags else ref.l_idx)
+        assert np.array_equal(got["xsup"][:c["nsuper"] + 1], ref.xsup) and np.array_equal(got["supno"], ref.supno)
+        assert (got["u_idx"][nu:] == -7).all() and (got["l_idx"][nl:] == -7).all()
+    # the limits are those of the traversal: what it refuses for want of room is
+    # refused here with the same totals
+    small = dict(out, u_idx=out["u_idx"][:max(nu - 1, 0)])
+    counts = []
+    for o in (opts, dict(opts, concurrent_sources=1 << 20)):
+        with pytest.raises(g.GsofaError) as e:
+            g.symbolic_noalloc(n, drp, dci, **small, **o)
+        assert e.value.code == g.ECAPACITY
+        counts.append([e.value.counts[k] for k in ("nnz_u", "nnz_l", "fills", "scratch_bytes")])
+    if "concurrent_sources" not in opts:
+        assert counts[0] == counts[1]
