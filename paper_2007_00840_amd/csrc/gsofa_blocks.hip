@@ -982,9 +982,31 @@ __global__ __launch_bounds__(64 * W, 4) void k_bm_factor(BlockArgs a) {
 
 // -------------------------------------------------------------- row counts
 
-// Entries of L and U per row: a row's count is the popcount of a ballot over 64
-// columns' masks; each of the four wavefronts counts 16 of the block's rows.
+namespace {
+constexpr int kPlanes = 16;  // a wavefront counts less than 2^16 tiles
+
+// m's bits, 64 by 64, with rows and columns exchanged
+__device__ __forceinline__ u64 transpose64(u64 x) {
+    const int ln = lane();
+    u64 keep = 0x00000000FFFFFFFFull;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        const u64 y = __shfl_xor(x, d, 64);
+        x = ln & d ? (x & ~keep) | ((y >> d) & keep) : (x & keep) | ((y << d) & ~keep);
+        keep ^= keep << (d >> 1);
+    }
+    return x;
+}
+}  // namespace
+
+// Entries of L and U per row. A lane adds its columns' masks up in bit planes
+// (plane j holds bit j of 64 counters, one per row), four tiles in flight; then
+// the planes change rows with columns and lane r sums row r's popcounts. A
+// ballot per tile and row instead took 468 us on the 64^3 27-point stencil (204 on
+// 1000^2 9-point); this way 64 (69): the tiles are
+// read once.
 __global__ __launch_bounds__(kThreads) void k_bm_count(BlockArgs a) {
+    __shared__ int32_t s_cnt[2][64];
     const int ln = lane(), wv = rfl(threadIdx.x >> 6);
     if (ld_dev(&a.ctl[kBmAbort]) != 0u) return;
     const int32_t gb = blockIdx.x;
@@ -993,24 +1015,49 @@ __global__ __launch_bounds__(kThreads) void k_bm_count(BlockArgs a) {
     const int32_t g = gb - (int32_t)J->item_base;
     const int32_t nr = min(64, J->n - 64 * g);
     const BlockRec rec = a.rec[gb];
-    int32_t lc = 0, uc = 0;  // lane i < 16: row 16 wv + i
-    auto add = [&](u64 m, int32_t& c) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int p = __popcll(__ballot((m >> (16 * wv + i)) & 1ull));
-            if (ln == i) c += p;
-        }
-    };
+    if (threadIdx.x < 128) s_cnt[threadIdx.x >> 6][ln] = 0;
+    __syncthreads();
     const u64 d = a.diag[64 * (int64_t)gb + ln];
-    add(d & above(ln), lc);
-    add(d & ~above(ln), uc);
-    for (int i = 0; i < rec.l_cnt; ++i) add(a.masks[64 * (rec.l_off + i) + ln], lc);
-    for (int i = 0; i < rec.u_cnt; ++i) add(a.masks[64 * (rec.u_off + i) + ln], uc);
-    const int r = 16 * wv + ln;
-    if (ln < 16 && r < nr) {
-        const int64_t row = J->row_base + 64 * (int64_t)g + r;
-        a.row_lcnt[row] = lc;
-        a.row_ucnt[row] = uc;
+#pragma unroll
+    for (int part = 0; part < 2; ++part) {
+        const int64_t off = part ? rec.u_off : rec.l_off;
+        const int32_t cnt = part ? rec.u_cnt : rec.l_cnt;
+        u64 c[kPlanes];
+#pragma unroll
+        for (int p = 0; p < kPlanes; ++p) c[p] = 0;
+        int k = 0;  // masks added so far
+        auto add = [&](u64 m) {
+            ++k;
+#pragma unroll
+            for (int p = 0; p < kPlanes; ++p) {
+                const u64 t = c[p] & m;
+                c[p] ^= m;
+                m = t;
+                if (k < (2 << p)) break;
+            }
+        };
+        if (wv == 0) add(part ? d & ~above(ln) : d & above(ln));
+        for (int i0 = wv; i0 < cnt; i0 += 16) {
+            u64 m[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) m[j] = i0 + 4 * j < cnt ? a.masks[64 * (off + i0 + 4 * j) + ln] : 0ull;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (i0 + 4 * j < cnt) add(m[j]);
+        }
+        int sum = 0;
+#pragma unroll
+        for (int p = 0; p < kPlanes; ++p) {
+            if (k < (1 << p)) break;
+            sum += __popcll(transpose64(c[p])) << p;
+        }
+        if (k) atomicAdd(&s_cnt[part][ln], sum);
+    }
+    __syncthreads();
+    if (threadIdx.x < nr) {
+        const int64_t row = J->row_base + 64 * (int64_t)g + threadIdx.x;
+        a.row_lcnt[row] = s_cnt[0][threadIdx.x];
+        a.row_ucnt[row] = s_cnt[1][threadIdx.x];
     }
 }
 
@@ -1094,23 +1141,17 @@ __global__ __launch_bounds__(64) void k_bm_lists(BlockArgs a, BlockCols c, int32
 }
 
 // ---------------------------------------------------------------- emission
+//
+// Both kernels write 16 of a block's rows (columns) per wavefront. The places of
+// the 16 are scalar registers and move by scalar popcounts; a row's ids of one
+// tile are the set bits of one mask, stored side by side by the lanes that hold
+// them. Tiles are loaded four ahead of their turn. 64^3 27-point: rows 395 -> 288
+// us, columns 489 -> 345, 130 of it without the stores; 1000^2 9-point 206 -> 124
+// and 192 -> 129, 99 of it without the stores. (Collecting 64 ids per row in LDS,
+// for whole aligned stores, took 377 and 421 us; masks by scalar loads as long
+// as this on the first and longer on the second.)
 
-// Sixteen rows (or columns) of a tile at a time: the ids of row r0 + i are the
-// set bits of a ballot over the lanes' masks, stored consecutively at the
-// position that lane i carries.
-__device__ __forceinline__ void emit16(u64 m, int r0, int32_t id, int64_t& at, int32_t* idx) {
-#pragma unroll 4
-    for (int i = 0; i < 16; ++i) {
-        const bool has = (m >> (r0 + i)) & 1ull;
-        const u64 b = __ballot(has);
-        const int64_t base = (int64_t)readlane64((u64)at, i);
-        if (has) idx[base + (int)below_count(b)] = id;
-        if (lane() == i) at += __popcll(b);
-    }
-}
-
-// Rows of U, or of L row-wise; each of the four wavefronts writes 16 of the
-// block's rows.
+// Rows of U, or of L row-wise.
 template <bool upper>
 __global__ __launch_bounds__(kThreads) void k_bm_rows(BlockArgs a, const int64_t* ptr, int32_t* idx) {
     const int ln = lane(), wv = rfl(threadIdx.x >> 6);
@@ -1122,19 +1163,54 @@ __global__ __launch_bounds__(kThreads) void k_bm_rows(BlockArgs a, const int64_t
     const BlockRec rec = a.rec[gb];
     const int r0 = 16 * wv;
     if (r0 >= nr) return;
-    int64_t at = 0;
-    if (ln < 16 && r0 + ln < nr) at = ptr[J->row_base + 64 * (int64_t)g + r0 + ln];
+    // (no branch on the lane: the places stay known as scalars)
+    const int64_t at = ptr[J->row_base + 64 * (int64_t)g + r0 + min(ln, min(16, nr - r0) - 1)];
+    int32_t* p[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) p[i] = idx + readlane64((u64)at, i);
+    auto put = [&](u64 m, int32_t id) {
+        const uint32_t w = (uint32_t)(m >> r0);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const u64 b = __ballot((w & (1u << i)) != 0u);
+            if (__builtin_amdgcn_inverse_ballot_w64(b)) p[i][below_count(b)] = id;
+            p[i] += __popcll(b);
+        }
+    };
     const u64 d = a.diag[64 * (int64_t)gb + ln];
-    if (upper) emit16(d & ~above(ln), r0, 64 * g + ln, at, idx);
+    if (upper) put(d & ~above(ln), 64 * g + ln);
     const int64_t off = upper ? rec.u_off : rec.l_off;
     const int32_t cnt = upper ? rec.u_cnt : rec.l_cnt;
-    for (int i = 0; i < cnt; ++i) emit16(a.masks[64 * (off + i) + ln], r0, 64 * a.tids[off + i] + ln, at, idx);
-    if (!upper) emit16(d & above(ln), r0, 64 * g + ln, at, idx);
+    u64 m[4];
+    int32_t t[4];
+    auto load = [&](int i, int32_t tl) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            m[j] = i + j < cnt ? a.masks[64 * (off + i + j) + ln] : 0ull;
+            t[j] = __builtin_amdgcn_readlane(tl, (i + j) & 63);
+        }
+    };
+    int32_t tl = ln < cnt ? a.tids[off + ln] : 0;
+    load(0, tl);
+    for (int i = 0; i < cnt; i += 4) {
+        u64 m0[4];
+        int32_t t0[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            m0[j] = m[j];
+            t0[j] = t[j];
+        }
+        if (((i + 4) & 63) == 0) tl = i + 4 + ln < cnt ? a.tids[off + i + 4 + ln] : 0;
+        load(i + 4, tl);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) put(m0[j], 64 * t0[j] + ln);
+    }
+    if (!upper) put(d & above(ln), 64 * g + ln);
 }
 
 // Columns of L: the tiles of a block of columns by ascending row block, the rows
-// of a column being the set bits of its mask; each of the four wavefronts
-// writes 16 of the block's columns.
+// of a column being the set bits of its mask. One load brings the wavefront's 16
+// columns of four tiles.
 __global__ __launch_bounds__(kThreads) void k_bm_cols(BlockArgs a, BlockCols c, const int64_t* l_ptr, int32_t* l_idx) {
     const int ln = lane(), wv = rfl(threadIdx.x >> 6);
     const int32_t cb = blockIdx.x;
@@ -1143,22 +1219,107 @@ __global__ __launch_bounds__(kThreads) void k_bm_cols(BlockArgs a, BlockCols c, 
     const int32_t c0 = cb - (int32_t)J->item_base;
     const int nc = min(16, J->n - 64 * c0 - 16 * wv);
     if (nc <= 0) return;
-    int64_t at = 0;
-    if (ln < nc) at = l_ptr[J->row_base + 64 * (int64_t)c0 + 16 * wv + ln];
-    auto put = [&](int32_t g, u64 m) {
-#pragma unroll 4
+    // (no branch on the lane: the places stay known as scalars)
+    const int64_t at = l_ptr[J->row_base + 64 * (int64_t)c0 + 16 * wv + min(ln, nc - 1)];
+    int32_t* p[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) p[i] = l_idx + readlane64((u64)at, i);
+    const int col = 16 * wv + (ln & 15);
+    auto put = [&](int32_t g, u64 m, int j) {
+#pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const u64 w = readlane64(m, i);
-            if (w == 0ull) continue;
-            const int64_t base = (int64_t)readlane64((u64)at, i);
-            if ((w >> ln) & 1ull) l_idx[base + (int)below_count(w)] = 64 * g + ln;
-            if (ln == i) at += __popcll(w);
+            const u64 w = readlane64(m, 16 * j + i);
+            if (__builtin_amdgcn_inverse_ballot_w64(w)) p[i][below_count(w)] = 64 * g + ln;
+            p[i] += __popcll(w);
         }
     };
-    const int col = 16 * wv + (ln & 15);  // lane i < 16: the mask of column 16 wv + i
-    put(c0, a.diag[64 * (int64_t)cb + col] & above(col));
-    for (int64_t e = c.ptr[cb]; e < c.ptr[cb + 1]; ++e)
-        put(c.blk2[e], a.masks[64 * (int64_t)c.tile2[e] + col]);
+    put(c0, a.diag[64 * (int64_t)cb + col] & above(col), 0);
+    const int64_t e0 = c.ptr[cb];
+    const int cnt = (int)(c.ptr[cb + 1] - e0);
+    int32_t bl = 0, tl = 0;
+    auto ids = [&](int i) {
+        const bool in = i + ln < cnt;
+        bl = in ? c.blk2[e0 + i + ln] : 0;
+        tl = in ? c.tile2[e0 + i + ln] : 0;
+    };
+    // (the shuffle before the test: it reads lanes that the test leaves out)
+    auto load = [&](int i) -> u64 {
+        const int32_t q = __shfl(tl, (i + (ln >> 4)) & 63, 64);
+        return i + (ln >> 4) < cnt ? a.masks[64 * (int64_t)q + col] : 0ull;
+    };
+    ids(0);
+    u64 m = load(0);
+    for (int i = 0; i < cnt; i += 4) {
+        const u64 m0 = m;
+        int32_t g[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) g[j] = __builtin_amdgcn_readlane(bl, (i + j) & 63);
+        if (((i + 4) & 63) == 0) ids(i + 4);
+        m = load(i + 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) put(g[j], m0, j);
+    }
+}
+
+// -------------------------------------------------------------- supernodes
+//
+// Phase I: a row with one U entry less than the row above may extend that
+// row's supernode (inside the same run of max_super rows). Phase II: a chain of
+// such rows is cut before every row s without L(s, r), r the supernode's first
+// row so far. A wavefront takes the chains that begin in its block and follows
+// the last one into the next blocks; inside a block the next cut is the first
+// bit missing from column r's mask, a few scalar instructions, where one lane
+// per chain and a binary search of L per row took 344 us on the 64^3 27-point
+// stencil (1000^2 9-point 298), this 11 (26).
+__global__ __launch_bounds__(kThreads) void k_bm_supernodes(BlockArgs a, int64_t max_super, int32_t* is_start) {
+    const int ln = lane();
+    const int32_t gb = (int32_t)blockIdx.x * (kThreads / 64) + rfl(threadIdx.x >> 6);
+    if (gb >= a.nblocks || ld_dev(&a.ctl[kBmAbort]) != 0u) return;
+    const int32_t jb = a.blk_job ? a.blk_job[gb] : 0;
+    const Job* J = &a.jobs[jb];
+    const int32_t b0 = (int32_t)J->item_base, n = J->n;
+    const int32_t* uc = a.row_ucnt + J->row_base;
+    int32_t* out = is_start + J->row_base;
+    int32_t r = -1;  // first row of the supernode that goes on
+    for (int32_t g = gb - b0; 64 * (int64_t)g < n; ++g) {
+        const int32_t v = 64 * g + ln;
+        const bool in = v < n;
+        const int32_t u = in ? uc[v] : 0, above_u = in && v > 0 ? uc[v - 1] : 0;
+        const u64 d = a.diag[64 * (int64_t)(b0 + g) + ln];
+        const u64 rows = __ballot(in);
+        const u64 F = __ballot(in && v > 0 && (max_super <= 0 || v % max_super != 0) && u == above_u - 1);
+        const bool first = g == gb - b0;
+        // rows of chains that begin here, or of the one that goes on
+        const int lead = rows & ~F ? __builtin_ctzll(rows & ~F) : 64;
+        u64 todo = first ? (lead < 64 ? rows & ~below(lead) : 0ull) : lead < 64 ? rows & below(lead) : rows;
+        if (todo == 0ull) break;
+        const u64 mine = todo;
+        u64 starts = 0;
+        u64 C = 0;  // rows of this block with an entry in column r
+        if (!first) {
+            // the tile of r's column block, near the end of the block's L list
+            const BlockRec rec = a.rec[b0 + g];
+            for (int i = rec.l_cnt; i > 0; i -= 64) {
+                const int32_t t = i - 64 + ln >= 0 ? a.tids[rec.l_off + i - 64 + ln] : -1;
+                const u64 hit = __ballot(t == (r >> 6));
+                if (hit) C = a.masks[64 * (rec.l_off + i - 64 + __builtin_ctzll(hit)) + (r & 63)];
+                if (hit || __builtin_amdgcn_readlane(t, 0) < (r >> 6)) break;
+            }
+        }
+        for (;;) {
+            // (the first row of a chain is no follower and starts one here)
+            const u64 cut = todo & ~(F & C);
+            if (cut == 0ull) break;
+            const int s = __builtin_ctzll(cut);
+            starts |= 1ull << s;
+            r = 64 * g + s;
+            C = readlane64(d, s);
+            todo &= above(s);
+        }
+        if ((mine >> ln) & 1ull) out[v] = (int32_t)((starts >> ln) & 1ull);
+        // (a chain that reaches the block's last row may go on in the next block)
+        if (!(mine >> 63)) break;
+    }
 }
 
 // ------------------------------------------------------------------- reach
@@ -1404,6 +1565,14 @@ hipError_t launch_block_cols(const BlockArgs& a, const BlockCols& c, const int64
                              hipStream_t st) {
     if (a.nblocks <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_bm_cols, dim3((unsigned)a.nblocks), dim3(kThreads), 0, st, a, c, l_ptr, l_idx);
+    return hipGetLastError();
+}
+
+hipError_t launch_block_supernodes(const BlockArgs& a, int64_t max_super, int32_t* is_start, hipStream_t st) {
+    if (a.nblocks <= 0) return hipSuccess;
+    const int per = kThreads / 64;
+    hipLaunchKernelGGL(k_bm_supernodes, dim3((unsigned)((a.nblocks + per - 1) / per)), dim3(kThreads), 0, st, a,
+                       max_super, is_start);
     return hipGetLastError();
 }
 

@@ -1701,7 +1701,7 @@ struct Engine {
         if (have_sn) {
             const hipStream_t s = ph_sn.stream();
             chk(launch_supernodes(rs, nbk, d_bf, d_bl, u_ptr.as<int64_t>(), l_rptr.as<int64_t>(),
-                                  l_ridx.as<int32_t>(), false, is_start.as<int32_t>(), s));
+                                  l_ridx.as<int32_t>(), is_start.as<int32_t>(), s));
             chk(launch_scan_counts(is_start.as<int32_t>(), nullptr, nrows, start_scan.as<int64_t>(),
                                    scan_scr.as<int64_t>(), s));
             chk(launch_supernode_assemble(rs, nj, is_start.as<int32_t>(), start_scan.as<int64_t>(),
@@ -2034,23 +2034,10 @@ struct Engine {
         const int64_t nr1 = std::max<int64_t>(nrows, 1), nb1 = std::max<int64_t>(nblocks, 1);
         auto up16 = [](int64_t b) { return (b + 15) & ~int64_t(15); };
 
-        // small host tables in one upload: jobs, matrix bounds, block order,
-        // supernode blocks
-        std::vector<int64_t> bf;
-        std::vector<int32_t> bl;
-        if (have_sn)
-            for (int32_t j = 0; j < nj; ++j) {
-                const int64_t M = plan.max_super > 0 ? plan.max_super : std::max<int64_t>(mats[j].n, 1);
-                for (int64_t b = 0; b < mats[j].n; b += M) {
-                    bf.push_back(row_base[j] + b);
-                    bl.push_back((int32_t)std::min<int64_t>(M, mats[j].n - b));
-                }
-            }
-        const int64_t nbk = (int64_t)bf.size();
+        // small host tables in one upload: jobs, matrix bounds, block order
         const int64_t o_jn = up16((int64_t)sizeof(Job) * nj), o_jrb = o_jn + up16(4 * (int64_t)nj),
                       o_ord = o_jrb + up16(8 * (int64_t)nj), o_cum = o_ord + up16(4 * (int64_t)nj),
-                      o_bf = o_cum + up16(8 * (max_blocks + 1)), o_bl = o_bf + up16(8 * nbk),
-                      up_bytes = o_bl + up16(4 * nbk) + 16;
+                      up_bytes = o_cum + up16(8 * (max_blocks + 1)) + 16;
         PinnedBuf h_up((size_t)up_bytes);
         DBuf d_up((size_t)up_bytes);
         {
@@ -2074,17 +2061,11 @@ struct Engine {
                     at += m;
                 }
             }
-            if (nbk) {
-                std::memcpy(c + o_bf, bf.data(), 8 * (size_t)nbk);
-                std::memcpy(c + o_bl, bl.data(), 4 * (size_t)nbk);
-            }
         }
         char* const du = d_up.as<char>();
         const Job* d_jobs = reinterpret_cast<const Job*>(du);
         const int32_t* d_jn = reinterpret_cast<const int32_t*>(du + o_jn);
         const int64_t* d_jrb = reinterpret_cast<const int64_t*>(du + o_jrb);
-        const int64_t* d_bf = reinterpret_cast<const int64_t*>(du + o_bf);
-        const int32_t* d_bl = reinterpret_cast<const int32_t*>(du + o_bl);
 
         // arrays cleared before the factorisation: control words, headers, tile
         // counts, per-matrix statistics
@@ -2252,8 +2233,7 @@ struct Engine {
         {
             const hipStream_t s = ph_sn.stream();
             if (have_sn) {
-                chk(launch_supernodes(rs, nbk, d_bf, d_bl, u_ptr.as<int64_t>(), l_ptr.as<int64_t>(),
-                                      f.l_idx.as<int32_t>(), !l_csr, is_start.as<int32_t>(), s));
+                chk(launch_block_supernodes(ba, plan.max_super, is_start.as<int32_t>(), s));
                 chk(launch_scan_counts(is_start.as<int32_t>(), nullptr, nrows, start_scan.as<int64_t>(),
                                        scan_scr.as<int64_t>(), s));
                 chk(launch_supernode_assemble(rs, nj, is_start.as<int32_t>(), start_scan.as<int64_t>(),

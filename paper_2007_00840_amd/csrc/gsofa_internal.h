@@ -167,6 +167,8 @@ hipError_t launch_block_rows(const BlockArgs& a, bool upper, const int64_t* ptr,
 // columns of L at l_ptr (per row of the row space)
 hipError_t launch_block_cols(const BlockArgs& a, const BlockCols& c, const int64_t* l_ptr, int32_t* l_idx,
                              hipStream_t st);
+// supernode starts (1 or 0 per row), at most max_super rows each (<= 0: any)
+hipError_t launch_block_supernodes(const BlockArgs& a, int64_t max_super, int32_t* is_start, hipStream_t st);
 // edges_alg less the sources' own degrees, added to jstats
 hipError_t launch_block_reach(const BlockArgs& a, const BlockCols& c, hipStream_t st);
 
@@ -220,7 +222,7 @@ hipError_t launch_zero_i32(int32_t* p, int64_t n, hipStream_t st);
 // row-wise or, with by_col, column-wise.
 hipError_t launch_supernodes(RowSpace rs, int64_t nblocks, const int64_t* block_first_row,
                              const int32_t* block_len, const int64_t* u_ptr,
-                             const int64_t* l_ptr, const int32_t* l_idx, bool by_col,
+                             const int64_t* l_rptr, const int32_t* l_ridx,
                              int32_t* is_start, hipStream_t st);
 // xsup/supno from the start flags and their exclusive scan.
 hipError_t launch_supernode_assemble(RowSpace rs, int32_t njobs, const int32_t* is_start,

@@ -2382,7 +2382,7 @@ __device__ __forceinline__ bool l_has(const int64_t* l_rptr, const int32_t* l_ri
 
 __global__ __launch_bounds__(256) void k_supernodes(RowSpace rs, int64_t nblocks, const int64_t* first,
                                                     const int32_t* len, const int64_t* u_ptr,
-                                                    const int64_t* l_ptr, const int32_t* l_idx, bool by_col,
+                                                    const int64_t* l_rptr, const int32_t* l_ridx,
                                                     int32_t* is_start) {
     const int64_t b = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (b >= nblocks) return;
@@ -2400,8 +2400,7 @@ __global__ __launch_bounds__(256) void k_supernodes(RowSpace rs, int64_t nblocks
         int64_t r = r0;
         for (int64_t s = r0 + 1; s < end; ++s) {
             if (ucount(u_ptr, s) != ucount(u_ptr, s - 1) - 1) break;  // next phase-I leader
-            // L(s, r): in row s, or in column r where L is stored by columns
-            if (!(by_col ? l_has(l_ptr, l_idx, r, (int32_t)(s - jb)) : l_has(l_ptr, l_idx, s, (int32_t)(r - jb)))) {
+            if (!l_has(l_rptr, l_ridx, s, (int32_t)(r - jb))) {
                 is_start[s] = 1;
                 r = s;
             }
@@ -2410,11 +2409,11 @@ __global__ __launch_bounds__(256) void k_supernodes(RowSpace rs, int64_t nblocks
 }
 
 hipError_t launch_supernodes(RowSpace rs, int64_t nblocks, const int64_t* block_first_row,
-                             const int32_t* block_len, const int64_t* u_ptr, const int64_t* l_ptr,
-                             const int32_t* l_idx, bool by_col, int32_t* is_start, hipStream_t st) {
+                             const int32_t* block_len, const int64_t* u_ptr, const int64_t* l_rptr,
+                             const int32_t* l_ridx, int32_t* is_start, hipStream_t st) {
     if (nblocks <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_supernodes, dim3((unsigned)((nblocks + 3) / 4)), dim3(256), 0, st, rs, nblocks,
-                       block_first_row, block_len, u_ptr, l_ptr, l_idx, by_col, is_start);
+                       block_first_row, block_len, u_ptr, l_rptr, l_ridx, is_start);
     return hipGetLastError();
 }
 

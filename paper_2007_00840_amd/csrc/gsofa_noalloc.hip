@@ -123,9 +123,7 @@ struct Call {
     int64_t* scan_scr;
     int32_t *row_ucnt, *row_lcnt, *is_start;
     int64_t* start_scan;
-    const int64_t* bfirst;
-    const int32_t* blen;
-    int64_t nsb;                  // supernode blocks
+    int64_t max_super;
     size_t slot_cap, pool_at;     // the traversal's layout: bytes of its slots, its
     int64_t pool_cap;             // pool's place and entries
     hipStream_t st;
@@ -234,7 +232,7 @@ int blocks_noalloc(const Call& k, uint8_t* base, size_t cap, double t0, gsofa_co
     const double ts0 = now_ms();
     if (k.want_sn) {
         const RowSpace rs{k.n, nullptr, nullptr};
-        NA_CHK(launch_supernodes(rs, k.nsb, k.bfirst, k.blen, k.u_ptr, k.l_ptr, k.l_idx, !k.l_csr, k.is_start, st));
+        NA_CHK(launch_block_supernodes(a, k.max_super, k.is_start, st));
         NA_CHK(launch_scan_counts(k.is_start, nullptr, k.n, k.start_scan, k.scan_scr, st));
         NA_CHK(launch_supernode_assemble(rs, 1, k.is_start, k.start_scan, k.xsup, k.supno, st));
         NA_CHK(launch_supernode_terminals(1, k.jrb, k.jn, k.start_scan, k.xsup, st));
@@ -404,9 +402,7 @@ int run_noalloc(int32_t n, const int32_t* row_ptr, const int32_t* col_idx, const
         k.row_lcnt = row_lcnt;
         k.is_start = is_start;
         k.start_scan = start_scan;
-        k.bfirst = bfirst;
-        k.blen = blen;
-        k.nsb = nblocks;
+        k.max_super = M;
         k.slot_cap = spA.cap;
         k.pool_at = (size_t)(spB.base - base);
         k.pool_cap = pool_cap;
@@ -488,7 +484,7 @@ int run_noalloc(int32_t n, const int32_t* row_ptr, const int32_t* col_idx, const
                             big_cnt, st));
     const double ts0 = now_ms();
     if (want_sn) {
-        NA_CHK(launch_supernodes(rs, nblocks, bfirst, blen, u_ptr, l_rptr, l_ridx, false, is_start, st));
+        NA_CHK(launch_supernodes(rs, nblocks, bfirst, blen, u_ptr, l_rptr, l_ridx, is_start, st));
         NA_CHK(launch_scan_counts(is_start, nullptr, n, start_scan, scan_scr, st));
         NA_CHK(launch_supernode_assemble(rs, 1, is_start, start_scan, xsup, supno, st));
         NA_CHK(launch_supernode_terminals(1, d_jrb, d_jn, start_scan, xsup, st));

@@ -170,3 +170,26 @@ def test_noalloc_path_and_result(g, name):
         counts.append([e.value.counts[k] for k in ("nnz_u", "nnz_l", "fills", "scratch_bytes")])
     if "concurrent_sources" not in opts:
         assert counts[0] == counts[1]
+
+
+SUPERNODES = {
+    "dense": lambda: _csr(300, [list(range(300)) for _ in range(300)]),
+    "band_lower": lambda: _band(700, 40, 0, 1),
+    "band_wide": lambda: _band(1500, 150, 90, 3),
+    "nd_3d": lambda: _stencil(27, (19, 18, 17), True, 6),
+    "n64": lambda: _band(64, 9, 11, 64),
+    "n65": lambda: _band(65, 30, 30, 65),
+}
+
+
+@pytest.mark.parametrize("name", SUPERNODES)
+def test_block_supernodes_match_traversal(g, name):
+    """Chains that cross blocks of rows, at limits below, at and above a block."""
+    n, rp, ci = SUPERNODES[name]()
+    print(f"supernodes {name} n={n}", flush=True)
+    for limit in (1, 50, 64, 65, 200, -1):
+        for flags in (0, g.L_CSR):
+            r = g.symbolic(n, rp, ci, flags=flags, max_supernode=limit)
+            t = g.symbolic(n, rp, ci, flags=flags | g.MAP_WAVE32, max_supernode=limit)
+            assert (r.stats["mapping"], t.stats["mapping"]) == (7, 0)
+            assert np.array_equal(r.xsup, t.xsup) and np.array_equal(r.supno, t.supno), limit
