@@ -117,6 +117,14 @@ __device__ __forceinline__ int min64(int v) {
     GSOFA_DPP_SCAN(0x7FFFFFFF, op_min)
     return __builtin_amdgcn_readlane(v, 63);
 }
+// of lanes 0 to 15
+__device__ __forceinline__ int min16(int v) {
+    GSOFA_DPP_STEP(0x111, 0xf, 0x7FFFFFFF, op_min)
+    GSOFA_DPP_STEP(0x112, 0xf, 0x7FFFFFFF, op_min)
+    GSOFA_DPP_STEP(0x114, 0xf, 0x7FFFFFFF, op_min)
+    GSOFA_DPP_STEP(0x118, 0xf, 0x7FFFFFFF, op_min)
+    return __builtin_amdgcn_readlane(v, 15);
+}
 __device__ __forceinline__ int or32(int v) {
     GSOFA_DPP_SCAN(0, op_or)
     return __builtin_amdgcn_readlane(v, 63);
@@ -1082,8 +1090,18 @@ __global__ __launch_bounds__(kThreads) void k_bm_scatter(BlockArgs a, BlockCols 
     }
 }
 
+// the rows of block g up to (and with) a column's match
+__device__ __forceinline__ u64 upto(u64 m, int32_t g, int32_t match) {
+    if (g < (match >> 6)) return m;
+    if (g > (match >> 6)) return 0ull;
+    return m & ~above(match & 63);
+}
+
 // One wavefront per block of columns. Lists of more than 64 tiles are ranked in a
 // bitmap over the row blocks (dynamic LDS: one bit and one prefix per 64 blocks).
+// The tiles with an entry up to their column's first match, all that the reach
+// counts need and one or two in a separator, stay as (blk, tile) at the list's
+// start, the first of them in the block's record.
 __global__ __launch_bounds__(64) void k_bm_lists(BlockArgs a, BlockCols c, int32_t* col_cnt) {
     extern __shared__ u64 s_dyn[];
     if (ld_dev(&a.ctl[kBmAbort]) != 0u) return;
@@ -1094,19 +1112,51 @@ __global__ __launch_bounds__(64) void k_bm_lists(BlockArgs a, BlockCols c, int32
     const int32_t c0 = cb - (int32_t)J->item_base;
     const int64_t e0 = c.ptr[cb], e1 = c.ptr[cb + 1];
     const int cnt = (int)(e1 - e0);
+    const int32_t match = a.kmatch[64 * (int64_t)cb + ln];
     int32_t sum = __popcll(a.diag[64 * (int64_t)cb + ln] & above(ln));
+    int kept = 0;
+    int32_t word = 0;  // the record: lane 0 the count, lanes 1.. row blocks, 8.. tiles
+    // k tiles of a list (lane i: row block b, tile q): their entries per column,
+    // and which of them the reach counts need
+    auto walk = [&](int k, int32_t b, int32_t q) {
+        u64 keep = 0;
+        for (int i0 = 0; i0 < k; i0 += 4) {
+            u64 m[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                m[j] = i0 + j < k ? a.masks[64 * (int64_t)__builtin_amdgcn_readlane(q, (i0 + j) & 63) + ln] : 0ull;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                sum += __popcll(m[j]);
+                const int32_t g = __builtin_amdgcn_readlane(b, (i0 + j) & 63);
+                if (__ballot(upto(m[j], g, match) != 0ull) != 0ull) keep |= 1ull << ((i0 + j) & 63);
+            }
+        }
+        if ((keep >> ln) & 1ull) {
+            const int64_t d = e0 + kept + (int)below_count(keep);
+            c.blk[d] = b;
+            c.tile[d] = q;
+        }
+        for (u64 w = keep; w && kept < kReachInline; w &= w - 1ull) {
+            const int i = __builtin_ctzll(w);
+            const int32_t bi = __builtin_amdgcn_readlane(b, i), qi = __builtin_amdgcn_readlane(q, i);
+            if (ln == 1 + kept) word = bi;
+            if (ln == 1 + kReachInline + kept) word = qi;
+            ++kept;
+            keep &= keep - 1ull;
+        }
+        kept += __popcll(keep);
+    };
     if (cnt <= 64) {
         const int32_t b = ln < cnt ? c.blk[e0 + ln] : kNoMatch;
         const int32_t q = ln < cnt ? c.tile[e0 + ln] : 0;
         int rank = 0;
-        for (int i = 0; i < cnt; ++i) {
-            rank += __builtin_amdgcn_readlane(b, i) < b ? 1 : 0;
-            sum += __popcll(a.masks[64 * (int64_t)__builtin_amdgcn_readlane(q, i) + ln]);
-        }
+        for (int i = 0; i < cnt; ++i) rank += __builtin_amdgcn_readlane(b, i) < b ? 1 : 0;
         if (ln < cnt) {
             c.blk2[e0 + rank] = b;
             c.tile2[e0 + rank] = q;
         }
+        walk(cnt, b, q);
     } else {
         const int nw = a.bit_words;
         u64* bits = s_dyn;
@@ -1126,16 +1176,17 @@ __global__ __launch_bounds__(64) void k_bm_lists(BlockArgs a, BlockCols c, int32
         for (int64_t f0 = e0; f0 < e1; f0 += 64) {
             const int k = (int)min((int64_t)64, e1 - f0);
             const int32_t q = ln < k ? c.tile[f0 + ln] : 0;
+            const int32_t b = ln < k ? c.blk[f0 + ln] : 0;
             if (ln < k) {
-                const int32_t b = c.blk[f0 + ln];
                 const int64_t d = e0 + pre[b >> 6] + __popcll(bits[b >> 6] & below(b & 63));
                 c.blk2[d] = b;
                 c.tile2[d] = q;
             }
-            for (int i = 0; i < k; ++i)
-                sum += __popcll(a.masks[64 * (int64_t)__builtin_amdgcn_readlane(q, i) + ln]);
+            walk(k, b, q);  // (keeps no more than it has read: in place)
         }
     }
+    if (ln == 0) word = kept;
+    if (ln < kReachWords) c.reach[(int64_t)cb * kReachWords + ln] = word;
     const int64_t v = 64 * (int64_t)c0 + ln;
     if (v < J->n) col_cnt[J->row_base + v] = sum;
 }
@@ -1151,11 +1202,12 @@ __global__ __launch_bounds__(64) void k_bm_lists(BlockArgs a, BlockCols c, int32
 // for whole aligned stores, took 377 and 421 us; masks by scalar loads as long
 // as this on the first and longer on the second.)
 
+namespace {
+
 // Rows of U, or of L row-wise.
 template <bool upper>
-__global__ __launch_bounds__(kThreads) void k_bm_rows(BlockArgs a, const int64_t* ptr, int32_t* idx) {
+__device__ __forceinline__ void emit_rows(const BlockArgs& a, int32_t gb, const int64_t* ptr, int32_t* idx) {
     const int ln = lane(), wv = rfl(threadIdx.x >> 6);
-    const int32_t gb = blockIdx.x;
     const int32_t jb = a.blk_job ? a.blk_job[gb] : 0;
     const Job* J = &a.jobs[jb];
     const int32_t g = gb - (int32_t)J->item_base;
@@ -1211,9 +1263,9 @@ __global__ __launch_bounds__(kThreads) void k_bm_rows(BlockArgs a, const int64_t
 // Columns of L: the tiles of a block of columns by ascending row block, the rows
 // of a column being the set bits of its mask. One load brings the wavefront's 16
 // columns of four tiles.
-__global__ __launch_bounds__(kThreads) void k_bm_cols(BlockArgs a, BlockCols c, const int64_t* l_ptr, int32_t* l_idx) {
+__device__ __forceinline__ void emit_cols(const BlockArgs& a, const BlockCols& c, int32_t cb, const int64_t* l_ptr,
+                                          int32_t* l_idx) {
     const int ln = lane(), wv = rfl(threadIdx.x >> 6);
-    const int32_t cb = blockIdx.x;
     const int32_t jb = a.blk_job ? a.blk_job[cb] : 0;
     const Job* J = &a.jobs[jb];
     const int32_t c0 = cb - (int32_t)J->item_base;
@@ -1260,6 +1312,8 @@ __global__ __launch_bounds__(kThreads) void k_bm_cols(BlockArgs a, BlockCols c, 
         for (int j = 0; j < 4; ++j) put(g[j], m0, j);
     }
 }
+
+}  // namespace
 
 // -------------------------------------------------------------- supernodes
 //
@@ -1332,24 +1386,21 @@ __global__ __launch_bounds__(kThreads) void k_bm_supernodes(BlockArgs a, int64_t
 // other, the mask of c's vertices that each row reaches: rows of a block among
 // each other through the closure lcl, later blocks through L's tiles up to
 // each column's match (a row beyond the match reaches everything through it).
-// Few blocks wait at a time, so they sit in kReachTiles LDS tiles; a wavefront
+// Few blocks wait at a time, so they sit in a few LDS tiles; a wavefront
 // that needs more hands its block to k_bm_reach_big.
+// Bound by its instructions, some 300 per block of rows on the way up: what a
+// block needs comes from one record, loaded while the one before it is worked on;
+// few rows' words go through the closure one by one, more by table; the degrees'
+// planes sit in registers.
 
 namespace {
-constexpr int kReachTiles = 8;
-constexpr int kReachWaves = 4;
-
-// the rows of block g up to (and with) a column's match
-__device__ __forceinline__ u64 upto(u64 m, int32_t g, int32_t match) {
-    if (g < (match >> 6)) return m;
-    if (g > (match >> 6)) return 0ull;
-    return m & ~above(match & 63);
-}
+constexpr int kReachPlanes = 6;
+constexpr int kReachRows = 12;  // rows in use up to which their words go one by one
 
 // sum of the degrees in a mask: bit planes of the degrees, one popcount each
-__device__ __forceinline__ u64 weigh(u64 z, const u64* planes, int np) {
+__device__ __forceinline__ u64 weigh(u64 z, const u64* planes, int np, int first) {
     u64 s = 0;
-    for (int j = 0; j < np; ++j) s += (u64)__popcll(z & planes[j]) << j;
+    for (int j = first; j < np; ++j) s += (u64)__popcll(z & planes[j]) << j;
     return s;
 }
 
@@ -1367,72 +1418,146 @@ __device__ __forceinline__ int degree_planes(const Job* J, int32_t c, u64* plane
 }
 }  // namespace
 
-__global__ __launch_bounds__(64 * kReachWaves) void k_bm_reach(BlockArgs a, BlockCols cl) {
-    __shared__ u64 s_tile[kReachWaves][kReachTiles][64];
-    __shared__ __attribute__((aligned(16))) u64 s_xs[kReachWaves][64];
-    __shared__ u64 s_tab[kReachWaves][256];
-    __shared__ u64 s_planes[kReachWaves][32];
-    const int ln = lane(), wv = rfl(threadIdx.x >> 6);
-    const int32_t cb = blockIdx.x * kReachWaves + wv;
+namespace {
+template <int kTiles>
+struct ReachLds {
+    __attribute__((aligned(16))) u64 xs[64];
+    u64 tile[kTiles][64];
+    u64 tab[256];
+    u64 planes[32];
+};
+
+template <int kTiles>
+__device__ __forceinline__ void reach_of(const BlockArgs& a, const BlockCols& cl, int32_t cb, ReachLds<kTiles>& S) {
+    const int ln = lane();
     if (cb >= a.nblocks || ld_dev(&a.ctl[kBmAbort]) != 0u) return;
     const int32_t jb = a.blk_job ? a.blk_job[cb] : 0;
     const Job* J = &a.jobs[jb];
     const int32_t b0 = (int32_t)J->item_base;
     const int32_t c = cb - b0;
-    u64(*tile)[64] = s_tile[wv];
-    u64* planes = s_planes[wv];
-    const int np = degree_planes(J, c, planes);
-    int32_t key = kNoMatch;  // lane i < kReachTiles: block waiting in tile i
+    const int np = degree_planes(J, c, S.planes);
+    int32_t key = kNoMatch;  // lane i < kTiles: block waiting in tile i
     if (ln == 0) key = c;
-    tile[0][ln] = 64 * (int64_t)c + ln < J->n ? 1ull << ln : 0ull;
+    static_assert(kTiles <= 16 && kReachInline < 16, "min16");
+    S.tile[0][ln] = 64 * (int64_t)c + ln < J->n ? 1ull << ln : 0ull;
     wave_sync();
+    // the degrees' lowest planes and their counts in registers
+    u64 plane[kReachPlanes];
+    uint32_t hits[kReachPlanes];
+#pragma unroll
+    for (int j = 0; j < kReachPlanes; ++j) {
+        plane[j] = j < np ? S.planes[j] : 0ull;
+        hits[j] = 0;
+    }
     u64 sum = 0;
-    bool over = false;
+    // what a block needs, loaded while the one before it is worked on
+    u64 M;
+    int32_t match, word, at = -1;
+    auto fetch = [&](int32_t h) {
+        at = h;
+        const int64_t hb = b0 + h;
+        M = a.lcl[64 * hb + ln];
+        match = a.kmatch[64 * hb + ln];
+        word = cl.reach[hb * kReachWords + (ln & (kReachWords - 1))];
+    };
     for (;;) {
-        const int32_t h = (min64(key));
+        const int32_t h = min16(key);
         if (h == kNoMatch) break;
+        if (h != at) fetch(h);
         const int sl = __builtin_ctzll(__ballot(key == h));
         const int64_t hb = b0 + h;
-        const u64 M = a.lcl[64 * hb + ln];
-        const int32_t match = a.kmatch[64 * hb + ln];
-        const int64_t e0 = cl.ptr[hb], e1 = cl.ptr[hb + 1];
-        const u64 z0 = tile[sl][ln];
-        const u64 z = z0 | lane_or(z0, M, s_xs[wv], s_tab[wv]);
+        const int cnt = __builtin_amdgcn_readlane(word, 0);
+        const int32_t w0 = word, match0 = match;
+        u64 m[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            m[j] = j < cnt ? a.masks[64 * (int64_t)__builtin_amdgcn_readlane(w0, 1 + kReachInline + j) + ln] : 0ull;
+        const u64 z0 = S.tile[sl][ln], M0 = M;
         if (ln == sl) key = kNoMatch;
-        sum += weigh(h == c ? z & ~(1ull << ln) : z, planes, np);
-        // later blocks, up to the last match of the columns in use
-        const int32_t gmax = (max64(z != 0ull ? match >> 6 : -1));
-        for (int64_t e = e0; e < e1; ++e) {
-            const int32_t g = cl.blk2[e];
-            if (g > gmax) break;
-            const u64 m = z != 0ull ? upto(a.masks[64 * (int64_t)cl.tile2[e] + ln], g, match) : 0ull;
-            if (__ballot(m != 0ull) == 0ull) continue;
+        // the next one is waiting already or comes in now
+        {
+            const int32_t mine = ln >= 1 && ln <= min(cnt, kReachInline) ? w0 : kNoMatch;
+            const int32_t next = min16(min(key, mine));
+            if (next != kNoMatch) fetch(next);
+        }
+        u64 z = z0;
+        const u64 from = __ballot(z0 != 0ull);
+        if (h == c) {
+            z |= M0;  // (row k starts with vertex k)
+        } else if (__popcll(from) <= kReachRows) {
+            for (u64 w = from; w; w &= w - 1ull) {
+                const int k = __builtin_ctzll(w);
+                const u64 zk = readlane64(z0, k);
+                z |= (M0 >> k) & 1ull ? zk : 0ull;
+            }
+        } else {
+            z |= lane_or(z0, M0, S.xs, S.tab);
+        }
+#pragma unroll
+        for (int j = 0; j < kReachPlanes; ++j) hits[j] += (uint32_t)__popcll(z & plane[j]);
+        if (np > kReachPlanes) sum += weigh(z, S.planes, np, kReachPlanes);
+        bool over = false;
+        auto push = [&](int32_t g, u64 mask) {
+            const u64 x = z != 0ull ? upto(mask, g, match0) : 0ull;
+            if (__ballot(x != 0ull) == 0ull) return;
             const u64 hit = __ballot(key == g);
             int s2;
             if (hit) {
                 s2 = __builtin_ctzll(hit);
             } else {
-                const u64 fr = __ballot(ln < kReachTiles && key == kNoMatch);
+                const u64 fr = __ballot(ln < kTiles && key == kNoMatch);
                 if (fr == 0ull) {
                     over = true;
-                    break;
+                    return;
                 }
                 s2 = __builtin_ctzll(fr);
                 if (ln == s2) key = g;
-                tile[s2][ln] = 0ull;
+                S.tile[s2][ln] = 0ull;
                 wave_sync();
             }
-            for (u64 t = m; t; t &= t - 1ull) atomicOr(&tile[s2][__builtin_ctzll(t)], z);
+            for (u64 t = x; t; t &= t - 1ull) atomicOr(&S.tile[s2][__builtin_ctzll(t)], z);
             wave_sync();
+        };
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (j < cnt && !over) push(__builtin_amdgcn_readlane(w0, 1 + j), m[j]);
+        if (cnt > 4) {
+            const int64_t e0 = cl.ptr[hb];
+            for (int i = 4; i < cnt && !over; ++i) {
+                const int32_t g = cl.blk[e0 + i];
+                push(rfl(g), a.masks[64 * (int64_t)cl.tile[e0 + i] + ln]);
+            }
         }
-        if (over) break;
+        if (over) {
+            if (ln == 0) cl.big[atomicAdd(cl.nbig, 1)] = cb;
+            return;
+        }
     }
-    if (over) {
-        if (ln == 0) cl.big[atomicAdd(cl.nbig, 1)] = cb;
-        return;
-    }
+    // (every vertex has counted itself once)
+    for (int j = 0; j < np; ++j) sum -= (u64)((S.planes[j] >> ln) & 1ull) << j;
+#pragma unroll
+    for (int j = 0; j < kReachPlanes; ++j) sum += (u64)hits[j] << j;
     sum = sum64(sum);
     if (ln == 0 && sum) atomicAdd(&a.jstats[jb].edges_alg, sum);
+}
+}  // namespace
+
+// Everything that is written once the sizes of U and L are known, in one launch
+// (64^3 27-point: 980 -> 663 us; 1000^2 9-point 685 -> 558; 512 batch members 1,043 -> 729).
+// Of nine workgroups one takes reach counts and eight rows and columns of four
+// blocks, so that both kinds are in flight all the time.
+template <bool l_csr, int kTiles>
+__global__ __launch_bounds__(kThreads) void k_bm_emit(BlockArgs a, BlockCols c, const int64_t* u_ptr, int32_t* u_idx,
+                                                      const int64_t* l_ptr, int32_t* l_idx) {
+    __shared__ ReachLds<kTiles> s_reach[kThreads / 64];
+    const int32_t k = (int32_t)(blockIdx.x / 9u), what = (int32_t)(blockIdx.x % 9u);
+    const int32_t b = 4 * k + ((what - 1) >> 1);
+    const int wv = rfl(threadIdx.x >> 6);
+    if (what == 0) reach_of<kTiles>(a, c, 4 * k + wv, s_reach[wv]);
+    else if (b >= a.nblocks) return;
+    else if (what & 1) emit_rows<true>(a, b, u_ptr, u_idx);
+    else if (l_csr) emit_rows<false>(a, b, l_ptr, l_idx);
+    else emit_cols(a, c, b, l_ptr, l_idx);
 }
 
 // The same with the waiting blocks' masks in a slot of X (all zero between
@@ -1473,13 +1598,13 @@ __global__ __launch_bounds__(64) void k_bm_reach_big(BlockArgs a, BlockCols cl) 
             u64 z = ld_wg(&Z[64 * (int64_t)h + ln]);
             Z[64 * (int64_t)h + ln] = 0ull;
             z |= lane_or(z, a.lcl[64 * hb + ln], s_xs, s_tab);
-            sum += weigh(h == c ? z & ~(1ull << ln) : z, s_planes, np);
+            sum += weigh(h == c ? z & ~(1ull << ln) : z, s_planes, np, 0);
             const int32_t match = a.kmatch[64 * hb + ln];
-            const int32_t gmax = (max64(z != 0ull ? match >> 6 : -1));
-            for (int64_t e = cl.ptr[hb]; e < cl.ptr[hb + 1]; ++e) {
-                const int32_t g = cl.blk2[e];
-                if (g > gmax) break;
-                const u64 m = z != 0ull ? upto(a.masks[64 * (int64_t)cl.tile2[e] + ln], g, match) : 0ull;
+            const int64_t e0 = cl.ptr[hb];
+            const int cnt = cl.reach[hb * kReachWords];
+            for (int i = 0; i < cnt; ++i) {
+                const int32_t g = cl.blk[e0 + i];
+                const u64 m = z != 0ull ? upto(a.masks[64 * (int64_t)cl.tile[e0 + i] + ln], g, match) : 0ull;
                 if (__ballot(m != 0ull) == 0ull) continue;
                 for (u64 t = m; t; t &= t - 1ull) or_wg(&Z[64 * (int64_t)g + __builtin_ctzll(t)], z);
                 if (ln == 0) s_bits[g >> 6] |= 1ull << (g & 63);
@@ -1554,17 +1679,20 @@ hipError_t launch_block_counts(const BlockArgs& a, const BlockCols& c, int32_t* 
     return hipGetLastError();
 }
 
-hipError_t launch_block_rows(const BlockArgs& a, bool upper, const int64_t* ptr, int32_t* idx, hipStream_t st) {
+hipError_t launch_block_emit(const BlockArgs& a, const BlockCols& c, const int64_t* u_ptr, int32_t* u_idx,
+                             const int64_t* l_ptr, int32_t* l_idx, bool l_csr, hipStream_t st) {
     if (a.nblocks <= 0) return hipSuccess;
-    if (upper) hipLaunchKernelGGL(k_bm_rows<true>, dim3((unsigned)a.nblocks), dim3(kThreads), 0, st, a, ptr, idx);
-    else hipLaunchKernelGGL(k_bm_rows<false>, dim3((unsigned)a.nblocks), dim3(kThreads), 0, st, a, ptr, idx);
-    return hipGetLastError();
-}
-
-hipError_t launch_block_cols(const BlockArgs& a, const BlockCols& c, const int64_t* l_ptr, int32_t* l_idx,
-                             hipStream_t st) {
-    if (a.nblocks <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_bm_cols, dim3((unsigned)a.nblocks), dim3(kThreads), 0, st, a, c, l_ptr, l_idx);
+    static_assert(kThreads / 64 == 4, "a workgroup takes the reach counts of four blocks");
+    const dim3 grid(9u * (unsigned)((a.nblocks + 3) / 4));
+    // Tiles for waiting blocks: eight keep five workgroups on a CU, which one
+    // matrix wants (1000^2 9-point: 638 us with eight, 704 with twelve); among
+    // many matrices some block needs more, and finishing it afterwards costs the
+    // launch of 220 us (512 batch members: 942 in all with eight, 733 with twelve)
+    const auto kernel = a.blk_job ? (l_csr ? k_bm_emit<true, 12> : k_bm_emit<false, 12>)
+                                  : (l_csr ? k_bm_emit<true, 8> : k_bm_emit<false, 8>);
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, a, c, u_ptr, u_idx, l_ptr, l_idx);
+    hipLaunchKernelGGL(k_bm_reach_big, dim3((unsigned)std::min(a.nslots, 256)), dim3(64), (size_t)a.bit_words * 8, st,
+                       a, c);
     return hipGetLastError();
 }
 
@@ -1573,15 +1701,6 @@ hipError_t launch_block_supernodes(const BlockArgs& a, int64_t max_super, int32_
     const int per = kThreads / 64;
     hipLaunchKernelGGL(k_bm_supernodes, dim3((unsigned)((a.nblocks + per - 1) / per)), dim3(kThreads), 0, st, a,
                        max_super, is_start);
-    return hipGetLastError();
-}
-
-hipError_t launch_block_reach(const BlockArgs& a, const BlockCols& c, hipStream_t st) {
-    if (a.nblocks <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_bm_reach, dim3((unsigned)((a.nblocks + kReachWaves - 1) / kReachWaves)),
-                       dim3(64 * kReachWaves), 0, st, a, c);
-    hipLaunchKernelGGL(k_bm_reach_big, dim3((unsigned)std::min(a.nslots, 256)), dim3(64), (size_t)a.bit_words * 8, st,
-                       a, c);
     return hipGetLastError();
 }
 

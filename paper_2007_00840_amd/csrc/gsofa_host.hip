@@ -2014,7 +2014,7 @@ struct Engine {
             if (it != block_ratios().end()) ratio = it->second;
         }
         int64_t cap = (int64_t)(ratio * 1.15 * (double)nblocks) + 64 * ns + 64;
-        constexpr int64_t kPerBlock = 8 * kBmHeadWords + 1024 + 256 + 512 + 512 + sizeof(BlockRec) + 16;
+        constexpr int64_t kPerBlock = 8 * kBmHeadWords + 1024 + 256 + 512 + 512 + sizeof(BlockRec) + 4 * kReachWords + 16;
         auto need = [&](int64_t tiles) {
             return fixed_bytes(nrows, total_nnz) + nrows * 64 + nblocks * kPerBlock + ns * stride * 8 + tiles * 540 + 24 * total_nnz;
         };
@@ -2075,7 +2075,8 @@ struct Engine {
         uint32_t* d_ctl = zero.as<uint32_t>();  // [0] next block, [1] abort, [4] reach list, [8..9] pool tail
         JobStats* d_js = reinterpret_cast<JobStats*>(zero.as<char>() + z_js);
         DBuf tcl(1024 * (size_t)nb1), kmatch(256 * (size_t)nb1),
-            diag(512 * (size_t)nb1), lcl(512 * (size_t)nb1), rec(sizeof(BlockRec) * (size_t)nb1);
+            diag(512 * (size_t)nb1), lcl(512 * (size_t)nb1), rec(sizeof(BlockRec) * (size_t)nb1),
+            reach(4 * kReachWords * (size_t)nb1);
         DBuf row_ucnt(4 * (size_t)nr1), row_lcnt(4 * (size_t)nr1), col_cnt(4 * (size_t)nr1);
         DBuf u_ptr(8 * (size_t)(nrows + 1)), l_ptr(8 * (size_t)(nrows + 1)), list_ptr(8 * (size_t)(nb1 + 1));
         DBuf scan_scr(8 * (size_t)scan_scratch_elems(nrows + 1) + 64);
@@ -2122,6 +2123,7 @@ struct Engine {
         BlockCols bc{};
         bc.ptr = list_ptr.as<int64_t>();
         bc.big = big.as<int32_t>();
+        bc.reach = reach.as<int32_t>();
         bc.nbig = reinterpret_cast<int32_t*>(d_ctl + 4);
         for (;;) {
             if (cap > 0x7FFFFFFFll) {
@@ -2221,10 +2223,8 @@ struct Engine {
         Phase ph_emit(kPhaseSort, graphs, st);
         {
             const hipStream_t s = ph_emit.stream();
-            chk(launch_block_rows(ba, true, u_ptr.as<int64_t>(), f.u_idx.as<int32_t>(), s));
-            if (l_csr) chk(launch_block_rows(ba, false, l_ptr.as<int64_t>(), f.l_idx.as<int32_t>(), s));
-            else chk(launch_block_cols(ba, bc, l_ptr.as<int64_t>(), f.l_idx.as<int32_t>(), s));
-            chk(launch_block_reach(ba, bc, s));
+            chk(launch_block_emit(ba, bc, u_ptr.as<int64_t>(), f.u_idx.as<int32_t>(), l_ptr.as<int64_t>(),
+                                  f.l_idx.as<int32_t>(), l_csr, s));
             chk(launch_copy_to_host(h_js, d_js, sizeof(JobStats) * (size_t)nj, s));
             ph_emit.launch();
         }

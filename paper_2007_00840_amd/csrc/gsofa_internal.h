@@ -101,6 +101,7 @@ struct TraverseArgs {
 // ---- block path (gsofa_blocks.hip): 64 rows at a time as bit masks
 
 constexpr int64_t kBlockMaxRows = int64_t(1) << 22;  // LDS bitmaps: one bit per 64 columns
+constexpr int kReachWords = 16, kReachInline = 7;
 constexpr int32_t kMapBlocks = 7;                    // the path's number in stats.mapping
 constexpr int kBmHeadWords = 32;                     // 64-bit words per block: headers of its two publications
 enum BmCtl { kBmNext = 0, kBmAbort = 1 };
@@ -148,6 +149,8 @@ struct BlockArgs {
 struct BlockCols {
     const int64_t* ptr;
     int32_t *blk, *tile, *blk2, *tile2;
+    int32_t* reach;               // per block kReachWords: how many tiles the reach counts need
+                                  // (they stay in blk, tile), the first kReachInline's blk, tile
     int32_t* big;                 // per block
     int32_t* nbig;                // zero beforehand
 };
@@ -162,15 +165,12 @@ hipError_t launch_block_tables(const Job* jobs, const int32_t* ord, const int64_
 hipError_t launch_block_factor(const BlockArgs& a, hipStream_t st);
 // entries of L and U per row, L's tiles by columns, entries of L per column
 hipError_t launch_block_counts(const BlockArgs& a, const BlockCols& c, int32_t* col_cnt, hipStream_t st);
-// rows of U (upper) or L from the masks, at ptr (per row of the row space)
-hipError_t launch_block_rows(const BlockArgs& a, bool upper, const int64_t* ptr, int32_t* idx, hipStream_t st);
-// columns of L at l_ptr (per row of the row space)
-hipError_t launch_block_cols(const BlockArgs& a, const BlockCols& c, const int64_t* l_ptr, int32_t* l_idx,
-                             hipStream_t st);
+// rows of U, columns (l_csr: rows) of L at u_ptr, l_ptr (per row of the row space);
+// edges_alg less the sources' own degrees, added to jstats
+hipError_t launch_block_emit(const BlockArgs& a, const BlockCols& c, const int64_t* u_ptr, int32_t* u_idx,
+                             const int64_t* l_ptr, int32_t* l_idx, bool l_csr, hipStream_t st);
 // supernode starts (1 or 0 per row), at most max_super rows each (<= 0: any)
 hipError_t launch_block_supernodes(const BlockArgs& a, int64_t max_super, int32_t* is_start, hipStream_t st);
-// edges_alg less the sources' own degrees, added to jstats
-hipError_t launch_block_reach(const BlockArgs& a, const BlockCols& c, hipStream_t st);
 
 // Row-space description shared by the assembly kernels. With one job,
 // row_job == nullptr and every base is 0.

@@ -163,6 +163,7 @@ int blocks_noalloc(const Call& k, uint8_t* base, size_t cap, double t0, gsofa_co
     BlockCols bc{};
     bc.ptr = list_ptr;
     bc.big = sp.take<int32_t>(nb);
+    bc.reach = sp.take<int32_t>(kReachWords * nb);
     if (sp.off + 4096 >= cap) return kNotHere;
     // column masks of all resident workgroups, at most a third of what is left
     int64_t ns = std::min<int64_t>(block_resident_groups(k.cus, a.waves, words), nb);
@@ -225,10 +226,7 @@ int blocks_noalloc(const Call& k, uint8_t* base, size_t cap, double t0, gsofa_co
             }
     }
 
-    NA_CHK(launch_block_rows(a, true, k.u_ptr, k.u_idx, st));
-    if (k.l_csr) NA_CHK(launch_block_rows(a, false, k.l_ptr, k.l_idx, st));
-    else NA_CHK(launch_block_cols(a, bc, k.l_ptr, k.l_idx, st));
-    NA_CHK(launch_block_reach(a, bc, st));
+    NA_CHK(launch_block_emit(a, bc, k.u_ptr, k.u_idx, k.l_ptr, k.l_idx, k.l_csr, st));
     const double ts0 = now_ms();
     if (k.want_sn) {
         const RowSpace rs{k.n, nullptr, nullptr};
