@@ -1013,16 +1013,24 @@ __device__ __forceinline__ u64 transpose64(u64 x) {
 // ballot per tile and row instead took 468 us on the 64^3 27-point stencil (204 on
 // 1000^2 9-point); this way 64 (69): the tiles are
 // read once.
-__global__ __launch_bounds__(kThreads) void k_bm_count(BlockArgs a) {
+// On the way the block's L tiles go into the lists of their columns.
+__global__ __launch_bounds__(kThreads) void k_bm_count(BlockArgs a, BlockCols cl) {
     __shared__ int32_t s_cnt[2][64];
     const int ln = lane(), wv = rfl(threadIdx.x >> 6);
     if (ld_dev(&a.ctl[kBmAbort]) != 0u) return;
     const int32_t gb = blockIdx.x;
     const int32_t jb = a.blk_job ? a.blk_job[gb] : 0;
     const Job* J = &a.jobs[jb];
-    const int32_t g = gb - (int32_t)J->item_base;
+    const int32_t b0 = (int32_t)J->item_base;
+    const int32_t g = gb - b0;
     const int32_t nr = min(64, J->n - 64 * g);
     const BlockRec rec = a.rec[gb];
+    for (int i = threadIdx.x; i < rec.l_cnt; i += kThreads) {
+        const int64_t q = rec.l_off + i;
+        const int64_t e = cl.ptr[b0 + a.tids[q]] + a.slot[q];
+        cl.blk[e] = g;
+        cl.tile[e] = (int32_t)q;
+    }
     if (threadIdx.x < 128) s_cnt[threadIdx.x >> 6][ln] = 0;
     __syncthreads();
     const u64 d = a.diag[64 * (int64_t)gb + ln];
@@ -1072,23 +1080,9 @@ __global__ __launch_bounds__(kThreads) void k_bm_count(BlockArgs a) {
 // ---------------------------------------------------------- L by columns
 //
 // L's tiles seen from the columns: for every block of columns the blocks of
-// rows with a tile there. k_bm_scatter puts each tile into its column block's
-// list (in the place it took during the factorisation), k_bm_lists sorts the
-// lists by row block and counts the entries of every column.
-
-__global__ __launch_bounds__(kThreads) void k_bm_scatter(BlockArgs a, BlockCols c) {
-    if (ld_dev(&a.ctl[kBmAbort]) != 0u) return;
-    const int32_t gb = blockIdx.x;
-    const int32_t jb = a.blk_job ? a.blk_job[gb] : 0;
-    const int32_t b0 = (int32_t)a.jobs[jb].item_base;
-    const BlockRec rec = a.rec[gb];
-    for (int i = threadIdx.x; i < rec.l_cnt; i += kThreads) {
-        const int64_t q = rec.l_off + i;
-        const int64_t d = c.ptr[b0 + a.tids[q]] + a.slot[q];
-        c.blk[d] = gb - b0;
-        c.tile[d] = (int32_t)q;
-    }
-}
+// rows with a tile there. k_bm_count puts each tile into its column block's list
+// (in the place it took during the factorisation), k_bm_lists sorts the lists by
+// row block and counts the entries of every column.
 
 // the rows of block g up to (and with) a column's match
 __device__ __forceinline__ u64 upto(u64 m, int32_t g, int32_t match) {
@@ -1097,12 +1091,73 @@ __device__ __forceinline__ u64 upto(u64 m, int32_t g, int32_t match) {
     return m & ~above(match & 63);
 }
 
+namespace {
+// Phase I: a row with one U entry less than the row above may extend that
+// row's supernode (inside the same run of max_super rows). Phase II: a chain of
+// such rows is cut before every row s without L(s, r), r the supernode's first
+// row so far. A wavefront takes the chains that begin in its block and follows
+// the last one into the next blocks; inside a block the next cut is the first
+// bit missing from column r's mask, a few scalar instructions, where one lane
+// per chain and a binary search of L per row took 344 us on the 64^3 27-point
+// stencil (1000^2 9-point 298), this 11 (26).
+__device__ __forceinline__ void supernodes_of(const BlockArgs& a, int32_t gb, int64_t max_super, int32_t* is_start) {
+    const int ln = lane();
+    const int32_t jb = a.blk_job ? a.blk_job[gb] : 0;
+    const Job* J = &a.jobs[jb];
+    const int32_t b0 = (int32_t)J->item_base, n = J->n;
+    const int32_t* uc = a.row_ucnt + J->row_base;
+    int32_t* out = is_start + J->row_base;
+    int32_t r = -1;  // first row of the supernode that goes on
+    for (int32_t g = gb - b0; 64 * (int64_t)g < n; ++g) {
+        const int32_t v = 64 * g + ln;
+        const bool in = v < n;
+        const int32_t u = in ? uc[v] : 0, above_u = in && v > 0 ? uc[v - 1] : 0;
+        const u64 d = a.diag[64 * (int64_t)(b0 + g) + ln];
+        const u64 rows = __ballot(in);
+        const u64 F = __ballot(in && v > 0 && (max_super <= 0 || v % max_super != 0) && u == above_u - 1);
+        const bool first = g == gb - b0;
+        // rows of chains that begin here, or of the one that goes on
+        const int lead = rows & ~F ? __builtin_ctzll(rows & ~F) : 64;
+        u64 todo = first ? (lead < 64 ? rows & ~below(lead) : 0ull) : lead < 64 ? rows & below(lead) : rows;
+        if (todo == 0ull) break;
+        const u64 mine = todo;
+        u64 starts = 0;
+        u64 C = 0;  // rows of this block with an entry in column r
+        if (!first) {
+            // the tile of r's column block, near the end of the block's L list
+            const BlockRec rec = a.rec[b0 + g];
+            for (int i = rec.l_cnt; i > 0; i -= 64) {
+                const int32_t t = i - 64 + ln >= 0 ? a.tids[rec.l_off + i - 64 + ln] : -1;
+                const u64 hit = __ballot(t == (r >> 6));
+                if (hit) C = a.masks[64 * (rec.l_off + i - 64 + __builtin_ctzll(hit)) + (r & 63)];
+                if (hit || __builtin_amdgcn_readlane(t, 0) < (r >> 6)) break;
+            }
+        }
+        for (;;) {
+            // (the first row of a chain is no follower and starts one here)
+            const u64 cut = todo & ~(F & C);
+            if (cut == 0ull) break;
+            const int s = __builtin_ctzll(cut);
+            starts |= 1ull << s;
+            r = 64 * g + s;
+            C = readlane64(d, s);
+            todo &= above(s);
+        }
+        if ((mine >> ln) & 1ull) out[v] = (int32_t)((starts >> ln) & 1ull);
+        // (a chain that reaches the block's last row may go on in the next block)
+        if (!(mine >> 63)) break;
+    }
+}
+}  // namespace
+
 // One wavefront per block of columns. Lists of more than 64 tiles are ranked in a
 // bitmap over the row blocks (dynamic LDS: one bit and one prefix per 64 blocks).
 // The tiles with an entry up to their column's first match, all that the reach
 // counts need and one or two in a separator, stay as (blk, tile) at the list's
 // start, the first of them in the block's record.
-__global__ __launch_bounds__(64) void k_bm_lists(BlockArgs a, BlockCols c, int32_t* col_cnt) {
+// The block's supernodes follow (is_start; nullptr: not wanted).
+__global__ __launch_bounds__(64) void k_bm_lists(BlockArgs a, BlockCols c, int32_t* col_cnt, int64_t max_super,
+                                                 int32_t* is_start) {
     extern __shared__ u64 s_dyn[];
     if (ld_dev(&a.ctl[kBmAbort]) != 0u) return;
     const int ln = lane();
@@ -1189,6 +1244,7 @@ __global__ __launch_bounds__(64) void k_bm_lists(BlockArgs a, BlockCols c, int32
     if (ln < kReachWords) c.reach[(int64_t)cb * kReachWords + ln] = word;
     const int64_t v = 64 * (int64_t)c0 + ln;
     if (v < J->n) col_cnt[J->row_base + v] = sum;
+    if (is_start) supernodes_of(a, cb, max_super, is_start);
 }
 
 // ---------------------------------------------------------------- emission
@@ -1314,67 +1370,6 @@ __device__ __forceinline__ void emit_cols(const BlockArgs& a, const BlockCols& c
 }
 
 }  // namespace
-
-// -------------------------------------------------------------- supernodes
-//
-// Phase I: a row with one U entry less than the row above may extend that
-// row's supernode (inside the same run of max_super rows). Phase II: a chain of
-// such rows is cut before every row s without L(s, r), r the supernode's first
-// row so far. A wavefront takes the chains that begin in its block and follows
-// the last one into the next blocks; inside a block the next cut is the first
-// bit missing from column r's mask, a few scalar instructions, where one lane
-// per chain and a binary search of L per row took 344 us on the 64^3 27-point
-// stencil (1000^2 9-point 298), this 11 (26).
-__global__ __launch_bounds__(kThreads) void k_bm_supernodes(BlockArgs a, int64_t max_super, int32_t* is_start) {
-    const int ln = lane();
-    const int32_t gb = (int32_t)blockIdx.x * (kThreads / 64) + rfl(threadIdx.x >> 6);
-    if (gb >= a.nblocks || ld_dev(&a.ctl[kBmAbort]) != 0u) return;
-    const int32_t jb = a.blk_job ? a.blk_job[gb] : 0;
-    const Job* J = &a.jobs[jb];
-    const int32_t b0 = (int32_t)J->item_base, n = J->n;
-    const int32_t* uc = a.row_ucnt + J->row_base;
-    int32_t* out = is_start + J->row_base;
-    int32_t r = -1;  // first row of the supernode that goes on
-    for (int32_t g = gb - b0; 64 * (int64_t)g < n; ++g) {
-        const int32_t v = 64 * g + ln;
-        const bool in = v < n;
-        const int32_t u = in ? uc[v] : 0, above_u = in && v > 0 ? uc[v - 1] : 0;
-        const u64 d = a.diag[64 * (int64_t)(b0 + g) + ln];
-        const u64 rows = __ballot(in);
-        const u64 F = __ballot(in && v > 0 && (max_super <= 0 || v % max_super != 0) && u == above_u - 1);
-        const bool first = g == gb - b0;
-        // rows of chains that begin here, or of the one that goes on
-        const int lead = rows & ~F ? __builtin_ctzll(rows & ~F) : 64;
-        u64 todo = first ? (lead < 64 ? rows & ~below(lead) : 0ull) : lead < 64 ? rows & below(lead) : rows;
-        if (todo == 0ull) break;
-        const u64 mine = todo;
-        u64 starts = 0;
-        u64 C = 0;  // rows of this block with an entry in column r
-        if (!first) {
-            // the tile of r's column block, near the end of the block's L list
-            const BlockRec rec = a.rec[b0 + g];
-            for (int i = rec.l_cnt; i > 0; i -= 64) {
-                const int32_t t = i - 64 + ln >= 0 ? a.tids[rec.l_off + i - 64 + ln] : -1;
-                const u64 hit = __ballot(t == (r >> 6));
-                if (hit) C = a.masks[64 * (rec.l_off + i - 64 + __builtin_ctzll(hit)) + (r & 63)];
-                if (hit || __builtin_amdgcn_readlane(t, 0) < (r >> 6)) break;
-            }
-        }
-        for (;;) {
-            // (the first row of a chain is no follower and starts one here)
-            const u64 cut = todo & ~(F & C);
-            if (cut == 0ull) break;
-            const int s = __builtin_ctzll(cut);
-            starts |= 1ull << s;
-            r = 64 * g + s;
-            C = readlane64(d, s);
-            todo &= above(s);
-        }
-        if ((mine >> ln) & 1ull) out[v] = (int32_t)((starts >> ln) & 1ull);
-        // (a chain that reaches the block's last row may go on in the next block)
-        if (!(mine >> 63)) break;
-    }
-}
 
 // ------------------------------------------------------------------- reach
 //
@@ -1617,6 +1612,187 @@ __global__ __launch_bounds__(64) void k_bm_reach_big(BlockArgs a, BlockCols cl) 
     }
 }
 
+// ------------------------------------------------------- sums and results
+//
+// Small calls are made of launches that do next to nothing (4 to 5 us each, 33 of
+// them around a factorisation of 270 us on a 40 x 40 grid), so what can share
+// one does: the running sums of up to three arrays of a length, everything the
+// host waits for, everything that only needs the finished sums.
+
+namespace {
+constexpr int kScanThreads = 1024;
+constexpr int kScanItems = 8;
+constexpr int kScanTile = kScanThreads * kScanItems;
+// One workgroup per array up to here: 8,192 values a turn (4.7 us for one turn, 16
+// for two), against two launches of at least 4.5 us and a second pass beyond.
+constexpr int64_t kScanOne = kScanTile;
+
+struct BlockScans {
+    BlockScan s[3];
+};
+
+// A tile's values, kScanItems per thread; scan returns their sum, *at what comes
+// before the thread's own.
+struct TileScan {
+    int32_t v[kScanItems];
+
+    __device__ __forceinline__ void load(const int32_t* in, int64_t t0, int64_t n) {
+        const int64_t i0 = t0 + (int64_t)threadIdx.x * kScanItems;
+        if (i0 + kScanItems <= n) {  // (in: 16-byte aligned)
+#pragma unroll
+            for (int k = 0; k < kScanItems; k += 4) {
+                const int4 w = *(const int4*)(in + i0 + k);
+                v[k] = w.x;
+                v[k + 1] = w.y;
+                v[k + 2] = w.z;
+                v[k + 3] = w.w;
+            }
+            return;
+        }
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) v[k] = i0 + k < n ? in[i0 + k] : 0;
+    }
+    __device__ __forceinline__ int64_t scan(int64_t* sh, int64_t* at) {
+        const int wv = threadIdx.x >> 6;
+        int64_t sum = 0;
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) sum += v[k];
+        int64_t x = sum;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int64_t t = __shfl_up(x, (unsigned)d, 64);
+            if (lane() >= d) x += t;
+        }
+        if (lane() == 63) sh[wv] = x;
+        __syncthreads();
+        int64_t pre = 0, total = 0;
+        for (int w = 0; w < kScanThreads / 64; ++w) {
+            if (w < wv) pre += sh[w];
+            total += sh[w];
+        }
+        __syncthreads();
+        *at = pre + x - sum;
+        return total;
+    }
+    __device__ __forceinline__ void store(int64_t* out, int64_t t0, int64_t n, int64_t at) const {
+        const int64_t i0 = t0 + (int64_t)threadIdx.x * kScanItems;
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) {
+            if (i0 + k < n) out[i0 + k] = at;
+            at += v[k];
+        }
+    }
+};
+}  // namespace
+
+__global__ __launch_bounds__(kScanThreads) void k_bm_scan_one(BlockScans all, int64_t n) {
+    __shared__ int64_t sh[kScanThreads / 64];
+    const BlockScan s = all.s[blockIdx.x];
+    TileScan t;
+    int64_t carry = 0;
+    t.load(s.in, 0, n);
+    for (int64_t t0 = 0; t0 < n; t0 += kScanTile) {
+        TileScan cur = t;
+        if (t0 + kScanTile < n) t.load(s.in, t0 + kScanTile, n);
+        int64_t at;
+        const int64_t total = cur.scan(sh, &at);
+        cur.store(s.out, t0, n, carry + at);
+        carry += total;
+    }
+    if (threadIdx.x == 0) s.out[n] = carry;
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_bm_scan_sums(BlockScans all, int64_t n, int64_t* sums) {
+    __shared__ int64_t sh[kScanThreads / 64];
+    TileScan t;
+    t.load(all.s[blockIdx.y].in, (int64_t)blockIdx.x * kScanTile, n);
+    int64_t at;
+    const int64_t total = t.scan(sh, &at);
+    if (threadIdx.x == 0) sums[blockIdx.y * (int64_t)gridDim.x + blockIdx.x] = total;
+}
+
+// (each workgroup adds up the tiles before its own: at most 512 for 2^22 rows)
+__global__ __launch_bounds__(kScanThreads) void k_bm_scan_apply(BlockScans all, int64_t n, const int64_t* sums) {
+    __shared__ int64_t sh[kScanThreads / 64];
+    const BlockScan s = all.s[blockIdx.y];
+    sums += blockIdx.y * (int64_t)gridDim.x;
+    int64_t part = 0;
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += kScanThreads) part += sums[i];
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) part += __shfl_xor(part, d, 64);
+    if (lane() == 0) sh[threadIdx.x >> 6] = part;
+    __syncthreads();
+    int64_t carry = 0;
+    for (int w = 0; w < kScanThreads / 64; ++w) carry += sh[w];
+    __syncthreads();
+    TileScan t;
+    const int64_t t0 = (int64_t)blockIdx.x * kScanTile;
+    t.load(s.in, t0, n);
+    int64_t at;
+    const int64_t total = t.scan(sh, &at);
+    t.store(s.out, t0, n, carry + at);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) s.out[n] = carry + total;
+}
+
+namespace {
+// to memory that the host may read
+__device__ __forceinline__ void put_host(void* dst, const void* src, int64_t bytes, int64_t i, int64_t step) {
+    for (; i < bytes / 4; i += step)
+        __hip_atomic_store((uint32_t*)dst + i, ((const uint32_t*)src)[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+}  // namespace
+
+// What the host waits for: control words, totals, statistics.
+__global__ __launch_bounds__(kThreads) void k_bm_status(BlockArgs a, int32_t nj, const int64_t* u_total,
+                                                        const int64_t* l_total, const int64_t* s_total,
+                                                        BlockStatus* out, JobStats* js) {
+    const int t = threadIdx.x;
+    put_host(out->ctl, a.ctl, sizeof(out->ctl), t, kThreads);
+    if (u_total) put_host(&out->nnz_u, u_total, 8, t, kThreads);
+    if (l_total) put_host(&out->nnz_l, l_total, 8, t, kThreads);
+    if (s_total) put_host(&out->nsuper, s_total, 8, t, kThreads);
+    put_host(js, a.jstats, (int64_t)sizeof(JobStats) * nj, t, kThreads);
+    __threadfence_system();
+}
+
+// What is left once rows and columns are written: supernodes from their starts
+// and the starts' sums, each matrix's own pointers, pointer values at the
+// matrices' ends and the statistics for the host.
+__global__ __launch_bounds__(256) void k_bm_finish(BlockArgs a, BlockFinish f) {
+    const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t r = i0; r < f.nrows; r += step) {
+        const int32_t j = a.blk_job ? f.row_job[r] : 0;
+        const int64_t b = a.jobs[j].row_base;
+        if (f.supno) {
+            const int64_t k = f.start_scan[r];  // supernode starts before r, all matrices
+            const int32_t start = f.is_start[r];
+            if (start) f.xsup[k + j] = (int32_t)(r - b);
+            f.supno[r] = (int32_t)(k + start - 1 - f.start_scan[b]);
+        }
+        if (f.u_loc) {
+            f.u_loc[r + j] = f.u_ptr[r] - f.u_ptr[b];
+            f.l_loc[r + j] = f.l_ptr[r] - f.l_ptr[b];
+        }
+    }
+    for (int64_t j = i0; j <= f.nj; j += step) {
+        const int64_t b = j < f.nj ? a.jobs[j].row_base : f.nrows;
+        const int64_t v[3] = {f.u_ptr[b], f.l_ptr[b], f.supno ? f.start_scan[b] : 0};
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if (f.bounds) put_host(&f.bounds[k * (int64_t)(f.nj + 1) + j], &v[k], 8, 0, 1);
+        if (j == f.nj) break;
+        const int32_t n = a.jobs[j].n;
+        if (f.supno) f.xsup[f.start_scan[b + n] + j] = n;
+        if (f.u_loc) {
+            f.u_loc[b + n + j] = f.u_ptr[b + n] - v[0];
+            f.l_loc[b + n + j] = f.l_ptr[b + n] - v[1];
+        }
+    }
+    if (f.js) put_host(f.js, a.jstats, (int64_t)sizeof(JobStats) * f.nj, i0, step);
+    // (the others' fence would write the whole L2 back: 250 us on 10^6 rows, not 14)
+    if (i0 <= f.nj * (int64_t)(sizeof(JobStats) / 4)) __threadfence_system();
+}
+
 // ------------------------------------------------------------------ launches
 
 // Several matrices: blocks with the same local index are taken together, so
@@ -1670,12 +1846,40 @@ hipError_t launch_block_factor(const BlockArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_block_counts(const BlockArgs& a, const BlockCols& c, int32_t* col_cnt, hipStream_t st) {
+hipError_t launch_block_counts(const BlockArgs& a, const BlockCols& c, int32_t* col_cnt, int64_t max_super,
+                               int32_t* is_start, hipStream_t st) {
     if (a.nblocks <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_bm_count, dim3((unsigned)a.nblocks), dim3(kThreads), 0, st, a);
-    hipLaunchKernelGGL(k_bm_scatter, dim3((unsigned)a.nblocks), dim3(kThreads), 0, st, a, c);
+    hipLaunchKernelGGL(k_bm_count, dim3((unsigned)a.nblocks), dim3(kThreads), 0, st, a, c);
     hipLaunchKernelGGL(k_bm_lists, dim3((unsigned)a.nblocks), dim3(64), (size_t)a.bit_words * 12 + 8, st, a, c,
-                       col_cnt);
+                       col_cnt, max_super, is_start);
+    return hipGetLastError();
+}
+
+int64_t block_scan_tiles(int64_t n) { return (n + kScanTile - 1) / kScanTile; }
+
+hipError_t launch_block_scan(const BlockScan* s, int count, int64_t n, int64_t* scratch, hipStream_t st) {
+    BlockScans all{};
+    for (int i = 0; i < count; ++i) all.s[i] = s[i];
+    if (n <= kScanOne) {
+        hipLaunchKernelGGL(k_bm_scan_one, dim3((unsigned)count), dim3(kScanThreads), 0, st, all, n);
+        return hipGetLastError();
+    }
+    const int64_t nt = block_scan_tiles(n);
+    hipLaunchKernelGGL(k_bm_scan_sums, dim3((unsigned)nt, (unsigned)count), dim3(kScanThreads), 0, st, all, n, scratch);
+    hipLaunchKernelGGL(k_bm_scan_apply, dim3((unsigned)nt, (unsigned)count), dim3(kScanThreads), 0, st, all, n,
+                       scratch);
+    return hipGetLastError();
+}
+
+hipError_t launch_block_status(const BlockArgs& a, int32_t nj, const int64_t* u_total, const int64_t* l_total,
+                               const int64_t* s_total, BlockStatus* out, JobStats* js, hipStream_t st) {
+    hipLaunchKernelGGL(k_bm_status, dim3(1), dim3(kThreads), 0, st, a, nj, u_total, l_total, s_total, out, js);
+    return hipGetLastError();
+}
+
+hipError_t launch_block_finish(const BlockArgs& a, const BlockFinish& f, hipStream_t st) {
+    const unsigned g = (unsigned)std::min<int64_t>((f.nrows + f.nj + 1 + 255) / 256, 4096);
+    hipLaunchKernelGGL(k_bm_finish, dim3(std::max(g, 1u)), dim3(256), 0, st, a, f);
     return hipGetLastError();
 }
 
@@ -1693,14 +1897,6 @@ hipError_t launch_block_emit(const BlockArgs& a, const BlockCols& c, const int64
     hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, a, c, u_ptr, u_idx, l_ptr, l_idx);
     hipLaunchKernelGGL(k_bm_reach_big, dim3((unsigned)std::min(a.nslots, 256)), dim3(64), (size_t)a.bit_words * 8, st,
                        a, c);
-    return hipGetLastError();
-}
-
-hipError_t launch_block_supernodes(const BlockArgs& a, int64_t max_super, int32_t* is_start, hipStream_t st) {
-    if (a.nblocks <= 0) return hipSuccess;
-    const int per = kThreads / 64;
-    hipLaunchKernelGGL(k_bm_supernodes, dim3((unsigned)((a.nblocks + per - 1) / per)), dim3(kThreads), 0, st, a,
-                       max_super, is_start);
     return hipGetLastError();
 }
 

@@ -1009,13 +1009,6 @@ int64_t budget_for(int64_t nrows, int64_t nnz, int64_t nslots, const SlotLayout&
     return fixed_bytes(nrows, nnz) + 2 * nslots * lay.bytes_per_slot + 12 * pool_estimate(nrows, nnz);
 }
 
-// out[j] = row_ptr_j[n_j]: the entry count of every matrix of a batch.
-__global__ void k_gather_last(int32_t njobs, const Job* jobs, int64_t* out) {
-    const int32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= njobs) return;
-    out[j] = jobs[j].n > 0 ? (int64_t)jobs[j].row_ptr[jobs[j].n] : 0;
-}
-
 // out[j] = a[job_row_base[j]] for j < njobs, out[njobs] = a[nrows]: the values
 // of a global pointer array at the matrix boundaries.
 __global__ void k_gather_bounds(int32_t njobs, const int64_t* job_row_base, int64_t nrows, const int64_t* a,
@@ -1098,30 +1091,10 @@ struct Engine {
         std::vector<Job> jobs(nj);
         DBuf in_rp, in_ci;
         if (on_device) {
-            // every matrix's entry count (row_ptr[n]) in one gather and one copy
             for (int32_t j = 0; j < nj; ++j) {
                 jobs[j].row_ptr = mats[j].rp;
                 jobs[j].col_idx = mats[j].ci;
-                jobs[j].n = mats[j].n;
             }
-            DBuf d_tab(sizeof(Job) * std::max(nj, 1)), d_last(8 * std::max(nj, 1));
-            PinnedBuf h_last(8 * std::max(nj, 1));
-            h2d(d_tab.p, jobs.data(), sizeof(Job) * nj, st, false);
-            if (nj > 0)
-                hipLaunchKernelGGL(k_gather_last, dim3((nj + 255) / 256), dim3(256), 0, st, nj, d_tab.as<Job>(),
-                                   d_last.as<int64_t>());
-            chk(hipGetLastError());
-            chk(launch_copy_to_host(h_last.p, d_last.p, 8 * nj, st));
-            chk(hipStreamSynchronize(st));
-            for (int32_t j = 0; j < nj; ++j) {
-                const int64_t last = h_last.as<int64_t>()[j];
-                // a negative count, or entries with no column array, is malformed
-                if (last < 0 || (last > 0 && !mats[j].ci)) jstat[j] = GSOFA_EINVAL;
-                nnz[j] = std::max<int64_t>(last, 0);
-            }
-            // nothing may read such a matrix's arrays: fail before the validation kernel
-            for (int32_t j = 0; j < nj; ++j)
-                if (jstat[j] != GSOFA_OK) return finish_failed(jstat, t0);
         } else {
             std::vector<int64_t> rp_off(nj), ci_off(nj);
             int64_t rp_tot = 0, ci_tot = 0;
@@ -1154,8 +1127,6 @@ struct Engine {
                 jobs[j].col_idx = in_ci.as<int32_t>() + ci_off[j];
             }
         }
-        for (int32_t j = 0; j < nj; ++j) total_nnz += nnz[j];
-
         // work order: larger matrices first; inside a matrix, larger row ids first
         std::vector<int32_t> ord(nj);
         for (int32_t j = 0; j < nj; ++j) ord[j] = j;
@@ -1177,19 +1148,24 @@ struct Engine {
         h2d(d_jobs.p, jt.data(), sizeof(Job) * nj, st, false);
 
         if (on_device) {
-            DBuf bad(4 * std::max(nj, 1));
-            chk(launch_zero_i32(bad.as<int32_t>(), nj, st));
-            chk(launch_validate(d_jobs.as<Job>(), nj, N, bad.as<int32_t>(), st));
-            PinnedBuf h_bad(4 * (size_t)std::max(nj, 1));
-            chk(launch_copy_to_host(h_bad.p, bad.p, 4 * (size_t)nj, st));
+            // the structure and every matrix's entry count in one pass
+            const size_t nf = 2 * (size_t)std::max(nj, 1);
+            DBuf found(4 * nf);
+            PinnedBuf h_found(4 * nf);
+            chk(launch_zero_i32(found.as<int32_t>(), (int64_t)nf, st));
+            chk(launch_validate(d_jobs.as<Job>(), nj, N, found.as<int32_t>(), st, found.as<int32_t>() + nj));
+            chk(launch_copy_to_host(h_found.p, found.p, 8 * (size_t)nj, st));
             chk(hipStreamSynchronize(st));
-            const int32_t* hb = h_bad.as<int32_t>();
-            for (int32_t q = 0; q < nj; ++q)
-                if (hb[q]) jstat[ord[q]] = GSOFA_EINVAL;
-            bool any_bad = false;
-            for (int32_t j = 0; j < nj; ++j) any_bad |= jstat[j] != GSOFA_OK;
-            if (any_bad) return finish_failed(jstat, t0);
+            const int32_t* hb = h_found.as<int32_t>();
+            int32_t worst = 0;  // 2: nothing of the matrix was looked at
+            for (int32_t q = 0; q < nj; ++q) worst = std::max(worst, hb[q]);
+            for (int32_t q = 0; q < nj; ++q) {
+                nnz[ord[q]] = std::max<int64_t>(hb[nj + q], 0);
+                if (worst > 0 && hb[q] == worst) jstat[ord[q]] = GSOFA_EINVAL;
+            }
+            if (worst > 0) return finish_failed(jstat, t0);
         }
+        for (int32_t j = 0; j < nj; ++j) total_nnz += nnz[j];
 
         // ---- the block path, where nothing asks for the per-source traversal
         const TuneKey key{device_cus(), ceil_log2(N), ceil_log2(std::max<int64_t>(total_nnz * 4 / std::max<int64_t>(nrows, 1), 1)),
@@ -2034,22 +2010,17 @@ struct Engine {
         const int64_t nr1 = std::max<int64_t>(nrows, 1), nb1 = std::max<int64_t>(nblocks, 1);
         auto up16 = [](int64_t b) { return (b + 15) & ~int64_t(15); };
 
-        // small host tables in one upload: jobs, matrix bounds, block order
-        const int64_t o_jn = up16((int64_t)sizeof(Job) * nj), o_jrb = o_jn + up16(4 * (int64_t)nj),
-                      o_ord = o_jrb + up16(8 * (int64_t)nj), o_cum = o_ord + up16(4 * (int64_t)nj),
+        // small host tables in one upload: jobs, block order
+        const int64_t o_ord = up16((int64_t)sizeof(Job) * nj), o_cum = o_ord + up16(4 * (int64_t)nj),
                       up_bytes = o_cum + up16(8 * (max_blocks + 1)) + 16;
         PinnedBuf h_up((size_t)up_bytes);
         DBuf d_up((size_t)up_bytes);
         {
             char* c = h_up.as<char>();
             std::memcpy(c, jt.data(), sizeof(Job) * (size_t)nj);
-            int32_t* jn = reinterpret_cast<int32_t*>(c + o_jn);
-            int64_t* jrb = reinterpret_cast<int64_t*>(c + o_jrb);
             int32_t* ord = reinterpret_cast<int32_t*>(c + o_ord);
             int64_t* cum = reinterpret_cast<int64_t*>(c + o_cum);
             for (int32_t j = 0; j < nj; ++j) {
-                jn[j] = mats[j].n;
-                jrb[j] = row_base[j];
                 ord[j] = j;
             }
             if (nj > 1) {
@@ -2064,8 +2035,6 @@ struct Engine {
         }
         char* const du = d_up.as<char>();
         const Job* d_jobs = reinterpret_cast<const Job*>(du);
-        const int32_t* d_jn = reinterpret_cast<const int32_t*>(du + o_jn);
-        const int64_t* d_jrb = reinterpret_cast<const int64_t*>(du + o_jrb);
 
         // arrays cleared before the factorisation: control words, headers, tile
         // counts, per-matrix statistics
@@ -2079,17 +2048,21 @@ struct Engine {
             reach(4 * kReachWords * (size_t)nb1);
         DBuf row_ucnt(4 * (size_t)nr1), row_lcnt(4 * (size_t)nr1), col_cnt(4 * (size_t)nr1);
         DBuf u_ptr(8 * (size_t)(nrows + 1)), l_ptr(8 * (size_t)(nrows + 1)), list_ptr(8 * (size_t)(nb1 + 1));
-        DBuf scan_scr(8 * (size_t)scan_scratch_elems(nrows + 1) + 64);
-        DBuf items, blk_job, row_job, big(4 * (size_t)nb1);
+        DBuf scan_scr(8 * 3 * (size_t)block_scan_tiles(std::max(nrows, nb1)) + 64);
+        DBuf items, blk_job, row_job, big(4 * (size_t)nb1), is_start, start_scan;
+        if (have_sn) {
+            is_start = DBuf(4 * (size_t)nrows);
+            start_scan = DBuf(8 * (size_t)(nrows + 1));
+        }
         if (nj > 1) {
             items = DBuf(4 * (size_t)nb1);
             blk_job = DBuf(4 * (size_t)nb1);
             row_job = DBuf(4 * (size_t)nr1);
         }
-        PinnedBuf h_st((size_t)(64 + 32 + sizeof(JobStats) * (size_t)std::max(nj, 1)));
-        uint32_t* h_ctl = h_st.as<uint32_t>();
-        int64_t* h_tot = reinterpret_cast<int64_t*>(h_st.as<char>() + 64);
-        JobStats* h_js = reinterpret_cast<JobStats*>(h_st.as<char>() + 96);
+        PinnedBuf h_st(sizeof(BlockStatus) + sizeof(JobStats) * (size_t)std::max(nj, 1));
+        BlockStatus* h_status = h_st.as<BlockStatus>();
+        const uint32_t* h_ctl = h_status->ctl;
+        JobStats* h_js = reinterpret_cast<JobStats*>(h_status + 1);
         EventSet ev;
 
         auto masks = take_masks(stride, (int32_t)ns, st);
@@ -2154,16 +2127,15 @@ struct Engine {
                     chk(launch_row_job(d_jobs, nj, N, row_job.as<int32_t>(), s));
                 }
                 chk(launch_block_factor(ba, s));
-                chk(launch_scan_counts(ba.tcount, nullptr, nblocks, list_ptr.as<int64_t>(), scan_scr.as<int64_t>(), s));
-                chk(launch_block_counts(ba, bc, col_cnt.as<int32_t>(), s));
-                chk(launch_scan_counts(row_ucnt.as<int32_t>(), nullptr, nrows, u_ptr.as<int64_t>(),
-                                       scan_scr.as<int64_t>(), s));
-                chk(launch_scan_counts(l_csr ? row_lcnt.as<int32_t>() : col_cnt.as<int32_t>(), nullptr, nrows,
-                                       l_ptr.as<int64_t>(), scan_scr.as<int64_t>(), s));
-                chk(launch_copy_to_host(h_ctl, d_ctl, 64, s));
-                chk(launch_copy_to_host(h_tot, u_ptr.as<int64_t>() + nrows, 8, s));
-                chk(launch_copy_to_host(h_tot + 1, l_ptr.as<int64_t>() + nrows, 8, s));
-                chk(launch_copy_to_host(h_js, d_js, sizeof(JobStats) * (size_t)nj, s));
+                const BlockScan lists{ba.tcount, list_ptr.as<int64_t>()};
+                chk(launch_block_scan(&lists, 1, nblocks, scan_scr.as<int64_t>(), s));
+                chk(launch_block_counts(ba, bc, col_cnt.as<int32_t>(), plan.max_super, is_start.as<int32_t>(), s));
+                const BlockScan sums[3] = {{row_ucnt.as<int32_t>(), u_ptr.as<int64_t>()},
+                                           {l_csr ? row_lcnt.as<int32_t>() : col_cnt.as<int32_t>(), l_ptr.as<int64_t>()},
+                                           {is_start.as<int32_t>(), start_scan.as<int64_t>()}};
+                chk(launch_block_scan(sums, have_sn ? 3 : 2, nrows, scan_scr.as<int64_t>(), s));
+                chk(launch_block_status(ba, nj, u_ptr.as<int64_t>() + nrows, l_ptr.as<int64_t>() + nrows, nullptr,
+                                        h_status, h_js, s));
                 ph.launch();
                 ++launches;
                 if (yh && yh->enqueued) yh->enqueued();
@@ -2177,7 +2149,7 @@ struct Engine {
             if (h_ctl[kBmAbort] != kBmOverflow) throw HipError{hipErrorLaunchTimeOut};
             tiles.reset();
             tabs.reset();
-            cap = 4 * std::max<int64_t>(cap, (int64_t)*reinterpret_cast<unsigned long long*>(h_ctl + 8));
+            cap = 4 * std::max<int64_t>(cap, (int64_t)*reinterpret_cast<const unsigned long long*>(h_ctl + 8));
             if (!fits(cap)) {
                 chk(hipStreamSynchronize(st));
                 give_masks(std::move(masks));
@@ -2187,13 +2159,13 @@ struct Engine {
         }
         if (yh && yh->finished) yh->finished();
         if (nblocks > 0) {
-            const double used = (double)*reinterpret_cast<unsigned long long*>(h_ctl + 8);
+            const double used = (double)*reinterpret_cast<const unsigned long long*>(h_ctl + 8);
             std::lock_guard<std::mutex> g(g_fill_mu);
             block_ratios()[key] = std::max(4.0, used / (double)nblocks);
         }
         for (int32_t j = 0; j < nj; ++j)
             if (h_js[j].err & kErrDuplicate) jstat[j] = GSOFA_EINVAL;
-        const int64_t nnz_u = h_tot[0], nnz_l = h_tot[1];
+        const int64_t nnz_u = h_status->nnz_u, nnz_l = h_status->nnz_l;
         if (total_nnz > 0) note_fill_ratio(key, std::max(4.0, (double)(nnz_u + nnz_l) / (double)total_nnz));
         chk(hipEventRecord(ev[1], st));
 
@@ -2201,15 +2173,7 @@ struct Engine {
         Factors f;
         f.u_idx = DBuf(4 * (size_t)std::max<int64_t>(nnz_u, 1));
         f.l_idx = DBuf(4 * (size_t)std::max<int64_t>(nnz_l, 1));
-        RowSpace rs{nrows, nullptr, nullptr};
-        if (nj > 1) {
-            rs.row_job = row_job.as<int32_t>();
-            rs.job_row_base = d_jrb;
-        }
-        DBuf is_start, start_scan;
         if (have_sn) {
-            is_start = DBuf(4 * (size_t)nrows);
-            start_scan = DBuf(8 * (size_t)(nrows + 1));
             f.xsup = DBuf(4 * (size_t)(nrows + nj));
             f.supno = DBuf(4 * (size_t)nrows);
         }
@@ -2217,52 +2181,29 @@ struct Engine {
             f.u_ptr_loc = DBuf(8 * (size_t)(nrows + nj));
             f.l_ptr_loc = DBuf(8 * (size_t)(nrows + nj));
         }
-        DBuf d_b(8 * 3 * (size_t)(nj + 1));
         PinnedBuf h_b(8 * 3 * (size_t)(nj + 1));
+        BlockFinish bf{};
+        bf.nrows = nrows;
+        bf.nj = nj;
+        bf.row_job = row_job.as<int32_t>();
+        bf.u_ptr = u_ptr.as<int64_t>();
+        bf.l_ptr = l_ptr.as<int64_t>();
+        bf.u_loc = f.u_ptr_loc.as<int64_t>();
+        bf.l_loc = f.l_ptr_loc.as<int64_t>();
+        bf.is_start = is_start.as<int32_t>();
+        bf.start_scan = start_scan.as<int64_t>();
+        bf.xsup = f.xsup.as<int32_t>();
+        bf.supno = f.supno.as<int32_t>();
+        bf.bounds = h_b.as<int64_t>();
+        bf.js = h_js;
 
-        Phase ph_emit(kPhaseSort, graphs, st);
-        {
-            const hipStream_t s = ph_emit.stream();
-            chk(launch_block_emit(ba, bc, u_ptr.as<int64_t>(), f.u_idx.as<int32_t>(), l_ptr.as<int64_t>(),
-                                  f.l_idx.as<int32_t>(), l_csr, s));
-            chk(launch_copy_to_host(h_js, d_js, sizeof(JobStats) * (size_t)nj, s));
-            ph_emit.launch();
-        }
+        // (three launches: nothing for a graph to save)
+        chk(launch_block_emit(ba, bc, u_ptr.as<int64_t>(), f.u_idx.as<int32_t>(), l_ptr.as<int64_t>(),
+                              f.l_idx.as<int32_t>(), l_csr, st));
         chk(hipEventRecord(ev[2], st));
-        Phase ph_sn(kPhaseSupernodes, graphs, st);
-        {
-            const hipStream_t s = ph_sn.stream();
-            if (have_sn) {
-                chk(launch_block_supernodes(ba, plan.max_super, is_start.as<int32_t>(), s));
-                chk(launch_scan_counts(is_start.as<int32_t>(), nullptr, nrows, start_scan.as<int64_t>(),
-                                       scan_scr.as<int64_t>(), s));
-                chk(launch_supernode_assemble(rs, nj, is_start.as<int32_t>(), start_scan.as<int64_t>(),
-                                              f.xsup.as<int32_t>(), f.supno.as<int32_t>(), s));
-                chk(launch_supernode_terminals(nj, d_jrb, d_jn, start_scan.as<int64_t>(), f.xsup.as<int32_t>(), s));
-            }
-            if (nj > 1) {
-                const unsigned gx = (unsigned)std::min<int64_t>((N + 256) / 256, 64);
-                hipLaunchKernelGGL(k_rebase_ptr, dim3(gx, nj), dim3(256), 0, s, nj, d_jrb, d_jn, u_ptr.as<int64_t>(),
-                                   f.u_ptr_loc.as<int64_t>());
-                hipLaunchKernelGGL(k_rebase_ptr, dim3(gx, nj), dim3(256), 0, s, nj, d_jrb, d_jn, l_ptr.as<int64_t>(),
-                                   f.l_ptr_loc.as<int64_t>());
-            }
-            const dim3 gb((nj + 1 + 255) / 256);
-            hipLaunchKernelGGL(k_gather_bounds, gb, dim3(256), 0, s, nj, d_jrb, nrows, u_ptr.as<int64_t>(),
-                               d_b.as<int64_t>());
-            hipLaunchKernelGGL(k_gather_bounds, gb, dim3(256), 0, s, nj, d_jrb, nrows, l_ptr.as<int64_t>(),
-                               d_b.as<int64_t>() + (nj + 1));
-            if (have_sn)
-                hipLaunchKernelGGL(k_gather_bounds, gb, dim3(256), 0, s, nj, d_jrb, nrows, start_scan.as<int64_t>(),
-                                   d_b.as<int64_t>() + 2 * (nj + 1));
-            chk(hipGetLastError());
-            chk(launch_copy_to_host(h_b.p, d_b.p, 8 * 3 * (size_t)(nj + 1), s));
-            ph_sn.launch();
-        }
+        chk(launch_block_finish(ba, bf, st));
         chk(hipEventRecord(ev[3], st));
         chk(hipStreamSynchronize(st));
-        ph_emit.done();
-        ph_sn.done();
         give_masks(std::move(masks));
 
         std::vector<JobStats> js(h_js, h_js + nj);

@@ -163,14 +163,46 @@ hipError_t launch_block_tables(const Job* jobs, const int32_t* ord, const int64_
                                int32_t nblocks, int32_t* items, int32_t* blk_job, hipStream_t st);
 // structure of every block
 hipError_t launch_block_factor(const BlockArgs& a, hipStream_t st);
-// entries of L and U per row, L's tiles by columns, entries of L per column
-hipError_t launch_block_counts(const BlockArgs& a, const BlockCols& c, int32_t* col_cnt, hipStream_t st);
+// entries of L and U per row, L's tiles by columns, entries of L per column; supernode
+// starts (1 or 0 per row), at most max_super rows each (<= 0: any; nullptr: none wanted)
+hipError_t launch_block_counts(const BlockArgs& a, const BlockCols& c, int32_t* col_cnt, int64_t max_super,
+                               int32_t* is_start, hipStream_t st);
+// out[0..n]: exclusive sums of in[0..n), for up to three arrays; scratch holds
+// 3 * block_scan_tiles(n) sums
+struct BlockScan {
+    const int32_t* in;
+    int64_t* out;
+};
+int64_t block_scan_tiles(int64_t n);
+hipError_t launch_block_scan(const BlockScan* s, int count, int64_t n, int64_t* scratch, hipStream_t st);
+// control words, totals (nullptr: not written) and statistics to memory that the host
+// reads, or that is copied there
+struct BlockStatus {
+    uint32_t ctl[16];
+    int64_t nnz_u, nnz_l, nsuper;
+};
+hipError_t launch_block_status(const BlockArgs& a, int32_t nj, const int64_t* u_total, const int64_t* l_total,
+                               const int64_t* s_total, BlockStatus* out, JobStats* js, hipStream_t st);
+// supernodes (supno: nullptr for none), per-matrix pointers (u_loc: nullptr for none),
+// to the host the pointers at the matrices' bounds (u, l, supernode starts: nj + 1
+// each) and statistics (nullptr: none)
+struct BlockFinish {
+    int64_t nrows;
+    int32_t nj;
+    const int32_t* row_job;
+    const int64_t *u_ptr, *l_ptr;
+    int64_t *u_loc, *l_loc;
+    const int32_t* is_start;
+    const int64_t* start_scan;
+    int32_t *xsup, *supno;
+    int64_t* bounds;
+    JobStats* js;
+};
+hipError_t launch_block_finish(const BlockArgs& a, const BlockFinish& f, hipStream_t st);
 // rows of U, columns (l_csr: rows) of L at u_ptr, l_ptr (per row of the row space);
 // edges_alg less the sources' own degrees, added to jstats
 hipError_t launch_block_emit(const BlockArgs& a, const BlockCols& c, const int64_t* u_ptr, int32_t* u_idx,
                              const int64_t* l_ptr, int32_t* l_idx, bool l_csr, hipStream_t st);
-// supernode starts (1 or 0 per row), at most max_super rows each (<= 0: any)
-hipError_t launch_block_supernodes(const BlockArgs& a, int64_t max_super, int32_t* is_start, hipStream_t st);
 
 // Row-space description shared by the assembly kernels. With one job,
 // row_job == nullptr and every base is 0.
@@ -180,8 +212,10 @@ struct RowSpace {
     const int64_t* job_row_base;  // job -> first global row
 };
 
+// bad[j] != 0: matrix j is malformed; last (may be nullptr): every matrix's entry
+// count, 2 in bad where it is negative or there is no column array
 hipError_t launch_validate(const Job* jobs_dev, int32_t njobs, int64_t max_n,
-                           int32_t* bad_dev, hipStream_t st);
+                           int32_t* bad_dev, hipStream_t st, int32_t* last = nullptr);
 hipError_t launch_init_slots(uint8_t* slots, int32_t nslots, SlotLayout lay, hipStream_t st);
 hipError_t launch_traverse(const TraverseArgs& a, hipStream_t st);
 // bytes (a multiple of 4) from device memory to pinned host memory, by a kernel

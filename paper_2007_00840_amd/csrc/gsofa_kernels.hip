@@ -225,10 +225,18 @@ hipError_t launch_init_slots(uint8_t* slots, int32_t nslots, SlotLayout lay, hip
 
 // Input checks for device-resident CSR: row_ptr[0] == 0, non-decreasing,
 // columns in [0, n). Rows whose bounds are broken are not read.
-__global__ void k_validate(const Job* jobs, int32_t njobs, int64_t max_n, int32_t* bad) {
+__global__ void k_validate(const Job* jobs, int32_t njobs, int64_t max_n, int32_t* bad, int32_t* last) {
     const int32_t j = blockIdx.y;
     if (j >= njobs) return;
     const Job J = jobs[j];
+    const int32_t nnz = last && J.n > 0 ? J.row_ptr[J.n] : 0;
+    if (last && blockIdx.x == 0 && threadIdx.x == 0) last[j] = nnz;
+    // a negative count, or entries with no column array, is malformed (2): nothing
+    // else of the matrix is read
+    if (nnz < 0 || (nnz > 0 && !J.col_idx)) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) bad[j] = 2;
+        return;
+    }
     for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < J.n;
          r += (int64_t)gridDim.x * blockDim.x) {
         int32_t a = J.row_ptr[r], b = J.row_ptr[r + 1];
@@ -245,11 +253,11 @@ __global__ void k_validate(const Job* jobs, int32_t njobs, int64_t max_n, int32_
 }
 
 hipError_t launch_validate(const Job* jobs_dev, int32_t njobs, int64_t max_n, int32_t* bad_dev,
-                           hipStream_t st) {
+                           hipStream_t st, int32_t* last) {
     if (njobs <= 0) return hipSuccess;
     int gx = (int)std::min<int64_t>((max_n + 255) / 256, 1024);
     if (gx < 1) gx = 1;
-    hipLaunchKernelGGL(k_validate, dim3(gx, njobs), dim3(256), 0, st, jobs_dev, njobs, max_n, bad_dev);
+    hipLaunchKernelGGL(k_validate, dim3(gx, njobs), dim3(256), 0, st, jobs_dev, njobs, max_n, bad_dev, last);
     return hipGetLastError();
 }
 

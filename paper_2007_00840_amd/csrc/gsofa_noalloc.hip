@@ -118,8 +118,6 @@ struct Call {
     bool want_sn, l_csr;
     const Job* job;
     JobStats* js;
-    const int64_t* jrb;
-    const int32_t* jn;
     int64_t* scan_scr;
     int32_t *row_ucnt, *row_lcnt, *is_start;
     int64_t* start_scan;
@@ -160,6 +158,7 @@ int blocks_noalloc(const Call& k, uint8_t* base, size_t cap, double t0, gsofa_co
     a.rec = sp.take<BlockRec>(nb);
     int32_t* col_cnt = sp.take<int32_t>(k.n);
     int64_t* list_ptr = sp.take<int64_t>(nb + 1);
+    BlockStatus* status = reinterpret_cast<BlockStatus*>(sp.take<uint8_t>(sizeof(BlockStatus) + sizeof(JobStats)));
     BlockCols bc{};
     bc.ptr = list_ptr;
     bc.big = sp.take<int32_t>(nb);
@@ -192,30 +191,32 @@ int blocks_noalloc(const Call& k, uint8_t* base, size_t cap, double t0, gsofa_co
     NA_CHK(launch_zero_i32(reinterpret_cast<int32_t*>(zero), z_bytes / 4, st));
     NA_CHK(launch_zero_i32(reinterpret_cast<int32_t*>(a.x), 2 * ns * stride, st));
     NA_CHK(launch_block_factor(a, st));
-    uint32_t ctl[16];
-    NA_CHK(hipMemcpyAsync(ctl, a.ctl, sizeof(ctl), hipMemcpyDeviceToHost, st));
-    NA_CHK(launch_scan_counts(a.tcount, nullptr, nb, list_ptr, k.scan_scr, st));
-    NA_CHK(launch_block_counts(a, bc, col_cnt, st));
-    NA_CHK(launch_scan_counts(k.row_ucnt, nullptr, k.n, k.u_ptr, k.scan_scr, st));
-    NA_CHK(launch_scan_counts(k.l_csr ? k.row_lcnt : col_cnt, nullptr, k.n, k.l_ptr, k.scan_scr, st));
-    JobStats hs{};
-    int64_t tot[2] = {0, 0};
-    NA_CHK(hipMemcpyAsync(&tot[0], k.u_ptr + k.n, 8, hipMemcpyDeviceToHost, st));
-    NA_CHK(hipMemcpyAsync(&tot[1], k.l_ptr + k.n, 8, hipMemcpyDeviceToHost, st));
-    NA_CHK(hipMemcpyAsync(&hs, k.js, sizeof(JobStats), hipMemcpyDeviceToHost, st));
+    const BlockScan lists{a.tcount, list_ptr};
+    NA_CHK(launch_block_scan(&lists, 1, nb, k.scan_scr, st));
+    NA_CHK(launch_block_counts(a, bc, col_cnt, k.max_super, k.is_start, st));
+    const BlockScan sums[3] = {
+        {k.row_ucnt, k.u_ptr}, {k.l_csr ? k.row_lcnt : col_cnt, k.l_ptr}, {k.is_start, k.start_scan}};
+    NA_CHK(launch_block_scan(sums, k.want_sn ? 3 : 2, k.n, k.scan_scr, st));
+    struct {
+        BlockStatus s;
+        JobStats js;
+    } h{};
+    NA_CHK(launch_block_status(a, 1, k.u_ptr + k.n, k.l_ptr + k.n, k.want_sn ? k.start_scan + k.n : nullptr, status,
+                               reinterpret_cast<JobStats*>(status + 1), st));
+    NA_CHK(hipMemcpyAsync(&h, status, sizeof(h), hipMemcpyDeviceToHost, st));
     NA_CHK(hipStreamSynchronize(st));
     const double tt1 = now_ms();
-    if (ctl[kBmAbort] == (uint32_t)kBmOverflow) return kNotHere;
-    if (ctl[kBmAbort] != 0u) return GSOFA_EDEVICE;
-    if (hs.err & kErrDuplicate) return GSOFA_EINVAL;
+    if (h.s.ctl[kBmAbort] == (uint32_t)kBmOverflow) return kNotHere;
+    if (h.s.ctl[kBmAbort] != 0u) return GSOFA_EDEVICE;
+    if (h.js.err & kErrDuplicate) return GSOFA_EINVAL;
 
     // what fits is what the traversal's pool and its row-wise L would
-    const int64_t nnz_u = tot[0], nnz_l = tot[1];
+    const int64_t nnz_u = h.s.nnz_u, nnz_l = h.s.nnz_l;
     c->scratch_bytes = (int64_t)k.pool_at + 4 * (nnz_u + nnz_l);
     if (nnz_u + nnz_l > k.pool_cap) return GSOFA_ECAPACITY;
     c->nnz_u = nnz_u;
     c->nnz_l = nnz_l;
-    c->fills = nnz_u + nnz_l - (k.nnz + k.n - (int64_t)hs.diag);
+    c->fills = nnz_u + nnz_l - (k.nnz + k.n - (int64_t)h.js.diag);
     if (nnz_u > k.u_cap || nnz_l > k.l_cap) return GSOFA_ECAPACITY;
     if (!k.l_csr) {
         Span slots{base, k.slot_cap, 0}, rest{base, 4 * (size_t)k.pool_cap, 4 * (size_t)(nnz_u + nnz_l)};
@@ -229,19 +230,23 @@ int blocks_noalloc(const Call& k, uint8_t* base, size_t cap, double t0, gsofa_co
     NA_CHK(launch_block_emit(a, bc, k.u_ptr, k.u_idx, k.l_ptr, k.l_idx, k.l_csr, st));
     const double ts0 = now_ms();
     if (k.want_sn) {
-        const RowSpace rs{k.n, nullptr, nullptr};
-        NA_CHK(launch_block_supernodes(a, k.max_super, k.is_start, st));
-        NA_CHK(launch_scan_counts(k.is_start, nullptr, k.n, k.start_scan, k.scan_scr, st));
-        NA_CHK(launch_supernode_assemble(rs, 1, k.is_start, k.start_scan, k.xsup, k.supno, st));
-        NA_CHK(launch_supernode_terminals(1, k.jrb, k.jn, k.start_scan, k.xsup, st));
+        BlockFinish f{};
+        f.nrows = k.n;
+        f.nj = 1;
+        f.u_ptr = k.u_ptr;
+        f.l_ptr = k.l_ptr;
+        f.is_start = k.is_start;
+        f.start_scan = k.start_scan;
+        f.xsup = k.xsup;
+        f.supno = k.supno;
+        NA_CHK(launch_block_finish(a, f, st));
     }
-    int64_t h_ns = 0;
+    JobStats hs{};
     NA_CHK(hipMemcpyAsync(&hs, k.js, sizeof(JobStats), hipMemcpyDeviceToHost, st));
-    if (k.want_sn) NA_CHK(hipMemcpyAsync(&h_ns, k.start_scan + k.n, 8, hipMemcpyDeviceToHost, st));
     NA_CHK(hipStreamSynchronize(st));
     const double t1 = now_ms();
 
-    c->nsuper = (int32_t)h_ns;
+    c->nsuper = (int32_t)h.s.nsuper;
     c->stats.concurrent_sources = (int32_t)std::min<int64_t>(64 * ns, k.n);
     c->stats.iterations = hs.iterations;
     c->stats.windows = (uint64_t)nb;
@@ -393,8 +398,6 @@ int run_noalloc(int32_t n, const int32_t* row_ptr, const int32_t* col_idx, const
         k.l_csr = l_csr;
         k.job = d_job;
         k.js = d_js;
-        k.jrb = d_jrb;
-        k.jn = d_jn;
         k.scan_scr = scan_scr;
         k.row_ucnt = row_cnt;
         k.row_lcnt = row_lcnt;

@@ -193,3 +193,42 @@ def test_block_supernodes_match_traversal(g, name):
             t = g.symbolic(n, rp, ci, flags=flags | g.MAP_WAVE32, max_supernode=limit)
             assert (r.stats["mapping"], t.stats["mapping"]) == (7, 0)
             assert np.array_equal(r.xsup, t.xsup) and np.array_equal(r.supno, t.supno), limit
+
+
+@pytest.mark.parametrize("n", [8191, 8192, 8193, 3 * 8192 + 5])
+def test_block_sums_at_tile_edges(g, n):
+    """Row counts, columns and supernode starts are summed in tiles of 8,192; a
+    batch also by its blocks and between its matrices."""
+    rp, ci = np.arange(n + 1, dtype=np.int32), np.arange(n, dtype=np.int32)
+    small = _band(129, 9, 11, n)
+    r = g.symbolic(n, rp, ci)
+    assert r.stats["mapping"] == 7 and r.nsuper == n
+    assert np.array_equal(r.u_ptr, np.arange(n + 1)) and np.array_equal(r.u_idx, ci) and r.nnz_l == 0
+    assert np.array_equal(r.supno, ci) and np.array_equal(r.xsup, np.arange(n + 1))
+    ref = oracle.symbolic(*small)
+    for a, b in zip(g.batch([small, (n, rp, ci), small]), (ref, r, ref)):
+        assert np.array_equal(a.u_ptr, b.u_ptr) and np.array_equal(a.l_ptr, b.l_ptr)
+        assert np.array_equal(a.u_idx, b.u_idx) and np.array_equal(a.l_idx, b.l_idx)
+        assert np.array_equal(a.xsup, b.xsup) and np.array_equal(a.supno, b.supno)
+
+
+def test_malformed_device_input_is_told_apart(g):
+    """A negative entry count is found without looking at anything else, and is
+    then the only matrix of the batch that is refused."""
+    import torch
+    n, rp, ci = _stencil(9, (20, 20), True, 8)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    good = (n, dev(rp), dev(ci))
+    neg = rp.copy()
+    neg[n] = -1
+    off = ci.copy()
+    off[3] = n
+    for bad in ((n, dev(neg), dev(ci)), (n, dev(rp), dev(off))):
+        with pytest.raises(g.GsofaError) as e:
+            g.symbolic(*bad)
+        assert e.value.code == g.EINVAL
+        r = g.batch([good, bad, good], raise_on_error=False)
+        assert r[1] is None
+    both = g.batch([(n, dev(rp), dev(off)), (n, dev(neg), dev(ci))], raise_on_error=False)
+    assert both[1] is None
+    assert g.symbolic(*good).fills == g.symbolic(n, rp, ci).fills
