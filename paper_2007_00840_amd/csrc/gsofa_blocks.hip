@@ -11,8 +11,8 @@
 // once, and finally its own rows among each other. The per-source traversal
 // (k_traverse) walks every vertex reachable from every source instead: on the
 // 64^3 27-point stencil 51 G edge visits, where the block path makes 1.8e5 block
-// merges of 2.5e6 64-column tiles: 4.6 ms instead of 221 (1000^2 9-point stencil:
-// 3.1 instead of 218 ms; 512 batch members: 2.5 instead of 90 ms).
+// merges of 2.5e6 64-column tiles: 4.0 ms instead of 221 (1000^2 9-point stencil:
+// 3.0 instead of 218 ms; 512 batch members: 2.3 instead of 90 ms).
 //
 // What bounds it is the chain of blocks that wait for one another, not
 // throughput, and four things keep that chain short:
@@ -61,6 +61,11 @@ constexpr int kRangeTiles = 1024;     // column tiles (64 columns) listed at a t
 constexpr uint32_t kSpinLimit = 1u << 22;
 constexpr int32_t kNoMatch = 0x7FFFFFFF;
 constexpr int kHeadTiles = 20;        // tile ids in a list's header
+// Tiles of a shared merge that a wavefront takes, and of a list that it writes, at
+// a time: their round trips overlap (64^3 27-point: 4.14 ms with four, 4.00 with six
+// or eight; 1000^2 9-point 3.03 and 2.96; 512 batch members 2.35, with six 2.47)
+constexpr int kShare = 8;
+constexpr int kWrite = 8;
 
 // word of the header that holds tiles i and i + 1 (i even), and the other way
 __device__ __forceinline__ int head_word(int i) { return i < 6 ? 4 + (i >> 1) : 8 + ((i - 6) >> 1); }
@@ -501,12 +506,12 @@ __global__ __launch_bounds__(64 * W, 4) void k_bm_factor(BlockArgs a) {
                 lds_barrier();
                 if (s_stop) return false;
                 const int nt = s_ntile;
-                // four tiles of a wavefront at once: their round trips overlap
-                for (int i0 = wv; i0 < nt; i0 += 4 * W) {
-                    int32_t t[4];
-                    u64 m[4], m0[4];
+                // several tiles of a wavefront at once: their round trips overlap
+                for (int i0 = wv; i0 < nt; i0 += kWrite * W) {
+                    int32_t t[kWrite];
+                    u64 m[kWrite], m0[kWrite];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
+                    for (int j = 0; j < kWrite; ++j) {
                         m[j] = 0;
                         if (i0 + j * W < nt) {
                             t[j] = R * kRangeTiles + s_tile[i0 + j * W];
@@ -515,7 +520,7 @@ __global__ __launch_bounds__(64 * W, 4) void k_bm_factor(BlockArgs a) {
                         m0[j] = m[j];
                     }
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
+                    for (int j = 0; j < kWrite; ++j) {
                         if (i0 + j * W >= nt) break;
                         for (u64 q = m[j] & S; q;) {
                             const int k = __builtin_ctzll(q);
@@ -611,13 +616,13 @@ __global__ __launch_bounds__(64 * W, 4) void k_bm_factor(BlockArgs a) {
         if (!stop && s_ext0 != 0ull) {
             const int npw = (g + 63) >> 6;
             uint32_t spins = 0;
-            // ORs up to four tiles t (masks m) of a published list into this block's
+            // ORs up to kT tiles t (masks m) of a published list into this block's
             // masks: for every column the masks y of the rows in `use` that hold it
-            auto merge_tiles = [&](int cnt, const int32_t (&t)[4], const u64 (&m)[4], const u64* y, u64 use, u64 open,
-                                   int64_t hb) {
-                u64 z[4], o[4];
+            auto merge_tiles = [&](int cnt, const auto& t, const auto& m, const u64* y, u64 use, u64 open, int64_t hb) {
+                constexpr int kT = sizeof(m) / sizeof(m[0]);
+                u64 z[kT], o[kT];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int i = 0; i < kT; ++i) {
                     z[i] = o[i] = 0;
                     if (i < cnt) {
                         for (u64 w = m[i] & use; w; w &= w - 1ull) z[i] |= y[__builtin_ctzll(w)];
@@ -625,7 +630,7 @@ __global__ __launch_bounds__(64 * W, 4) void k_bm_factor(BlockArgs a) {
                     }
                 }
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int i = 0; i < kT; ++i) {
                     if (i >= cnt) break;
                     if (t[i] == g) {
                         // U(k, v) with v a row of this block: a match where L(v, k) is
@@ -724,12 +729,12 @@ __global__ __launch_bounds__(64 * W, 4) void k_bm_factor(BlockArgs a) {
                     const int c = min(step, nt - i);
                     const int64_t q = (int64_t)s_toff[k] + i;
                     const int32_t tl = ln < c ? ld_dev(&a.tids[q + ln]) : 0;
-                    u64 m[4];
-                    int32_t t[4];
+                    u64 m[kShare];
+                    int32_t t[kShare];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) m[j] = j < c ? ld_dev(&a.masks[64 * (q + j) + ln]) : 0ull;
+                    for (int j = 0; j < kShare; ++j) m[j] = j < c ? ld_dev(&a.masks[64 * (q + j) + ln]) : 0ull;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) t[j] = __builtin_amdgcn_readlane(tl, j);
+                    for (int j = 0; j < kShare; ++j) t[j] = __builtin_amdgcn_readlane(tl, j);
                     merge_tiles(c, t, m, s_ty[k], s_tuse[k], s_topen[k], b0 + s_tblk[k]);
                     wave_sync();
                     if (ln == 0 && atomicAdd(&s_tdone[k], c) + c == nt) {
@@ -906,7 +911,7 @@ __global__ __launch_bounds__(64 * W, 4) void k_bm_factor(BlockArgs a) {
                         s_topen[task] = open;
                         s_tblk[task] = h;
                         s_tdone[task] = 0;
-                        s_tstep[task] = min(4, (cnt - 4 + W - 1) / W);
+                        s_tstep[task] = min(kShare, (cnt - 4 + W - 1) / W);
                     }
                     wave_sync();
                     if (ln == 0) atomicExch(&s_tnext[task], ((u64)cnt << 32) | 4ull);
