@@ -797,18 +797,36 @@ int check_csr_host(int32_t n, const int32_t* rp, const int32_t* ci, std::vector<
     if (n < 0 || n > GSOFA_MAX_N) return GSOFA_EINVAL;
     if (n == 0) return GSOFA_OK;
     if (!rp || rp[0] != 0) return GSOFA_EINVAL;
-    for (int32_t i = 0; i < n; ++i)
-        if (rp[i + 1] < rp[i]) return GSOFA_EINVAL;
-    if (rp[n] > 0 && !ci) return GSOFA_EINVAL;
+    bool falls = false;
+    for (int32_t i = 0; i < n; ++i) falls |= rp[i + 1] < rp[i];
+    if (falls) return GSOFA_EINVAL;
+    const int32_t nnz = rp[n];
+    if (nnz == 0) return GSOFA_OK;
+    if (!ci) return GSOFA_EINVAL;
+    // Rows whose columns ascend repeat none, and most inputs' do: count the places
+    // where a column is not above the one before it, and take those between two
+    // rows off again. Both loops run several entries at a time, without a branch
+    // (2.3 M entries of the 48^3 27-point stencil: 1.6 ms with a stamp per entry,
+    // 0.35 so).
+    uint32_t outside = (uint32_t)ci[0] >= (uint32_t)n;
+    int32_t back = 0;
+    for (int32_t e = 1; e < nnz; ++e) {
+        outside |= (uint32_t)ci[e] >= (uint32_t)n;
+        back += ci[e] <= ci[e - 1];
+    }
+    if (outside) return GSOFA_EINVAL;
+    for (int32_t i = 1; i < n; ++i) {
+        const int32_t a = rp[i];
+        if (a > 0 && rp[i + 1] > a) back -= ci[a] <= ci[a - 1];
+    }
+    if (back == 0) return GSOFA_OK;
     if ((int64_t)stamp.size() < n) stamp.assign(n, 0u);
     else std::fill(stamp.begin(), stamp.begin() + n, 0u);
     for (int32_t i = 0; i < n; ++i) {
         const uint32_t tag = (uint32_t)i + 1u;
         for (int32_t e = rp[i]; e < rp[i + 1]; ++e) {
-            const int32_t c = ci[e];
-            if (c < 0 || c >= n) return GSOFA_EINVAL;
-            if (stamp[c] == tag) return GSOFA_EINVAL;  // repeated column
-            stamp[c] = tag;
+            if (stamp[ci[e]] == tag) return GSOFA_EINVAL;  // repeated column
+            stamp[ci[e]] = tag;
         }
     }
     return GSOFA_OK;
