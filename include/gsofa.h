@@ -178,7 +178,9 @@ typedef struct {
     double t_traverse_ms;       /* fill-detection kernel time: the per-source seed (the
                                    source row's own entries) runs inside the traversal
                                    kernel, so seed and traversal are timed together       */
-    double t_emit_ms;           /* pointer scans and per-row sort into CSR                */
+    double t_emit_ms;           /* pointer scans and per-row sort into CSR (block path:
+                                   rows, columns and reach counts; the scans and the
+                                   supernodes' starts are in t_traverse_ms)               */
     double t_supernode_ms;
     double t_total_ms;          /* whole call, host copies included                       */
     int32_t window;             /* threshold-window span used (0: block path)             */
