@@ -1602,12 +1602,25 @@ __global__ __launch_bounds__(64) void k_bm_reach_big(BlockArgs a, BlockCols cl) 
             const int32_t match = a.kmatch[64 * hb + ln];
             const int64_t e0 = cl.ptr[hb];
             const int cnt = cl.reach[hb * kReachWords];
-            for (int i = 0; i < cnt; ++i) {
-                const int32_t g = cl.blk[e0 + i];
-                const u64 m = z != 0ull ? upto(a.masks[64 * (int64_t)cl.tile[e0 + i] + ln], g, match) : 0ull;
-                if (__ballot(m != 0ull) == 0ull) continue;
-                for (u64 t = m; t; t &= t - 1ull) or_wg(&Z[64 * (int64_t)g + __builtin_ctzll(t)], z);
-                if (ln == 0) s_bits[g >> 6] |= 1ull << (g & 63);
+            int32_t gl = 0, tl = 0;
+            for (int i = 0; i < cnt; i += 4) {
+                if ((i & 63) == 0) {
+                    gl = i + ln < cnt ? cl.blk[e0 + i + ln] : 0;
+                    tl = i + ln < cnt ? cl.tile[e0 + i + ln] : 0;
+                }
+                u64 m[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    m[j] = i + j < cnt ? a.masks[64 * (int64_t)__builtin_amdgcn_readlane(tl, (i + j) & 63) + ln] : 0ull;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (i + j >= cnt) break;
+                    const int32_t g = __builtin_amdgcn_readlane(gl, (i + j) & 63);
+                    const u64 x = z != 0ull ? upto(m[j], g, match) : 0ull;
+                    if (__ballot(x != 0ull) == 0ull) continue;
+                    for (u64 t = x; t; t &= t - 1ull) or_wg(&Z[64 * (int64_t)g + __builtin_ctzll(t)], z);
+                    if (ln == 0) s_bits[g >> 6] |= 1ull << (g & 63);
+                }
             }
             wave_sync_all();
         }
@@ -1900,8 +1913,9 @@ hipError_t launch_block_emit(const BlockArgs& a, const BlockCols& c, const int64
     const auto kernel = a.blk_job ? (l_csr ? k_bm_emit<true, 12> : k_bm_emit<false, 12>)
                                   : (l_csr ? k_bm_emit<true, 8> : k_bm_emit<false, 8>);
     hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, a, c, u_ptr, u_idx, l_ptr, l_idx);
-    hipLaunchKernelGGL(k_bm_reach_big, dim3((unsigned)std::min(a.nslots, 256)), dim3(64), (size_t)a.bit_words * 8, st,
-                       a, c);
+    // (as many as there are slots: 10^6 rows coupled two by two at random, where every
+    // block comes here, took 24 ms with 256 workgroups and a tile at a time, now 4)
+    hipLaunchKernelGGL(k_bm_reach_big, dim3((unsigned)a.nslots), dim3(64), (size_t)a.bit_words * 8, st, a, c);
     return hipGetLastError();
 }
 

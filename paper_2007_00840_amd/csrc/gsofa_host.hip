@@ -1963,10 +1963,10 @@ struct Engine {
 
     // Wavefronts per block. Eight shorten a block's own work, four put more blocks
     // in flight, which counts for one matrix of many blocks, whose separators wait
-    // for chains far behind them (1000^2 9-point, 15,625 blocks: 3.1 ms with four,
-    // 3.6 with eight, 4.9 with sixteen; 64^3 27-point, 4,096 blocks: 5.4, 4.6 and
-    // 4.7; 20,000 blocks of 512 batch members: 2.7, 2.5 and 3.3). Batches with a
-    // member of more than 2^21 rows take four too: the bitmaps and eight
+    // for chains far behind them (1000^2 9-point, 15,625 blocks: 2.9 ms with four, 3.4
+    // with eight; 64^3 27-point, 4,096 blocks: 4.6 and 4.0; 20,000 blocks of 512 batch
+    // members: 2.7 and 2.3; sixteen never beat the better of the two).
+    // Batches with a member of more than 2^21 rows take four too: the bitmaps and eight
     // wavefronts' tables together would pass 64 KiB of LDS.
     static int32_t block_waves(int64_t nblocks, int32_t nj, int32_t words) {
         return (nj == 1 && nblocks > 8192) || words > 512 ? 4 : 8;

@@ -80,6 +80,7 @@ CASES = {
     "last_row_dense": lambda: _last_row_dense(70000),
     "first_column_dense": lambda: _first_column_dense(70000),
     "pool_regrowth": lambda: _dense_rows(24576, 64),
+    "pairs": lambda: _pairs(20000, 9),
 }
 
 
