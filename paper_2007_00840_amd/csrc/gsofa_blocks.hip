@@ -1179,7 +1179,7 @@ __global__ __launch_bounds__(64) void k_bm_lists(BlockArgs a, BlockCols c, int32
     // k tiles of a list (lane i: row block b, tile q): their entries per column,
     // and which of them the reach counts need
     auto walk = [&](int k, int32_t b, int32_t q) {
-        u64 keep = 0;
+        u64 keep = 0, occ = 0;
         for (int i0 = 0; i0 < k; i0 += 4) {
             u64 m[4];
 #pragma unroll
@@ -1189,13 +1189,16 @@ __global__ __launch_bounds__(64) void k_bm_lists(BlockArgs a, BlockCols c, int32
             for (int j = 0; j < 4; ++j) {
                 sum += __popcll(m[j]);
                 const int32_t g = __builtin_amdgcn_readlane(b, (i0 + j) & 63);
-                if (__ballot(upto(m[j], g, match) != 0ull) != 0ull) keep |= 1ull << ((i0 + j) & 63);
+                const u64 cols = __ballot(upto(m[j], g, match) != 0ull);
+                if (cols != 0ull) keep |= 1ull << ((i0 + j) & 63);
+                if (ln == ((i0 + j) & 63)) occ = cols;
             }
         }
         if ((keep >> ln) & 1ull) {
             const int64_t d = e0 + kept + (int)below_count(keep);
             c.blk[d] = b;
             c.tile[d] = q;
+            c.occ[d] = occ;
         }
         for (u64 w = keep; w && kept < kReachInline; w &= w - 1ull) {
             const int i = __builtin_ctzll(w);
@@ -1523,9 +1526,14 @@ __device__ __forceinline__ void reach_of(const BlockArgs& a, const BlockCols& cl
             if (j < cnt && !over) push(__builtin_amdgcn_readlane(w0, 1 + j), m[j]);
         if (cnt > 4) {
             const int64_t e0 = cl.ptr[hb];
-            for (int i = 4; i < cnt && !over; ++i) {
-                const int32_t g = cl.blk[e0 + i];
-                push(rfl(g), a.masks[64 * (int64_t)cl.tile[e0 + i] + ln]);
+            const u64 used = __ballot(z != 0ull);
+            for (int i0 = 4; i0 < cnt && !over; i0 += 64) {
+                const bool in = i0 + ln < cnt;
+                const int32_t gl = in ? cl.blk[e0 + i0 + ln] : 0, tl = in ? cl.tile[e0 + i0 + ln] : 0;
+                for (u64 w = __ballot(in && (cl.occ[e0 + i0 + ln] & used) != 0ull); w && !over; w &= w - 1ull) {
+                    const int i = __builtin_ctzll(w);
+                    push(__builtin_amdgcn_readlane(gl, i), a.masks[64 * (int64_t)__builtin_amdgcn_readlane(tl, i) + ln]);
+                }
             }
         }
         if (over) {
@@ -1602,24 +1610,32 @@ __global__ __launch_bounds__(64) void k_bm_reach_big(BlockArgs a, BlockCols cl) 
             const int32_t match = a.kmatch[64 * hb + ln];
             const int64_t e0 = cl.ptr[hb];
             const int cnt = cl.reach[hb * kReachWords];
-            int32_t gl = 0, tl = 0;
-            for (int i = 0; i < cnt; i += 4) {
-                if ((i & 63) == 0) {
-                    gl = i + ln < cnt ? cl.blk[e0 + i + ln] : 0;
-                    tl = i + ln < cnt ? cl.tile[e0 + i + ln] : 0;
-                }
-                u64 m[4];
+            const u64 used = __ballot(z != 0ull);
+            for (int i0 = 0; i0 < cnt; i0 += 64) {
+                const bool in = i0 + ln < cnt;
+                const int32_t gl = in ? cl.blk[e0 + i0 + ln] : 0, tl = in ? cl.tile[e0 + i0 + ln] : 0;
+                // only the tiles with an entry in a column in use, four at a time
+                for (u64 w = __ballot(in && (cl.occ[e0 + i0 + ln] & used) != 0ull); w;) {
+                    u64 m[4];
+                    int32_t g[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    m[j] = i + j < cnt ? a.masks[64 * (int64_t)__builtin_amdgcn_readlane(tl, (i + j) & 63) + ln] : 0ull;
+                    for (int j = 0; j < 4; ++j) {
+                        m[j] = 0;
+                        g[j] = 0;
+                        if (w) {
+                            const int i = __builtin_ctzll(w);
+                            w &= w - 1ull;
+                            g[j] = __builtin_amdgcn_readlane(gl, i);
+                            m[j] = a.masks[64 * (int64_t)__builtin_amdgcn_readlane(tl, i) + ln];
+                        }
+                    }
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (i + j >= cnt) break;
-                    const int32_t g = __builtin_amdgcn_readlane(gl, (i + j) & 63);
-                    const u64 x = z != 0ull ? upto(m[j], g, match) : 0ull;
-                    if (__ballot(x != 0ull) == 0ull) continue;
-                    for (u64 t = x; t; t &= t - 1ull) or_wg(&Z[64 * (int64_t)g + __builtin_ctzll(t)], z);
-                    if (ln == 0) s_bits[g >> 6] |= 1ull << (g & 63);
+                    for (int j = 0; j < 4; ++j) {
+                        const u64 x = z != 0ull ? upto(m[j], g[j], match) : 0ull;
+                        if (__ballot(x != 0ull) == 0ull) continue;
+                        for (u64 t = x; t; t &= t - 1ull) or_wg(&Z[64 * (int64_t)g[j] + __builtin_ctzll(t)], z);
+                        if (ln == 0) s_bits[g[j] >> 6] |= 1ull << (g[j] & 63);
+                    }
                 }
             }
             wave_sync_all();

@@ -2010,7 +2010,7 @@ struct Engine {
         int64_t cap = (int64_t)(ratio * 1.15 * (double)nblocks) + 64 * ns + 64;
         constexpr int64_t kPerBlock = 8 * kBmHeadWords + 1024 + 256 + 512 + 512 + sizeof(BlockRec) + 4 * kReachWords + 16;
         auto need = [&](int64_t tiles) {
-            return fixed_bytes(nrows, total_nnz) + nrows * 64 + nblocks * kPerBlock + ns * stride * 8 + tiles * 540 + 24 * total_nnz;
+            return fixed_bytes(nrows, total_nnz) + nrows * 64 + nblocks * kPerBlock + ns * stride * 8 + tiles * 548 + 24 * total_nnz;
         };
         auto fits = [&](int64_t tiles) {
             if (plan.budget > 0) return need(tiles) <= plan.budget;
@@ -2110,7 +2110,7 @@ struct Engine {
         if (yh && yh->before_traverse) yh->before_traverse();
         chk(hipEventRecord(ev[0], st));
         int32_t launches = 0;
-        DBuf tiles, tabs;  // tabs: tile ids, list places, lists unsorted and sorted
+        DBuf tiles, tabs;  // tabs: columns in use, tile ids, list places, lists unsorted and sorted
         BlockCols bc{};
         bc.ptr = list_ptr.as<int64_t>();
         bc.big = big.as<int32_t>();
@@ -2124,9 +2124,10 @@ struct Engine {
                 return false;
             }
             tiles = DBuf(512 * (size_t)cap);
-            tabs = DBuf(24 * (size_t)cap);
+            tabs = DBuf(32 * (size_t)cap);
             ba.masks = tiles.as<unsigned long long>();
-            ba.tids = tabs.as<int32_t>();
+            bc.occ = tabs.as<unsigned long long>();
+            ba.tids = reinterpret_cast<int32_t*>(bc.occ + cap);
             ba.slot = ba.tids + cap;
             bc.blk = ba.tids + 2 * cap;
             bc.tile = ba.tids + 3 * cap;
@@ -2240,7 +2241,7 @@ struct Engine {
         cs.concurrent_sources = (int32_t)std::min<int64_t>(64 * ns, std::max<int64_t>(nrows, 1));
         cs.mapping = kMapBlocks;
         cs.launches = launches;
-        cs.peak_device_bytes = (uint64_t)(ns * stride * 8 + cap * 536 + nblocks * kPerBlock + nrows * 64 +
+        cs.peak_device_bytes = (uint64_t)(ns * stride * 8 + cap * 544 + nblocks * kPerBlock + nrows * 64 +
                                           4 * (nnz_u + nnz_l));
         f.u_ptr = std::move(u_ptr);
         f.l_ptr = std::move(l_ptr);

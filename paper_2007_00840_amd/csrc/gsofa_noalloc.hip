@@ -170,11 +170,12 @@ int blocks_noalloc(const Call& k, uint8_t* base, size_t cap, double t0, gsofa_co
     if (ns < 1) return kNotHere;
     a.nslots = (int32_t)ns;
     a.x = sp.take<unsigned long long>(ns * stride);
-    const int64_t tiles = ((int64_t)(cap - sp.off) - 8 * 256) / (512 + 24);
+    const int64_t tiles = ((int64_t)(cap - sp.off) - 9 * 256) / (512 + 32);
     if (tiles < 2 * nb) return kNotHere;
     a.masks = sp.take<unsigned long long>(64 * tiles);
     a.tids = sp.take<int32_t>(tiles);
     a.slot = sp.take<int32_t>(tiles);
+    bc.occ = sp.take<unsigned long long>(tiles);
     bc.blk = sp.take<int32_t>(tiles);
     bc.tile = sp.take<int32_t>(tiles);
     bc.blk2 = sp.take<int32_t>(tiles);
