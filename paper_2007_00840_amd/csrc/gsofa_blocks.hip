@@ -1568,17 +1568,30 @@ __global__ __launch_bounds__(kThreads) void k_bm_emit(BlockArgs a, BlockCols c, 
     else emit_cols(a, c, b, l_ptr, l_idx);
 }
 
-// The same with the waiting blocks' masks in a slot of X (all zero between
-// uses) and a bitmap of the waiting blocks in LDS.
-__global__ __launch_bounds__(64) void k_bm_reach_big(BlockArgs a, BlockCols cl) {
+// The same with the blocks' masks in a slot of X (all zero between uses) and bitmaps
+// of the blocks waiting and met in LDS. A block of columns may reach most of the
+// matrix here, so sixteen wavefronts share it: they take waiting blocks, lowest first,
+// and whoever adds to a block's masks sets it waiting (again). A wavefront counts
+// itself active from before it clears a block's bit until it has passed the block
+// on, so with nothing waiting and nobody active the masks are final, and are
+// weighed. (200,000 rows with an entry below the diagonal at random each, where
+// nothing can be pruned: 73 ms with a wavefront per block of columns, 10 so.)
+namespace {
+constexpr int kBigWaves = 16;
+}
+
+__global__ __launch_bounds__(64 * kBigWaves) void k_bm_reach_big(BlockArgs a, BlockCols cl) {
     extern __shared__ u64 s_bits[];
-    __shared__ __attribute__((aligned(16))) u64 s_xs[64];
-    __shared__ u64 s_tab[256];
+    __shared__ __attribute__((aligned(16))) u64 s_xs[kBigWaves][64];
+    __shared__ u64 s_tab[kBigWaves][256];
     __shared__ u64 s_planes[32];
+    __shared__ int s_np, s_active;
     if (ld_dev(&a.ctl[kBmAbort]) != 0u) return;
-    const int ln = lane();
+    const int ln = lane(), wv = rfl(threadIdx.x >> 6);
     u64* Z = a.x + (int64_t)blockIdx.x * a.x_stride;
     const int nw = a.bit_words;
+    u64* wait = s_bits;
+    u64* met = s_bits + nw;
     const int32_t total = *cl.nbig;
     for (int32_t q = blockIdx.x; q < total; q += gridDim.x) {
         const int32_t cb = cl.big[q];
@@ -1586,30 +1599,55 @@ __global__ __launch_bounds__(64) void k_bm_reach_big(BlockArgs a, BlockCols cl) 
         const Job* J = &a.jobs[jb];
         const int32_t b0 = (int32_t)J->item_base;
         const int32_t c = cb - b0;
-        for (int i = ln; i < nw; i += 64) s_bits[i] = 0ull;
-        wave_sync_all();
-        const int np = degree_planes(J, c, s_planes);
-        if (ln == 0) s_bits[c >> 6] = 1ull << (c & 63);
-        if (64 * (int64_t)c + ln < J->n) Z[64 * (int64_t)c + ln] = 1ull << ln;
-        wave_sync_all();
-        u64 sum = 0;
-        for (int w0 = c >> 6; w0 < nw;) {
-            const u64 word = s_bits[w0];
-            if (word == 0ull) {
-                ++w0;
+        for (int i = threadIdx.x; i < 2 * nw; i += 64 * kBigWaves) s_bits[i] = 0ull;
+        if (wv == 0) {
+            const int np = degree_planes(J, c, s_planes);
+            if (ln == 0) {
+                s_np = np;
+                s_active = 0;
+            }
+            if (64 * (int64_t)c + ln < J->n) or_wg(&Z[64 * (int64_t)c + ln], 1ull << ln);
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) wait[c >> 6] = met[c >> 6] = 1ull << (c & 63);
+        __syncthreads();
+        for (;;) {
+            int32_t h = -1;
+            for (int w0 = 0; w0 < nw && h < 0; w0 += 64) {
+                for (;;) {
+                    const u64 w = w0 + ln < nw ? ld_lds(&wait[w0 + ln]) : 0ull;
+                    const u64 nz = __ballot(w != 0ull);
+                    if (nz == 0ull) break;
+                    const int l = __builtin_ctzll(nz);
+                    const int b = __builtin_ctzll(readlane64(w, l));
+                    int got = 0;
+                    if (ln == 0) {
+                        atomicAdd(&s_active, 1);
+                        got = (int)((atomicAnd(&wait[w0 + l], ~(1ull << b)) >> b) & 1ull);
+                        if (!got) atomicSub(&s_active, 1);
+                    }
+                    if (rfl(got)) {
+                        h = (w0 + l) * 64 + b;
+                        break;
+                    }
+                }
+            }
+            if (h < 0) {
+                // (looked after the scan: a block set waiting before the last active
+                // wavefront left would have been seen by that wavefront itself)
+                if (rfl(ld_lds(&s_active)) == 0) break;
+                __builtin_amdgcn_s_sleep(2);
                 continue;
             }
-            const int32_t h = w0 * 64 + __builtin_ctzll(word);
-            wave_sync_all();
-            if (ln == 0) s_bits[w0] = word & (word - 1ull);
+            wave_sync();
             const int64_t hb = b0 + h;
-            u64 z = ld_wg(&Z[64 * (int64_t)h + ln]);
-            Z[64 * (int64_t)h + ln] = 0ull;
-            z |= lane_or(z, a.lcl[64 * hb + ln], s_xs, s_tab);
-            sum += weigh(h == c ? z & ~(1ull << ln) : z, s_planes, np, 0);
+            const u64 z0 = ld_wg(&Z[64 * (int64_t)h + ln]);
+            const u64 M = a.lcl[64 * hb + ln];
             const int32_t match = a.kmatch[64 * hb + ln];
             const int64_t e0 = cl.ptr[hb];
             const int cnt = cl.reach[hb * kReachWords];
+            const u64 z = z0 | lane_or(z0, M, s_xs[wv], s_tab[wv]);
+            if (z != z0) or_wg(&Z[64 * (int64_t)h + ln], z);
             const u64 used = __ballot(z != 0ull);
             for (int i0 = 0; i0 < cnt; i0 += 64) {
                 const bool in = i0 + ln < cnt;
@@ -1632,17 +1670,37 @@ __global__ __launch_bounds__(64) void k_bm_reach_big(BlockArgs a, BlockCols cl) 
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         const u64 x = z != 0ull ? upto(m[j], g[j], match) : 0ull;
-                        if (__ballot(x != 0ull) == 0ull) continue;
-                        for (u64 t = x; t; t &= t - 1ull) or_wg(&Z[64 * (int64_t)g[j] + __builtin_ctzll(t)], z);
-                        if (ln == 0) s_bits[g[j] >> 6] |= 1ull << (g[j] & 63);
+                        // lane r: what the columns in use bring to row r of block g
+                        u64 add = 0;
+                        for (u64 k = __ballot(x != 0ull); k; k &= k - 1ull) {
+                            const int i = __builtin_ctzll(k);
+                            const u64 zi = readlane64(z, i);
+                            add |= (readlane64(x, i) >> ln) & 1ull ? zi : 0ull;
+                        }
+                        bool more = false;
+                        if (add) more = (add & ~or_wg(&Z[64 * (int64_t)g[j] + ln], add)) != 0ull;
+                        if (__ballot(more) != 0ull && ln == 0) {
+                            atomicOr(&met[g[j] >> 6], 1ull << (g[j] & 63));
+                            atomicOr(&wait[g[j] >> 6], 1ull << (g[j] & 63));
+                        }
                     }
                 }
             }
-            wave_sync_all();
+            wave_sync();
+            if (ln == 0) atomicSub(&s_active, 1);
         }
+        __syncthreads();
+        u64 sum = 0;
+        for (int i = wv; i < nw; i += kBigWaves)
+            for (u64 w = met[i]; w; w &= w - 1ull) {
+                const int32_t h = i * 64 + __builtin_ctzll(w);
+                const u64 z = ld_wg(&Z[64 * (int64_t)h + ln]);
+                Z[64 * (int64_t)h + ln] = 0ull;
+                sum += weigh(h == c ? z & ~(1ull << ln) : z, s_planes, s_np, 0);
+            }
         sum = sum64(sum);
         if (ln == 0 && sum) atomicAdd(&a.jstats[jb].edges_alg, sum);
-        wave_sync_all();
+        __syncthreads();  // (also the stores to Z, before the next block's)
     }
 }
 
@@ -1931,7 +1989,8 @@ hipError_t launch_block_emit(const BlockArgs& a, const BlockCols& c, const int64
     hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, a, c, u_ptr, u_idx, l_ptr, l_idx);
     // (as many as there are slots: 10^6 rows coupled two by two at random, where every
     // block comes here, took 24 ms with 256 workgroups and a tile at a time, now 4)
-    hipLaunchKernelGGL(k_bm_reach_big, dim3((unsigned)a.nslots), dim3(64), (size_t)a.bit_words * 8, st, a, c);
+    hipLaunchKernelGGL(k_bm_reach_big, dim3((unsigned)a.nslots), dim3(64 * kBigWaves), (size_t)a.bit_words * 16, st, a,
+                       c);
     return hipGetLastError();
 }
 
