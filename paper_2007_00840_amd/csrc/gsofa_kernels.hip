@@ -32,6 +32,7 @@
 //           list)
 //   rowb  : the source row's structure, copied to the output pool at the end
 #include <atomic>
+#include "gsofa_checks.h"
 #include "gsofa_internal.h"
 #include "gsofa.h"
 
@@ -224,12 +225,13 @@ hipError_t launch_init_slots(uint8_t* slots, int32_t nslots, SlotLayout lay, hip
 // ------------------------------------------------------------ validation
 
 // Input checks for device-resident CSR: row_ptr[0] == 0, non-decreasing,
-// columns in [0, n). Rows whose bounds are broken are not read.
+// columns in [0, n). Rows whose bounds are broken or leave the entries
+// (row_ptr[n]) are not read.
 __global__ void k_validate(const Job* jobs, int32_t njobs, int64_t max_n, int32_t* bad, int32_t* last) {
     const int32_t j = blockIdx.y;
     if (j >= njobs) return;
     const Job J = jobs[j];
-    const int32_t nnz = last && J.n > 0 ? J.row_ptr[J.n] : 0;
+    const int32_t nnz = J.n > 0 ? J.row_ptr[J.n] : 0;
     if (last && blockIdx.x == 0 && threadIdx.x == 0) last[j] = nnz;
     // a negative count, or entries with no column array, is malformed (2): nothing
     // else of the matrix is read
@@ -240,7 +242,7 @@ __global__ void k_validate(const Job* jobs, int32_t njobs, int64_t max_n, int32_
     for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < J.n;
          r += (int64_t)gridDim.x * blockDim.x) {
         int32_t a = J.row_ptr[r], b = J.row_ptr[r + 1];
-        bool ok = (a >= 0) && (b >= a) && (r != 0 || a == 0);
+        bool ok = csr_row_readable(r, a, b, nnz);
         if (ok) {
             for (int32_t e = a; e < b; ++e) {
                 int32_t c = J.col_idx[e];

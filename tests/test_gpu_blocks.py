@@ -233,3 +233,27 @@ def test_malformed_device_input_is_told_apart(g):
     both = g.batch([(n, dev(rp), dev(off)), (n, dev(neg), dev(ci))], raise_on_error=False)
     assert both[1] is None
     assert g.symbolic(*good).fills == g.symbolic(n, rp, ci).fills
+
+
+def test_row_pointers_beyond_the_entries_are_refused(g):
+    """A row that ascends on its own but ends beyond row_ptr[n]: refused without a
+    read of the columns there (the bound itself is tested on the host), by every
+    entry point that takes device arrays."""
+    import torch
+    n, rp, ci = _stencil(9, (20, 20), True, 8)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    for at in (1, n // 2, n - 1):
+        far = rp.copy()
+        far[at] = 1 << 30
+        bad = (n, dev(far), dev(ci))
+        with pytest.raises(g.GsofaError) as e:
+            g.symbolic(*bad)
+        assert e.value.code == g.EINVAL
+        assert g.batch([bad], raise_on_error=False) == [None]
+        out = {k: torch.zeros(m, dtype=t, device="cuda")
+               for k, m, t in (("u_ptr", n + 1, torch.int64), ("l_ptr", n + 1, torch.int64),
+                               ("u_idx", 4, torch.int32), ("l_idx", 4, torch.int32),
+                               ("xsup", n + 1, torch.int32), ("supno", n, torch.int32))}
+        with pytest.raises(g.GsofaError) as e:
+            g.symbolic_noalloc(*bad, **out)
+        assert e.value.code == g.EINVAL
