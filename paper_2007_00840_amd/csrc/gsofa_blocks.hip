@@ -453,8 +453,8 @@ __global__ __launch_bounds__(64 * W, 4) void k_bm_factor(BlockArgs a) {
             // Header of a published list, one word per lane: the rows it covers, the
             // rows whose entries beyond the block others need, where the tiles
             // are, how many, and the ids of the first kHeadTiles (n of the list's
-            // first range). Words 7 and 15 stay 0 until everything is stored: each
-            // 64-byte half of the line carries its own state.
+            // first range). Words 7 and 15 stay 0 until everything is stored (one per
+            // 64-byte half of the line, so that a reader's two copies seldom differ).
             auto header = [&](int n, int t0) {
                 wave_sync();
                 n = min(n, kHeadTiles);
@@ -835,15 +835,26 @@ __global__ __launch_bounds__(64 * W, 4) void k_bm_factor(BlockArgs a) {
                     }
                     if (dead || back) break;
                     asm volatile("" ::: "memory");
+                    // Nothing orders the words of one load: that it saw the state
+                    // words says nothing about the rest. So the header is read again
+                    // behind the state, and that copy counts. What the first one says
+                    // about the tiles (a word is 0 or final) is good enough to load the
+                    // first masks with the same round trip; where the copies differ
+                    // they are loaded again.
+                    const u64 seen = w;
+                    w = ln < kBmHeadWords ? ld_dev(&a.head[hb * kBmHeadWords + ln]) : 0ull;
                     const u64 T = ld_dev(&a.tcl[hb * 128 + part * 64 + ln]);
                     const u64 x = ld_wg(&X[64 * (int64_t)h + ln]);
                     match = ld_dev(&a.kmatch[64 * hb + ln]);
-                    // the first tiles' masks with the same round trip
-                    const int64_t q = (int64_t)readlane64(w, 16 * part + 2);
-                    const int cnt = (int)lo32(readlane64(w, 16 * part + 3));
+                    auto first_tiles = [&](u64 head) {
+                        const int64_t q = (int64_t)readlane64(head, 16 * part + 2);
+                        const int cnt = (int)lo32(readlane64(head, 16 * part + 3));
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (i < cnt) m[i] = ld_dev(&a.masks[64 * (q + i) + ln]);
+                        for (int i = 0; i < 4; ++i)
+                            if (i < cnt) m[i] = ld_dev(&a.masks[64 * (q + i) + ln]);
+                    };
+                    first_tiles(seen);
+                    if (__ballot(w != seen) != 0ull) first_tiles(w);
                     y = x | lane_or(x, T, xs, tab);
                     if (part == 0 && (__ballot(y != 0ull) & ~readlane64(w, 0)) != 0ull) {
                         both = true;  // rows of the second publication are needed
