@@ -400,12 +400,14 @@ __global__ __launch_bounds__(64 * W, 4) void k_bm_factor(BlockArgs a) {
         u64 ext = 0;
         bool dup = false;
         int ndiag = 0;
-        for (int32_t e = s_rp[0] + tid; e < s_rp[nr]; e += 64 * W) {
+        // (unsigned: a step beyond up to 2^31 - 1 entries still compares right)
+        const uint32_t e1 = (uint32_t)s_rp[nr];
+        for (uint32_t e = (uint32_t)s_rp[0] + tid; e < e1; e += 64 * W) {
             const int32_t w = ci[e];
             int lo = 0, hi = nr - 1;
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
-                if (s_rp[mid] <= e) lo = mid;
+                if ((uint32_t)s_rp[mid] <= e) lo = mid;
                 else hi = mid - 1;
             }
             const u64 bit = 1ull << lo;

@@ -257,3 +257,56 @@ def test_row_pointers_beyond_the_entries_are_refused(g):
         with pytest.raises(g.GsofaError) as e:
             g.symbolic_noalloc(*bad, **out)
         assert e.value.code == g.EINVAL
+
+
+def test_largest_order_and_entry_count(g):
+    """2^22 rows, the most the block path takes, in dense blocks of 512 with
+    2^31 - 1 entries in all: the last step over a block's entries passes 2^31."""
+    import torch
+    n, nnz = 1 << 22, 2**31 - 1
+    ci = torch.empty(nnz, dtype=torch.int32, device="cuda")
+    step = 1 << 28
+    for a in range(0, nnz, step):
+        i = torch.arange(a, min(a + step, nnz), device="cuda")
+        ci[a:a + step] = ((i >> 18 << 9) + (i & 511)).to(torch.int32)
+    r = torch.arange(n + 1, device="cuda")
+    rp = (512 * r).clamp(max=nnz).to(torch.int32)
+    print(f"blocks n={n} nnz={nnz}", flush=True)
+    d = g.symbolic(n, rp, ci, flags=g.RESULT_ON_DEVICE)
+    assert d.stats["mapping"] == 7 and d.fills == 0
+    assert (d.nnz_u, d.nnz_l, d.nsuper) == (n // 512 * (512 * 513 // 2), n // 512 * (512 * 511 // 2), n // 128)
+    # every source reaches the rows of its dense block above it, 512 entries each
+    # (the last row, only a source, lacks one)
+    assert d.stats["edges_alg"] == n // 512 * 512 * (512 * 513 // 2) - 1
+    t = d.to_torch()
+    d.free()
+    m = torch.arange(512, device="cuda")
+    at = torch.cat([m.new_zeros(1), (512 - m).cumsum(0)])  # of a block's rows of U
+    assert torch.equal(t["u_ptr"], (r >> 9) * at[512] + at[r & 511])
+    at = torch.cat([m.new_zeros(1), (511 - m).cumsum(0)])  # of its columns of L
+    assert torch.equal(t["l_ptr"], (r >> 9) * at[512] + at[r & 511])
+    for k, first in (("u_idx", 0), ("l_idx", 1)):
+        one = torch.cat([m[c + first:] for c in range(512)])
+        x = t[k].view(n // 512, -1)
+        for a in range(0, n // 512, 1024):
+            want = one[None] + 512 * torch.arange(a, a + 1024, device="cuda")[:, None]
+            assert torch.equal(x[a:a + 1024], want.to(torch.int32)), (k, a)
+
+
+@pytest.mark.parametrize("nd", [1, 2])
+def test_batch_with_a_member_of_more_than_2_21_rows(g, nd):
+    """The bitmaps of 2^21 rows and more leave room for four wavefronts per block."""
+    n = (1 << 21) + 64 * nd + 5
+    big = (n, np.arange(n + 1, dtype=np.int32), np.arange(n, dtype=np.int32)[::-1].copy())
+    small = _band(129, 9, 11, nd)
+    ref = oracle.symbolic(*small)
+    a, b = g.batch([small, big])
+    assert (a.stats["mapping"], b.stats["mapping"]) == (7, 7)
+    assert np.array_equal(a.u_idx, ref.u_idx) and np.array_equal(a.l_idx, ref.l_idx)
+    # row i holds column n - 1 - i: an entry of U above the middle, of L below it,
+    # whose row n - 1 - i holds nothing beyond its own diagonal
+    i = np.arange(n)
+    assert np.array_equal(b.u_ptr, np.concatenate([[0], np.cumsum(np.where(i < n // 2, 2, 1))]))
+    assert np.array_equal(b.l_ptr, np.concatenate([[0], np.cumsum(np.where(i < n // 2, 1, 0))]))
+    assert np.array_equal(b.l_idx, n - 1 - i[:n // 2])
+    assert b.fills == 0
