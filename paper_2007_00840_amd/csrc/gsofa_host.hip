@@ -1973,11 +1973,28 @@ struct Engine {
     }
 
     // The block path (gsofa_blocks.hip). False: the call's memory budget does not
-    // hold it, the general path takes the call.
+    // hold it, or the memory that was to hold it could not be had; the general path
+    // takes the call.
     template <typename Upload>
     bool run_blocks(const std::vector<Job>& jobs, const std::vector<int64_t>& row_base, const std::vector<int64_t>& nnz,
                     std::vector<int>& jstat, int64_t nrows, int64_t total_nnz, int64_t N, const TuneKey& key,
                     Upload& h2d, double t0, int& rc) {
+        bool written = false;  // results follow
+        try {
+            if (blocks(jobs, row_base, nnz, jstat, nrows, total_nnz, N, key, h2d, t0, rc, written)) return true;
+        } catch (const Status& e) {
+            if (e.code != GSOFA_ENOMEM || written) throw;
+        }
+        // what the path held goes back before the traversal plans
+        chk(hipStreamSynchronize(st));
+        if (t_calloc) t_calloc->flush();
+        return false;
+    }
+
+    template <typename Upload>
+    bool blocks(const std::vector<Job>& jobs, const std::vector<int64_t>& row_base, const std::vector<int64_t>& nnz,
+                std::vector<int>& jstat, int64_t nrows, int64_t total_nnz, int64_t N, const TuneKey& key,
+                Upload& h2d, double t0, int& rc, bool& written) {
         const int32_t nj = (int32_t)mats.size();
         // blocks of all matrices side by side
         std::vector<Job> jt(nj);
@@ -2012,12 +2029,16 @@ struct Engine {
         auto need = [&](int64_t tiles) {
             return fixed_bytes(nrows, total_nnz) + nrows * 64 + nblocks * kPerBlock + ns * stride * 8 + tiles * 548 + 24 * total_nnz;
         };
-        auto fits = [&](int64_t tiles) {
-            if (plan.budget > 0) return need(tiles) <= plan.budget;
-            if (need(tiles) < (int64_t(4) << 30)) return true;
+        // What the call may hold: the caller's budget or 90 % of the memory that is
+        // free now (asking takes 2.7 us). A caller's allocator may hold more than the
+        // device shows as free: up to 4 GiB it is asked in any case.
+        int64_t room = plan.budget;
+        if (room <= 0) {
             const DeviceInfo di = device_info();
-            return need(tiles) <= (int64_t)((double)(di.free_b + di.reclaimable) * 0.9);
-        };
+            room = (int64_t)((double)(di.free_b + di.reclaimable) * 0.9);
+            if (t_calloc) room = std::max<int64_t>(room, int64_t(4) << 30);
+        }
+        auto fits = [&](int64_t tiles) { return need(tiles) <= room; };
         while (!fits(cap) && ns > 64) ns /= 2;
         if (!fits(cap)) return false;
 
@@ -2117,10 +2138,10 @@ struct Engine {
         bc.reach = reach.as<int32_t>();
         bc.nbig = reinterpret_cast<int32_t*>(d_ctl + 4);
         for (;;) {
+            // (the traversal that takes the call then tells the server when it ends)
             if (cap > 0x7FFFFFFFll) {
                 chk(hipStreamSynchronize(st));
                 give_masks(std::move(masks));
-                if (yh && yh->finished) yh->finished();
                 return false;
             }
             tiles = DBuf(512 * (size_t)cap);
@@ -2172,7 +2193,6 @@ struct Engine {
             if (!fits(cap)) {
                 chk(hipStreamSynchronize(st));
                 give_masks(std::move(masks));
-                if (yh && yh->finished) yh->finished();
                 return false;
             }
         }
@@ -2247,6 +2267,7 @@ struct Engine {
         f.l_ptr = std::move(l_ptr);
         f.nnz_u = nnz_u;
         f.nnz_l = nnz_l;
+        written = true;
         rc = finish(f, h_b.as<int64_t>(), jstat, js, nnz, row_base, nrows, cs, t0);
         return true;
     }

@@ -310,3 +310,64 @@ def test_batch_with_a_member_of_more_than_2_21_rows(g, nd):
     assert np.array_equal(b.l_ptr, np.concatenate([[0], np.cumsum(np.where(i < n // 2, 1, 0))]))
     assert np.array_equal(b.l_idx, n - 1 - i[:n // 2])
     assert b.fills == 0
+
+
+def _same(r, ref):
+    assert np.array_equal(r.u_ptr, ref.u_ptr) and np.array_equal(r.u_idx, ref.u_idx)
+    assert np.array_equal(r.l_ptr, ref.l_ptr) and np.array_equal(r.l_idx, ref.l_idx)
+    assert np.array_equal(r.xsup, ref.xsup) and np.array_equal(r.supno, ref.supno)
+    assert r.stats["edges_alg"] == ref.edges_alg
+
+
+def test_memory_that_cannot_be_had_leaves_the_call_to_the_traversal(g):
+    """One request of a caller's allocator fails, at several places of the call."""
+    m = _stencil(9, (70, 61), True, 5)
+    ref = oracle.symbolic(*m)
+
+    class Failing(g.TorchAllocator):
+        def __init__(self, at):
+            super().__init__()
+            self.asked, inner = 0, self.alloc_fn
+
+            def alloc(nbytes, ctx):
+                self.asked += 1
+                return None if self.asked == at else inner(nbytes, ctx)
+            self._inner, self.alloc_fn = inner, g.ALLOC_FN(alloc)
+
+    al = Failing(0)
+    r = g.symbolic(*m, allocator=al)
+    assert r.stats["mapping"] == 7
+    _same(r, ref)
+    inputs = 3  # row pointers, columns, the job table
+    for at in (inputs + 1, al.asked // 2, al.asked - 2, al.asked):
+        print(f"allocation {at} of {al.asked} fails", flush=True)
+        f = Failing(at)
+        r = g.symbolic(*m, allocator=f)
+        assert r.stats["mapping"] != 7
+        _same(r, ref)
+        assert f.frees == f.allocs and not f.live
+
+
+def test_little_device_memory_free(g):
+    """A call whose planned workgroups do not fit the free memory runs with fewer."""
+    import torch
+    n, rp, ci = _stencil(9, (350, 350), True, 5)
+    g.symbolic(n, rp, ci)  # (the first call of a size class takes more tiles)
+    full = g.symbolic(n, rp, ci)
+    assert full.stats["mapping"] == 7
+    need = full.stats["peak_device_bytes"]
+    g.release_cache()
+    torch.cuda.empty_cache()
+    free = lambda: torch.cuda.mem_get_info()[0]
+    held = []
+    try:
+        while free() > need and len(held) < 8:
+            held.append(torch.empty(free() - need + (1 << 22), dtype=torch.uint8, device="cuda"))
+        print(f"free {free()} of {need} that a call takes", flush=True)
+        r = g.symbolic(n, rp, ci)
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    assert r.stats["mapping"] == 7 and r.stats["concurrent_sources"] < full.stats["concurrent_sources"]
+    for k in ("u_ptr", "u_idx", "l_ptr", "l_idx", "xsup", "supno"):
+        assert np.array_equal(getattr(r, k), getattr(full, k)), k
