@@ -106,8 +106,8 @@ typedef enum {
 #define GSOFA_EAGER             0x200u
 /* With window = 0, concurrent_sources = 0 and no mapping or ablation flag, a call
  * takes the block path: no per-source traversal, nothing to tune. Matrices of more
- * than 2^22 rows and calls whose mem_budget_bytes does not hold its working memory
- * take the traversal, whose window span, mapping and sources in flight are then
+ * than 2^22 rows and calls whose mem_budget_bytes does not hold its working memory,
+ * the result included, take the traversal, whose window span, mapping and sources in flight are then
  * autotuned: for each size class (device, log2 of the largest n, mean row length,
  * batch size) the first call with at least 65,536 source rows times every
  * candidate on one stratified sample of its rows and keeps the fastest for later

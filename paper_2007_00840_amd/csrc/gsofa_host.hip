@@ -1056,10 +1056,12 @@ __global__ void k_rebase_ptr(int32_t njobs, const int64_t* job_row_base, const i
 // then, or a bounded wait has passed). `enqueued` runs once the first traversal
 // launch of the call is on the stream, `finished` once the traversal is done.
 // `before_traverse` runs before the traversal is enqueued (the call's uploads
-// and sorts are on the stream by then) and may wait.
+// and sorts are on the stream by then) and may wait. `grown` adds to the memory
+// that the server reserves for the call.
 struct YieldHooks {
     uint32_t* flag = nullptr;
     std::function<void()> enqueued, finished, before_resume, before_traverse;
+    std::function<void(int64_t)> grown;
     bool sources_set = false;  // the server's options name the sources in flight
 };
 
@@ -2026,9 +2028,13 @@ struct Engine {
         }
         int64_t cap = (int64_t)(ratio * 1.15 * (double)nblocks) + 64 * ns + 64;
         constexpr int64_t kPerBlock = 8 * kBmHeadWords + 1024 + 256 + 512 + 512 + sizeof(BlockRec) + 4 * kReachWords + 16;
-        auto need = [&](int64_t tiles) {
-            return fixed_bytes(nrows, total_nnz) + nrows * 64 + nblocks * kPerBlock + ns * stride * 8 + tiles * 548 + 24 * total_nnz;
+        // with the rows and columns of the result beside the tiles they are written
+        // from: as many entries as the size class had last, until they are known
+        auto need = [&](int64_t tiles, int64_t entries) {
+            return fixed_bytes(nrows, total_nnz) + nrows * 64 + nblocks * kPerBlock + ns * stride * 8 + tiles * 548 +
+                   4 * entries;
         };
+        const int64_t expected = (int64_t)(fill_ratio_for(key) * (double)total_nnz) + nrows;
         // What the call may hold: the caller's budget or 90 % of the memory that is
         // free now (asking takes 2.7 us). A caller's allocator may hold more than the
         // device shows as free: up to 4 GiB it is asked in any case.
@@ -2038,7 +2044,7 @@ struct Engine {
             room = (int64_t)((double)(di.free_b + di.reclaimable) * 0.9);
             if (t_calloc) room = std::max<int64_t>(room, int64_t(4) << 30);
         }
-        auto fits = [&](int64_t tiles) { return need(tiles) <= room; };
+        auto fits = [&](int64_t tiles) { return need(tiles, expected) <= room; };
         while (!fits(cap) && ns > 64) ns /= 2;
         if (!fits(cap)) return false;
 
@@ -2196,7 +2202,6 @@ struct Engine {
                 return false;
             }
         }
-        if (yh && yh->finished) yh->finished();
         if (nblocks > 0) {
             const double used = (double)*reinterpret_cast<const unsigned long long*>(h_ctl + 8);
             std::lock_guard<std::mutex> g(g_fill_mu);
@@ -2206,6 +2211,15 @@ struct Engine {
             if (h_js[j].err & kErrDuplicate) jstat[j] = GSOFA_EINVAL;
         const int64_t nnz_u = h_status->nnz_u, nnz_l = h_status->nnz_l;
         if (total_nnz > 0) note_fill_ratio(key, std::max(4.0, (double)(nnz_u + nnz_l) / (double)total_nnz));
+        // More entries than expected: a call keeps to the cap it was given, and the
+        // server, whose estimate was the cap, reserves the rest.
+        const int64_t over = plan.budget > 0 ? need(cap, nnz_u + nnz_l) - plan.budget : 0;
+        if (over > 0 && !yh) {
+            give_masks(std::move(masks));
+            return false;
+        }
+        if (over > 0 && yh->grown) yh->grown(over);
+        if (yh && yh->finished) yh->finished();
         chk(hipEventRecord(ev[1], st));
 
         // ---- rows of U, columns (or rows) of L, the reach counts, supernodes
@@ -2906,6 +2920,11 @@ void serve_worker(gsofa_server* s, int sid) {
                 me.alone_trav = false;
                 s->cv.notify_all();
             }
+        };
+        hooks.grown = [&](int64_t bytes) {
+            std::lock_guard<std::mutex> g(s->mu);
+            grp_est += bytes;
+            s->mem_in_use += bytes;
         };
         // A large request admitted while one that was given the idle device
         // traverses uploads and sorts at once but starts its traversal when that

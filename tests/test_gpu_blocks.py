@@ -371,3 +371,40 @@ def test_little_device_memory_free(g):
     assert r.stats["mapping"] == 7 and r.stats["concurrent_sources"] < full.stats["concurrent_sources"]
     for k in ("u_ptr", "u_idx", "l_ptr", "l_idx", "xsup", "supno"):
         assert np.array_equal(getattr(r, k), getattr(full, k)), k
+
+
+def test_the_budget_holds_the_result_too(g):
+    """A call with a budget takes the block path only where what it holds at a time,
+    its result included, is within the budget: refused before the launch where the
+    size class tells, after it where the result turns out larger."""
+    n, rp, ci = _random(12000, 5, 11)  # 60,000 entries fill to some 60 million
+    full = g.symbolic(n, rp, ci, flags=g.NO_TUNE)
+    out = 4 * (full.nnz_u + full.nnz_l)
+    assert full.stats["mapping"] == 7 and full.stats["peak_device_bytes"] > out > 64 << 20
+    few = _band(n, 6, 6, 3)  # of the same size class, with a small result
+    paths = []
+    for budget in (72 << 20, out, out + (64 << 20), 2 * out + (128 << 20)):
+        for warm in ((n, rp, ci), few):  # what the class had last
+            g.symbolic(*warm, flags=g.NO_TUNE)
+            r = g.symbolic(n, rp, ci, flags=g.NO_TUNE, mem_budget_bytes=budget)
+            paths.append(r.stats["mapping"])
+            print(f"budget {budget >> 20} MiB of {out >> 20}: path {paths[-1]}", flush=True)
+            assert r.stats["mapping"] != 7 or r.stats["peak_device_bytes"] <= budget
+            for k in ("u_ptr", "u_idx", "l_ptr", "l_idx", "xsup", "supno"):
+                assert np.array_equal(getattr(r, k), getattr(full, k)), k
+            assert r.stats["edges_alg"] == full.stats["edges_alg"]
+    assert paths[:4] == [0, 0, 0, 0] and paths[-2:] == [7, 7]
+    # the masks of the launches that were given up are clean
+    _same(g.symbolic(*few), oracle.symbolic(*few))
+
+
+def test_a_served_request_larger_than_its_estimate(g):
+    """The server runs it all the same, and has its whole budget back afterwards."""
+    m, few = _random(12000, 5, 11), _band(12000, 6, 6, 3)
+    ref = g.symbolic(*m)
+    with g.Server(max_inflight=2, mem_budget_bytes=200 << 20) as s:
+        for _ in range(4):
+            g.symbolic(*few)  # (estimates follow the last result)
+            r = s.poll(s.submit(*m), timeout_us=-1)
+            assert r.stats["mapping"] == 7 and r.stats["peak_device_bytes"] > 200 << 20
+            assert np.array_equal(r.u_idx, ref.u_idx)
