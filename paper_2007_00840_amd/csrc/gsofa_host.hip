@@ -933,6 +933,7 @@ struct TuneChoice {
     int32_t window;  // threshold-window span
     uint32_t flags;  // extra flags: GSOFA_NO_LINE95 (the access-order check switched off)
     int32_t div;     // sources in flight: the planned count divided by div (#C)
+    bool asked = false;  // GSOFA_TUNE_NOW asked for it: calls of the class keep to the traversal
 };
 
 constexpr TuneChoice kTuneCandidates[] = {
@@ -1252,6 +1253,7 @@ struct Engine {
                 plan.slot_div = c.div;
                 std::lock_guard<std::mutex> lk(g_tune_mu);
                 tune_table()[key] = c;
+                tune_table()[key].asked = force;
             }
         }
         const int64_t nslots = budget_mode ? 0 : div_slots(plan_slots(mapping), plan.slot_div);
@@ -1954,13 +1956,16 @@ struct Engine {
     }
 
     // Whether the block path may take the call: no option names a traversal
-    // (window, sources in flight, mapping, ablation), none is tuned for its size
-    // class, and the order is within the bitmaps of the kernels.
+    // (window, sources in flight, mapping, ablation), no GSOFA_TUNE_NOW chose one
+    // for its size class, and the order is within the bitmaps of the kernels. (A
+    // choice made because one call's memory did not hold the path binds traversals
+    // only: 64^3 27-point 5 ms here, 229 there.)
     bool blocks_apply(int64_t N, const TuneKey& key) const {
         if (!plan.window_auto || (plan.flags & GSOFA_TUNE_NOW) || N > kBlockMaxRows) return false;
         if (yh && yh->sources_set) return false;
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        return tune_table().count(key) == 0;
+        const auto it = tune_table().find(key);
+        return it == tune_table().end() || !it->second.asked;
     }
 
     // Wavefronts per block. Eight shorten a block's own work, four put more blocks

@@ -408,3 +408,19 @@ def test_a_served_request_larger_than_its_estimate(g):
             r = s.poll(s.submit(*m), timeout_us=-1)
             assert r.stats["mapping"] == 7 and r.stats["peak_device_bytes"] > 200 << 20
             assert np.array_equal(r.u_idx, ref.u_idx)
+
+
+def test_a_budgeted_call_does_not_tune_others_off_the_path(g):
+    """A call whose budget does not hold the block path may time the tuner's trials;
+    what they choose holds for traversals, later default calls of the size class
+    take the block path."""
+    m = _pairs(70000, 10)
+    a = g.symbolic(*m, mem_budget_bytes=110 << 20)
+    assert a.stats["mapping"] != 7 and a.stats["t_tune_ms"] > 0
+    b = g.symbolic(*m)
+    assert b.stats["mapping"] == 7
+    c = g.symbolic(*m, mem_budget_bytes=110 << 20)
+    assert c.stats["mapping"] == a.stats["mapping"] and c.stats["t_tune_ms"] == 0
+    for r in (a, c):
+        for k in ("u_ptr", "u_idx", "l_ptr", "l_idx", "xsup", "supno"):
+            assert np.array_equal(getattr(r, k), getattr(b, k)), k
