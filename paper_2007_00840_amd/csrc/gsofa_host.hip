@@ -982,8 +982,11 @@ struct EngineOut {
 // Tiles per 64-row block of the block path, per size class: sizes the pool of
 // later calls. A class not seen yet starts at kBlockTiles (the 64^3 27-point
 // stencil needs 61 a block, batch members 14, the 1000^2 9-point stencil 16); a pool
-// that overflows all the same is grown and the call's launch repeated.
-constexpr double kBlockTiles = 80.0;
+// that overflows all the same is grown and the call's launch repeated. A class holds
+// 2D and 3D matrices alike (9-point and 7-point stencils have as many entries per
+// row), so it keeps the most it has seen, up to kKeepTiles (3 GB of tiles for 10^6
+// rows); beyond that it follows the last call.
+constexpr double kBlockTiles = 80.0, kKeepTiles = 4 * kBlockTiles;
 std::map<TuneKey, double>& block_ratios() {
     static auto* m = new std::map<TuneKey, double>();
     return *m;
@@ -2031,7 +2034,8 @@ struct Engine {
             auto it = block_ratios().find(key);
             if (it != block_ratios().end()) ratio = it->second;
         }
-        int64_t cap = (int64_t)(ratio * 1.15 * (double)nblocks) + 64 * ns + 64;
+        auto cap_for = [&](double r) { return (int64_t)(r * 1.15 * (double)nblocks) + 64 * ns + 64; };
+        int64_t cap = cap_for(ratio);
         constexpr int64_t kPerBlock = 8 * kBmHeadWords + 1024 + 256 + 512 + 512 + sizeof(BlockRec) + 4 * kReachWords + 16;
         // with the rows and columns of the result beside the tiles they are written
         // from: as many entries as the size class had last, until they are known
@@ -2050,6 +2054,7 @@ struct Engine {
             if (t_calloc) room = std::max<int64_t>(room, int64_t(4) << 30);
         }
         auto fits = [&](int64_t tiles) { return need(tiles, expected) <= room; };
+        if (!fits(cap) && ratio > kBlockTiles) cap = cap_for(kBlockTiles);  // (and grown if need be)
         while (!fits(cap) && ns > 64) ns /= 2;
         if (!fits(cap)) return false;
 
@@ -2210,7 +2215,8 @@ struct Engine {
         if (nblocks > 0) {
             const double used = (double)*reinterpret_cast<const unsigned long long*>(h_ctl + 8);
             std::lock_guard<std::mutex> g(g_fill_mu);
-            block_ratios()[key] = std::max(4.0, used / (double)nblocks);
+            double& kept = block_ratios()[key];
+            kept = std::max(std::max(4.0, used / (double)nblocks), std::min(kept, kKeepTiles));
         }
         for (int32_t j = 0; j < nj; ++j)
             if (h_js[j].err & kErrDuplicate) jstat[j] = GSOFA_EINVAL;

@@ -424,3 +424,34 @@ def test_a_budgeted_call_does_not_tune_others_off_the_path(g):
     for r in (a, c):
         for k in ("u_ptr", "u_idx", "l_ptr", "l_idx", "xsup", "supno"):
             assert np.array_equal(getattr(r, k), getattr(b, k)), k
+
+
+def test_pool_regrowth_is_paid_once_per_size_class(g):
+    """A first call of a class whose blocks have 312 tiles on average (the first pool
+    holds at most 156 a block) runs its launch again, the next one does not; a 2D
+    matrix between two 3D ones of its class leaves the pool as it is."""
+    n, rp, ci = _dense_rows(40000, 64)
+    first = g.symbolic(n, rp, ci, flags=g.NO_TUNE)
+    again = g.symbolic(n, rp, ci, flags=g.NO_TUNE)
+    assert (first.stats["mapping"], again.stats["mapping"]) == (7, 7)
+    assert first.stats["launches"] >= 2 and again.stats["launches"] == 1
+    nnz_l = len(ci) - n  # (no fill)
+    for r in (first, again):
+        assert r.fills == 0 and r.nnz_l == nnz_l and np.array_equal(r.u_idx, np.arange(n))
+    m3, m2 = _stencil(7, (64, 64, 64), True, 5), _stencil(9, (510, 510), True, 5)
+    a = g.symbolic(*m3, flags=g.NO_TUNE)
+    for _ in range(2):
+        assert g.symbolic(*m2, flags=g.NO_TUNE).stats["mapping"] == 7
+    b = g.symbolic(*m3, flags=g.NO_TUNE)
+    assert b.stats["launches"] == 1 and np.array_equal(a.u_idx, b.u_idx) and np.array_equal(a.l_idx, b.l_idx)
+
+
+def test_pool_regrowth_in_a_batch(g):
+    """The launch of all members runs again, the small ones' results with it."""
+    n, rp, ci = _dense_rows(30000, 64)
+    small = [_band(k, 9, 11, k) for k in (64, 129, 700)]
+    res = g.batch([small[0], (n, rp, ci), small[1], small[2]], flags=g.NO_TUNE)
+    assert res[0].stats["mapping"] == 7 and res[0].stats["launches"] >= 2
+    assert res[1].fills == 0 and np.array_equal(res[1].u_idx, np.arange(n))
+    for m, r in zip(small, (res[0], res[2], res[3])):
+        _same(r, oracle.symbolic(*m))
