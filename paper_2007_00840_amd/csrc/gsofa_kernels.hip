@@ -457,9 +457,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W, 8))) voi
         int32_t ndiag = 0;
         bool dup = false;
         int32_t pmin = 0x7FFFFFFF;
-        for (int32_t e0 = rs; e0 < re; e0 += 64) {
-            const int32_t e = e0 + ln;
-            const bool act = e < re;
+        // (unsigned: a step beyond up to 2^31 - 1 entries still compares right)
+        for (uint32_t e0 = (uint32_t)rs; e0 < (uint32_t)re; e0 += 64) {
+            const uint32_t e = e0 + ln;
+            const bool act = e < (uint32_t)re;
             const int32_t w = act ? ci[e] : -1;
             ndiag += __popcll(__ballot(act && w == s));
             bool fresh = false;
@@ -937,9 +938,10 @@ __global__ __launch_bounds__(256) void k_traverse8(TraverseArgs a) {
         int32_t ndiag = 0;
         bool dup = false;
         int32_t pmin = 0x7FFFFFFF;
-        for (int32_t e0 = rs; e0 < re; e0 += 64) {
-            const int32_t e = e0 + ln;
-            const bool act = e < re;
+        // (unsigned: a step beyond up to 2^31 - 1 entries still compares right)
+        for (uint32_t e0 = (uint32_t)rs; e0 < (uint32_t)re; e0 += 64) {
+            const uint32_t e = e0 + ln;
+            const bool act = e < (uint32_t)re;
             const int32_t w = act ? ci[e] : -1;
             ndiag += __popcll(__ballot(act && w == s));
             bool fresh = false;
@@ -1385,9 +1387,10 @@ __global__ __launch_bounds__(64 * NW) void k_traverse_wg(TraverseArgs a) {
         const int32_t rs = rp[s], re = rp[s + 1];
         {
             int32_t pmin = 0x7FFFFFFF;
-            for (int32_t e0 = rs; e0 < re; e0 += 64 * NW) {
-                const int32_t e = e0 + tid;
-                const bool act = e < re;
+            // (unsigned: a step beyond up to 2^31 - 1 entries still compares right)
+            for (uint32_t e0 = (uint32_t)rs; e0 < (uint32_t)re; e0 += 64 * NW) {
+                const uint32_t e = e0 + tid;
+                const bool act = e < (uint32_t)re;
                 const int32_t w = act ? ci[e] : -1;
                 const int32_t nd = __popcll(__ballot(act && w == s));
                 if (ln == 0 && nd) atomicAdd(&C.ndiag, nd);

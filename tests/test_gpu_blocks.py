@@ -259,9 +259,10 @@ def test_row_pointers_beyond_the_entries_are_refused(g):
         assert e.value.code == g.EINVAL
 
 
-def test_largest_order_and_entry_count(g):
+@pytest.mark.parametrize("path", ["blocks", "traversal"])
+def test_largest_order_and_entry_count(g, path):
     """2^22 rows, the most the block path takes, in dense blocks of 512 with
-    2^31 - 1 entries in all: the last step over a block's entries passes 2^31."""
+    2^31 - 1 entries in all: the last step over a row's (block's) entries passes 2^31."""
     import torch
     n, nnz = 1 << 22, 2**31 - 1
     ci = torch.empty(nnz, dtype=torch.int32, device="cuda")
@@ -271,9 +272,10 @@ def test_largest_order_and_entry_count(g):
         ci[a:a + step] = ((i >> 18 << 9) + (i & 511)).to(torch.int32)
     r = torch.arange(n + 1, device="cuda")
     rp = (512 * r).clamp(max=nnz).to(torch.int32)
-    print(f"blocks n={n} nnz={nnz}", flush=True)
-    d = g.symbolic(n, rp, ci, flags=g.RESULT_ON_DEVICE)
-    assert d.stats["mapping"] == 7 and d.fills == 0
+    print(f"{path} n={n} nnz={nnz}", flush=True)
+    flags, mapping = {"blocks": (0, 7), "traversal": (g.MAP_WAVE32, 0)}[path]
+    d = g.symbolic(n, rp, ci, flags=g.RESULT_ON_DEVICE | flags)
+    assert d.stats["mapping"] == mapping and d.fills == 0
     assert (d.nnz_u, d.nnz_l, d.nsuper) == (n // 512 * (512 * 513 // 2), n // 512 * (512 * 511 // 2), n // 128)
     # every source reaches the rows of its dense block above it, 512 entries each
     # (the last row, only a source, lacks one)
@@ -291,6 +293,8 @@ def test_largest_order_and_entry_count(g):
         for a in range(0, n // 512, 1024):
             want = one[None] + 512 * torch.arange(a, a + 1024, device="cuda")[:, None]
             assert torch.equal(x[a:a + 1024], want.to(torch.int32)), (k, a)
+    del t, ci
+    g.release_cache()
 
 
 @pytest.mark.parametrize("nd", [1, 2])
