@@ -2037,13 +2037,16 @@ struct Engine {
         auto cap_for = [&](double r) { return (int64_t)(r * 1.15 * (double)nblocks) + 64 * ns + 64; };
         int64_t cap = cap_for(ratio);
         constexpr int64_t kPerBlock = 8 * kBmHeadWords + 1024 + 256 + 512 + 512 + sizeof(BlockRec) + 4 * kReachWords + 16;
-        // with the rows and columns of the result beside the tiles they are written
-        // from: as many entries as the size class had last, until they are known
+        // with the rows and columns of the result beside the tiles they are written from
         auto need = [&](int64_t tiles, int64_t entries) {
             return fixed_bytes(nrows, total_nnz) + nrows * 64 + nblocks * kPerBlock + ns * stride * 8 + tiles * 548 +
                    4 * entries;
         };
-        const int64_t expected = (int64_t)(fill_ratio_for(key) * (double)total_nnz) + nrows;
+        // Entries of the result: for the workgroups in flight as many as the size class
+        // had last, for the decision whether the path takes the call those it has at
+        // least (a diagonal and the matrix's own); the true count is looked at later.
+        const int64_t least = std::max(nrows, total_nnz);
+        const int64_t expected = std::max(least, (int64_t)(fill_ratio_for(key) * (double)total_nnz));
         // What the call may hold: the caller's budget or 90 % of the memory that is
         // free now (asking takes 2.7 us). A caller's allocator may hold more than the
         // device shows as free: up to 4 GiB it is asked in any case.
@@ -2053,9 +2056,9 @@ struct Engine {
             room = (int64_t)((double)(di.free_b + di.reclaimable) * 0.9);
             if (t_calloc) room = std::max<int64_t>(room, int64_t(4) << 30);
         }
-        auto fits = [&](int64_t tiles) { return need(tiles, expected) <= room; };
+        auto fits = [&](int64_t tiles) { return need(tiles, least) <= room; };
         if (!fits(cap) && ratio > kBlockTiles) cap = cap_for(kBlockTiles);  // (and grown if need be)
-        while (!fits(cap) && ns > 64) ns /= 2;
+        while (need(cap, expected) > room && ns > 64) ns /= 2;
         if (!fits(cap)) return false;
 
         const bool want_sn = (plan.flags & GSOFA_NO_SUPERNODES) == 0;
