@@ -1,5 +1,5 @@
-// Predicates of the input check, free of device code so that a plain host
-// compiler takes them too (constexpr functions are callable from kernels).
+// Decisions free of device code, so that a plain host compiler takes them too
+// (constexpr functions are callable from kernels).
 #pragma once
 #include <cstdint>
 
@@ -11,6 +11,19 @@ namespace gsofa {
 // seen by row 1 only.)
 constexpr bool csr_row_readable(int64_t r, int32_t a, int32_t b, int32_t nnz) {
     return a >= 0 && b >= a && b <= nnz && (r != 0 || a == 0);
+}
+
+// How a launch of the block path's factorisation ended: with everything done, for
+// want of tiles, or because a wait gave up.
+enum BmAbortCode : uint32_t { kBmNoAbort = 0, kBmOverflow = 1, kBmStall = 2 };
+
+// What follows: the results, the launch again with a larger pool if one fits, or the
+// traversal. A wait gives up after a number of polls, which a long chain of blocks
+// or a device shared with other work can use up: no error of the call.
+enum class BmNext { kResults, kAgain, kTraverse };
+constexpr BmNext bm_next(uint32_t abort, bool larger_pool_fits) {
+    return abort == kBmNoAbort ? BmNext::kResults
+                               : abort == kBmOverflow && larger_pool_fits ? BmNext::kAgain : BmNext::kTraverse;
 }
 
 }  // namespace gsofa

@@ -2059,7 +2059,7 @@ struct Engine {
         auto fits = [&](int64_t tiles) { return need(tiles, least) <= room; };
         if (!fits(cap) && ratio > kBlockTiles) cap = cap_for(kBlockTiles);  // (and grown if need be)
         while (need(cap, expected) > room && ns > 64) ns /= 2;
-        if (!fits(cap)) return false;
+        if (!fits(cap) || cap > 0x7FFFFFFFll) return false;
 
         const bool want_sn = (plan.flags & GSOFA_NO_SUPERNODES) == 0;
         const bool have_sn = want_sn && nrows > 0;
@@ -2157,12 +2157,6 @@ struct Engine {
         bc.reach = reach.as<int32_t>();
         bc.nbig = reinterpret_cast<int32_t*>(d_ctl + 4);
         for (;;) {
-            // (the traversal that takes the call then tells the server when it ends)
-            if (cap > 0x7FFFFFFFll) {
-                chk(hipStreamSynchronize(st));
-                give_masks(std::move(masks));
-                return false;
-            }
             tiles = DBuf(512 * (size_t)cap);
             tabs = DBuf(32 * (size_t)cap);
             ba.masks = tiles.as<unsigned long long>();
@@ -2202,14 +2196,14 @@ struct Engine {
                 chk(hipStreamSynchronize(st));
                 ph.done();
             }
-            if (h_ctl[kBmAbort] == 0) break;
+            if (bm_next(h_ctl[kBmAbort], true) == BmNext::kResults) break;
             // an aborted launch leaves masks behind: clear them for the next one
             chk(launch_zero_i32(masks->buf.as<int32_t>(), masks->stride * masks->nslots * 2, st));
-            if (h_ctl[kBmAbort] != kBmOverflow) throw HipError{hipErrorLaunchTimeOut};
             tiles.reset();
             tabs.reset();
             cap = 4 * std::max<int64_t>(cap, (int64_t)*reinterpret_cast<const unsigned long long*>(h_ctl + 8));
-            if (!fits(cap)) {
+            if (bm_next(h_ctl[kBmAbort], cap <= 0x7FFFFFFFll && fits(cap)) == BmNext::kTraverse) {
+                // (the traversal then tells the server when it ends)
                 chk(hipStreamSynchronize(st));
                 give_masks(std::move(masks));
                 return false;

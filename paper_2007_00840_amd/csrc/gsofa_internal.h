@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gsofa_checks.h"
+
 namespace gsofa {
 
 constexpr int kWave = 64;
@@ -105,7 +107,6 @@ constexpr int kReachWords = 16, kReachInline = 7;
 constexpr int32_t kMapBlocks = 7;                    // the path's number in stats.mapping
 constexpr int kBmHeadWords = 32;                     // 64-bit words per block: headers of its two publications
 enum BmCtl { kBmNext = 0, kBmAbort = 1 };
-enum BmAbortCode { kBmOverflow = 1, kBmStall = 2 };
 
 // Where a finished block's tiles lie in the pool: U beyond the block, L before it.
 struct BlockRec {

@@ -32,7 +32,6 @@
 //           list)
 //   rowb  : the source row's structure, copied to the output pool at the end
 #include <atomic>
-#include "gsofa_checks.h"
 #include "gsofa_internal.h"
 #include "gsofa.h"
 

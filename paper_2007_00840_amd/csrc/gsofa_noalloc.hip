@@ -132,8 +132,9 @@ struct Call {
 // tiles taking what the other arrays leave. Whole calls, traversal and blocks:
 // 44 x 45 9-point 1.6 and 0.45 ms, 100 x 100 8.1 and 0.61, 30^3 27-point 210 and
 // 1.17, 350 x 350 2,234 and 2.6 (the traversal has few slots there). Left to the
-// traversal: the options that name it, and matrices whose tiles hold few entries
-// and overflow the pool, which an aborted launch of a few milliseconds finds.
+// traversal: the options that name it, matrices whose tiles hold few entries and
+// overflow the pool, which an aborted launch of a few milliseconds finds, and calls
+// in which a wait gave up.
 int blocks_noalloc(const Call& k, uint8_t* base, size_t cap, double t0, gsofa_counts* c) {
     const hipStream_t st = k.st;
     const int64_t nb = ((int64_t)k.n + 63) / 64, stride = 64 * nb;
@@ -207,8 +208,7 @@ int blocks_noalloc(const Call& k, uint8_t* base, size_t cap, double t0, gsofa_co
     NA_CHK(hipMemcpyAsync(&h, status, sizeof(h), hipMemcpyDeviceToHost, st));
     NA_CHK(hipStreamSynchronize(st));
     const double tt1 = now_ms();
-    if (h.s.ctl[kBmAbort] == (uint32_t)kBmOverflow) return kNotHere;
-    if (h.s.ctl[kBmAbort] != 0u) return GSOFA_EDEVICE;
+    if (bm_next(h.s.ctl[kBmAbort], false) == BmNext::kTraverse) return kNotHere;
     if (h.js.err & kErrDuplicate) return GSOFA_EINVAL;
 
     // what fits is what the traversal's pool and its row-wise L would

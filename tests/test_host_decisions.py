@@ -1,7 +1,8 @@
-"""The predicate by which the device's input check decides whether a row's
-columns may be read, compiled for the host (the kernel uses the same header):
-whatever row_ptr holds, no admitted row leaves the entries, and of a
-non-decreasing row_ptr every row is admitted."""
+"""Decisions of the library compiled for the host from the header that its own
+code uses. The device's input check reads a row's columns only if a predicate
+admits it: whatever row_ptr holds, no admitted row leaves the entries, and of a
+non-decreasing row_ptr every row is admitted. After a launch of the block path:
+a wait that gave up or a pool that cannot grow leaves the call to the traversal."""
 import ctypes
 import os
 import subprocess
@@ -14,14 +15,22 @@ CSRC = os.path.join(ROOT, "paper_2007_00840_amd", "csrc")
 
 
 @pytest.fixture(scope="module")
-def readable(tmp_path_factory):
-    d = tmp_path_factory.mktemp("rows")
-    src, lib = d / "rows.cpp", d / "rows.so"
+def checks(tmp_path_factory):
+    d = tmp_path_factory.mktemp("checks")
+    src, lib = d / "checks.cpp", d / "checks.so"
     src.write_text('#include "gsofa_checks.h"\n'
                    'extern "C" int row(int64_t r, int32_t a, int32_t b, int32_t nnz)\n'
-                   '{ return gsofa::csr_row_readable(r, a, b, nnz); }\n')
+                   '{ return gsofa::csr_row_readable(r, a, b, nnz); }\n'
+                   'extern "C" int next(int how, int fits)\n'
+                   '{ const uint32_t code[] = {gsofa::kBmNoAbort, gsofa::kBmOverflow, gsofa::kBmStall};\n'
+                   '  return (int)gsofa::bm_next(code[how], fits != 0); }\n')
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", f"-I{CSRC}", str(src), "-o", str(lib)], check=True)
-    fn = ctypes.CDLL(str(lib)).row
+    return ctypes.CDLL(str(lib))
+
+
+@pytest.fixture(scope="module")
+def readable(checks):
+    fn = checks.row
     fn.argtypes = [ctypes.c_int64] + 3 * [ctypes.c_int32]
     return lambda rp: [bool(fn(r, int(rp[r]), int(rp[r + 1]), int(rp[-1]))) for r in range(len(rp) - 1)]
 
@@ -44,3 +53,11 @@ def test_rows_of_random_pointers(readable):
             assert not ok or (0 <= rp[r] <= rp[r + 1] <= rp[-1])
         up = np.sort(np.abs(rp)) - np.abs(rp).min()
         assert all(readable(up))
+
+
+def test_what_follows_a_launch(checks):
+    results, again, traverse = range(3)
+    done, overflow, stall = range(3)
+    assert [checks.next(done, f) for f in (0, 1)] == [results, results]
+    assert [checks.next(overflow, f) for f in (0, 1)] == [traverse, again]
+    assert [checks.next(stall, f) for f in (0, 1)] == [traverse, traverse]
