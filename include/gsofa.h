@@ -144,14 +144,14 @@ typedef enum {
  * source (O(n) per source) instead of moving to a fresh value range. Results
  * are unchanged. */
 #define GSOFA_RESET_LABELS      0x10000u
-/* Server: work-item admission. A large request's traversal (more than 65,536
- * rows) gives its wave slots up when a request is admitted onto a full device:
- * it takes no further source, finishes the ones it holds, and resumes from
- * where it stopped once the new request's traversal is on the device (at most
- * once per 20 ms). Results are unchanged. Off by default: the server already
- * keeps a reserve of wave slots that large traversals never take, and a yield
- * idles the large traversal until its slowest current source is done. Ignored
- * outside the server. */
+/* Server: work-item admission. A large request (more than 65,536 rows) gives its
+ * wave slots up when a request is admitted onto a full device: its launch takes
+ * no further source (block path: block of 64 rows), finishes the ones it holds,
+ * and resumes from where it stopped once the new request's launch is on the
+ * device (at most once per 20 ms). Results are unchanged. Off by default: the
+ * server already keeps a reserve of wave slots that large launches never take,
+ * and a yield idles the large request until its slowest current source (block)
+ * is done. Ignored outside the server. */
 #define GSOFA_SERVE_YIELD       0x20000u
 
 /* A CSR pattern: n rows, row_ptr[n+1], col_idx[row_ptr[n]]; host pointers

@@ -41,7 +41,9 @@
 // the ones it can depend on (ascending inside a matrix), so a block waits only
 // for blocks that resident workgroups have already taken, and the first
 // unfinished one waits for nothing: the launch always drains. Every wait also
-// ends on the abort word and after kSpinLimit polls.
+// ends on the abort word and after kSpinLimit polls. A launch that is asked to yield
+// takes no further block and finishes those it has taken (they wait for one another
+// only, as before); the next launch goes on at the counter.
 //
 // Data that crosses workgroups (masks, columns, headers, kmatch, flags) is
 // written and read with device-scope atomics, which reach memory past the
@@ -371,8 +373,9 @@ __global__ __launch_bounds__(64 * W, 4) void k_bm_factor(BlockArgs a) {
 
     for (;;) {
         if (tid == 0) {
-            s_item = (int)atomicAdd(&a.ctl[kBmNext], 1u);
+            const uint32_t asked = a.yield ? __hip_atomic_load(a.yield, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) : 0u;
             s_stop = ld_dev(&a.ctl[kBmAbort]) != 0u;
+            s_item = asked ? a.nblocks : (int)atomicAdd(&a.ctl[kBmNext], 1u);
             s_ext = 0;
             s_active = 0;
             s_poll = 0;
@@ -1009,6 +1012,11 @@ __global__ __launch_bounds__(64 * W, 4) void k_bm_factor(BlockArgs a) {
 // -------------------------------------------------------------- row counts
 
 namespace {
+// the factorisation neither gave up nor yielded before its last block
+__device__ __forceinline__ bool all_done(const BlockArgs& a) {
+    return ld_dev(&a.ctl[kBmAbort]) == 0u && ld_dev(&a.ctl[kBmNext]) >= (uint32_t)a.nblocks;
+}
+
 constexpr int kPlanes = 16;  // a wavefront counts less than 2^16 tiles
 
 // m's bits, 64 by 64, with rows and columns exchanged
@@ -1035,7 +1043,7 @@ __device__ __forceinline__ u64 transpose64(u64 x) {
 __global__ __launch_bounds__(kThreads) void k_bm_count(BlockArgs a, BlockCols cl) {
     __shared__ int32_t s_cnt[2][64];
     const int ln = lane(), wv = rfl(threadIdx.x >> 6);
-    if (ld_dev(&a.ctl[kBmAbort]) != 0u) return;
+    if (!all_done(a)) return;
     const int32_t gb = blockIdx.x;
     const int32_t jb = a.blk_job ? a.blk_job[gb] : 0;
     const Job* J = &a.jobs[jb];
@@ -1177,7 +1185,7 @@ __device__ __forceinline__ void supernodes_of(const BlockArgs& a, int32_t gb, in
 __global__ __launch_bounds__(64) void k_bm_lists(BlockArgs a, BlockCols c, int32_t* col_cnt, int64_t max_super,
                                                  int32_t* is_start) {
     extern __shared__ u64 s_dyn[];
-    if (ld_dev(&a.ctl[kBmAbort]) != 0u) return;
+    if (!all_done(a)) return;
     const int ln = lane();
     const int32_t cb = blockIdx.x;
     const int32_t jb = a.blk_job ? a.blk_job[cb] : 0;

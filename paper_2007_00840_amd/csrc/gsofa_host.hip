@@ -2168,16 +2168,24 @@ struct Engine {
             bc.blk2 = ba.tids + 4 * cap;
             bc.tile2 = ba.tids + 5 * cap;
             ba.pool_cap = cap;
-            {
-                Phase ph(kPhaseTraverse, graphs, st);
+            // A launch asked to yield stopped taking blocks: it goes on once the server
+            // says so. Two launches in a row that take nothing (the flag keeps being
+            // set) end the yielding.
+            ba.yield = yh ? yh->flag : nullptr;
+            uint32_t taken = 0;
+            int32_t idle = 0;
+            for (bool first = true;; first = false) {
+                Phase ph(kPhaseTraverse, graphs && first, st);
                 const hipStream_t s = ph.stream();
-                h2d(d_up.p, h_up.p, (size_t)up_bytes, s, true);
-                chk(launch_zero_i32(zero.as<int32_t>(), z_bytes / 4, s));
-                if (nj > 1) {
-                    chk(launch_block_tables(d_jobs, reinterpret_cast<const int32_t*>(du + o_ord),
-                                            reinterpret_cast<const int64_t*>(du + o_cum), (int32_t)max_blocks,
-                                            (int32_t)nblocks, items.as<int32_t>(), blk_job.as<int32_t>(), s));
-                    chk(launch_row_job(d_jobs, nj, N, row_job.as<int32_t>(), s));
+                if (first) {
+                    h2d(d_up.p, h_up.p, (size_t)up_bytes, s, true);
+                    chk(launch_zero_i32(zero.as<int32_t>(), z_bytes / 4, s));
+                    if (nj > 1) {
+                        chk(launch_block_tables(d_jobs, reinterpret_cast<const int32_t*>(du + o_ord),
+                                                reinterpret_cast<const int64_t*>(du + o_cum), (int32_t)max_blocks,
+                                                (int32_t)nblocks, items.as<int32_t>(), blk_job.as<int32_t>(), s));
+                        chk(launch_row_job(d_jobs, nj, N, row_job.as<int32_t>(), s));
+                    }
                 }
                 chk(launch_block_factor(ba, s));
                 const BlockScan lists{ba.tcount, list_ptr.as<int64_t>()};
@@ -2191,10 +2199,16 @@ struct Engine {
                                         h_status, h_js, s));
                 ph.launch();
                 ++launches;
-                if (yh && yh->enqueued) yh->enqueued();
+                if (first && yh && yh->enqueued) yh->enqueued();
                 chk(hipEventRecord(ev[4], st));
                 chk(hipStreamSynchronize(st));
                 ph.done();
+                if (h_ctl[kBmAbort] != 0 || h_ctl[kBmNext] >= (uint32_t)nblocks) break;
+                if (yh->before_resume) yh->before_resume();
+                __atomic_store_n(yh->flag, 0u, __ATOMIC_RELEASE);
+                idle = h_ctl[kBmNext] == taken ? idle + 1 : 0;
+                taken = h_ctl[kBmNext];
+                if (idle >= 2) ba.yield = nullptr;
             }
             if (bm_next(h_ctl[kBmAbort], true) == BmNext::kResults) break;
             // an aborted launch leaves masks behind: clear them for the next one

@@ -143,6 +143,8 @@ struct BlockArgs {
     int32_t* row_ucnt;
     int32_t* row_lcnt;
     JobStats* jstats;             // per matrix
+    const uint32_t* yield;        // host flag (nullptr: none): set, the launch takes no further
+                                  // block; ctl[kBmNext] then tells where to go on
 };
 
 // L's tiles by columns: block c's list is entries [ptr[c], ptr[c + 1]) of (row

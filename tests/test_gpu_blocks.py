@@ -459,3 +459,36 @@ def test_pool_regrowth_in_a_batch(g):
     assert res[1].fills == 0 and np.array_equal(res[1].u_idx, np.arange(n))
     for m, r in zip(small, (res[0], res[2], res[3])):
         _same(r, oracle.symbolic(*m))
+
+
+def test_served_blocks_yield(g):
+    """A large request on the block path (a tridiagonal matrix: 9,375 blocks one after
+    another) gives the device up for requests admitted meanwhile with
+    GSOFA_SERVE_YIELD: its launch stops taking blocks and is run again from there.
+    Without the flag one launch does it all; the results are the same."""
+    import time
+    n = 600000
+    i = np.arange(n)
+    c = i[:, None] + np.arange(-1, 2)[None]
+    ok = (c >= 0) & (c < n)
+    rp = np.concatenate([[0], ok.sum(1).cumsum()]).astype(np.int32)
+    tri = (n, rp, c[ok].astype(np.int32))
+    small = [_band(700, 9, 11, k) for k in range(8)]
+    refs = [oracle.symbolic(*m) for m in small]
+    launches = {}
+    for flags in (g.SERVE_YIELD, 0):
+        with g.Server(max_inflight=4, flags=flags) as s:
+            t = s.submit(*tri)
+            ts = []
+            for m in small:
+                time.sleep(0.006)
+                ts.append(s.submit(*m))
+            r = s.poll(t, timeout_us=-1)
+            rs = [s.poll(x, timeout_us=-1) for x in ts]
+        launches[flags] = r.stats["launches"]
+        print(f"flags {flags:#x}: {launches[flags]} launches", flush=True)
+        assert r.stats["mapping"] == 7 and r.fills == 0 and r.nnz_l == n - 1
+        assert np.array_equal(r.u_idx, c[ok & (c >= i[:, None])]) and np.array_equal(r.l_idx, i[1:])
+        for x, ref in zip(rs, refs):
+            _same(x, ref)
+    assert launches[g.SERVE_YIELD] >= 2 and launches[0] == 1
