@@ -492,3 +492,24 @@ def test_served_blocks_yield(g):
         for x, ref in zip(rs, refs):
             _same(x, ref)
     assert launches[g.SERVE_YIELD] >= 2 and launches[0] == 1
+
+
+def test_pool_of_a_small_call_grows(g):
+    """24,000 rows with a dense first row and column fill up: the first pool is small
+    enough for the device's free memory not to be asked for, the next one is not."""
+    import torch
+    n = 24000
+    first = np.arange(n)
+    rest = np.stack([np.zeros(n - 1, dtype=np.int64), np.arange(1, n)], 1).reshape(-1)
+    rp = np.concatenate([[0], n + 2 * np.arange(n)]).astype(np.int32)
+    d = g.symbolic(n, torch.from_numpy(rp).cuda(), torch.from_numpy(np.concatenate([first, rest]).astype(np.int32)).cuda(),
+                   flags=g.RESULT_ON_DEVICE)
+    assert d.stats["mapping"] == 7 and d.stats["launches"] >= 2
+    assert d.nnz_u == n * (n + 1) // 2 and d.nnz_l == n * (n - 1) // 2
+    t = d.to_torch()
+    d.free()
+    k = torch.arange(n + 1, device="cuda")
+    assert torch.equal(t["u_ptr"], k * n - k * (k - 1) // 2) and torch.equal(t["l_ptr"], k * (n - 1) - k * (k - 1) // 2)
+    for r in (0, 1, 63, 64, 12345, n - 1):
+        assert torch.equal(t["u_idx"][t["u_ptr"][r]:t["u_ptr"][r + 1]], k[r:n].int())
+        assert torch.equal(t["l_idx"][t["l_ptr"][r]:t["l_ptr"][r + 1]], k[r + 1:n].int())
