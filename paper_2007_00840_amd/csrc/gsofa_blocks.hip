@@ -1110,6 +1110,23 @@ __global__ __launch_bounds__(kThreads) void k_bm_count(BlockArgs a, BlockCols cl
 // (in the place it took during the factorisation), k_bm_lists sorts the lists by
 // row block and counts the entries of every column.
 
+// A tile of which the reach counts need one entry stands in their lists (not in the
+// blocks' records) as that entry, row and column inside their blocks, in place of its
+// place in the pool: nobody loads 512 bytes for a bit, and k_bm_reach_big takes 64
+// such tiles at a time, a lane each. (200,000 rows with one entry below the diagonal
+// at random each, where the first block of columns reaches every row through 200,000
+// such tiles: 10.5 ms four tiles at a time, 2.2 so; three entries each 41 and 11.)
+__device__ __forceinline__ int32_t one_entry(int row, int col) { return ~((row << 6) | col); }
+__device__ __forceinline__ int entry_row(int32_t q) { return ~q >> 6; }
+__device__ __forceinline__ int entry_col(int32_t q) { return ~q & 63; }
+
+// the masks of a list's tile (the same for all lanes)
+__device__ __forceinline__ u64 listed_masks(const u64* masks, int32_t q) {
+    const int ln = lane();
+    if (q < 0) return ln == entry_col(q) ? 1ull << entry_row(q) : 0ull;
+    return masks[64 * (int64_t)q + ln];
+}
+
 // the rows of block g up to (and with) a column's match
 __device__ __forceinline__ u64 upto(u64 m, int32_t g, int32_t match) {
     if (g < (match >> 6)) return m;
@@ -1201,6 +1218,7 @@ __global__ __launch_bounds__(64) void k_bm_lists(BlockArgs a, BlockCols c, int32
     // and which of them the reach counts need
     auto walk = [&](int k, int32_t b, int32_t q) {
         u64 keep = 0, occ = 0;
+        int32_t t = q;
         for (int i0 = 0; i0 < k; i0 += 4) {
             u64 m[4];
 #pragma unroll
@@ -1209,16 +1227,23 @@ __global__ __launch_bounds__(64) void k_bm_lists(BlockArgs a, BlockCols c, int32
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 sum += __popcll(m[j]);
-                const int32_t g = __builtin_amdgcn_readlane(b, (i0 + j) & 63);
-                const u64 cols = __ballot(upto(m[j], g, match) != 0ull);
-                if (cols != 0ull) keep |= 1ull << ((i0 + j) & 63);
-                if (ln == ((i0 + j) & 63)) occ = cols;
+                const int i = (i0 + j) & 63;
+                const int32_t g = __builtin_amdgcn_readlane(b, i);
+                const u64 x = upto(m[j], g, match);
+                const u64 cols = __ballot(x != 0ull);
+                if (cols != 0ull) keep |= 1ull << i;
+                if (ln == i) occ = cols;
+                if (cols != 0ull && (cols & (cols - 1ull)) == 0ull) {
+                    const int k = __builtin_ctzll(cols);
+                    const u64 rows = readlane64(x, k);
+                    if ((rows & (rows - 1ull)) == 0ull && ln == i) t = one_entry(__builtin_ctzll(rows), k);
+                }
             }
         }
         if ((keep >> ln) & 1ull) {
             const int64_t d = e0 + kept + (int)below_count(keep);
             c.blk[d] = b;
-            c.tile[d] = q;
+            c.tile[d] = t;
             c.occ[d] = occ;
         }
         for (u64 w = keep; w && kept < kReachInline; w &= w - 1ull) {
@@ -1553,7 +1578,7 @@ __device__ __forceinline__ void reach_of(const BlockArgs& a, const BlockCols& cl
                 const int32_t gl = in ? cl.blk[e0 + i0 + ln] : 0, tl = in ? cl.tile[e0 + i0 + ln] : 0;
                 for (u64 w = __ballot(in && (cl.occ[e0 + i0 + ln] & used) != 0ull); w && !over; w &= w - 1ull) {
                     const int i = __builtin_ctzll(w);
-                    push(__builtin_amdgcn_readlane(gl, i), a.masks[64 * (int64_t)__builtin_amdgcn_readlane(tl, i) + ln]);
+                    push(__builtin_amdgcn_readlane(gl, i), listed_masks(a.masks, __builtin_amdgcn_readlane(tl, i)));
                 }
             }
         }
@@ -1596,7 +1621,8 @@ __global__ __launch_bounds__(kThreads) void k_bm_emit(BlockArgs a, BlockCols c, 
 // itself active from before it clears a block's bit until it has passed the block
 // on, so with nothing waiting and nobody active the masks are final, and are
 // weighed. (200,000 rows with an entry below the diagonal at random each, where
-// nothing can be pruned: 73 ms with a wavefront per block of columns, 10 so.)
+// nothing can be pruned: 73 ms with a wavefront per block of columns, 10 so, 2.2
+// with lanes for tiles of one entry.)
 namespace {
 constexpr int kBigWaves = 16;
 }
@@ -1673,8 +1699,18 @@ __global__ __launch_bounds__(64 * kBigWaves) void k_bm_reach_big(BlockArgs a, Bl
             for (int i0 = 0; i0 < cnt; i0 += 64) {
                 const bool in = i0 + ln < cnt;
                 const int32_t gl = in ? cl.blk[e0 + i0 + ln] : 0, tl = in ? cl.tile[e0 + i0 + ln] : 0;
-                // only the tiles with an entry in a column in use, four at a time
-                for (u64 w = __ballot(in && (cl.occ[e0 + i0 + ln] & used) != 0ull); w;) {
+                // only the tiles with an entry in a column in use: single entries a lane
+                // each, the others four at a time
+                const bool need = in && (cl.occ[e0 + i0 + ln] & used) != 0ull;
+                const u64 zk = __shfl(z, entry_col(tl), 64);
+                if (need && tl < 0) {
+                    const u64 old = or_wg(&Z[64 * (int64_t)gl + entry_row(tl)], zk);
+                    if (zk & ~old) {
+                        atomicOr(&met[gl >> 6], 1ull << (gl & 63));
+                        atomicOr(&wait[gl >> 6], 1ull << (gl & 63));
+                    }
+                }
+                for (u64 w = __ballot(need && tl >= 0); w;) {
                     u64 m[4];
                     int32_t g[4];
 #pragma unroll

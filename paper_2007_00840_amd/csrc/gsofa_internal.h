@@ -154,7 +154,8 @@ struct BlockCols {
     int32_t *blk, *tile, *blk2, *tile2;
     unsigned long long* occ;      // of those tiles: the columns with an entry that they need
     int32_t* reach;               // per block kReachWords: how many tiles the reach counts need
-                                  // (they stay in blk, tile), the first kReachInline's blk, tile
+                                  // (they stay in blk, tile; a tile of one entry as that entry),
+                                  // the first kReachInline's blk, tile
     int32_t* big;                 // per block
     int32_t* nbig;                // zero beforehand
 };

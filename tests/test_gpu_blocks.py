@@ -513,3 +513,46 @@ def test_pool_of_a_small_call_grows(g):
     for r in (0, 1, 63, 64, 12345, n - 1):
         assert torch.equal(t["u_idx"][t["u_ptr"][r]:t["u_ptr"][r + 1]], k[r:n].int())
         assert torch.equal(t["l_idx"][t["l_ptr"][r]:t["l_ptr"][r + 1]], k[r + 1:n].int())
+
+
+def _entries(n, cols):
+    """A diagonal and the given columns per row (n x k, repeats dropped)."""
+    c = np.sort(np.concatenate([np.arange(n)[:, None], cols], axis=1), axis=1)
+    keep = np.ones_like(c, dtype=bool)
+    keep[:, 1:] = c[:, 1:] != c[:, :-1]
+    return n, np.concatenate([[0], keep.sum(1).cumsum()]).astype(np.int32), c[keep].astype(np.int32)
+
+
+def _below(n, k, seed):
+    return _entries(n, np.random.default_rng(seed).integers(0, np.maximum(np.arange(n), 1)[:, None], (n, k)))
+
+
+def _tree(n, width, seed):
+    """A symmetric tree, every parent at most `width` rows below its child."""
+    p = np.minimum(n - 1, np.arange(n - 1) + 1 + np.random.default_rng(seed).integers(0, width, n - 1))
+    rows = [[i] for i in range(n)]
+    for i, j in enumerate(p):
+        rows[i].append(j)
+        rows[j].append(i)
+    return _csr(n, [sorted(set(r)) for r in rows])
+
+
+SPARSE = {
+    "below_1": lambda: _below(12000, 1, 1),    # tiles of one entry, lists of more than 64
+    "below_3": lambda: _below(3000, 3, 2),     # tiles of one and of several
+    "anywhere": lambda: _entries(9000, np.random.default_rng(3).integers(0, 9000, (9000, 1))),
+    "first_rows": lambda: _entries(9000, np.random.default_rng(4).integers(0, 40, (9000, 2))),
+    "tree": lambda: _tree(9000, 1500, 5),
+    "n65": lambda: _below(65, 1, 6),
+}
+
+
+@pytest.mark.parametrize("name", SPARSE)
+def test_reach_counts_of_scattered_entries(g, name):
+    m = SPARSE[name]()
+    ref = oracle.symbolic(*m)
+    small = _band(129, 9, 11, 1)
+    print(f"scattered {name} n={m[0]} nnz={len(m[2])}", flush=True)
+    for r in (g.symbolic(*m), g.batch([small, m, small])[1]):
+        assert r.stats["mapping"] == 7
+        _same(r, ref)
