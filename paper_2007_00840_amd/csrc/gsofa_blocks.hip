@@ -120,10 +120,6 @@ __device__ __forceinline__ int max64(int v) {
     GSOFA_DPP_SCAN((int)0x80000000, op_max)
     return __builtin_amdgcn_readlane(v, 63);
 }
-__device__ __forceinline__ int min64(int v) {
-    GSOFA_DPP_SCAN(0x7FFFFFFF, op_min)
-    return __builtin_amdgcn_readlane(v, 63);
-}
 // of lanes 0 to 15
 __device__ __forceinline__ int min16(int v) {
     GSOFA_DPP_STEP(0x111, 0xf, 0x7FFFFFFF, op_min)
@@ -173,11 +169,6 @@ __device__ __forceinline__ u64 or_wg(u64* p, u64 v) {
 // of workgroup scope also waits for every global store to be acknowledged.)
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-// The same with its global accesses.
-__device__ __forceinline__ void wave_sync_all() {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     __builtin_amdgcn_wave_barrier();
 }
 // Barrier of the workgroup for what its wavefronts pass on in LDS; global stores
@@ -1772,8 +1763,8 @@ namespace {
 constexpr int kScanThreads = 1024;
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanThreads * kScanItems;
-// One workgroup per array up to here: 8,192 values a turn (4.7 us for one turn, 16
-// for two), against two launches of at least 4.5 us and a second pass beyond.
+// One workgroup per array up to a tile, 8,192 values (4.7 us; a second turn of the
+// same workgroup made it 16), beyond it two launches of at least 4.5 us each.
 constexpr int64_t kScanOne = kScanTile;
 
 struct BlockScans {
@@ -1838,17 +1829,11 @@ __global__ __launch_bounds__(kScanThreads) void k_bm_scan_one(BlockScans all, in
     __shared__ int64_t sh[kScanThreads / 64];
     const BlockScan s = all.s[blockIdx.x];
     TileScan t;
-    int64_t carry = 0;
     t.load(s.in, 0, n);
-    for (int64_t t0 = 0; t0 < n; t0 += kScanTile) {
-        TileScan cur = t;
-        if (t0 + kScanTile < n) t.load(s.in, t0 + kScanTile, n);
-        int64_t at;
-        const int64_t total = cur.scan(sh, &at);
-        cur.store(s.out, t0, n, carry + at);
-        carry += total;
-    }
-    if (threadIdx.x == 0) s.out[n] = carry;
+    int64_t at;
+    const int64_t total = t.scan(sh, &at);
+    t.store(s.out, 0, n, at);
+    if (threadIdx.x == 0) s.out[n] = total;
 }
 
 __global__ __launch_bounds__(kScanThreads) void k_bm_scan_sums(BlockScans all, int64_t n, int64_t* sums) {
@@ -1860,7 +1845,8 @@ __global__ __launch_bounds__(kScanThreads) void k_bm_scan_sums(BlockScans all, i
     if (threadIdx.x == 0) sums[blockIdx.y * (int64_t)gridDim.x + blockIdx.x] = total;
 }
 
-// (each workgroup adds up the tiles before its own: at most 512 for 2^22 rows)
+// (each workgroup adds up the tiles before its own: 512 for 2^22 rows, 1,300 for the
+// 10^7 rows of 4,096 batch members)
 __global__ __launch_bounds__(kScanThreads) void k_bm_scan_apply(BlockScans all, int64_t n, const int64_t* sums) {
     __shared__ int64_t sh[kScanThreads / 64];
     const BlockScan s = all.s[blockIdx.y];

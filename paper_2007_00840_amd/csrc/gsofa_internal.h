@@ -257,8 +257,7 @@ hipError_t launch_transpose_l(RowSpace rs, const int64_t* l_rptr, const int32_t*
                               int64_t* scan_scratch, int32_t* cursor, int32_t* tmp,
                               int32_t* big_list, int32_t* big_count, hipStream_t st);
 hipError_t launch_zero_i32(int32_t* p, int64_t n, hipStream_t st);
-// Supernode starts (Definition T3) per block of rows. l_ptr / l_idx hold L
-// row-wise or, with by_col, column-wise.
+// Supernode starts (Definition T3) per block of rows.
 hipError_t launch_supernodes(RowSpace rs, int64_t nblocks, const int64_t* block_first_row,
                              const int32_t* block_len, const int64_t* u_ptr,
                              const int64_t* l_rptr, const int32_t* l_ridx,
