@@ -292,10 +292,12 @@ GSOFA_API int gsofa_batch(int32_t count, const gsofa_csr* mats, const gsofa_opts
  * persistent launch, as gsofa_batch does. Admitted work runs concurrently on
  * the device and finished requests release their memory, which admits the
  * next. A request's traversal takes a share of the resident wavefronts less
- * a reserve of 256 that kernels of requests admitted meanwhile run in; a
- * request admitted with nothing else running or queued takes every resident
- * wavefront but the reserve, and a large request (over 65,536 rows) admitted
- * while its traversal runs starts its own traversal when that one ends; with
+ * a reserve of 256 that kernels of requests admitted meanwhile run in (on the
+ * block path the same part of the resident workgroups); a request admitted
+ * with nothing else running or queued takes every resident wavefront but the
+ * reserve (a large one, over 65,536 rows, only if no other large one was
+ * admitted in the 100 ms before), and a large request admitted while its
+ * launch runs starts its own when that one ends; with
  * GSOFA_SERVE_YIELD running large traversals also give their wave slots up to
  * a request admitted onto a full device. Requests never time tuner trials
  * (cached choices or defaults).

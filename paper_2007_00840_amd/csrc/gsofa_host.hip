@@ -1972,10 +1972,13 @@ struct Engine {
     }
 
     // Wavefronts per block. Eight shorten a block's own work, four put more blocks
-    // in flight, which counts for one matrix of many blocks, whose separators wait
-    // for chains far behind them (1000^2 9-point, 15,625 blocks: 2.9 ms with four, 3.4
-    // with eight; 64^3 27-point, 4,096 blocks: 4.6 and 4.0; 20,000 blocks of 512 batch
-    // members: 2.7 and 2.3; sixteen never beat the better of the two).
+    // in flight. 2D stencils are faster with four at every size measured, 3D ones with
+    // eight (ms per call, four / eight: 9-point 300^2 0.65 / 0.71, 700^2 1.82 / 2.04,
+    // 1000^2 3.46 / 3.98; 27-point 40^3 1.36 / 1.21, 64^3 5.26 / 4.78, 84^3 14.6 / 13.0;
+    // 7-point 100^3 34.2 / 30.5; 512 batch members 2.7 / 2.3 for the factorisation;
+    // sixteen never beat the better of the two). What separates them, tiles per block,
+    // is not known beforehand, so the line is the size from which a single matrix is
+    // likelier 2D: 3D above 524,288 rows loses 12 %, 2D below it 10 to 20.
     // Batches with a member of more than 2^21 rows take four too: the bitmaps and eight
     // wavefronts' tables together would pass 64 KiB of LDS.
     static int32_t block_waves(int64_t nblocks, int32_t nj, int32_t words) {
@@ -2795,9 +2798,13 @@ int32_t serve_slots_alone(const gsofa_server* s, int32_t n, int64_t nnz) {
 // call: one persistent traversal launch over all their sources, as in
 // gsofa_batch. Larger requests run alone (their own launch fills the device).
 constexpr int32_t kServeSmallRows = 65536;
-// A large request that follows another within this time is not treated as a lone
-// one: a stream of large requests keeps to its shares, so that the next one finds
-// room at once (a 48^3 27-point stencil holds the device for a few milliseconds).
+// A large request that follows another within this time gets the ordinary share
+// although nothing else may be running: large requests in close succession keep to
+// equal shares, whether or not one ends just before the next arrives (a 48^3 27-point
+// stencil holds the device for a few milliseconds). Sixteen requests 1 to 30 ms apart
+// with small ones between, with and without the rule: p50 11.8 and 11.8 ms on that
+// stencil, 2.5 and 2.5 on 350^2 9-point, 8.9 and 8.4 on 700^2, whose blocks want every
+// workgroup.
 constexpr double kServeLoneGapMs = 100.0;
 constexpr size_t kServeMaxGroup = 64;
 constexpr int64_t kServeGroupRows = 1 << 20;
