@@ -1079,6 +1079,7 @@ struct Engine {
 
     // outputs
     std::vector<gsofa_result*> results;
+    bool refused = false;  // the input check ended the call: no matrix has arrays
 
     int run() {
         const double t0 = now_ms();
@@ -1181,13 +1182,13 @@ struct Engine {
             chk(launch_copy_to_host(h_found.p, found.p, 8 * (size_t)nj, st));
             chk(hipStreamSynchronize(st));
             const int32_t* hb = h_found.as<int32_t>();
-            int32_t worst = 0;  // 2: nothing of the matrix was looked at
-            for (int32_t q = 0; q < nj; ++q) worst = std::max(worst, hb[q]);
+            bool any = false;
             for (int32_t q = 0; q < nj; ++q) {
                 nnz[ord[q]] = std::max<int64_t>(hb[nj + q], 0);
-                if (worst > 0 && hb[q] == worst) jstat[ord[q]] = GSOFA_EINVAL;
+                if (hb[q]) jstat[ord[q]] = GSOFA_EINVAL;
+                any |= hb[q] != 0;
             }
-            if (worst > 0) return finish_failed(jstat, t0);
+            if (any) return finish_failed(jstat, t0);
         }
         for (int32_t j = 0; j < nj; ++j) total_nnz += nnz[j];
 
@@ -2457,6 +2458,7 @@ struct Engine {
     }
 
     int finish_failed(const std::vector<int>& jstat, double t0) {
+        refused = true;
         int first_bad = GSOFA_OK;
         for (size_t j = 0; j < jstat.size(); ++j) {
             gsofa_result* r = new_result();
@@ -2514,7 +2516,7 @@ std::mutex g_api_mu;  // one call at a time per process for the plain entry poin
 int run_engine(std::vector<MatIn> mats, const gsofa_opts* o, std::vector<gsofa_result*>& outs,
                bool allow_trials = true, bool tuned_with_slots = false, const YieldHooks* yh = nullptr) {
     Engine eng;
-    eng.mats = std::move(mats);
+    eng.mats = mats;
     eng.plan = make_plan(o);
     eng.yh = yh;
     eng.plan.allow_trials = allow_trials && !(eng.plan.flags & GSOFA_NO_TUNE);
@@ -2569,6 +2571,26 @@ int run_engine(std::vector<MatIn> mats, const gsofa_opts* o, std::vector<gsofa_r
         return GSOFA_ENOMEM;
     }
     outs = eng.results;
+    if (!eng.refused) return rc;
+    // the device found malformed matrices: the others run without them
+    size_t good = 0;
+    for (size_t j = 0; j < outs.size(); ++j)
+        if (outs[j]->stats.status == GSOFA_OK) mats[good++] = mats[j];
+    if (good == 0) return rc;
+    mats.resize(good);
+    std::vector<gsofa_result*> res;
+    const int rc2 = run_engine(std::move(mats), o, res, allow_trials, tuned_with_slots, yh);
+    if (res.empty()) {  // device or memory failure
+        for (auto* r : outs) free_result(r);
+        outs.clear();
+        return rc2;
+    }
+    size_t k = 0;
+    for (auto& r : outs)
+        if (r->stats.status == GSOFA_OK) {
+            free_result(r);
+            r = res[k++];
+        }
     return rc;
 }
 

@@ -556,3 +556,27 @@ def test_reach_counts_of_scattered_entries(g, name):
     for r in (g.symbolic(*m), g.batch([small, m, small])[1]):
         assert r.stats["mapping"] == 7
         _same(r, ref)
+
+
+def test_malformed_members_of_a_device_batch_leave_the_others_alone(g):
+    """Every malformed matrix is refused (out-of-range columns, a negative count, rows
+    that end beyond the entries, a repeated column) and every other one computed."""
+    import torch
+    dev = lambda m: (m[0],) + tuple(torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in m[1:])
+    n, rp, ci = _stencil(9, (20, 20), True, 8)
+    off, neg, far, twice = ci.copy(), rp.copy(), rp.copy(), ci.copy()
+    off[3], neg[n], far[5] = n, -1, 1 << 30
+    twice[rp[7] + 1] = twice[rp[7]]
+    bad = [(n, rp, off), (n, neg, ci), (n, far, ci), (n, rp, twice)]
+    good = [_band(k, 9, 11, k) for k in (1, 64, 200, 700)]
+    refs = [oracle.symbolic(*m) for m in good]
+    for pick in ((0,), (1,), (2,), (3,), (0, 1), (0, 1, 2, 3)):
+        mats = [x for k, m in enumerate(good) for x in ([m, bad[k]] if k in pick else [m])]
+        for flags in (0, g.MAP_WAVE32):
+            res = g.batch([dev(m) for m in mats], raise_on_error=False, flags=flags)
+            assert [r is None for r in res] == [any(m is b for b in bad) for m in mats]
+            for r, ref in zip([r for r in res if r is not None], refs):
+                _same(r, ref)
+    with pytest.raises(g.GsofaError) as e:
+        g.batch([dev(good[0]), dev(bad[0])])
+    assert e.value.code == g.EINVAL
