@@ -44,22 +44,35 @@ def traversal_source_hash():
     return hashlib.sha256(src[:end] if end >= 0 else src).hexdigest()[:16]
 
 
+def block_source_hash():
+    """SHA-256 (16 hex digits) of the block path's kernel source."""
+    import hashlib
+    here = os.path.dirname(os.path.abspath(__file__))
+    return hashlib.sha256(open(os.path.join(here, "paper_2007_00840_amd", "csrc", "gsofa_blocks.hip"),
+                               "rb").read()).hexdigest()[:16]
+
+
 PROFILE_OF_WORKLOAD = {"3d": "k_traverse_64cube_27pt.md", "2d": "k_traverse_1000sq_9pt.md",
                        "batch": "k_traverse_batch4096.md"}
 
 
 def recorded_traffic(kernel, mapping, window, sources, workload="3d"):
-    """HBM bytes per launch of the traversal kernel from the rocprofv3 PMC record
+    """HBM bytes per launch of the traversal (or block) kernel from the rocprofv3 PMC record
     in profiles/ (FETCH_SIZE and WRITE_SIZE scaled by a plain copy's readings),
     or None when no record matches this kernel source and configuration."""
     import re
     here = os.path.dirname(os.path.abspath(__file__))
-    rec = os.path.join(here, "profiles", PROFILE_OF_WORKLOAD[workload])
+    blocks = mapping == MAP_BLOCKS
+    rec = os.path.join(here, "profiles", "k_bm_blocks.md" if blocks else PROFILE_OF_WORKLOAD[workload])
     try:
-        sha = traversal_source_hash()
+        sha = block_source_hash() if blocks else traversal_source_hash()
         text = open(rec).read()
     except OSError:
         return None
+    if blocks:  # one record per workload
+        m = re.search(rf"traffic-record: workload={workload} kernel={kernel} source_sha256_16={sha} "
+                      rf"sources={sources} fetch_bytes=(\d+) write_bytes=(\d+)", text)
+        return int(m.group(1)) + int(m.group(2)) if m else None
     # one record per configuration the tuner may pick (its near-tie windows)
     for m in re.finditer(r"traffic-record: kernel=(\S+) source_sha256_16=(\S+) mapping=(\d+) window=(\d+) "
                          r"sources=(\d+) fetch_bytes=(\d+) write_bytes=(\d+)", text):
@@ -117,9 +130,9 @@ def cpu_baseline_batch(mats, every, threads=None):
 
 def roofline(e_alg, e_gpu, t_trav_ms, mapping, window, sources, workload):
     """HBM rate of the kernel that finds the structure against the 8 TB/s peak: 8 B
-    per algorithmic edge of the per-source traversal (with the PMC traffic record
-    if one matches), or per column mask that the block path merges, which visits
-    no edges."""
+    per algorithmic edge of the per-source traversal, or per column mask that the
+    block path merges, which visits no edges; with the PMC traffic record if one
+    matches."""
     kern = KERNEL_OF_MAPPING.get(mapping, "k_traverse<8>")
     if mapping == MAP_BLOCKS:
         e_alg = e_gpu

@@ -12,7 +12,7 @@
 // (k_traverse) walks every vertex reachable from every source instead: on the
 // 64^3 27-point stencil 51 G edge visits, where the block path makes 1.8e5 block
 // merges of 2.5e6 64-column tiles: 4.0 ms instead of 221 (1000^2 9-point stencil:
-// 3.0 instead of 218 ms; 512 batch members: 2.3 instead of 90 ms).
+// 2.8 instead of 211 ms; 512 batch members: 2.3 instead of 90 ms).
 //
 // What bounds it is the chain of blocks that wait for one another, not
 // throughput, and four things keep that chain short:
@@ -2031,7 +2031,7 @@ hipError_t launch_block_emit(const BlockArgs& a, const BlockCols& c, const int64
                                   : (l_csr ? k_bm_emit<true, 8> : k_bm_emit<false, 8>);
     hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, a, c, u_ptr, u_idx, l_ptr, l_idx);
     // (as many as there are slots: 10^6 rows coupled two by two at random, where every
-    // block comes here, took 24 ms with 256 workgroups and a tile at a time, now 4)
+    // block comes here, took 24 ms with 256 workgroups and a tile at a time, now 2.3)
     hipLaunchKernelGGL(k_bm_reach_big, dim3((unsigned)a.nslots), dim3(64 * kBigWaves), (size_t)a.bit_words * 16, st, a,
                        c);
     return hipGetLastError();

@@ -61,3 +61,21 @@ def test_what_follows_a_launch(checks):
     assert [checks.next(done, f) for f in (0, 1)] == [results, results]
     assert [checks.next(overflow, f) for f in (0, 1)] == [traverse, again]
     assert [checks.next(stall, f) for f in (0, 1)] == [traverse, traverse]
+
+
+def test_bench_reads_the_block_path_s_traffic_record():
+    """bench.py reports the committed counters of k_bm_factor only for the workload and
+    the workgroups they were taken with, and while the kernel source is the same."""
+    import re
+    import sys
+    if ROOT not in sys.path:
+        sys.path.insert(0, ROOT)
+    import bench
+    text = open(os.path.join(ROOT, "profiles", "k_bm_blocks.md")).read()
+    recs = re.findall(r"traffic-record: workload=(\S+) kernel=(\S+) source_sha256_16=(\S+) sources=(\d+) "
+                      r"fetch_bytes=(\d+) write_bytes=(\d+)", text)
+    assert {r[0] for r in recs} == {"3d", "2d"}
+    for workload, kernel, sha, sources, fetch, write in recs:
+        got = bench.recorded_traffic(kernel, bench.MAP_BLOCKS, 0, int(sources), workload)
+        assert got == (int(fetch) + int(write) if sha == bench.block_source_hash() else None)
+        assert bench.recorded_traffic(kernel, bench.MAP_BLOCKS, 0, int(sources) + 64, workload) is None
