@@ -106,8 +106,9 @@ typedef enum {
 #define GSOFA_EAGER             0x200u
 /* With window = 0, concurrent_sources = 0 and no mapping or ablation flag, a call
  * takes the block path: no per-source traversal, nothing to tune. Matrices of more
- * than 2^22 rows and calls whose mem_budget_bytes does not hold its working memory,
- * the result included, take the traversal, whose window span, mapping and sources in flight are then
+ * than 2^22 rows, calls whose mem_budget_bytes does not hold its working memory, the
+ * result included, and calls for which that memory could not be had (or a wait in the
+ * launch gave up) take the traversal, whose window span, mapping and sources in flight are then
  * autotuned: for each size class (device, log2 of the largest n, mean row length,
  * batch size) the first call with at least 65,536 source rows times every
  * candidate on one stratified sample of its rows and keeps the fastest for later
@@ -206,7 +207,8 @@ typedef void (*gsofa_free_fn)(void* ptr, void* ctx);
 typedef struct {
     uint32_t struct_size;       /* sizeof(gsofa_opts); 0 or a zeroed struct = defaults   */
     int32_t max_supernode;      /* block size for supernodes; 0 -> 128; <0 -> unbounded  */
-    int64_t mem_budget_bytes;   /* device working-memory cap; 0 -> 90 % of free memory    */
+    int64_t mem_budget_bytes;   /* device working-memory cap; 0 -> 90 % of free memory
+                                   (block path: looked at above 256 MiB of need)          */
     uint32_t flags;             /* GSOFA_* flags above                                    */
     int32_t window;             /* threshold-window span (vertex ids); 0 -> autotuned    */
     int32_t concurrent_sources; /* sources in flight; 0 -> planned from memory and CUs    */
